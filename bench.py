@@ -49,25 +49,10 @@ OPS_PER_SW_CELL = {(16, False): 10, (16, True): 10, (32, False): 9, (32, True): 
 ALGO_OPS_PER_SW_CELL = 11
 # x-drop: the same recurrence plus the drop test per live cell
 ALGO_OPS_PER_XD_CELL = 12
-# HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per
-# dispatch, profiles/sw_search_<workload>_kernel_stats.md), scaled by what the
-# counters read for a 1 GiB device copy (FETCH x 2.0, WRITE x 1.0); keyed by
-# workload and kernel (a strip bin's two launches: their sum), and only for
-# kernels unchanged since those counters were taken
-MEASURED_TRAFFIC_KIB = {
-    ("large", "sw16s_pass1_kernel<32, 9, 4> + sw16s_pass1_kernel<32, 10, 4>"): (690858.6, 61411.7),
-    ("large", "sw16s_pass1_kernel<32, 11, 4> + sw16s_pass1_kernel<32, 12, 4>"): (547507.7, 46009.6),
-    ("large", "sw16s_pass1_kernel<32, 13, 4> + sw16s_pass1_kernel<32, 14, 4>"): (455684.8, 36387.2),
-    ("large", "sw16s_pass1_kernel<32, 15, 4> + sw16s_pass1_kernel<32, 16, 4>"): (338121.6, 25849.5),
-    ("mid", "sw16s_pass1_kernel<32, 9, 4> + sw16s_pass1_kernel<32, 10, 4>"): (1448426.2, 152314.0),
-    ("mid", "sw16s_pass1_kernel<32, 11, 4> + sw16s_pass1_kernel<32, 12, 4>"): (1247509.3, 129182.3),
-    ("mid", "sw16s_pass1_kernel<32, 13, 4> + sw16s_pass1_kernel<32, 14, 4>"): (963776.0, 99906.1),
-    ("mid", "sw16s_pass1_kernel<32, 15, 4> + sw16s_pass1_kernel<32, 16, 4>"): (720457.1, 75910.6),
-    ("mid", "sw16_pass1_kernel<9, 2, false>"): (599028.2, 65327.9),
-    ("mid", "sw16_pass1_kernel<10, 2, false>"): (348941.0, 40720.7),
-}
-# the same counters for the kernels of the sparse-product stage (one launch of
-# each per step): the row scan that sizes each row's table, the headed
+# HBM KiB per dispatch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
+# (profiles/sw_search_<workload>_kernel_stats.md), scaled by what the counters
+# read for a 1 GiB device copy (FETCH x 2.0, WRITE x 1.0), of the kernels of
+# the sparse-product stage (one launch of each per step): the row scan that sizes each row's table, the headed
 # posting records, and the product kernels (LDS tables of 2K..32K slots, and
 # global-memory tables for the largest rows).  A row entry's posting list is a
 # scattered read (a header and its records share a line), so the traffic
@@ -228,30 +213,26 @@ def timed_steps(ctx, args, res, off):
 STAGE_NAMES = ["encode", "kmers", "subs_AS", "spgemm", "schedule", "sw_pass1", "sw_pass2", "edges", "mlp_filter"]
 
 
-def kernel_name(b, narrow):
-    """The pass-1 kernel(s) of a length bin.  A 16-bit strip bin (up to 8 rows
-    per lane) is two launches back to back on one stream: the sequences of up
-    to 64 R - 32 rows with one row per lane less (two in 16-lane strips),
-    then the rest; its events span both."""
+def kernel_name(b):
+    """The pass-1 kernel a length bin runs in: one launch per group of bins."""
     R = b["rows_per_lane"]
+    if b["multi_strip"]:
+        return "sw16_pass1_kernel<9, 16, 4, true>" if b["bits"] == 16 else "sw_pass1_kernel<9, 16, true>"
+    lo = (R - 1) // 4 * 4 + 1
     if b["bits"] == 16:
-        if b["multi_strip"]:
-            return "sw16_pass1_kernel<%d, 4, true>" % R
-        if R <= 8:
-            S = 16 if R <= min(narrow, 4) else 32
-            rp = 64 * R // S
-            return "sw16s_pass1_kernel<%d, %d, 4> + sw16s_pass1_kernel<%d, %d, 4>" % (S, rp - 32 // S, S, rp)
-        return "sw16_pass1_kernel<%d, 2, false>" % R
-    return "sw_pass1_kernel<%d, %s>" % (R, "true" if b["multi_strip"] else "false")
+        return "sw16s_pass1_kernel<%d, %d>" % (lo, lo + 3) if R <= 8 else "sw16_pass1_kernel<%d, %d, 2, false>" % (
+            lo, lo + 3)
+    return "sw_pass1_kernel<%d, %d, false>" % (lo, lo + 3)
 
 
-def roofline(st, pass1_ms, traffic_ok, workload, narrow):
-    """The dominant pass-1 kernel (the length bin with the most DP work; one
-    launch per step, or for a 16-bit strip bin its two rows classes back to
-    back on one stream) against the integer VALU peak of its lane width: its
-    cells x the method's 11 ops per cell over its HIP-event time on the
-    stream it was launched on.  The kernel's own formulation count (10 or 9
-    ops per cell) is reported beside it."""
+def roofline(st, pass1_ms):
+    """The dominant length bin of pass 1 (the one with the most DP work) against
+    the integer VALU peak of its lane width: its cells x the method's 11 ops
+    per cell over its span on the device's clock, from the first claim of its
+    queue to the last finish.  The groups of bins run beside one another, so
+    a span includes time shared with other bins; all_pass1_bins divides the
+    work of all of them by the stage's time.  The kernel's own formulation
+    count (10 or 9 ops per cell) is reported beside it."""
 
     def ops(b):
         return OPS_PER_SW_CELL[(b["bits"], bool(b["multi_strip"]))]
@@ -259,19 +240,13 @@ def roofline(st, pass1_ms, traffic_ok, workload, narrow):
     def peak_of(b):
         return PEAK_INT16_TOPS if b["bits"] == 16 else PEAK_INT32_TOPS
 
-    # chosen by work, not by event time: the multi-strip bins run on a second
-    # stream beside the one-strip bins, so their event spans include time
-    # shared with other kernels
+    # chosen by work, not by time: a bin's span includes time shared with others
     dom = max(st["sw_bins"], key=lambda b: b["cells"] / peak_of(b))
-    name = kernel_name(dom, narrow)
+    name = kernel_name(dom)
     peak = peak_of(dom)
     achieved = dom["cells"] * ALGO_OPS_PER_SW_CELL / (dom["ms"] * 1e-3) / 1e12
     kernel_ops = dom["cells"] * ops(dom) / (dom["ms"] * 1e-3) / 1e12
     mix_peak_s = sum(b["cells"] * ALGO_OPS_PER_SW_CELL / (peak_of(b) * 1e12) for b in st["sw_bins"])
-    traffic = None
-    if traffic_ok and (workload, name) in MEASURED_TRAFFIC_KIB:
-        f, w = MEASURED_TRAFFIC_KIB[(workload, name)]
-        traffic = 1024 * (FETCH_SCALE * f + WRITE_SCALE * w)
     return {
         "kernel": name,
         "bound": "alu",
@@ -279,7 +254,7 @@ def roofline(st, pass1_ms, traffic_ok, workload, narrow):
         "peak": peak,
         "unit": "Tops/s",
         "frac": achieved / peak,
-        "traffic": traffic,
+        "traffic": None,  # no counters of the group launches
         "kernel_ms": dom["ms"],
         "kernel_cells": dom["cells"],
         "ops_per_cell": ALGO_OPS_PER_SW_CELL,
@@ -455,7 +430,7 @@ def mid_leg(P, args, dev):
         "cells": cells,
         "edges": int(edges.size),
         "stage_ms": dict(zip(STAGE_NAMES, stage)),
-        "roofline": roofline(st, stage[5], args.families is None, "mid", ctx.get_tuning()["sw16_narrow_rows"]),
+        "roofline": roofline(st, stage[5]),
         "spgemm": spgemm_line(st, stage[3], "mid" if args.families is None else None),
     }
     if not args.no_xd:
@@ -559,8 +534,7 @@ def main():
         "stage_ms": dict(zip(STAGE_NAMES, stage)),
         "align_gcups": cells / ((stage[5] + stage[6]) * 1e-3) / 1e9,
         "spgemm": spgemm_line(st, stage[3], args.workload if args.families is None else None),
-        "roofline": roofline(st, stage[5], args.families is None, args.workload,
-                             ctx.get_tuning()["sw16_narrow_rows"]),
+        "roofline": roofline(st, stage[5]),
         "sw_bins": [dict(b, gcups=b["cells"] / max(b["ms"], 1e-9) / 1e6) for b in st["sw_bins"] if b["pairs"]],
         "schedule": tuning if tuning is not None else dict(ctx.get_tuning(), source="library default"),
     }

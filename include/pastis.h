@@ -168,10 +168,11 @@ typedef struct pastis_run_stats {
                            k-mers, S formation, SpGEMM, schedule, alignment pass 1,
                            alignment pass 2, identity/coverage cut and edges, learned
                            pre-alignment filter */
-    /* Smith-Waterman pass 1 per length bin (one kernel launch each): rows per
-     * lane R, whether the bin's pairs span several strips of 64 * R rows, and
-     * the bin's pairs, DP cells and device time (HIP events around the launch,
-     * on the call's stream).  sw_bins = 0 after an x-drop call. */
+    /* Smith-Waterman pass 1 per length bin: rows per lane R, whether the bin's
+     * pairs span several strips of 64 * R rows, and the bin's pairs, DP cells
+     * and device time (from the first pair begun to the last one finished, on
+     * the device's clock; bins run beside one another, so their times
+     * overlap).  sw_bins = 0 after an x-drop call. */
     int32_t sw_bins;
     int32_t sw_bin_rows[32];
     int32_t sw_bin_multi[32];

@@ -235,16 +235,17 @@ pastis_status make_sw_work(pastis_ctx *ctx, int64_t npairs, int max_len, SwWork 
     void *p = nullptr;
     PASTIS_TRY(ensure(ctx, kBufBinOf, (size_t)std::max<int64_t>(npairs, 1), &p));
     wk.bin_of = (int8_t *)p;
-    PASTIS_TRY(ensure(ctx, kBufBinMeta, sizeof(int) * 384 + sizeof(unsigned long long) * kNumCounters, &p));
+    constexpr int kMetaInts = 512;
+    PASTIS_TRY(ensure(ctx, kBufBinMeta, sizeof(int) * kMetaInts + sizeof(unsigned long long) * kNumCounters, &p));
     wk.counts = (int *)p;
-    wk.counters = (unsigned long long *)((int *)p + 384);
-    // counts: 32 bins; starts, starts2: 33 bounds each; cursor, split: 32;
-    // four work queues of 32 bins
+    wk.counters = (unsigned long long *)((int *)p + kMetaInts);
+    // counts: 32 bins; starts, starts2: 33 bounds each; cursor: 32; bounds: 65;
+    // seven work queues of 32 bins
     wk.starts = wk.counts + 32;
     wk.starts2 = wk.counts + 72;
     wk.cursor = wk.counts + 112;
-    wk.split = wk.counts + 144;
-    wk.queue = wk.counts + 176;
+    wk.bounds = wk.counts + 144;
+    wk.queue = wk.counts + 216;
     PASTIS_TRY(ensure(ctx, kBufIdx, sizeof(int) * (size_t)std::max<int64_t>(npairs, 1), &p));
     wk.idx = (int *)p;
     PASTIS_TRY(ensure(ctx, kBufIdx2, sizeof(int) * (size_t)std::max<int64_t>(npairs, 1), &p));
@@ -289,20 +290,20 @@ static uint64_t mix(uint64_t h, uint64_t v) {
 
 static pastis_status sw_graph(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pairs, int64_t npairs,
                               const Scoring &sc, SwPass1Out *p1, pastis_pair_record *out, const SwWork &wk,
-                              int stats_mode, int max16, hipStream_t s) {
-    const int grid = ctx->tune.sw_grid_scale, grid_wide = ctx->tune.sw_grid_scale_wide, intra = ctx->tune.sw_intra_pair;
-    const int narrow = ctx->tune.sw16_narrow_rows, long_blocks = ctx->tune.sw_long_blocks;
+                              int stats_mode, const SwPlan &plan, hipStream_t s) {
     uint64_t key = 0;
     const uint64_t parts[] = {(uint64_t)npairs, (uint64_t)codes, (uint64_t)pairs, (uint64_t)p1, (uint64_t)out,
                               (uint64_t)wk.counters, (uint64_t)wk.bin_of, (uint64_t)wk.counts, (uint64_t)wk.idx,
-                              (uint64_t)wk.idx2, (uint64_t)wk.scratch, (uint64_t)wk.scratch_per_wave,
+                              (uint64_t)wk.idx2, (uint64_t)wk.bounds, (uint64_t)wk.scratch, (uint64_t)wk.scratch_per_wave,
                               (uint64_t)wk.sort_keys, (uint64_t)wk.sort_keys_alt, (uint64_t)wk.sort_vals_alt,
                               (uint64_t)wk.sort_temp, (uint64_t)sc.gap_open, (uint64_t)sc.gap_extend,
                               (uint64_t)sc.id_pct, (uint64_t)sc.cov_pct, (uint64_t)sc.direct_pct,
-                              (uint64_t)stats_mode, (uint64_t)max16, (uint64_t)grid, (uint64_t)grid_wide, (uint64_t)intra,
-                              (uint64_t)narrow, (uint64_t)long_blocks,
-                              (uint64_t)ctx->d_blosum};
+                              (uint64_t)stats_mode, (uint64_t)ctx->d_blosum};
     for (uint64_t v : parts) key = mix(key, v);
+    // the launches of the plan (its grids and masks follow the pairs per bin)
+    const uint32_t *pw = (const uint32_t *)&plan;
+    static_assert(sizeof(SwPlan) % sizeof(uint32_t) == 0, "the plan is 32-bit words");
+    for (size_t t = 0; t < sizeof(SwPlan) / sizeof(uint32_t); ++t) key = mix(key, pw[t]);
     hipStream_t gs = ctx->graph_stream;
     if (!ctx->sw_exec || key != ctx->sw_key) {
         if (ctx->sw_exec) {
@@ -310,8 +311,8 @@ static pastis_status sw_graph(pastis_ctx *ctx, const uint8_t *codes, const PairD
             ctx->sw_exec = nullptr;
         }
         HIP_TRY(ctx, hipStreamBeginCapture(gs, hipStreamCaptureModeThreadLocal), "graph capture");
-        const hipError_t le = launch_sw(ctx, codes, pairs, npairs, ctx->d_blosum, sc, p1, out, wk, stats_mode, max16,
-                                        grid, grid_wide, intra, narrow, long_blocks, false, gs);
+        const hipError_t le =
+            launch_sw(ctx, codes, pairs, npairs, ctx->d_blosum, sc, p1, out, wk, stats_mode, plan, false, gs);
         hipGraph_t g = nullptr;
         const hipError_t ce = hipStreamEndCapture(gs, &g);
         if (le != hipSuccess || ce != hipSuccess) {
@@ -344,30 +345,32 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
                          pastis_pair_record *out, hipStream_t s) {
     ctx->stats.n_aligned = npairs;
     if (npairs == 0) return PASTIS_OK;
-    unsigned long long *d_flags = nullptr, h_flags[4];
-    PASTIS_TRY(reset_flags(ctx, &d_flags, s));
+    const bool sw = ctx->params.align_mode == PASTIS_ALIGN_SW;
+    SwWork wk;
+    PASTIS_TRY(make_sw_work(ctx, npairs, st.max_len, wk));
+    HIP_TRY(ctx, fill<unsigned long long>(wk.counters, kNumCounters, 0ull, s), "reset");
     void *pairs = nullptr;
     PASTIS_TRY(ensure(ctx, kBufPairs, sizeof(PairDesc) * (size_t)npairs, &pairs));
     HIP_TRY(ctx,
             launch_orient_pairs(st.d_off, n, pi, pj, seed1, seed2, npairs, ctx->params.k, (PairDesc *)pairs,
-                                d_flags + 1, s),
+                                wk.counters + kCounterBad, s),
             "orient kernel");
-    PASTIS_TRY(read_flags(ctx, d_flags, h_flags, 2, s));
-    if (h_flags[1] & 1ull) return set_error(ctx, PASTIS_E_INVAL, "pair index out of range or pi == pj");
+    // one read-back for the index check and the pairs per bin
+    if (sw) HIP_TRY(ctx, launch_sw_bins((const PairDesc *)pairs, npairs, wk, s), "binning kernel");
+    unsigned long long c[kNumCounters];
+    PASTIS_TRY(read_device(ctx, wk.counters, c, sizeof(c), s));
+    if (c[kCounterBad] & 1ull) return set_error(ctx, PASTIS_E_INVAL, "pair index out of range or pi == pj");
     const pastis_params &P = ctx->params;
     Scoring sc{P.gap_open, P.gap_extend, P.xdrop, P.min_identity_pct, P.min_coverage_pct, ctx->tune.sw_direct_pct};
     void *p1 = nullptr;
     PASTIS_TRY(ensure(ctx, kBufPass1, sizeof(SwPass1Out) * (size_t)npairs, &p1));
-    SwWork wk;
-    PASTIS_TRY(make_sw_work(ctx, npairs, st.max_len, wk));
-    HIP_TRY(ctx, fill<unsigned long long>(wk.counters, kNumCounters, 0ull, s), "reset");
     ctx->stats.sw_bins = 0;
     ctx->stats.int32_pairs = 0;
     ctx->last_max16 = 0;
     // traceback statistics: every pair on request; none for the normalised
     // score weight; otherwise only where the coverage cut can still hold
     const int stats_mode = P.full_records ? 1 : (P.weight_mode == PASTIS_WEIGHT_NS ? 2 : 0);
-    if (P.align_mode == PASTIS_ALIGN_SW) {
+    if (sw) {
         // 16-bit pass 1 on request, or by default where its records stay
         // inside the search (they omit end_b of pairs without statistics,
         // which no edge then reports)
@@ -376,14 +379,14 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
         const int max16 = !use16 ? 0 : P.score_width == 16 ? 16 : ctx->tune.sw16_max_rows;
         if (max16 > 0) PASTIS_TRY(make_sort_work(ctx, npairs, wk));
         ctx->last_max16 = max16;
+        const SwPlan plan = sw_plan(c + kCounterBinPairs, sc, max16, ctx->tune);
         if (P.graph_mode) {
             PASTIS_TRY(sw_graph(ctx, codes, (const PairDesc *)pairs, npairs, sc, (SwPass1Out *)p1, out, wk, stats_mode,
-                                max16, s));
+                                plan, s));
         } else {
             HIP_TRY(ctx,
                     launch_sw(ctx, codes, (const PairDesc *)pairs, npairs, ctx->d_blosum, sc, (SwPass1Out *)p1, out,
-                              wk, stats_mode, max16, ctx->tune.sw_grid_scale, ctx->tune.sw_grid_scale_wide,
-                              ctx->tune.sw_intra_pair, ctx->tune.sw16_narrow_rows, ctx->tune.sw_long_blocks, true, s),
+                              wk, stats_mode, plan, true, s),
                     "sw kernels");
         }
     } else {
@@ -397,7 +400,6 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
                           n_redo, (int *)ring, wk.counters, s),
                 "xd kernels");
     }
-    unsigned long long c[kNumCounters];
     PASTIS_TRY(read_device(ctx, wk.counters, c, sizeof(c), s));
     if (c[kCounterIntraFlag]) return set_error(ctx, PASTIS_E_DEVICE, "intra-pair pass 1: a strip hand-off wait ran out");
     ctx->stats.cells = (int64_t)c[0];
@@ -405,21 +407,19 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
     ctx->stats.stats_pass_cells = (int64_t)c[2];
     ctx->stats.bound_pass_pairs = (int64_t)c[3];
     ctx->stats.bound_pass_cells = (int64_t)c[4];
-    if (P.align_mode == PASTIS_ALIGN_SW && !P.graph_mode) {
-        int starts[33];  // pass-1 bin bounds (the pass-2 binning reuses the counts)
-        PASTIS_TRY(read_device(ctx, wk.starts, starts, sizeof(starts), s));
+    if (sw && !P.graph_mode) {
         const int nb = sw_num_bins();
         ctx->stats.sw_bins = nb;
         for (int b = 0; b < nb; ++b) {
             sw_bin_shape(b, &ctx->stats.sw_bin_rows[b], &ctx->stats.sw_bin_multi[b]);
             const bool b16 = sw_bin_is16(b, ctx->last_max16);
+            const int64_t n_b = (int64_t)c[kCounterBinPairs + b];
             ctx->stats.sw_bin_bits[b] = b16 ? 16 : 32;
-            if (!b16) ctx->stats.int32_pairs += starts[b + 1] - starts[b];
-            ctx->stats.sw_bin_pairs[b] = starts[b + 1] - starts[b];
+            if (!b16) ctx->stats.int32_pairs += n_b;
+            ctx->stats.sw_bin_pairs[b] = n_b;
             ctx->stats.sw_bin_cells[b] = (int64_t)c[kCounterBinCells + b];
-            float ms = 0.f;
-            HIP_TRY(ctx, hipEventElapsedTime(&ms, ctx->bin_ev[2 * b], ctx->bin_ev[2 * b + 1]), "event time");
-            ctx->stats.sw_bin_ms[b] = ms;
+            const unsigned long long *span = c + kCounterSpan + 2 * b;
+            ctx->stats.sw_bin_ms[b] = span[1] ? (double)(span[1] - ~span[0]) * ctx->ms_per_tick : 0.0;
         }
     }
     return PASTIS_OK;
@@ -511,20 +511,25 @@ pastis_status pastis_create(const pastis_params *p, int device, pastis_ctx **out
             return PASTIS_E_DEVICE;
         }
     }
-    for (auto &ev : ctx->bin_ev) {
-        if (hipEventCreate(&ev) != hipSuccess) {
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0) {
+        (void)hipGetLastError();
+        khz = 100000;  // 100 MHz
+    }
+    ctx->ms_per_tick = 1.0 / (double)khz;
+    // default priority; non-blocking so that they never wait on the null stream
+    hipStream_t *const streams[] = {&ctx->long_stream, &ctx->side_stream[0], &ctx->side_stream[1],
+                                    &ctx->side_stream[2]};
+    for (hipStream_t *st : streams) {
+        if (hipStreamCreateWithFlags(st, hipStreamNonBlocking) != hipSuccess) {
             pastis_destroy(ctx);
             return PASTIS_E_DEVICE;
         }
     }
-    // default priority; non-blocking so it never waits on the null stream
-    if (hipStreamCreateWithFlags(&ctx->long_stream, hipStreamNonBlocking) != hipSuccess) {
-        pastis_destroy(ctx);
-        return PASTIS_E_DEVICE;
-    }
     for (int i = 0; i < 3; ++i) {
-        if (hipEventCreateWithFlags(&ctx->long_fork[i], hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&ctx->long_join[i], hipEventDisableTiming) != hipSuccess) {
+        bool ok = hipEventCreateWithFlags(&ctx->fork_ev[i], hipEventDisableTiming) == hipSuccess;
+        for (auto &ev : ctx->join_ev[i]) ok = ok && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
+        if (!ok) {
             pastis_destroy(ctx);
             return PASTIS_E_DEVICE;
         }
@@ -552,16 +557,16 @@ void pastis_destroy(pastis_ctx *ctx) {
     if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
     for (auto &ev : ctx->ev)
         if (ev) (void)hipEventDestroy(ev);
-    for (auto &ev : ctx->bin_ev)
-        if (ev) (void)hipEventDestroy(ev);
     if (ctx->sw_exec) (void)hipGraphExecDestroy(ctx->sw_exec);
-    if (ctx->long_stream) {
-        (void)hipStreamSynchronize(ctx->long_stream);
-        (void)hipStreamDestroy(ctx->long_stream);
+    for (hipStream_t st : {ctx->long_stream, ctx->side_stream[0], ctx->side_stream[1], ctx->side_stream[2]}) {
+        if (!st) continue;
+        (void)hipStreamSynchronize(st);
+        (void)hipStreamDestroy(st);
     }
     for (int i = 0; i < 3; ++i) {
-        if (ctx->long_fork[i]) (void)hipEventDestroy(ctx->long_fork[i]);
-        if (ctx->long_join[i]) (void)hipEventDestroy(ctx->long_join[i]);
+        if (ctx->fork_ev[i]) (void)hipEventDestroy(ctx->fork_ev[i]);
+        for (auto &ev : ctx->join_ev[i])
+            if (ev) (void)hipEventDestroy(ev);
     }
     if (ctx->graph_stream) {
         (void)hipStreamSynchronize(ctx->graph_stream);

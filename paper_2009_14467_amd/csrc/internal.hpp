@@ -118,11 +118,12 @@ struct pastis_ctx {
     void *h_pinned = nullptr;
     size_t h_pinned_bytes = 0;
     hipEvent_t ev[2 * 9] = {};
-    hipEvent_t bin_ev[2 * 32] = {};  // around each SW pass-1 bin launch
-    // the multi-strip (long) SW bins run on a second stream, concurrently with
-    // the one-strip bins: fork / join events of pass 1, start bound, statistics
-    hipStream_t long_stream = nullptr;
-    hipEvent_t long_fork[3] = {}, long_join[3] = {};
+    double ms_per_tick = 0.0;  // device wall clock
+    // the SW groups of a pass run beside one another: the multi-strip (long)
+    // bins on the long stream, the others on the call's and the side streams;
+    // fork / join events of pass 1, start bound, statistics
+    hipStream_t long_stream = nullptr, side_stream[3] = {};
+    hipEvent_t fork_ev[3] = {}, join_ev[3][5] = {};
     // graph mode: the SW stage captured on a stream of the context
     hipStream_t graph_stream = nullptr;
     hipEvent_t graph_join[2] = {};
@@ -203,11 +204,16 @@ struct SwPass1Out {
 // ints per wave, for sw_scratch_waves() waves).
 // counters: [0] cells, [1] statistics-pass pairs, [2] their cells, [3]
 // start-bound pairs, [4] their cells, [kCounterXdQueue] the x-drop kernel's
-// work queue, [kCounterBinCells + b] pass-1 cells of SW bin b
+// work queue, [kCounterBinCells + b] and [kCounterBinPairs + b] pass-1 cells
+// and pairs of SW bin b, [kCounterSpan + 2 b ...] the bin's first claim and
+// last finish in device clock ticks (the former complemented)
 constexpr int kCounterXdQueue = 5;
 constexpr int kCounterIntraFlag = 6;  // an intra-pair wait ran out of its bound
+constexpr int kCounterBad = 7;        // a pair index out of range (bit 0)
 constexpr int kCounterBinCells = 8;
-constexpr int kNumCounters = kCounterBinCells + 32;
+constexpr int kCounterBinPairs = kCounterBinCells + 32;
+constexpr int kCounterSpan = kCounterBinPairs + 32;  // two words per bin
+constexpr int kNumCounters = kCounterSpan + 64;
 
 struct SwWork {
     unsigned long long *counters;
@@ -216,11 +222,11 @@ struct SwWork {
     int *idx, *idx2;
     int *scratch;
     int64_t scratch_per_wave;
-    int *queue;  // work-queue counters: pass 1, start bound, statistics, pass 1 of the taller half (32 bins each)
-    // per bin: the first pass-1 item of its taller half (16-bit strip bins of
-    // up to 8 rows per lane split their pairs by rows: up to 64 R - 32 rows,
-    // and more)
-    int *split;
+    int *queue;  // work-queue counters: 16-bit pass 1 (one per bin and rows class), 32-bit pass 1, start bound, statistics
+    // 16-bit pass 1: first item of each (bin, rows class), two per bin (strip
+    // bins of up to 8 rows per lane split their pairs by rows: up to 64 R - 32
+    // rows, and more)
+    int *bounds;
     // pairing of the 16-bit pass (pairs sorted by bin, then longer b first)
     uint64_t *sort_keys = nullptr, *sort_keys_alt = nullptr;
     uint32_t *sort_vals_alt = nullptr;
@@ -243,17 +249,27 @@ void sw_init_occupancy();
 // Sequences a of at most this many rows run in one strip (no boundary rows).
 int sw_one_strip_max_rows();
 
+// The launches of a Smith-Waterman call, planned on the host from the pairs
+// per bin: per group of bins (one-strip bins of 1-4, 5-8, 9-12 and 13-16 rows
+// per lane, multi-strip bins) the blocks of each pass (0: no launch) and the
+// pass-1 bins in 16-bit and in 32-bit lanes.
+struct SwPlan {
+    int max16 = 0, intra = 0, narrow = 0;
+    uint32_t bins16[5] = {}, bins32[5] = {};
+    int blocks16[5] = {}, blocks32[5] = {}, blocks_bound[5] = {}, blocks_stats[5] = {};
+};
 // max16 > 0: pass 1 of one-strip pairs with at most max16 rows per lane in
 // 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
-// that skip the statistics pass.  grid_scale multiplies the pass-1 grids;
-// intra = 1 runs pass 1 of the 32-bit multi-strip bins one workgroup per pair;
-// 16-bit bins of at most narrow16 (<= 4) rows per lane run strips of 16 lanes
-// (eight pairs per wave), the other bins up to 8 rows per lane strips of 32;
-// multi-strip launches take at most long_blocks (1..4) blocks per CU.
+// that skip the statistics pass.  tune: the grid scales of the one-strip
+// groups, intra-pair pass 1 of the 32-bit multi-strip bins, the 16-bit bins
+// in strips of 16 lanes, and the multi-strip grids.
+SwPlan sw_plan(const unsigned long long *bin_pairs, const Scoring &sc, int max16, const pastis_tuning &tune);
+// Bins of the pairs (bin_of, the per-bin counters) and cleared work queues;
+// the counters must be zero before.
+hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &wk, hipStream_t s);
 hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pairs, int64_t npairs,
                      const int8_t *blosum, const Scoring &sc, SwPass1Out *p1, pastis_pair_record *out,
-                     const SwWork &wk, int stats_mode, int max16, int grid_scale, int grid_scale_wide, int intra,
-                     int narrow16, int long_blocks, bool timed, hipStream_t s);
+                     const SwWork &wk, int stats_mode, const SwPlan &plan, bool timed, hipStream_t s);
 // 16-bit pass 1 needs o + e >= 4 (biased scores stay non-negative).
 bool sw16_supported(const Scoring &sc);
 bool sw_bin_is16(int bin, int max16);

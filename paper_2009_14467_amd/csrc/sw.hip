@@ -28,13 +28,13 @@
 // extension before opening; a zero diagonal predecessor starts a new path), so
 // by induction the end cell holds the traceback's statistics.  The strip rows
 // are padded at the top so the end cell is always row R-1 of lane 63.
+
 #include <algorithm>
-#include <type_traits>
+#include <atomic>
 
-#include <utility>
-
-#include "internal.hpp"
+#include "sw_common.hpp"
 #include "prim.hpp"
+#include "sw16.hpp"
 
 namespace pastis {
 
@@ -43,161 +43,38 @@ hipError_t launch_bins(const int8_t *bin_of, int64_t n, int nbins, int *counts, 
 
 namespace {
 
-constexpr int kWave = 64;
-constexpr int kNeg = -(1 << 28);
-// waves per block of the 32-bit kernels: one int8 profile of 25 x 64 x R
-// bytes per wave, blocks of at most ~51 KB of LDS (three per CU)
-__host__ __device__ constexpr int wpb32(int R) { return R <= 8 ? 4 : 2; }
-constexpr int kProfCodes = kAlpha + 1;  // 24 residues + the pad code
-constexpr int kMaxR = 16;               // rows per lane
-constexpr int kSingleBins = kMaxR;      // bins 0..15: one strip of 64 * (bin + 1) rows
-constexpr int kMultiBin = kSingleBins;  // bins 16..23: several strips of 64 * R rows, R = bin - 7
-constexpr int kMultiMinR = kMaxR / 2 + 1;
-// bins 24..31: as 16..23 for sequences a of at most kMax16Rows rows, whose
-// scores (at most 11 per row with BLOSUM62) stay below 2^15
-constexpr int kMulti16Bin = kMultiBin + kMaxR - kMultiMinR + 1;
-constexpr int kNumBins = kMulti16Bin + kMaxR - kMultiMinR + 1;
-constexpr int kMax16Rows = 32767 / 11;
-static_assert(kNumBins <= 32, "bin tables hold 32 entries");
-
-__host__ __device__ constexpr int rows_of_bin(int bin) {
-    return bin >= kMulti16Bin ? bin - kMulti16Bin + kMultiMinR : bin >= kMultiBin ? bin - kMultiBin + kMultiMinR
-                                                                                   : bin + 1;
-}
-constexpr int kDppWaveShr1 = 0x138;
-
-// lane l receives lane l-1's value; lane 0 receives `lane0`
-__device__ __forceinline__ int shr1(int lane0, int v) {
-    return __builtin_amdgcn_update_dpp(lane0, v, kDppWaveShr1, 0xF, 0xF, false);
-}
-
-// lane l receives lane l-1's value; lane 0 receives 0 (the move's bound
-// control zero-fills, so no separate write of lane 0's value is needed)
-__device__ __forceinline__ int shr1z(int v) { return __builtin_amdgcn_update_dpp(0, v, kDppWaveShr1, 0xF, 0xF, true); }
-
-// R int8 scores per lane and residue code, in ceil(R / 4) words
-template <int R>
-using ProfWord = typename std::conditional<
-    (R <= 4), uint32_t,
-    typename std::conditional<(R <= 8), uint2, typename std::conditional<(R <= 12), uint3, uint4>::type>::type>::type;
-
-template <int R>
-__device__ __forceinline__ uint32_t word_of(const ProfWord<R> &w, int k) {
-    if constexpr (R <= 4) {
-        return w;
-    } else if constexpr (R <= 8) {
-        return k == 0 ? w.x : w.y;
-    } else if constexpr (R <= 12) {
-        return k == 0 ? w.x : k == 1 ? w.y : w.z;
-    } else {
-        return k == 0 ? w.x : k == 1 ? w.y : k == 2 ? w.z : w.w;
-    }
-}
-
-template <int R>
-__device__ __forceinline__ ProfWord<R> make_word(const uint32_t (&w)[4]) {
-    if constexpr (R <= 4) {
-        return w[0];
-    } else if constexpr (R <= 8) {
-        return make_uint2(w[0], w[1]);
-    } else if constexpr (R <= 12) {
-        return make_uint3(w[0], w[1], w[2]);
-    } else {
-        return make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
-
-template <int R>
-__device__ __forceinline__ int sigma_at(const ProfWord<R> &w, int r) {
-    return (int)(int8_t)(word_of<R>(w, r >> 2) >> (8 * (r & 3)));
-}
-
-template <int R>
-__device__ __forceinline__ void build_profile(ProfWord<R> (*prof)[kWave], const int8_t *sblosum, const uint8_t *a,
-                                              int la, int base, int lane) {
-    int ar[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) ar[r] = (base + r >= 0 && base + r < la) ? a[base + r] : kPadCode;
-    for (int c = 0; c < kProfCodes; ++c) {
-        uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int r = 0; r < R; ++r) w[r >> 2] |= (uint32_t)(uint8_t)sblosum[ar[r] * kProfCodes + c] << (8 * (r & 3));
-        prof[c][lane] = make_word<R>(w);
-    }
-}
-
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
-        unsigned olo = __shfl_xor(lo, off, kWave), ohi = __shfl_xor(hi, off, kWave);
-        unsigned long long o = ((unsigned long long)ohi << 32) | olo;
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
-__device__ __forceinline__ void load_blosum(int8_t *sblosum, const int8_t *blosum) {
-    for (int t = threadIdx.x; t < kProfCodes * kProfCodes; t += blockDim.x) sblosum[t] = blosum[t];
-    __syncthreads();
-}
-
-// A load the compiler must issue per lane through the vector memory path (the
-// data was written by another lane of the same wave earlier in the kernel).
-template <typename T>
-__device__ __forceinline__ T vload(const T *p) {
-    return __builtin_nontemporal_load(p);
-}
-
-// A wave's next window of `count` consecutive items of its bin: lane 0 claims
-// it from the bin's queue counter (zeroed before the launch), so that a
-// resident grid stays busy until the bin is empty, waves that finish early
-// taking more work.  The counter is claimed by a vector atomic.
-__device__ __forceinline__ int64_t take(int *queue, const int *starts, int bin, int count) {
-    int v = 0;
-    if ((threadIdx.x & (kWave - 1)) == 0) v = atomicAdd(queue + bin, count);
-    return starts[bin] + (int64_t)__builtin_amdgcn_readfirstlane(v);
-}
-
-// the same from a counter of its own over items [begin, ...)
-__device__ __forceinline__ int64_t take_from(int *counter, int begin, int count) {
-    int v = 0;
-    if ((threadIdx.x & (kWave - 1)) == 0) v = atomicAdd(counter, count);
-    return begin + (int64_t)__builtin_amdgcn_readfirstlane(v);
-}
-
-// ---------------------------------------------------------------- pass 1
-
-// max(x - y, 0) for x >= 0, y >= 0 (one clamped subtract)
-__device__ __forceinline__ int subs(int x, int y) {
-    return (int)__builtin_elementwise_sub_sat((unsigned)x, (unsigned)y);
-}
+// ---------------------------------------------------------------- pass 1, 32-bit lanes
 
 // Pass 1, 32-bit lanes.  The gap states are kept floored at zero, E' =
 // max(E, 0) and F' = max(F, 0) (max(E' - e, 0) = max(E - e, 0) for e >= 0,
 // one clamped subtract); max(d, E', F') then already holds the local
 // alignment's zero.  The strip boundary carries F'.
+// One bin's work; the group kernels below run the bodies of several bins.
 template <int R, bool MULTI>
-__global__ __launch_bounds__(64 * wpb32(R)) void sw_pass1_kernel(const uint8_t *__restrict__ codes,
-                                                       const PairDesc *__restrict__ pairs,
-                                                       const int *__restrict__ idx, const int *__restrict__ starts,
-                                                       int bin, const int8_t *__restrict__ blosum, int go_ge, int ge,
-                                                       SwPass1Out *__restrict__ out, int *__restrict__ scratch,
-                                                       int64_t scratch_per_wave, int *queue) {
+__device__ __forceinline__ bool pass1_body(const SwArgs &A, int bin, char *lds, size_t wave_bytes,
+                                           const int8_t *sblosum) {
     constexpr int WPB = wpb32(R);
-    __shared__ ProfWord<R> prof_all[WPB][kProfCodes][kWave];
-    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
-    load_blosum(sblosum, blosum);
+    const uint8_t *__restrict__ codes = A.codes;
+    const PairDesc *__restrict__ pairs = A.pairs;
+    const int *__restrict__ idx = A.idx, *__restrict__ starts = A.starts;
+    const int go_ge = A.go_ge, ge = A.ge;
+    SwPass1Out *__restrict__ out = A.p1;
+    int *queue = A.queue;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    ProfWord<R>(*prof)[kWave] = prof_all[wave];
+    // waves of a block may be in bins of different profile sizes: each has a
+    // fixed share of the block's LDS
+    ProfWord<R>(*prof)[kWave] = (ProfWord<R>(*)[kWave])(lds + (size_t)wave * wave_bytes);
     const int64_t gwave = (int64_t)blockIdx.x * WPB + wave;
-    int *bnd_h = scratch + gwave * scratch_per_wave;  // bottom row H / F of the strip above
-    int *bnd_f = bnd_h + scratch_per_wave / 2;
+    int *bnd_h = A.scratch + gwave * A.scratch_per_wave;  // bottom row H / F of the strip above
+    int *bnd_f = bnd_h + A.scratch_per_wave / 2;
     const int item_end = starts[bin + 1];
     constexpr int RS = kWave * R;
 
+    bool any = false;  // this wave had work in the bin
+
     for (int64_t w = take(queue, starts, bin, 1); w < item_end; w = take(queue, starts, bin, 1)) {
+        any = true;
         const int q = idx[w];
         const PairDesc pd = pairs[q];
         const uint8_t *a = codes + pd.a_off;
@@ -328,6 +205,7 @@ __global__ __launch_bounds__(64 * wpb32(R)) void sw_pass1_kernel(const uint8_t *
             out[q] = o;
         }
     }
+    return any;
 }
 
 // ---------------------------------------------------------------- pass 1, one workgroup per long pair
@@ -350,6 +228,12 @@ __global__ __launch_bounds__(64 * wpb32(R)) void sw_pass1_kernel(const uint8_t *
 constexpr int kIntraWaves = 4;
 constexpr int kIntraSpinLimit = 1 << 24;
 
+struct IntraLds {
+    int prod[kIntraWaves], cons[kIntraWaves];
+    unsigned long long best[kIntraWaves];
+    int take;
+};
+
 __device__ __forceinline__ int lds_acquire(int *p) {
     return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -366,20 +250,24 @@ __device__ __forceinline__ bool lds_wait(int *p, int need) {
 }
 
 template <int R>
-__global__ __launch_bounds__(64 * kIntraWaves) void sw_intra_pass1_kernel(
-    const uint8_t *__restrict__ codes, const PairDesc *__restrict__ pairs, const int *__restrict__ idx,
-    const int *__restrict__ starts, int bin, const int8_t *__restrict__ blosum, int go_ge, int ge,
-    SwPass1Out *__restrict__ out, int *scratch, int64_t scratch_per_wave, int *queue, unsigned long long *flag) {
+__device__ __forceinline__ bool intra_body(const SwArgs &A, int bin, char *lds, size_t wave_bytes,
+                                           const int8_t *sblosum, IntraLds &L) {
     constexpr int W = kIntraWaves;
-    __shared__ ProfWord<R> prof_all[W][kProfCodes][kWave];
-    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
-    __shared__ int prod[W], cons[W];
-    __shared__ unsigned long long s_best[W];
-    __shared__ int s_take;
-    load_blosum(sblosum, blosum);
+    const uint8_t *__restrict__ codes = A.codes;
+    const PairDesc *__restrict__ pairs = A.pairs;
+    const int *__restrict__ idx = A.idx, *__restrict__ starts = A.starts;
+    const int go_ge = A.go_ge, ge = A.ge;
+    SwPass1Out *__restrict__ out = A.p1;
+    int *scratch = A.scratch;
+    const int64_t scratch_per_wave = A.scratch_per_wave;
+    int *queue = A.queue;
+    unsigned long long *flag = A.flag;
+    int *const prod = L.prod, *const cons = L.cons;
+    unsigned long long *const s_best = L.best;
+    int &s_take = L.take;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    ProfWord<R>(*prof)[kWave] = prof_all[wave];
+    ProfWord<R>(*prof)[kWave] = (ProfWord<R>(*)[kWave])(lds + (size_t)wave * wave_bytes);
     const int item_end = starts[bin + 1];
     constexpr int RS = kWave * R;
     const int in_slot = (wave + W - 1) % W;  // the slot this wave's strips read
@@ -388,6 +276,8 @@ __global__ __launch_bounds__(64 * kIntraWaves) void sw_intra_pass1_kernel(
     int *const out_f = out_h + scratch_per_wave / 2;
     const int *const in_h = scratch + ((int64_t)blockIdx.x * W + in_slot) * scratch_per_wave;
     const int *const in_f = in_h + scratch_per_wave / 2;
+
+    bool any = false;
 
     for (;;) {
         // every wave is past the last pair (the barrier at its end), so the
@@ -400,6 +290,7 @@ __global__ __launch_bounds__(64 * kIntraWaves) void sw_intra_pass1_kernel(
         __syncthreads();
         const int64_t w = starts[bin] + s_take;
         if (w >= item_end) break;
+        any = true;
         const int q = idx[w];
         const PairDesc pd = pairs[q];
         const uint8_t *a = codes + pd.a_off;
@@ -526,524 +417,7 @@ __global__ __launch_bounds__(64 * kIntraWaves) void sw_intra_pass1_kernel(
         }
         __syncthreads();
     }
-}
-
-// ---------------------------------------------------------------- pass 1, 16-bit lanes
-
-// Two pairs per wave in the 16-bit halves of every DP word (pair P low, Q
-// high), same lane layout as the 32-bit pass, one strip (R <= 16).  The two
-// pairs share their shorter sequence a (pairs are sorted by bin, then a, then
-// the longer b first), so one int8 profile serves both; a wave whose two
-// items differ in a runs them one after the other.  Only G = H - (o + e) is
-// kept per row: the diagonal term H(i-1, j-1) + s becomes G(i-1, j-1) +
-// (s + o + e), with the biased scores s + o + e >= 0 in the profile (each
-// row's two bytes are spread into the halves by one byte permute).  Padding
-// residues score -(o + e).  Each row keeps only its maximum: cells outside a
-// pair (padding rows and columns, columns before the first) score strictly
-// below its best real cell, so the score and the first row holding it are
-// exact; the end column is found later, for the pairs that need it (end_b =
-// -1 here).  Scores stay below 11 * 1024, far from the 16-bit limit.
-// The gap states are kept floored at zero, E' = max(E, 0) and F' = max(F, 0):
-// their recurrences stay closed (max(E' - e, 0) = max(E - e, 0) for e >= 0,
-// one saturating subtract), and max(d, E', F') then already holds the local
-// alignment's zero, so a cell takes 10 packed ops instead of 11.
-constexpr int kMax16R = kMaxR;
-
-typedef short short2_t __attribute__((ext_vector_type(2)));
-typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ short2_t s2(uint32_t x) { return __builtin_bit_cast(short2_t, x); }
-// max(x - y, 0) per half, for 0 <= x < 2^15
-__device__ __forceinline__ short2_t psubs(short2_t x, uint32_t y) {
-    return __builtin_bit_cast(short2_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(ushort2_t, x),
-                                                                      __builtin_bit_cast(ushort2_t, y)));
-}
-__device__ __forceinline__ uint32_t u2(short2_t x) { return __builtin_bit_cast(uint32_t, x); }
-__device__ __forceinline__ short2_t pmax(short2_t a, short2_t b) { return __builtin_elementwise_max(a, b); }
-__device__ __forceinline__ int shr1u(uint32_t lane0, uint32_t v) { return shr1((int)lane0, (int)v); }
-
-// 16-bit profile: entry [c][p] holds the biased scores s + o + e >= 0 (pad
-// rows: 0) of rows p * RP .. p * RP + RP - 1 of a against code c, one byte
-// each.  The calling thread writes the codes c = group (mod NG) for position
-// pos; NG groups of threads together cover all codes.
-template <int RP, int W, int NG>
-__device__ __forceinline__ void build_profile16(ProfWord<RP> (*prof)[W], const int8_t *sblosum, const uint8_t *a,
-                                                int la, int pos, int group, int oe) {
-    int ar[RP];
-#pragma unroll
-    for (int r = 0; r < RP; ++r) ar[r] = (pos * RP + r < la) ? a[pos * RP + r] : kPadCode;
-    for (int c = group; c < kProfCodes; c += NG) {
-        uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int r = 0; r < RP; ++r) {
-            const int sc = max((int)sblosum[ar[r] * kProfCodes + c], -oe) + oe;
-            w[r >> 2] |= (uint32_t)sc << (8 * (r & 3));
-        }
-        prof[c][pos] = make_word<RP>(w);
-    }
-}
-
-template <int R>
-__device__ __forceinline__ uint32_t prof_word(const ProfWord<R> &w, int r) {
-    return word_of<R>(w, r >> 2);
-}
-
-__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = max(v, (unsigned)__shfl_xor((int)v, off, kWave));
-    return v;
-}
-
-
-// Full-wave layout for the wider bins.  A block takes 2 * WPB consecutive
-// pairs (two per wave) and its waves share one profile, built once per
-// distinct sequence a among them (pairs are sorted by a), so the LDS of a
-// block does not grow with its wave count.  MULTI: sequences a of more than
-// 1024 rows (and at most kMax16Rows, so that scores stay below 2^15) run in
-// strips of 64 R rows, one after the other; lane 63 leaves the G and F' words
-// of the strip's bottom row for every column in a per-wave buffer, and lane 0
-// reads them back as the top boundary of the next strip.
-template <int R, int WPB, bool MULTI>
-__global__ __launch_bounds__(64 * WPB) void sw16_pass1_kernel(const uint8_t *__restrict__ codes,
-                                                              const PairDesc *__restrict__ pairs,
-                                                              const int *__restrict__ idx,
-                                                              const int *__restrict__ starts, int bin,
-                                                              const int8_t *__restrict__ blosum, int go_ge, int ge,
-                                                              SwPass1Out *__restrict__ out, uint32_t *scratch,
-                                                              int64_t scratch_per_wave, int *queue) {
-    static_assert(R > 8 && R <= kMax16R, "more than 512 rows per strip");
-    constexpr int NI = 2 * WPB;  // pairs per block
-    constexpr int RS = kWave * R;  // rows per strip
-    __shared__ ProfWord<R> prof[kProfCodes][kWave];
-    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
-    // first unfinished pair of each wave, double-buffered by round parity so
-    // that a round's writes never meet the previous round's reads
-    __shared__ int s_next[2][WPB];
-    __shared__ int s_take;  // the block's window, claimed from the bin's queue
-    load_blosum(sblosum, blosum);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int item_end = starts[bin + 1];
-    const uint32_t OE2 = (uint32_t)go_ge * 0x10001u, GE2 = (uint32_t)ge * 0x10001u;
-    const uint32_t G0 = ((uint32_t)(-go_ge) & 0xFFFFu) * 0x10001u;  // G of an H = 0 cell
-    uint32_t *bnd_g = nullptr, *bnd_f = nullptr;
-    if constexpr (MULTI) {
-        bnd_g = scratch + ((int64_t)blockIdx.x * WPB + wave) * scratch_per_wave;
-        bnd_f = bnd_g + scratch_per_wave / 2;
-    }
-    int par = 0;
-
-    for (;;) {
-        // every thread has read the last window before the round loop's
-        // first barrier, so thread 0 may claim the next one
-        if (threadIdx.x == 0) s_take = atomicAdd(queue + bin, NI);
-        __syncthreads();
-        const int64_t w = starts[bin] + s_take;
-        if (w >= item_end) break;
-        const int nit = (int)min((int64_t)NI, item_end - w);
-        const int iP = 2 * wave, iQ = iP + 1;
-        const int qP = iP < nit ? idx[w + iP] : -1;
-        const int qQ = iQ < nit ? idx[w + iQ] : -1;
-        const int q0 = idx[w];
-        const PairDesc dP = pairs[qP < 0 ? q0 : qP], dQ = pairs[qQ < 0 ? q0 : qQ];
-        bool doneP = qP < 0, doneQ = qQ < 0;
-        for (;;) {
-            // this round's sequence a: that of the block's first unfinished pair
-            if (lane == 0) s_next[par][wave] = !doneP ? iP : !doneQ ? iQ : NI;
-            __syncthreads();
-            int first = NI;
-#pragma unroll
-            for (int k = 0; k < WPB; ++k) first = min(first, s_next[par][k]);
-            par ^= 1;
-            if (first >= NI) break;
-            const PairDesc dA = pairs[idx[w + first]];
-            const bool actP = !doneP && dP.a_seq == dA.a_seq;
-            const bool actQ = !doneQ && dQ.a_seq == dA.a_seq;
-            const int laA = dA.la, lbP = actP ? dP.lb : 0, lbQ = actQ ? dQ.lb : 0;
-            const uint8_t *bP = codes + dP.b_off, *bQ = codes + dQ.b_off;
-            const int lb = max(lbP, lbQ);
-            const int steps = lb > 0 ? lb + kWave - 1 : 0;
-            const int nstrips = MULTI ? (laA + RS - 1) / RS : 1;
-            // best row of each pair: (score << 16) | (0xFFFF - row), maximised
-            unsigned kp = 0u, kq = 0u;
-            for (int sidx = 0; sidx < nstrips; ++sidx) {
-                const int base = sidx * RS;
-                if (sidx > 0) __syncthreads();  // every wave is done with the last strip's profile
-                build_profile16<R, kWave, WPB>(prof, sblosum, codes + dA.a_off + base, laA - base, lane, wave,
-                                               go_ge);
-                __syncthreads();
-                const bool from_above = MULTI && sidx > 0;
-                const bool to_below = MULTI && sidx + 1 < nstrips;
-                uint32_t G[R], E[R], M[R];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    G[r] = G0;
-                    E[r] = 0u;
-                    M[r] = 0u;
-                }
-                uint32_t glast = G0, flast = 0u, gprev = G0;
-                // column residues travel as byte offsets into the profile, P's
-                // in the low half and Q's in the high half (at most 24 * 1024)
-                constexpr uint32_t kStride = (uint32_t)(sizeof(ProfWord<R>) * kWave);
-                const char *plane = (const char *)&prof[0][lane];
-                int cres = (int)((kPadCode * kStride) * 0x10001u);
-                auto col = [&](int c) {
-                    const uint32_t x = c < lbP ? (uint32_t)bP[c] : (uint32_t)kPadCode;
-                    const uint32_t y = c < lbQ ? (uint32_t)bQ[c] : (uint32_t)kPadCode;
-                    return (int)((x * kStride) | ((y * kStride) << 16));
-                };
-                int chunk = col(lane);  // columns 0..63; nx holds the next 64
-                int nx = col(kWave + lane);
-                // top boundary words of columns 0..63 and 64..127 (columns past
-                // lb: an H = 0 row above)
-                uint32_t ch_g = G0, ch_f = 0u, nx_g = G0, nx_f = 0u;
-                if (from_above) {
-                    if (lane < lb) {
-                        ch_g = vload(bnd_g + lane);
-                        ch_f = vload(bnd_f + lane);
-                    }
-                    if (kWave + lane < lb) {
-                        nx_g = vload(bnd_g + kWave + lane);
-                        nx_f = vload(bnd_f + kWave + lane);
-                    }
-                }
-                // kTop: lane 0 takes its top boundary from the buffer (t < lb)
-                auto step = [&](const int t, auto top_tag) {
-                    constexpr bool kTop = decltype(top_tag)::value;
-                    if ((t & (kWave - 1)) == 0 && t > 0) {
-                        chunk = nx;
-                        nx = col(t + kWave + lane);
-                        if constexpr (kTop) {
-                            ch_g = nx_g;
-                            ch_f = nx_f;
-                            const int c = t + kWave + lane;
-                            nx_g = c < lb ? vload(bnd_g + c) : G0;
-                            nx_f = c < lb ? vload(bnd_f + c) : 0u;
-                        }
-                    }
-                    const int bt = __builtin_amdgcn_readlane(chunk, t & (kWave - 1));
-                    uint32_t rg, rf;
-                    if constexpr (kTop) {
-                        rg = (uint32_t)shr1u((uint32_t)__builtin_amdgcn_readlane((int)ch_g, t & (kWave - 1)), glast);
-                        rf = (uint32_t)shr1u((uint32_t)__builtin_amdgcn_readlane((int)ch_f, t & (kWave - 1)), flast);
-                    } else {
-                        rg = (uint32_t)shr1u(G0, glast);
-                        rf = (uint32_t)shr1z((int)flast);
-                    }
-                    cres = shr1(bt, cres);
-                    const ProfWord<R> cP = *(const ProfWord<R> *)(plane + ((uint32_t)cres & 0xFFFFu));
-                    const ProfWord<R> cQ = *(const ProfWord<R> *)(plane + ((uint32_t)cres >> 16));
-                    short2_t gd = s2(gprev), gu = s2(rg), fu = s2(rf);
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        // byte r of P's and Q's words into the two halves
-                        const uint32_t sel =
-                            (uint32_t)(r & 3) | 0x0C00u | ((uint32_t)(4 + (r & 3)) << 16) | 0x0C000000u;
-                        const short2_t sig =
-                            s2(__builtin_amdgcn_perm(prof_word<R>(cQ, r), prof_word<R>(cP, r), sel));
-                        const short2_t e = pmax(psubs(s2(E[r]), GE2), s2(G[r]));
-                        const short2_t f = pmax(psubs(fu, GE2), gu);
-                        const short2_t d = gd + sig;
-                        const short2_t h = pmax(d, pmax(e, f));
-                        gd = s2(G[r]);
-                        const short2_t g = h - s2(OE2);
-                        G[r] = u2(g);
-                        E[r] = u2(e);
-                        M[r] = u2(pmax(s2(M[r]), h));
-                        gu = g;
-                        fu = f;
-                    }
-                    glast = G[R - 1];
-                    flast = u2(fu);
-                    gprev = rg;
-                    if (to_below) {
-                        const int j = t - (kWave - 1);
-                        if (lane == kWave - 1 && j >= 0 && j < lb) {
-                            bnd_g[j] = glast;
-                            bnd_f[j] = flast;
-                        }
-                    }
-                };
-                // two steps per iteration, so the old and new G registers can
-                // swap roles instead of being copied back every step
-                int t = 0;
-                if (from_above) {
-                    for (; t + 1 < lb; t += 2) {
-                        step(t, std::true_type{});
-                        step(t + 1, std::true_type{});
-                    }
-                    if (t < lb) step(t++, std::true_type{});
-                }
-                for (; t + 1 < steps; t += 2) {
-                    step(t, std::false_type{});
-                    step(t + 1, std::false_type{});
-                }
-                if (t < steps) step(t, std::false_type{});
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int row = base + lane * R + r;
-                    const unsigned rk = 0xFFFFu - (unsigned)row;
-                    if (row < laA) {
-                        kp = max(kp, ((M[r] & 0xFFFFu) << 16) | rk);
-                        kq = max(kq, (M[r] & 0xFFFF0000u) | rk);
-                    }
-                }
-                if (to_below) __threadfence_block();  // lane 0 of the next strip reads lane 63's row
-            }
-            kp = wave_max_u32(kp);
-            kq = wave_max_u32(kq);
-            if (lane == 0) {
-                SwPass1Out o;
-                o.end_b = -1;
-                o.pad = 0;
-                if (actP) {
-                    o.score = (int32_t)(kp >> 16);
-                    o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kp & 0xFFFFu)) : -1;
-                    out[qP] = o;
-                }
-                if (actQ) {
-                    o.score = (int32_t)(kq >> 16);
-                    o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kq & 0xFFFFu)) : -1;
-                    out[qQ] = o;
-                }
-            }
-            doneP = doneP || actP;
-            doneQ = doneQ || actQ;
-        }
-    }
-}
-
-// ---------------------------------------------------------------- pass 1, 16-bit lanes, strips of S lanes
-
-// For short sequences a the wave splits into 64 / S independent strips of S
-// lanes (S = 16 or 32).  Each strip runs two pairs of the wave's sequence a in
-// the halves of its words, with the same recurrence as above; lane p of a
-// strip owns rows [p * RP, p * RP + RP), so a bin of 64 R rows takes RP =
-// 64 R / S rows per lane.  A pair then pays S - 1 steps of wavefront fill and
-// drain instead of 63, and the fixed work of a step (lane shifts, residue and
-// profile fetches) serves 64 / S times more cells.  All strips read one
-// profile of 25 codes x S lanes.  Column residues enter at a strip's first
-// lane from a chunk of 16 columns held across the strip's first 16 lanes,
-// rotated by one lane per step.
-constexpr int kDppRowShr1 = 0x111;
-constexpr int kDppRowRor15 = 0x12F;
-
-// lane p of a strip receives lane p - 1's value; the strip's first lane
-// receives `first`
-template <int S>
-__device__ __forceinline__ uint32_t strip_shr(uint32_t first, uint32_t v, int lane) {
-    if constexpr (S == 16) {
-        return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, kDppRowShr1, 0xF, 0xF, false);
-    } else {
-        // a zero-filled shift writes every lane (no prior value of the result
-        // is needed); the strips' first lanes, 0 and 32, then take `first`
-        const uint32_t t = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kDppWaveShr1, 0xF, 0xF, true);
-        return (lane & (S - 1)) == 0 ? first : t;
-    }
-}
-
-// as strip_shr with first = 0 (zero-filled by the move's bound control)
-template <int S>
-__device__ __forceinline__ uint32_t strip_shrz(uint32_t v, int lane) {
-    if constexpr (S == 16) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppRowShr1, 0xF, 0xF, true);
-    } else {
-        const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppWaveShr1, 0xF, 0xF, true);
-        return lane == kWave / 2 ? 0u : t;
-    }
-}
-
-template <int S>
-__device__ __forceinline__ unsigned strip_max_u32(unsigned v) {
-#pragma unroll
-    for (int off = S / 2; off > 0; off >>= 1) v = max(v, (unsigned)__shfl_xor((int)v, off, kWave));
-    return v;
-}
-
-__device__ __forceinline__ int wave_min_i32(int v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
-__device__ __forceinline__ int wave_max_i32(int v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
-
-// One launch takes one half of a bin's pairs (sorted by rows class first):
-// half 0 the items [starts[bin], split[bin]), half 1 [split[bin],
-// starts[bin + 1]), each with its own work-queue counter.
-template <int S, int RP, int WPB>
-__global__ __launch_bounds__(64 * WPB) void sw16s_pass1_kernel(const uint8_t *__restrict__ codes,
-                                                               const PairDesc *__restrict__ pairs,
-                                                               const int *__restrict__ idx,
-                                                               const int *__restrict__ starts,
-                                                               const int *__restrict__ split, int bin, int half,
-                                                               const int8_t *__restrict__ blosum, int go_ge, int ge,
-                                                               SwPass1Out *__restrict__ out, int *queue) {
-    static_assert((S == 16 || S == 32) && RP <= kMax16R, "strip shape");
-    constexpr int NI = 2 * kWave / S;  // pairs per wave: two per strip
-    __shared__ ProfWord<RP> prof_all[WPB][kProfCodes][S];
-    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
-    load_blosum(sblosum, blosum);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int pos = lane % S, strip = lane / S, cl = lane & 15;
-    ProfWord<RP>(*prof)[S] = prof_all[wave];
-    const int item_begin = half ? split[bin] : starts[bin];
-    const int item_end = half ? starts[bin + 1] : split[bin];
-    int *const counter = queue + (half ? 3 * kNumBins : 0) + bin;
-    const uint32_t OE2 = (uint32_t)go_ge * 0x10001u, GE2 = (uint32_t)ge * 0x10001u;
-    const uint32_t G0 = ((uint32_t)(-go_ge) & 0xFFFFu) * 0x10001u;  // G of an H = 0 cell
-
-    for (int64_t w = take_from(counter, item_begin, NI); w < item_end; w = take_from(counter, item_begin, NI)) {
-        const int nit = (int)min((int64_t)NI, item_end - w);
-        const int iP = 2 * strip, iQ = iP + 1;
-        const int qP = iP < nit ? idx[w + iP] : -1;
-        const int qQ = iQ < nit ? idx[w + iQ] : -1;
-        const int q0 = idx[w];
-        const PairDesc dP = pairs[qP < 0 ? q0 : qP], dQ = pairs[qQ < 0 ? q0 : qQ];
-        bool doneP = qP < 0, doneQ = qQ < 0;
-        // one round per distinct sequence a among the wave's pairs (pairs are
-        // sorted by a, so nearly always one)
-        for (;;) {
-            const int mine = !doneP ? iP : !doneQ ? iQ : NI;
-            const int first = __builtin_amdgcn_readfirstlane(wave_min_i32(mine));
-            if (first >= NI) break;
-            const int src = (first >> 1) * S;
-            const bool fq = (first & 1) != 0;
-            const int a_seq = __builtin_amdgcn_readlane(fq ? dQ.a_seq : dP.a_seq, src);
-            const int la = __builtin_amdgcn_readlane(fq ? dQ.la : dP.la, src);
-            const int64_t a_off_v = fq ? dQ.a_off : dP.a_off;
-            const uint32_t off_lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)a_off_v, src);
-            const uint32_t off_hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(a_off_v >> 32), src);
-            const int64_t a_off = (int64_t)(((uint64_t)off_hi << 32) | off_lo);
-            const bool actP = !doneP && dP.a_seq == a_seq;
-            const bool actQ = !doneQ && dQ.a_seq == a_seq;
-            const int lbP = actP ? dP.lb : 0, lbQ = actQ ? dQ.lb : 0;
-            const uint8_t *bP = codes + dP.b_off, *bQ = codes + dQ.b_off;
-            build_profile16<RP, S, kWave / S>(prof, sblosum, codes + a_off, la, pos, strip, go_ge);
-            // lanes read entries written by other lanes of the wave (LDS
-            // operations of one wave complete in order)
-            __builtin_amdgcn_wave_barrier();
-            const int lbmax = wave_max_i32(max(lbP, lbQ));
-            const int steps = __builtin_amdgcn_readfirstlane(lbmax > 0 ? lbmax + S - 1 : 0);
-            uint32_t G[RP], E[RP], M[RP];
-#pragma unroll
-            for (int r = 0; r < RP; ++r) {
-                G[r] = G0;
-                E[r] = 0u;
-                M[r] = 0u;
-            }
-            uint32_t glast = G0, flast = 0u, gprev = G0;
-            // column residues travel as byte offsets into the profile, P's in
-            // the low half and Q's in the high half (at most 24 * 512 bytes)
-            constexpr uint32_t kStride = (uint32_t)(sizeof(ProfWord<RP>) * S);
-            const char *plane = (const char *)&prof[0][pos];
-            uint32_t cres = (kPadCode * kStride) * 0x10001u;
-            auto col = [&](int c) -> uint32_t {
-                const uint32_t x = c < lbP ? (uint32_t)bP[c] : (uint32_t)kPadCode;
-                const uint32_t y = c < lbQ ? (uint32_t)bQ[c] : (uint32_t)kPadCode;
-                return (x * kStride) | ((y * kStride) << 16);
-            };
-            auto at = [&](uint32_t off) { return *(const ProfWord<RP> *)(plane + off); };
-            uint32_t chunk = col(cl);  // columns 0..15; nx holds the next 16
-            uint32_t nx = col(16 + cl);
-            // the residues of step tn enter at each strip's first lane
-            auto feed = [&](const int tn) {
-                if ((tn & 15) == 0 && tn > 0) {
-                    chunk = nx;
-                    nx = col(tn + 16 + cl);
-                }
-                cres = strip_shr<S>(chunk, cres, lane);
-                chunk = (uint32_t)__builtin_amdgcn_mov_dpp((int)chunk, kDppRowRor15, 0xF, 0xF, false);
-            };
-            // as in the full-wave kernel: with few rows per lane the profile
-            // words of step t + 1 are loaded during step t
-            constexpr bool kAhead = RP <= 8;
-            ProfWord<RP> wP = prof[kPadCode][pos], wQ = wP;
-            auto step = [&](const int t) {
-                const uint32_t rg = strip_shr<S>(G0, glast, lane);
-                const uint32_t rf = strip_shrz<S>(flast, lane);
-                ProfWord<RP> cP, cQ;
-                if constexpr (kAhead) {
-                    feed(t + 1);
-                    cP = wP;
-                    cQ = wQ;
-                    wP = at(cres & 0xFFFFu);
-                    wQ = at(cres >> 16);
-                } else {
-                    feed(t);
-                    cP = at(cres & 0xFFFFu);
-                    cQ = at(cres >> 16);
-                }
-                short2_t gd = s2(gprev), gu = s2(rg), fu = s2(rf);
-#pragma unroll
-                for (int r = 0; r < RP; ++r) {
-                    const uint32_t sel =
-                        (uint32_t)(r & 3) | 0x0C00u | ((uint32_t)(4 + (r & 3)) << 16) | 0x0C000000u;
-                    const short2_t sig = s2(__builtin_amdgcn_perm(prof_word<RP>(cQ, r), prof_word<RP>(cP, r), sel));
-                    const short2_t e = pmax(psubs(s2(E[r]), GE2), s2(G[r]));
-                    const short2_t f = pmax(psubs(fu, GE2), gu);
-                    const short2_t d = gd + sig;
-                    const short2_t h = pmax(d, pmax(e, f));
-                    gd = s2(G[r]);
-                    const short2_t g = h - s2(OE2);
-                    G[r] = u2(g);
-                    E[r] = u2(e);
-                    M[r] = u2(pmax(s2(M[r]), h));
-                    gu = g;
-                    fu = f;
-                }
-                glast = G[RP - 1];
-                flast = u2(fu);
-                gprev = rg;
-            };
-            if constexpr (kAhead) {
-                feed(0);
-                wP = at(cres & 0xFFFFu);
-                wQ = at(cres >> 16);
-            }
-            int t = 0;
-            for (; t + 1 < steps; t += 2) {
-                step(t);
-                step(t + 1);
-            }
-            if (t < steps) step(t);
-            unsigned kp = 0u, kq = 0u;
-#pragma unroll
-            for (int r = 0; r < RP; ++r) {
-                const int row = pos * RP + r;
-                const unsigned rk = 0xFFFFu - (unsigned)row;
-                if (row < la) {
-                    kp = max(kp, ((M[r] & 0xFFFFu) << 16) | rk);
-                    kq = max(kq, (M[r] & 0xFFFF0000u) | rk);
-                }
-            }
-            kp = strip_max_u32<S>(kp);
-            kq = strip_max_u32<S>(kq);
-            if (pos == 0) {
-                SwPass1Out o;
-                o.end_b = -1;
-                o.pad = 0;
-                if (actP) {
-                    o.score = (int32_t)(kp >> 16);
-                    o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kp & 0xFFFFu)) : -1;
-                    out[qP] = o;
-                }
-                if (actQ) {
-                    o.score = (int32_t)(kq >> 16);
-                    o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kq & 0xFFFFu)) : -1;
-                    out[qQ] = o;
-                }
-            }
-            doneP = doneP || actP;
-            doneQ = doneQ || actQ;
-        }
-    }
+    return any;
 }
 
 // sort keys of the pairing: bin, then the rows class (strip bins of up to
@@ -1065,22 +439,24 @@ __global__ void sw_pair_keys_kernel(const PairDesc *__restrict__ pairs, const in
     vals[q] = (uint32_t)q;
 }
 
-// split[bin] = the first sorted item of the bin's rows class 1 (a lower
-// bound over the bin's keys)
-__global__ void sw_split_kernel(const uint64_t *__restrict__ keys, const int *__restrict__ starts,
-                                int *__restrict__ split) {
-    const int bin = threadIdx.x;
-    if (bin >= kNumBins) return;
-    int lo = starts[bin], hi = starts[bin + 1];
-    const uint64_t k1 = (uint64_t)(2 * bin + 1) << 40;
+// Bounds of the sorted items: class c of bin b holds [bounds[2 b + c],
+// bounds[2 b + c + 1]) (lower bounds over the keys), and starts[b] =
+// bounds[2 b] for the kernels that take a bin's items whole.
+__global__ void sw_bounds_kernel(const uint64_t *__restrict__ keys, int npairs, int *__restrict__ bounds,
+                                 int *__restrict__ starts) {
+    const int k = threadIdx.x;
+    if (k > 2 * kNumBins) return;
+    int lo = 0, hi = npairs;
+    const uint64_t key = (uint64_t)k << 40;
     while (lo < hi) {
         const int mid = lo + (hi - lo) / 2;
-        if (keys[mid] < k1)
+        if (keys[mid] < key)
             lo = mid + 1;
         else
             hi = mid;
     }
-    split[bin] = lo;
+    bounds[k] = lo;
+    if ((k & 1) == 0) starts[k / 2] = lo;
 }
 
 // ---------------------------------------------------------------- between the passes
@@ -1098,13 +474,18 @@ __device__ __forceinline__ int rows_bin(int rows) {
 }
 
 // Bins by rows per lane; counters[0] += DP cells of the pairs, and
-// counters[kCounterBinCells + bin] += those of each bin.
+// counters[kCounterBinCells + bin] / [kCounterBinPairs + bin] += the cells and
+// pairs of each bin (the host plans the launches from the latter).
 __global__ void sw_bin1_kernel(const PairDesc *__restrict__ pairs, int64_t npairs, int8_t *__restrict__ bin_of,
                                unsigned long long *__restrict__ counters, int *__restrict__ queue) {
-    // the work queues of this call's launches (pass 1, start bound, statistics)
-    if (blockIdx.x == 0 && threadIdx.x < 4 * kNumBins) queue[threadIdx.x] = 0;
+    // the work queues of this call's launches
+    if (blockIdx.x == 0 && threadIdx.x < kSwQueues) queue[threadIdx.x] = 0;
     __shared__ unsigned long long cells[kNumBins];
-    if (threadIdx.x < kNumBins) cells[threadIdx.x] = 0;
+    __shared__ unsigned count[kNumBins];
+    if (threadIdx.x < kNumBins) {
+        cells[threadIdx.x] = 0;
+        count[threadIdx.x] = 0;
+    }
     __syncthreads();
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q < npairs) {
@@ -1112,11 +493,13 @@ __global__ void sw_bin1_kernel(const PairDesc *__restrict__ pairs, int64_t npair
         const int bin = rows_bin(pd.la);
         bin_of[q] = (int8_t)bin;
         atomicAdd(&cells[bin], (unsigned long long)pd.la * (unsigned long long)pd.lb);
+        atomicAdd(&count[bin], 1u);
     }
     __syncthreads();
-    if (threadIdx.x < kNumBins && cells[threadIdx.x]) {
+    if (threadIdx.x < kNumBins && count[threadIdx.x]) {
         atomicAdd(&counters[0], cells[threadIdx.x]);
         atomicAdd(&counters[kCounterBinCells + threadIdx.x], cells[threadIdx.x]);
+        atomicAdd(&counters[kCounterBinPairs + threadIdx.x], (unsigned long long)count[threadIdx.x]);
     }
 }
 
@@ -1205,22 +588,21 @@ constexpr int kBoundMaxRowsCoarse = (1 << 19) / 11;
 // bound rounded down to a multiple of 16 rows (still a valid bound); taller
 // ones keep bound 0 (no pruning).
 template <int R, bool MULTI>
-__global__ __launch_bounds__(64 * wpb32(R)) void sw_bound_kernel(const uint8_t *__restrict__ codes,
-                                                       const PairDesc *__restrict__ pairs,
-                                                       const int *__restrict__ idx, const int *__restrict__ starts,
-                                                       int bin, const int8_t *__restrict__ blosum, int go_ge, int ge,
-                                                       SwPass1Out *__restrict__ p1, int *__restrict__ scratch,
-                                                       int64_t scratch_per_wave, int *queue) {
+__device__ __forceinline__ void bound_body(const SwArgs &A, int bin, char *lds, size_t wave_bytes,
+                                           const int8_t *sblosum) {
     constexpr int WPB = wpb32(R);
-    __shared__ ProfWord<R> prof_all[WPB][kProfCodes][kWave];
-    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
-    load_blosum(sblosum, blosum);
+    const uint8_t *__restrict__ codes = A.codes;
+    const PairDesc *__restrict__ pairs = A.pairs;
+    const int *__restrict__ idx = A.idx, *__restrict__ starts = A.starts;
+    const int go_ge = A.go_ge, ge = A.ge;
+    SwPass1Out *__restrict__ p1 = A.p1;
+    int *queue = A.queue;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    ProfWord<R>(*prof)[kWave] = prof_all[wave];
+    ProfWord<R>(*prof)[kWave] = (ProfWord<R>(*)[kWave])(lds + (size_t)wave * wave_bytes);
     const int64_t gwave = (int64_t)blockIdx.x * WPB + wave;
-    int *bnd_h = scratch + gwave * scratch_per_wave;
-    int *bnd_f = bnd_h + scratch_per_wave / 2;
+    int *bnd_h = A.scratch + gwave * A.scratch_per_wave;
+    int *bnd_f = bnd_h + A.scratch_per_wave / 2;
     const int item_end = starts[bin + 1];
     constexpr int RS = kWave * R;
     constexpr int kNegP = -(1 << 30);
@@ -1405,35 +787,31 @@ __global__ __launch_bounds__(256) void sw_bin3_kernel(const PairDesc *__restrict
 
 // ---------------------------------------------------------------- pass 2
 
+// No per-wave profile: a row's score against the column residue is read from
+// the 625-entry table, so LDS does not limit the waves per SIMD (occupancy
+// matters here: the statistics selects are long dependent chains).  Entries
+// are 32-bit; the statistics increment of each code pair (0x10001 for
+// identical codes, else 1) follows the scores, so a cell reads it at its
+// score's address plus a constant.  Column residues travel as byte offsets
+// (code * 4) into a row of the table.
+constexpr int kTab = kProfCodes * kProfCodes;
+
 template <int R, bool MULTI>
-__global__ __launch_bounds__(64 * wpb32(R)) void sw_pass2_kernel(const uint8_t *__restrict__ codes,
-                                                       const PairDesc *__restrict__ pairs,
-                                                       const int *__restrict__ idx, const int *__restrict__ starts,
-                                                       int bin, const int8_t *__restrict__ blosum, int go_ge, int ge,
-                                                       int cov_pct, int id_pct, const SwPass1Out *__restrict__ p1,
-                                                       pastis_pair_record *__restrict__ out,
-                                                       int *__restrict__ scratch, int64_t scratch_per_wave, int *queue) {
+__device__ __forceinline__ void stats_body(const SwArgs &A, int bin, const int *stab) {
     constexpr int WPB = wpb32(R);
-    // no per-wave profile: a row's score against the column residue is read
-    // from the 625-byte table, so LDS does not limit the waves per SIMD
-    // (occupancy matters here: the statistics selects are long dependent
-    // chains).  Entries are 32-bit; the statistics increment of each code
-    // pair (0x10001 for identical codes, else 1) follows the scores, so a
-    // cell reads it at its score's address plus a constant.  Column residues
-    // travel as byte offsets (code * 4) into a row of the table.
-    constexpr int kTab = kProfCodes * kProfCodes;
-    __shared__ int stab[2 * kTab];
-    for (int t = threadIdx.x; t < kTab; t += blockDim.x) {
-        stab[t] = blosum[t];
-        stab[kTab + t] = t / kProfCodes == t % kProfCodes ? 0x10001 : 1;
-    }
-    __syncthreads();
+    const uint8_t *__restrict__ codes = A.codes;
+    const PairDesc *__restrict__ pairs = A.pairs;
+    const int *__restrict__ idx = A.idx, *__restrict__ starts = A.starts;
+    const int go_ge = A.go_ge, ge = A.ge, cov_pct = A.cov_pct, id_pct = A.id_pct;
+    const SwPass1Out *__restrict__ p1 = A.p1;
+    pastis_pair_record *__restrict__ out = A.rec;
+    int *queue = A.queue;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int64_t gwave = (int64_t)blockIdx.x * WPB + wave;
     // strip bottom row per column: H, F, H.beg, H.md, F.beg, F.md
-    int *bnd = scratch + gwave * scratch_per_wave;
-    const int64_t plane = scratch_per_wave / 6;
+    int *bnd = A.scratch + gwave * A.scratch_per_wave;
+    const int64_t plane = A.scratch_per_wave / 6;
     const int item_end = starts[bin + 1];
     constexpr int RS = kWave * R;
 
@@ -1640,189 +1018,145 @@ __global__ __launch_bounds__(64 * wpb32(R)) void sw_pass2_kernel(const uint8_t *
     }
 }
 
-template <int R>
-hipError_t launch_p1(int bin, int blocks, const uint8_t *codes, const PairDesc *pairs, const int *idx,
-                     const int *starts, const int8_t *blosum, int go_ge, int ge, SwPass1Out *p1, int *scratch,
-                     int64_t spw, int *queue, hipStream_t s) {
-    if (bin >= kMultiBin)
-        sw_pass1_kernel<R, true><<<blocks, 64 * wpb32(R), 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge, ge, p1,
-                                                                 scratch, spw, queue);
-    else
-        sw_pass1_kernel<R, false><<<blocks, 64 * wpb32(R), 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge, ge,
-                                                                  p1, scratch, spw, queue);
-    return hipGetLastError();
+// ---------------------------------------------------------------- group launches
+
+// One launch runs the bins of a group (a range of rows per lane), the tallest
+// first: a wave that finds a bin's queue empty goes on to the next bin, so a
+// call has one launch tail per group instead of one per bin.  A bin's tail is
+// as long as its longest pair (0.3 to 5 ms), whatever its pair count, so
+// launching bin after bin cost a set of 10,000 sequences 27 ms of pass 1 for
+// 3 ms of work.  The groups keep the occupancy of their bins: one profile size
+// and about one register count each.
+template <int R, bool MULTI>
+constexpr int bin_of_rows(int half) {
+    return !MULTI ? R - 1 : (half ? kMulti16Bin : kMultiBin) + R - kMultiMinR;
 }
 
 template <int R>
-hipError_t launch_p2(int bin, int blocks, const uint8_t *codes, const PairDesc *pairs, const int *idx,
-                     const int *starts, const int8_t *blosum, int go_ge, int ge, int cov, int id,
-                     const SwPass1Out *p1, pastis_pair_record *out, int *scratch, int64_t spw, int *queue,
-                     hipStream_t s) {
-    if (bin >= kMultiBin)
-        sw_pass2_kernel<R, true><<<blocks, 64 * wpb32(R), 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge, ge, cov,
-                                                                 id, p1, out, scratch, spw, queue);
-    else
-        sw_pass2_kernel<R, false><<<blocks, 64 * wpb32(R), 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge, ge,
-                                                                  cov, id, p1, out, scratch, spw, queue);
-    return hipGetLastError();
+__host__ __device__ constexpr size_t prof_bytes() {
+    return sizeof(ProfWord<R>) * kProfCodes * kWave;
 }
 
-template <int R>
-hipError_t launch_pb(int bin, int blocks, const uint8_t *codes, const PairDesc *pairs, const int *idx,
-                     const int *starts, const int8_t *blosum, int go_ge, int ge, SwPass1Out *p1, int *scratch,
-                     int64_t spw, int *queue, hipStream_t s) {
-    if (bin >= kMultiBin)
-        sw_bound_kernel<R, true><<<blocks, 64 * wpb32(R), 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge, ge, p1,
-                                                                 scratch, spw, queue);
-    else
-        sw_bound_kernel<R, false><<<blocks, 64 * wpb32(R), 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge, ge,
-                                                                  p1, scratch, spw, queue);
-    return hipGetLastError();
-}
-
-// waves per block of the 16-bit pass (strips: one profile per wave; full
-// waves: one profile per block) and the blocks that fit on the device at once
-constexpr int wpb16(int R) { return 4; }
-// one-strip bins of more than 512 rows share a profile between the waves of a
-// block, and a block runs one round per distinct sequence a of its window:
-// two waves (four pairs) per block keep those rounds few where sequences have
-// few partners, and eight (six) such blocks per CU keep four (three) waves
-// per SIMD within LDS
-constexpr int kWpbShared = 2;
-// pairs one block of the 16-bit one-strip launch takes per window
-// narrow: R <= 4 bins in strips of 16 lanes (eight pairs per wave) rather
-// than 32 (four pairs per wave)
-static int pairs_per_block16(int R, bool narrow) {
-    return R <= 4 && narrow ? 4 * 8 : R <= 8 ? 4 * 4 : 2 * kWpbShared;
-}
-static int blocks16(int R) { return R <= 4 ? 256 * 6 : R <= 8 ? 256 * 3 : R <= 12 ? 256 * 8 : 256 * 6; }
-
-// R <= 4: strips of 16 lanes with 4 R rows per lane (eight pairs per wave),
-// or, when not narrow, of 32 lanes with 2 R rows (four pairs per wave: fewer
-// pairs that must share their sequence a); R = 5..8: strips of 32 lanes with
-// 2 R rows; wider bins: the full-wave kernel (two pairs per wave)
-template <int R>
-hipError_t launch_p16(int bin, int blocks, bool narrow, const uint8_t *codes, const PairDesc *pairs, const int *idx,
-                      const int *starts, const int *split, const int8_t *blosum, int go_ge, int ge, SwPass1Out *p1,
-                      int *queue, hipStream_t s) {
-    constexpr int WPB = wpb16(R);
-    // strips: rows class 0 (at most 64 R - 32 rows) with one row per lane
-    // less in 32-lane strips (two in 16-lane ones), then class 1
-    if constexpr (R <= 4) {
-        if (narrow) {
-            sw16s_pass1_kernel<16, 4 * R - 2, WPB><<<blocks, 64 * WPB, 0, s>>>(codes, pairs, idx, starts, split, bin, 0,
-                                                                              blosum, go_ge, ge, p1, queue);
-            sw16s_pass1_kernel<16, 4 * R, WPB><<<blocks, 64 * WPB, 0, s>>>(codes, pairs, idx, starts, split, bin, 1,
-                                                                          blosum, go_ge, ge, p1, queue);
-        } else {
-            sw16s_pass1_kernel<32, 2 * R - 1, WPB><<<blocks, 64 * WPB, 0, s>>>(codes, pairs, idx, starts, split, bin, 0,
-                                                                              blosum, go_ge, ge, p1, queue);
-            sw16s_pass1_kernel<32, 2 * R, WPB><<<blocks, 64 * WPB, 0, s>>>(codes, pairs, idx, starts, split, bin, 1,
-                                                                          blosum, go_ge, ge, p1, queue);
-        }
-    } else if constexpr (R <= 8) {
-        sw16s_pass1_kernel<32, 2 * R - 1, WPB><<<blocks, 64 * WPB, 0, s>>>(codes, pairs, idx, starts, split, bin, 0,
-                                                                          blosum, go_ge, ge, p1, queue);
-        sw16s_pass1_kernel<32, 2 * R, WPB><<<blocks, 64 * WPB, 0, s>>>(codes, pairs, idx, starts, split, bin, 1,
-                                                                      blosum, go_ge, ge, p1, queue);
-    } else {
-        sw16_pass1_kernel<R, kWpbShared, false><<<blocks, 64 * kWpbShared, 0, s>>>(codes, pairs, idx, starts, bin,
-                                                                                  blosum, go_ge, ge, p1, nullptr, 0,
-                                                                                  queue);
+// Calls f(integral R, bin) for the group's non-empty bins of the mask, tallest first.
+template <int R, bool MULTI, typename F>
+__device__ __forceinline__ void for_rows(const int *starts, uint32_t bins, F &f) {
+#pragma unroll 1
+    for (int half = 0; half < (MULTI ? 2 : 1); ++half) {
+        const int bin = bin_of_rows<R, MULTI>(half);
+        if (((bins >> bin) & 1u) && starts[bin] < starts[bin + 1]) f(std::integral_constant<int, R>{}, bin);
     }
-    return hipGetLastError();
 }
 
-// 16-bit multi-strip bins: one boundary buffer per wave of the grid
-static int blocks16m() { return 256 * 3; }
-
-template <int R>
-hipError_t launch_p16m(int bin, int blocks, const uint8_t *codes, const PairDesc *pairs, const int *idx,
-                       const int *starts, const int8_t *blosum, int go_ge, int ge, SwPass1Out *p1, int *scratch,
-                       int64_t spw, int *queue, hipStream_t s) {
-    constexpr int WPB = wpb16(R);
-    sw16_pass1_kernel<R, WPB, true><<<blocks, 64 * WPB, 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge, ge, p1,
-                                                               (uint32_t *)scratch, spw, queue);
-    return hipGetLastError();
+template <int HI, bool MULTI, typename F, int... I>
+__device__ __forceinline__ void for_bins_of(const int *starts, uint32_t bins, F &f, std::integer_sequence<int, I...>) {
+    (for_rows<HI - I, MULTI>(starts, bins, f), ...);
 }
+
+template <int LO, int HI, bool MULTI, typename F>
+__device__ __forceinline__ void for_bins(const int *starts, uint32_t bins, F &&f) {
+    for_bins_of<HI, MULTI>(starts, bins, f, std::make_integer_sequence<int, HI - LO + 1>{});
+}
+
+template <int LO, int HI, bool MULTI>
+__global__ __launch_bounds__(64 * wpb32(HI)) void sw_pass1_kernel(SwArgs A, uint32_t bins) {
+    static_assert(wpb32(LO) == wpb32(HI), "one block size per group");
+    __shared__ __align__(16) char lds[wpb32(HI) * prof_bytes<HI>()];
+    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
+    load_blosum(sblosum, A.blosum);
+    for_bins<LO, HI, MULTI>(A.starts, bins, [&](auto r_tag, int bin) {
+        const unsigned long long t0 = span_now();
+        if (pass1_body<decltype(r_tag)::value, MULTI>(A, bin, lds, prof_bytes<HI>(), sblosum))
+            span_add(A.span + 2 * bin, t0);
+    });
+}
+
+template <int LO, int HI>
+__global__ __launch_bounds__(64 * kIntraWaves) void sw_intra_pass1_kernel(SwArgs A, uint32_t bins) {
+    __shared__ __align__(16) char lds[kIntraWaves * prof_bytes<HI>()];
+    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
+    __shared__ IntraLds L;
+    load_blosum(sblosum, A.blosum);
+    for_bins<LO, HI, true>(A.starts, bins, [&](auto r_tag, int bin) {
+        const unsigned long long t0 = span_now();
+        if (intra_body<decltype(r_tag)::value>(A, bin, lds, prof_bytes<HI>(), sblosum, L))
+            span_add(A.span + 2 * bin, t0);
+        __syncthreads();  // every wave has read the last window before the next bin's first claim
+    });
+}
+
+template <int LO, int HI, bool MULTI>
+__global__ __launch_bounds__(64 * wpb32(HI)) void sw_bound_kernel(SwArgs A, uint32_t bins) {
+    static_assert(wpb32(LO) == wpb32(HI), "one block size per group");
+    __shared__ __align__(16) char lds[wpb32(HI) * prof_bytes<HI>()];
+    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
+    load_blosum(sblosum, A.blosum);
+    for_bins<LO, HI, MULTI>(A.starts, bins, [&](auto r_tag, int bin) {
+        bound_body<decltype(r_tag)::value, MULTI>(A, bin, lds, prof_bytes<HI>(), sblosum);
+    });
+}
+
+// waves per SIMD the statistics groups ask for: those their bins reached
+// alone (the selects' dependent chains need them)
+constexpr int stats_waves(int HI) { return HI <= 4 ? 4 : HI <= 12 ? 2 : 1; }
+
+template <int LO, int HI, bool MULTI>
+__global__ __launch_bounds__(64 * wpb32(HI), stats_waves(HI)) void sw_pass2_kernel(SwArgs A, uint32_t bins) {
+    static_assert(wpb32(LO) == wpb32(HI), "one block size per group");
+    __shared__ int stab[2 * kTab];
+    for (int t = threadIdx.x; t < kTab; t += blockDim.x) {
+        stab[t] = A.blosum[t];
+        stab[kTab + t] = t / kProfCodes == t % kProfCodes ? 0x10001 : 1;
+    }
+    __syncthreads();
+    for_bins<LO, HI, MULTI>(A.starts, bins,
+                            [&](auto r_tag, int bin) { stats_body<decltype(r_tag)::value, MULTI>(A, bin, stab); });
+}
+
+// The groups: one-strip bins of 1-4, 5-8, 9-12 and 13-16 rows per lane, and
+// the multi-strip bins (all of a group's kernels take the same mask of bins).
+constexpr int kGroups = 5, kMultiGroup = 4;
+constexpr uint32_t kGroupBins[kGroups] = {0x000Fu, 0x00F0u, 0x0F00u, 0xF000u, 0xFFFF0000u};
+
+typedef void (*SwKernel)(SwArgs, uint32_t);
+const SwKernel kPass1[kGroups] = {sw_pass1_kernel<1, 4, false>, sw_pass1_kernel<5, 8, false>,
+                                  sw_pass1_kernel<9, 12, false>, sw_pass1_kernel<13, 16, false>,
+                                  sw_pass1_kernel<9, 16, true>};
+const SwKernel kBound[kGroups] = {sw_bound_kernel<1, 4, false>, sw_bound_kernel<5, 8, false>,
+                                  sw_bound_kernel<9, 12, false>, sw_bound_kernel<13, 16, false>,
+                                  sw_bound_kernel<9, 16, true>};
+const SwKernel kStats[kGroups] = {sw_pass2_kernel<1, 4, false>, sw_pass2_kernel<5, 8, false>,
+                                  sw_pass2_kernel<9, 12, false>, sw_pass2_kernel<13, 16, false>,
+                                  sw_pass2_kernel<9, 16, true>};
+constexpr int kGroupWpb[kGroups] = {4, 4, 2, 2, 2};
+// blocks that fit on the device at once: the LDS footprint of the profiles
+// (26, 52, 39 and 52 KB per block) on 256 CUs
+constexpr int kGroupBlocks[kGroups] = {256 * 6, 256 * 3, 256 * 4, 256 * 3, 256 * 3};
+// pairs per block of the 16-bit kernels: strips of 16 or 32 lanes take 8 or 4
+// pairs per wave, the wider bins two pairs per wave
+constexpr int kGroupBlocks16[kGroups] = {256 * 6, 256 * 3, 256 * 8, 256 * 6, 256 * 3};
 
 // intra-pair pass 1: one block of four waves per pair, one block per CU (the
 // four strip profiles take up to 100 KB of LDS); the row buffers of the
 // block's slots are four of the per-wave boundary buffers
 constexpr int kIntraBlocks = 256;
 
-typedef hipError_t (*PIFn)(int, const uint8_t *, const PairDesc *, const int *, const int *, const int8_t *, int, int,
-                           SwPass1Out *, int *, int64_t, int *, unsigned long long *, hipStream_t);
-
-template <int R>
-hipError_t launch_pi(int bin, const uint8_t *codes, const PairDesc *pairs, const int *idx, const int *starts,
-                     const int8_t *blosum, int go_ge, int ge, SwPass1Out *p1, int *scratch, int64_t spw, int *queue,
-                     unsigned long long *flag, hipStream_t s) {
-    sw_intra_pass1_kernel<R><<<kIntraBlocks, 64 * kIntraWaves, 0, s>>>(codes, pairs, idx, starts, bin, blosum, go_ge,
-                                                                      ge, p1, scratch, spw, queue, flag);
-    return hipGetLastError();
-}
-
-typedef hipError_t (*P1Fn)(int, int, const uint8_t *, const PairDesc *, const int *, const int *, const int8_t *, int,
-                           int, SwPass1Out *, int *, int64_t, int *, hipStream_t);
-typedef hipError_t (*P2Fn)(int, int, const uint8_t *, const PairDesc *, const int *, const int *, const int8_t *, int,
-                           int, int, int, const SwPass1Out *, pastis_pair_record *, int *, int64_t, int *,
-                           hipStream_t);
-
-const P1Fn kP1[kNumBins] = {launch_p1<1>,  launch_p1<2>,  launch_p1<3>,  launch_p1<4>,  launch_p1<5>,  launch_p1<6>,
-                            launch_p1<7>,  launch_p1<8>,  launch_p1<9>,  launch_p1<10>, launch_p1<11>, launch_p1<12>,
-                            launch_p1<13>, launch_p1<14>, launch_p1<15>, launch_p1<16>, launch_p1<9>,  launch_p1<10>,
-                            launch_p1<11>, launch_p1<12>, launch_p1<13>, launch_p1<14>, launch_p1<15>, launch_p1<16>,
-                            launch_p1<9>,  launch_p1<10>, launch_p1<11>, launch_p1<12>, launch_p1<13>, launch_p1<14>,
-                            launch_p1<15>, launch_p1<16>};
-typedef hipError_t (*P16Fn)(int, int, bool, const uint8_t *, const PairDesc *, const int *, const int *,
-                            const int *, const int8_t *, int, int, SwPass1Out *, int *, hipStream_t);
-const P16Fn kP16[kMax16R] = {launch_p16<1>,  launch_p16<2>,  launch_p16<3>,  launch_p16<4>,
-                            launch_p16<5>,  launch_p16<6>,  launch_p16<7>,  launch_p16<8>,
-                            launch_p16<9>,  launch_p16<10>, launch_p16<11>, launch_p16<12>,
-                            launch_p16<13>, launch_p16<14>, launch_p16<15>, launch_p16<16>};
-const PIFn kPI[kMaxR - kMultiMinR + 1] = {launch_pi<9>,  launch_pi<10>, launch_pi<11>, launch_pi<12>,
-                                          launch_pi<13>, launch_pi<14>, launch_pi<15>, launch_pi<16>};
-const P1Fn kP16M[kMaxR - kMultiMinR + 1] = {launch_p16m<9>,  launch_p16m<10>, launch_p16m<11>, launch_p16m<12>,
-                                           launch_p16m<13>, launch_p16m<14>, launch_p16m<15>, launch_p16m<16>};
-const P1Fn kPB[kNumBins] = {launch_pb<1>,  launch_pb<2>,  launch_pb<3>,  launch_pb<4>,  launch_pb<5>,  launch_pb<6>,
-                            launch_pb<7>,  launch_pb<8>,  launch_pb<9>,  launch_pb<10>, launch_pb<11>, launch_pb<12>,
-                            launch_pb<13>, launch_pb<14>, launch_pb<15>, launch_pb<16>, launch_pb<9>,  launch_pb<10>,
-                            launch_pb<11>, launch_pb<12>, launch_pb<13>, launch_pb<14>, launch_pb<15>, launch_pb<16>,
-                            launch_pb<9>,  launch_pb<10>, launch_pb<11>, launch_pb<12>, launch_pb<13>, launch_pb<14>,
-                            launch_pb<15>, launch_pb<16>};
-const P2Fn kP2[kNumBins] = {launch_p2<1>,  launch_p2<2>,  launch_p2<3>,  launch_p2<4>,  launch_p2<5>,  launch_p2<6>,
-                            launch_p2<7>,  launch_p2<8>,  launch_p2<9>,  launch_p2<10>, launch_p2<11>, launch_p2<12>,
-                            launch_p2<13>, launch_p2<14>, launch_p2<15>, launch_p2<16>, launch_p2<9>,  launch_p2<10>,
-                            launch_p2<11>, launch_p2<12>, launch_p2<13>, launch_p2<14>, launch_p2<15>, launch_p2<16>,
-                            launch_p2<9>,  launch_p2<10>, launch_p2<11>, launch_p2<12>, launch_p2<13>, launch_p2<14>,
-                            launch_p2<15>, launch_p2<16>};
-
 // Resident blocks per CU of the one-strip statistics kernels: they keep no
 // profile in LDS, so registers set their occupancy, which the runtime reports
-// for the compiled code; a grid of that many blocks per CU drains each bin.
-int stats_blocks_per_cu[kMaxR + 1];
-
-template <int R>
-void stats_occupancy() {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, sw_pass2_kernel<R, false>, 64 * wpb32(R), 0) != hipSuccess ||
-        nb < 1) {
-        (void)hipGetLastError();
-        nb = 2;
-    }
-    stats_blocks_per_cu[R] = nb;
-}
-
-template <int... Rs>
-void stats_occupancy_all(std::integer_sequence<int, Rs...>) {
-    (stats_occupancy<Rs + 1>(), ...);
-}
+// for the compiled code; a grid of that many blocks per CU drains each group.
+std::atomic<int> stats_blocks_per_cu[kGroups];
 
 }  // namespace
 
 void sw_init_occupancy() {
-    if (stats_blocks_per_cu[1] == 0) stats_occupancy_all(std::make_integer_sequence<int, kMaxR>{});
+    if (stats_blocks_per_cu[kGroups - 1].load(std::memory_order_acquire) != 0) return;
+    for (int g = 0; g < kGroups; ++g) {
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kStats[g], 64 * kGroupWpb[g], 0) != hipSuccess || nb < 1) {
+            (void)hipGetLastError();
+            nb = 2;
+        }
+        stats_blocks_per_cu[g].store(nb, std::memory_order_release);
+    }
 }
 
 int sw_num_bins() { return kNumBins; }
@@ -1832,26 +1166,14 @@ void sw_bin_shape(int bin, int32_t *rows_per_lane, int32_t *multi) {
     *rows_per_lane = rows_of_bin(bin);
 }
 
-// Blocks per bin launch: the blocks of the bin's LDS footprint (25 codes x
-// 64 lanes x 4, 8 or 16 profile bytes per wave) resident on 256 CUs at once;
-// the grid-stride loop reads the bin size on the device.
-static int blocks_for_bin(int bin) {
-    const int r = rows_of_bin(bin);
-    return r <= 4 ? 256 * 6 : (r > 8 && r <= 12) ? 256 * 4 : 256 * 3;
-}
-
 // Only the multi-strip bins use the boundary buffers (one per wave of the
 // grid, 32-bit or 16-bit kernel).
 int sw_one_strip_max_rows() { return kWave * kSingleBins; }
 
 int64_t sw_scratch_waves() {
-    int64_t w = 0;
-    for (int b = kMultiBin; b < kNumBins; ++b) {
-        w = std::max<int64_t>(w, (int64_t)blocks_for_bin(b) * wpb32(rows_of_bin(b)));
-        w = std::max<int64_t>(w, (int64_t)blocks16m() * wpb16(rows_of_bin(b)));
-        w = std::max<int64_t>(w, (int64_t)kIntraBlocks * kIntraWaves);
-    }
-    return w;
+    int64_t w = (int64_t)kGroupBlocks[kMultiGroup] * kGroupWpb[kMultiGroup];
+    w = std::max<int64_t>(w, (int64_t)kGroupBlocks16[kMultiGroup] * sw16_waves(kMultiGroup));
+    return std::max<int64_t>(w, (int64_t)kIntraBlocks * kIntraWaves);
 }
 
 // The 16-bit profile holds each biased score s + o + e in one byte, with
@@ -1865,135 +1187,176 @@ bool sw_bin_is16(int bin, int max16) {
     return (bin < kSingleBins || bin >= kMulti16Bin) && rows_of_bin(bin) <= max16;
 }
 
-hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pairs, int64_t npairs,
-                     const int8_t *blosum, const Scoring &sc, SwPass1Out *p1, pastis_pair_record *out,
-                     const SwWork &wk, int stats_mode, int max16, int grid_scale, int grid_scale_wide, int intra,
-                     int narrow16, int long_blocks, bool timed, hipStream_t s) {
-    // timed = false (graph capture): no stage or per-bin events
+hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &wk, hipStream_t s) {
+    if (npairs <= 0) return hipSuccess;
+    sw_bin1_kernel<<<(unsigned)((npairs + 255) / 256), 256, 0, s>>>(pairs, npairs, wk.bin_of, wk.counters, wk.queue);
+    return hipGetLastError();
+}
+
+// The launches of a call, from its pairs per bin.
+SwPlan sw_plan(const unsigned long long *bin_pairs, const Scoring &sc, int max16, const pastis_tuning &tune) {
+    SwPlan p;
+    p.max16 = max16;
+    p.intra = tune.sw_intra_pair;
+    p.narrow = tune.sw16_narrow_rows;
     // multi-strip launches: at most long_blocks blocks per CU (they run beside
-    // the one-strip bins on the second stream; fewer resident waves leave the
+    // the one-strip bins on another stream; fewer resident waves leave the
     // one-strip kernels more room).  Fewer blocks than the default never
     // exceed the boundary buffers, which are sized for the default grids.
-    auto long_cap = [&](int blocks) { return std::min(blocks, 256 * long_blocks); };
-    const bool use16 = max16 > 0;
+    auto fit = [&](int g, int blocks, int64_t pairs, int per_block) {
+        const int scale = g == kMultiGroup ? 1 : g < 2 ? tune.sw_grid_scale : tune.sw_grid_scale_wide;
+        int64_t b = g == kMultiGroup ? std::min(blocks, 256 * tune.sw_long_blocks) : (int64_t)blocks * scale;
+        // no launch needs more blocks than its pairs could fill
+        b = std::min<int64_t>(b, (pairs + per_block - 1) / per_block);
+        return (int)b;
+    };
+    // every bin from the group's tallest non-empty one down may hold pairs of
+    // the later passes, whose end rectangles are no taller than the pairs; a
+    // multi-strip pair may end in any bin
+    int64_t later = 0;
+    for (int g = kMultiGroup; g >= 0; --g) {
+        int64_t n16 = 0, n32 = 0;
+        p.bins16[g] = p.bins32[g] = 0;
+        for (int b = 0; b < kNumBins; ++b) {
+            if (!((kGroupBins[g] >> b) & 1u) || bin_pairs[b] == 0) continue;
+            if (sw_bin_is16(b, max16)) {
+                n16 += (int64_t)bin_pairs[b];
+                p.bins16[g] |= 1u << b;
+            } else {
+                n32 += (int64_t)bin_pairs[b];
+                p.bins32[g] |= 1u << b;
+            }
+        }
+        later += n16 + n32;
+        const int per16 = g == 0 ? (p.narrow > 0 ? 32 : 16) : g == 1 ? 16 : g == kMultiGroup ? 8 : 4;
+        p.blocks16[g] = n16 ? fit(g, kGroupBlocks16[g], n16, per16) : 0;
+        p.blocks32[g] = n32 ? fit(g, kGroupBlocks[g], n32, kGroupWpb[g]) : 0;
+        p.blocks_bound[g] = later ? fit(g, kGroupBlocks[g], later, kGroupWpb[g]) : 0;
+        const int per_cu = g == kMultiGroup ? 3 : std::max(1, stats_blocks_per_cu[g].load(std::memory_order_acquire));
+        p.blocks_stats[g] = later ? fit(g, 256 * per_cu, later, kGroupWpb[g]) : 0;
+    }
+    return p;
+}
+
+hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pairs, int64_t npairs,
+                     const int8_t *blosum, const Scoring &sc, SwPass1Out *p1, pastis_pair_record *out,
+                     const SwWork &wk, int stats_mode, const SwPlan &plan, bool timed, hipStream_t s) {
+    // timed = false (graph capture): no stage events
+    const bool use16 = plan.max16 > 0;
     auto begin = [&](int st) { return timed ? stage_begin(ctx, st, s) : hipSuccess; };
     auto end = [&](int st) { return timed ? stage_end(ctx, st, s) : hipSuccess; };
-    auto mark = [&](hipEvent_t ev, hipStream_t st) { return timed ? hipEventRecord(ev, st) : hipSuccess; };
-    // multi-strip bins (long sequences a, few pairs, long tails) run on the
-    // context's second stream beside the one-strip bins; they share the
-    // boundary buffers, so they stay in order among themselves there
-    const hipStream_t ls = ctx->long_stream;
-    auto fork = [&](int i) {
-        hipError_t r = hipEventRecord(ctx->long_fork[i], s);
-        return r != hipSuccess ? r : hipStreamWaitEvent(ls, ctx->long_fork[i], 0);
-    };
-    auto join = [&](int i) {
-        hipError_t r = hipEventRecord(ctx->long_join[i], ls);
-        return r != hipSuccess ? r : hipStreamWaitEvent(s, ctx->long_join[i], 0);
-    };
     if (npairs <= 0) return hipSuccess;
-    const int go_ge = sc.gap_open + sc.gap_extend, ge = sc.gap_extend;
-    // Every launch drains its bin's work queue with a resident grid (times
-    // the grid scale); no launch needs more blocks than the call's pairs
-    // could fill (per_block pairs each).
-    auto capped = [&](int blocks, int per_block) {
-        const int64_t fill = (npairs + per_block - 1) / per_block;
-        return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, fill));
+    // The groups of a pass run beside one another on streams of the context:
+    // the multi-strip group on the long stream, the others on the call's
+    // stream and the side streams.  run(phase, f) calls f(group, stream) for
+    // every group and orders its work after the call's stream's and before
+    // what follows on it.
+    auto run = [&](int phase, auto &&busy, auto &&f) -> hipError_t {
+        hipStream_t st[kGroups] = {ctx->side_stream[0], s, ctx->side_stream[1], ctx->side_stream[2], ctx->long_stream};
+        int first = -1, n = 0;
+        for (int g = 0; g < kGroups; ++g)
+            if (busy(g)) {
+                ++n;
+                first = g;
+            }
+        if (n == 0) return hipSuccess;
+        if (n == 1) return f(first, s);  // alone: no fork
+        hipError_t e = hipEventRecord(ctx->fork_ev[phase], s);
+        if (e != hipSuccess) return e;
+        for (int g = kGroups - 1; g >= 0; --g) {  // long pairs first
+            if (!busy(g)) continue;
+            if (st[g] != s && (e = hipStreamWaitEvent(st[g], ctx->fork_ev[phase], 0)) != hipSuccess) return e;
+            if ((e = f(g, st[g])) != hipSuccess) return e;
+            if (st[g] != s && (e = hipEventRecord(ctx->join_ev[phase][g], st[g])) != hipSuccess) return e;
+        }
+        for (int g = 0; g < kGroups; ++g)
+            if (busy(g) && st[g] != s && (e = hipStreamWaitEvent(s, ctx->join_ev[phase][g], 0)) != hipSuccess) return e;
+        return hipSuccess;
     };
     const int nb = (int)((npairs + 255) / 256);
+    SwArgs A{};
+    A.codes = codes;
+    A.pairs = pairs;
+    A.blosum = blosum;
+    A.go_ge = sc.gap_open + sc.gap_extend;
+    A.ge = sc.gap_extend;
+    A.p1 = p1;
+    A.rec = out;
+    A.scratch = wk.scratch;
+    A.scratch_per_wave = wk.scratch_per_wave;
+    A.cov_pct = sc.cov_pct;
+    A.id_pct = sc.id_pct;
+    A.span = wk.counters + kCounterSpan;
+    A.flag = wk.counters + kCounterIntraFlag;
+    A.bounds = wk.bounds;
     hipError_t e = begin(kStSched);
     if (e != hipSuccess) return e;
-    sw_bin1_kernel<<<nb, 256, 0, s>>>(pairs, npairs, wk.bin_of, wk.counters, wk.queue);
-    if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts, wk.cursor, wk.idx, s)) != hipSuccess)
-        return e;
-    const int *idx1 = wk.idx;
+    A.idx = wk.idx;
+    A.starts = wk.starts;
     if (use16) {
-        // pair up pairs of one sequence a with similar column counts
+        // pair up pairs of one sequence a with similar column counts; the sort
+        // by (bin, rows class, a) also bins the pairs
         sw_pair_keys_kernel<<<nb, 256, 0, s>>>(pairs, wk.bin_of, npairs, wk.sort_keys, (uint32_t *)wk.idx);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         bool alt = false;
         if ((e = radix_sort(wk.sort_keys, (uint32_t *)wk.idx, wk.sort_keys_alt, wk.sort_vals_alt, npairs,
                             kPairKeyBits, wk.sort_temp, s, &alt)) != hipSuccess)
             return e;
-        if (alt) idx1 = (const int *)wk.sort_vals_alt;
-        sw_split_kernel<<<1, 64, 0, s>>>(alt ? wk.sort_keys_alt : wk.sort_keys, wk.starts, wk.split);
+        if (alt) A.idx = (const int *)wk.sort_vals_alt;
+        sw_bounds_kernel<<<1, 128, 0, s>>>(alt ? wk.sort_keys_alt : wk.sort_keys, (int)npairs, wk.bounds, wk.starts);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if ((e = end(kStSched)) != hipSuccess || (e = begin(kStAlign1)) != hipSuccess || (e = fork(0)) != hipSuccess)
+    } else if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts, wk.cursor, wk.idx, s)) !=
+               hipSuccess) {
         return e;
-    // long bins first, so that their tails overlap the one-strip bins
-    for (int k = 0; k < kNumBins; ++k) {
-        const int bin = (k + kMultiBin) % kNumBins;
-        const hipStream_t st = bin >= kMultiBin ? ls : s;
-        if ((e = mark(ctx->bin_ev[2 * bin], st)) != hipSuccess) return e;
-        // multi-strip bins use per-wave boundary buffers: they keep their grid
-        const int R = rows_of_bin(bin);
-        const int scale = bin >= kMultiBin ? 1 : R <= 8 ? grid_scale : grid_scale_wide;
-        if (sw_bin_is16(bin, max16) && bin >= kMulti16Bin)
-            e = kP16M[bin - kMulti16Bin](bin, long_cap(blocks16m()), codes, pairs, idx1, wk.starts, blosum, go_ge, ge,
-                                         p1, wk.scratch, wk.scratch_per_wave, wk.queue, st);
-        else if (intra && bin >= kMultiBin)
-            e = kPI[R - kMultiMinR](bin, codes, pairs, idx1, wk.starts, blosum, go_ge, ge, p1, wk.scratch,
-                                    wk.scratch_per_wave, wk.queue, wk.counters + kCounterIntraFlag, st);
-        else if (sw_bin_is16(bin, max16))
-            e = kP16[bin](bin, capped(scale * blocks16(R), pairs_per_block16(R, R <= narrow16)), R <= narrow16, codes,
-                          pairs, idx1, wk.starts, wk.split, blosum, go_ge, ge, p1, wk.queue, st);
-        else
-            e = kP1[bin](bin,
-                         capped(bin >= kMultiBin ? long_cap(blocks_for_bin(bin)) : scale * blocks_for_bin(bin),
-                                wpb32(R)),
-                         codes, pairs, idx1, wk.starts, blosum, go_ge, ge, p1, wk.scratch, wk.scratch_per_wave,
-                         wk.queue, st);
-        if (e != hipSuccess) return e;
-        if ((e = mark(ctx->bin_ev[2 * bin + 1], st)) != hipSuccess) return e;
     }
-    if ((e = join(0)) != hipSuccess || (e = end(kStAlign1)) != hipSuccess || (e = begin(kStAlign2)) != hipSuccess)
-        return e;
-    // the start-bound and statistics launches take the same grid scales
-    // (multi-strip bins keep a resident grid: one boundary buffer per wave)
-    auto scale2 = [&](int bin) {
-        return bin >= kMultiBin ? 1 : rows_of_bin(bin) <= 8 ? grid_scale : grid_scale_wide;
-    };
-    auto blocks2 = [&](int bin) {
-        return bin >= kMultiBin ? long_cap(blocks_for_bin(bin)) : scale2(bin) * blocks_for_bin(bin);
-    };
-    auto blocks_stats = [&](int bin) {
-        const int per_cu = stats_blocks_per_cu[rows_of_bin(bin)];
-        return bin >= kMultiBin || per_cu < 1 ? blocks2(bin) : scale2(bin) * 256 * per_cu;
-    };
+    if ((e = end(kStSched)) != hipSuccess || (e = begin(kStAlign1)) != hipSuccess) return e;
+    e = run(0, [&](int g) { return plan.blocks16[g] + plan.blocks32[g] > 0; },
+            [&](int g, hipStream_t st) -> hipError_t {
+                if (plan.blocks16[g]) {
+                    A.queue = wk.queue;
+                    const hipError_t r = launch_sw16(g, plan.blocks16[g], plan.narrow, A, plan.bins16[g], st);
+                    if (r != hipSuccess) return r;
+                }
+                if (plan.blocks32[g]) {
+                    A.queue = wk.queue + 2 * kNumBins;
+                    if (g == kMultiGroup && plan.intra)
+                        sw_intra_pass1_kernel<9, 16><<<kIntraBlocks, 64 * kIntraWaves, 0, st>>>(A, plan.bins32[g]);
+                    else
+                        kPass1[g]<<<plan.blocks32[g], 64 * kGroupWpb[g], 0, st>>>(A, plan.bins32[g]);
+                    return hipGetLastError();
+                }
+                return hipSuccess;
+            });
+    if (e != hipSuccess || (e = end(kStAlign1)) != hipSuccess || (e = begin(kStAlign2)) != hipSuccess) return e;
     sw_bin2_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, stats_mode, sc.direct_pct, out, wk.bin_of,
                                       wk.counters);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (stats_mode == 2) return end(kStAlign2);  // every record is final
     if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) != hipSuccess)
         return e;
+    A.idx = wk.idx2;
+    A.starts = wk.starts2;
     if (stats_mode == 0) {
         // start bound, then only the pairs whose coverage can still hold
-        if ((e = fork(1)) != hipSuccess) return e;
-        for (int k = 0; k < kNumBins; ++k) {
-            const int bin = (k + kMultiBin) % kNumBins;
-            const hipStream_t st = bin >= kMultiBin ? ls : s;
-            const int R = rows_of_bin(bin);
-            e = kPB[bin](bin, capped(blocks2(bin), wpb32(R)), codes, pairs,
-                         wk.idx2, wk.starts2, blosum, go_ge, ge, p1, wk.scratch, wk.scratch_per_wave,
-                         wk.queue + kNumBins, st);
-            if (e != hipSuccess) return e;
-        }
-        if ((e = join(1)) != hipSuccess) return e;
+        A.queue = wk.queue + 3 * kNumBins;
+        e = run(1, [&](int g) { return plan.blocks_bound[g] > 0; },
+                [&](int g, hipStream_t st) {
+                    kBound[g]<<<plan.blocks_bound[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
+                    return hipGetLastError();
+                });
+        if (e != hipSuccess) return e;
         sw_bin3_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, out, wk.bin_of, wk.counters);
         if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
             hipSuccess)
             return e;
     }
-    if ((e = fork(2)) != hipSuccess) return e;
-    for (int k = 0; k < kNumBins; ++k) {
-        const int bin = (k + kMultiBin) % kNumBins;
-        const hipStream_t st = bin >= kMultiBin ? ls : s;
-        const int R = rows_of_bin(bin);
-        e = kP2[bin](bin, capped(blocks_stats(bin), wpb32(R)), codes, pairs,
-                     wk.idx2, wk.starts2, blosum, go_ge, ge, sc.cov_pct, sc.id_pct, p1, out, wk.scratch,
-                     wk.scratch_per_wave, wk.queue + 2 * kNumBins, st);
-        if (e != hipSuccess) return e;
-    }
-    if ((e = join(2)) != hipSuccess) return e;
+    A.queue = wk.queue + 4 * kNumBins;
+    e = run(2, [&](int g) { return plan.blocks_stats[g] > 0; },
+            [&](int g, hipStream_t st) {
+                kStats[g]<<<plan.blocks_stats[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
+                return hipGetLastError();
+            });
+    if (e != hipSuccess) return e;
     return end(kStAlign2);
 }
 
