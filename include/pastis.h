@@ -85,8 +85,9 @@ typedef struct pastis_params {
                                  2^15) two per wave in 16-bit lanes (records of pairs without
                                  the statistics pass then carry end_b = -1); 32 runs
                                  every pair in 32-bit lanes; 0 (automatic) takes 16
-                                 inside pastis_search with identity weights and 32
-                                 elsewhere.  16 needs gap_open + gap_extend >= 4. */
+                                 inside pastis_search with identity weights and for
+                                 full records, and 32 elsewhere.  16 needs gap_open +
+                                 gap_extend >= 4. */
     int32_t full_records;     /* 1: traceback statistics (beg, matches, columns) for every
                                  aligned pair; 0: only for pairs whose coverage cut can
                                  still hold (the others report beg = -1, passed = 0) */
@@ -181,7 +182,8 @@ typedef struct pastis_run_stats {
     int64_t sw_bin_cells[32];
     double sw_bin_ms[32];
     /* Smith-Waterman pairs (and their end-rectangle cells) that took the
-     * start-bound pass, and cells of the statistics pass. */
+     * start-bound pass, and cells of the statistics pass (traceback or
+     * statistics carried along; the end rectangles' cells either way). */
     int64_t bound_pass_pairs;
     int64_t bound_pass_cells;
     int64_t stats_pass_cells;

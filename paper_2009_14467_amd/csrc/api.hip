@@ -239,30 +239,33 @@ pastis_status make_sw_work(pastis_ctx *ctx, int64_t npairs, int max_len, SwWork 
     PASTIS_TRY(ensure(ctx, kBufBinMeta, sizeof(int) * kMetaInts + sizeof(unsigned long long) * kNumCounters, &p));
     wk.counts = (int *)p;
     wk.counters = (unsigned long long *)((int *)p + kMetaInts);
-    // counts: 32 bins; starts, starts2: 33 bounds each; cursor: 32; bounds: 65;
-    // seven work queues of 32 bins
+    // counts: 32 bins; starts, starts2: 33 bounds each; cursor: 32; bounds,
+    // trace_bounds: 65 each; seven work queues of 32 bins
     wk.starts = wk.counts + 32;
     wk.starts2 = wk.counts + 72;
     wk.cursor = wk.counts + 112;
     wk.bounds = wk.counts + 144;
-    wk.queue = wk.counts + 216;
+    wk.trace_bounds = wk.counts + 212;
+    wk.queue = wk.counts + 280;
     PASTIS_TRY(ensure(ctx, kBufIdx, sizeof(int) * (size_t)std::max<int64_t>(npairs, 1), &p));
     wk.idx = (int *)p;
     PASTIS_TRY(ensure(ctx, kBufIdx2, sizeof(int) * (size_t)std::max<int64_t>(npairs, 1), &p));
     wk.idx2 = (int *)p;
     wk.scratch_per_wave = 6 * (int64_t)std::max(max_len, 1);
+    wk.scratch16_per_wave = 2 * (int64_t)std::max(max_len, 1);
     // only multi-strip pairs (a sequence a longer than one strip) touch the
-    // boundary rows; without such a sequence the buffer is never read
-    const size_t scratch_bytes = max_len > sw_one_strip_max_rows()
-                                     ? sizeof(int) * (size_t)wk.scratch_per_wave * (size_t)sw_scratch_waves()
-                                     : 256;
-    PASTIS_TRY(ensure(ctx, kBufScratch, scratch_bytes, &p));
+    // boundary rows; without such a sequence the buffer is never read.  The
+    // 16-bit kernels, which run beside the 32-bit ones, have rows of their own.
+    const int64_t words32 = wk.scratch_per_wave * sw_scratch_waves(), words16 = wk.scratch16_per_wave * sw16_scratch_waves();
+    const bool multi = max_len > sw_one_strip_max_rows();
+    PASTIS_TRY(ensure(ctx, kBufScratch, multi ? sizeof(int) * (size_t)(words32 + words16) : 256, &p));
     wk.scratch = (int *)p;
+    wk.scratch16 = multi ? wk.scratch + words32 : wk.scratch;
     return PASTIS_OK;
 }
 
 static pastis_status make_sort_work(pastis_ctx *ctx, int64_t npairs, SwWork &wk) {
-    const size_t n = (size_t)std::max<int64_t>(npairs, 1);
+    const size_t n = (size_t)std::max<int64_t>(npairs, 1) + 2;  // the traceback's list reuses the keys
     void *p = nullptr;
     PASTIS_TRY(ensure(ctx, kBufSortKeys, sizeof(uint64_t) * n, &p));
     wk.sort_keys = (uint64_t *)p;
@@ -294,7 +297,7 @@ static pastis_status sw_graph(pastis_ctx *ctx, const uint8_t *codes, const PairD
     uint64_t key = 0;
     const uint64_t parts[] = {(uint64_t)npairs, (uint64_t)codes, (uint64_t)pairs, (uint64_t)p1, (uint64_t)out,
                               (uint64_t)wk.counters, (uint64_t)wk.bin_of, (uint64_t)wk.counts, (uint64_t)wk.idx,
-                              (uint64_t)wk.idx2, (uint64_t)wk.bounds, (uint64_t)wk.scratch, (uint64_t)wk.scratch_per_wave,
+                              (uint64_t)wk.idx2, (uint64_t)wk.bounds, (uint64_t)wk.dirs, (uint64_t)wk.scratch, (uint64_t)wk.scratch_per_wave, (uint64_t)wk.scratch16,
                               (uint64_t)wk.sort_keys, (uint64_t)wk.sort_keys_alt, (uint64_t)wk.sort_vals_alt,
                               (uint64_t)wk.sort_temp, (uint64_t)sc.gap_open, (uint64_t)sc.gap_extend,
                               (uint64_t)sc.id_pct, (uint64_t)sc.cov_pct, (uint64_t)sc.direct_pct,
@@ -374,12 +377,22 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
         // 16-bit pass 1 on request, or by default where its records stay
         // inside the search (they omit end_b of pairs without statistics,
         // which no edge then reports)
-        const bool use16 = sw16_supported(sc) && stats_mode != 1 &&
-                           (P.score_width == 16 || (P.score_width == 0 && ctx->records_internal));
+        // and, with full records, where the traceback gives every pair's
+        const bool traced = !ctx->arena;
+        const bool use16 = sw16_supported(sc) && (stats_mode != 1 || traced) &&
+                           (P.score_width == 16 ||
+                            (P.score_width == 0 && (ctx->records_internal || stats_mode == 1)));
         const int max16 = !use16 ? 0 : P.score_width == 16 ? 16 : ctx->tune.sw16_max_rows;
         if (max16 > 0) PASTIS_TRY(make_sort_work(ctx, npairs, wk));
         ctx->last_max16 = max16;
-        const SwPlan plan = sw_plan(c + kCounterBinPairs, sc, max16, ctx->tune);
+        const SwPlan plan = sw_plan(c + kCounterBinPairs, max16, st.max_len, ctx->tune);
+        if (traced && stats_mode != 2 && plan.dirs_words > 0) {
+            void *dirs = nullptr;
+            // a device too full for the direction bits runs the statistics kernels
+            const pastis_status ds = ensure(ctx, kBufDirs, sizeof(uint32_t) * (size_t)plan.dirs_words, &dirs);
+            if (ds != PASTIS_OK && ds != PASTIS_E_NOMEM) return ds;
+            wk.dirs = ds == PASTIS_OK ? (uint32_t *)dirs : nullptr;
+        }
         if (P.graph_mode) {
             PASTIS_TRY(sw_graph(ctx, codes, (const PairDesc *)pairs, npairs, sc, (SwPass1Out *)p1, out, wk, stats_mode,
                                 plan, s));

@@ -171,6 +171,7 @@ enum BufId {
     kBufSortKeysAlt,
     kBufSortValsAlt,
     kBufSortTemp,
+    kBufDirs,
     kBufCount  // first id used by the discovery stage
 };
 constexpr int kNumBufs = 128;
@@ -201,7 +202,8 @@ struct SwPass1Out {
 // Work buffers of an alignment stage (device): per-pair bin ids, bin counts,
 // bin starts for the two passes, a cursor, the two binned index lists, and
 // boundary-row scratch for pairs taller than one strip (6 planes of max_len
-// ints per wave, for sw_scratch_waves() waves).
+// ints per wave, for sw_scratch_waves() waves; 2 planes for the
+// sw16_scratch_waves() waves of the 16-bit kernels).
 // counters: [0] cells, [1] statistics-pass pairs, [2] their cells, [3]
 // start-bound pairs, [4] their cells, [kCounterXdQueue] the x-drop kernel's
 // work queue, [kCounterBinCells + b] and [kCounterBinPairs + b] pass-1 cells
@@ -220,9 +222,9 @@ struct SwWork {
     int8_t *bin_of;
     int *counts, *starts, *starts2, *cursor;
     int *idx, *idx2;
-    int *scratch;
-    int64_t scratch_per_wave;
-    int *queue;  // work-queue counters: 16-bit pass 1 (one per bin and rows class), 32-bit pass 1, start bound, statistics
+    int *scratch, *scratch16;
+    int64_t scratch_per_wave, scratch16_per_wave;
+    int *queue;  // work-queue counters: 16-bit pass 1 (one per bin and rows class), 32-bit pass 1, start bound, statistics, traceback
     // 16-bit pass 1: first item of each (bin, rows class), two per bin (strip
     // bins of up to 8 rows per lane split their pairs by rows: up to 64 R - 32
     // rows, and more)
@@ -231,6 +233,10 @@ struct SwWork {
     uint64_t *sort_keys = nullptr, *sort_keys_alt = nullptr;
     uint32_t *sort_vals_alt = nullptr;
     void *sort_temp = nullptr;
+    // traced statistics pass: direction words (null: statistics kernels only)
+    // and the list's class bounds
+    uint32_t *dirs = nullptr;
+    int *trace_bounds;
 };
 int sw_num_bins();
 void sw_bin_shape(int bin, int32_t *rows_per_lane, int32_t *multi);
@@ -243,27 +249,43 @@ hipError_t launch_xd(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
                      const int8_t *blosum, const Scoring &sc, int k, pastis_pair_record *out, uint32_t *redo,
                      uint32_t *n_redo, int *gring, unsigned long long *counters, hipStream_t s);
 int64_t sw_scratch_waves();
+int64_t sw16_scratch_waves();
 // Queries the resident blocks of the SW kernels whose grids follow their
 // occupancy (once per process, before any launch is captured).
 void sw_init_occupancy();
 // Sequences a of at most this many rows run in one strip (no boundary rows).
 int sw_one_strip_max_rows();
 
-// The launches of a Smith-Waterman call, planned on the host from the pairs
-// per bin: per group of bins (one-strip bins of 1-4, 5-8, 9-12 and 13-16 rows
-// per lane, multi-strip bins) the blocks of each pass (0: no launch) and the
-// pass-1 bins in 16-bit and in 32-bit lanes.
-struct SwPlan {
-    int max16 = 0, intra = 0, narrow = 0;
-    uint32_t bins16[5] = {}, bins32[5] = {};
-    int blocks16[5] = {}, blocks32[5] = {}, blocks_bound[5] = {}, blocks_stats[5] = {};
+// One launch of a 16-bit kernel: its bins, grid, the blocks that take the
+// multi-strip bins, the bins of up to 4 rows per lane in strips of 16 lanes,
+// and whether those of up to 8 run across all 64 lanes instead.
+struct Sw16Launch {
+    uint32_t bins = 0;
+    int blocks = 0, multi_blocks = 0, narrow = 0, wide = 0;
 };
+
+// The launches of a Smith-Waterman call, planned on the host from the pairs
+// per bin: pass 1 and traceback in 16-bit lanes, and per group of bins
+// (one-strip bins of 1-4, 5-8, 9-12 and 13-16 rows per lane, multi-strip bins)
+// the blocks of the 32-bit passes (0: no launch) and the pass-1 bins.
+struct SwPlan {
+    int max16 = 0, intra = 0;
+    Sw16Launch p16, t16;
+    uint32_t bins32[5] = {};
+    int blocks32[5] = {}, blocks_bound[5] = {}, blocks_stats[5] = {};
+    // whether some pair may still need the statistics kernels, and the
+    // traceback's direction words: per wave of the grid, per wave of its
+    // multi-strip blocks, and in all
+    int stats_after_trace = 0, pad = 0;
+    int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
+};
+static_assert(sizeof(SwPlan) == (2 + 10 + 20 + 2) * 4 + 3 * 8, "no hidden padding: the plan is hashed as words");
 // max16 > 0: pass 1 of one-strip pairs with at most max16 rows per lane in
 // 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
 // that skip the statistics pass.  tune: the grid scales of the one-strip
 // groups, intra-pair pass 1 of the 32-bit multi-strip bins, the 16-bit bins
 // in strips of 16 lanes, and the multi-strip grids.
-SwPlan sw_plan(const unsigned long long *bin_pairs, const Scoring &sc, int max16, const pastis_tuning &tune);
+SwPlan sw_plan(const unsigned long long *bin_pairs, int max16, int max_len, const pastis_tuning &tune);
 // Bins of the pairs (bin_of, the per-bin counters) and cleared work queues;
 // the counters must be zero before.
 hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &wk, hipStream_t s);

@@ -426,7 +426,6 @@ __device__ __forceinline__ bool intra_body(const SwArgs &A, int bin, char *lds, 
 // sequence a (low 24 bits of its index; the kernel checks equality itself),
 // then the longer b first
 constexpr int kPairKeyBits = 48;
-constexpr int kSplitBins = 8;  // one-strip bins 0..7 (up to 8 rows per lane)
 __global__ void sw_pair_keys_kernel(const PairDesc *__restrict__ pairs, const int8_t *__restrict__ bin_of,
                                     int64_t npairs, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -518,7 +517,7 @@ __device__ __forceinline__ void sw_final_record(const PairDesc &pd, const SwPass
     rec.score = r1.score;
     rec.beg_a = rec.beg_b = -1;
     rec.end_a = r1.end_a;
-    rec.end_b = r1.end_b;
+    rec.end_b = max(r1.end_b, -1);  // (a 16-bit pair's end column is a hint until a later pass finds it)
     rec.matches = rec.columns = 0;
     rec.seed_used = -1;
     rec.passed = 0;
@@ -527,14 +526,28 @@ __device__ __forceinline__ void sw_final_record(const PairDesc &pd, const SwPass
     out[q] = rec;
 }
 
+// Pairs whose statistics come from the traceback: 16-bit pass-1 bins whose
+// longer sequence fits the direction buffers.
+struct TraceRule {
+    uint32_t bins;              // pass-1 bins in 16-bit lanes (0: no traceback)
+    int max_cols, max_cols_multi;  // longest b of one-strip and of multi-strip pairs
+};
+constexpr int8_t kToTrace = -2;  // bin_of of a pair listed for the traceback
+
+__device__ __forceinline__ bool can_trace(const TraceRule &T, const PairDesc &pd) {
+    const int bin = rows_bin(pd.la);
+    return ((T.bins >> bin) & 1u) && pd.lb <= (bin < kSingleBins ? T.max_cols : T.max_cols_multi);
+}
+
 // Records of pairs that need no statistics pass are final here; the others
-// are binned by the height of their end rectangle (counters[3], [4]: pairs
-// and cells of the start-bound pass; counters[1], [2] in full-records mode).
-// stats_mode: 0 = only pairs whose coverage cut can hold, 1 = every aligned
-// pair, 2 = none (the normalised-score weight needs no traceback).
+// are listed for the traceback, or binned by the height of their end
+// rectangle (counters[3], [4]: pairs and cells of the start-bound pass;
+// counters[1], [2] in full-records mode).  stats_mode: 0 = only pairs whose
+// coverage cut can hold, 1 = every aligned pair, 2 = none (the
+// normalised-score weight needs no traceback).
 __global__ __launch_bounds__(256) void sw_bin2_kernel(const PairDesc *__restrict__ pairs,
                                                       SwPass1Out *__restrict__ p1, int64_t npairs, int cov_pct,
-                                                      int stats_mode, int direct_pct,
+                                                      int stats_mode, int direct_pct, TraceRule T,
                                                       pastis_pair_record *__restrict__ out,
                                                       int8_t *__restrict__ bin_of,
                                                       unsigned long long *__restrict__ counters) {
@@ -549,16 +562,16 @@ __global__ __launch_bounds__(256) void sw_bin2_kernel(const PairDesc *__restrict
         const bool need = r1.score > 0 && stats_mode != 2 &&
                           (stats_mode == 1 || 100LL * (r1.end_a + 1) >= (long long)cov_pct * pd.la);
         if (need) {
-            bin_of[q] = (int8_t)rows_bin(r1.end_a + 1);
-            if (stats_mode == 1) {  // no start bound: every such pair takes pass 2
-                atomicAdd(&acc[0], 1ull);
-                atomicAdd(&acc[1], (unsigned long long)(r1.end_a + 1) * (unsigned long long)(r1.end_b + 1));
-            } else if (100LL * r1.score >= (long long)direct_pct * pd.la) {
-                p1[q].pad = -1;  // likely to pass: no start bound
-            } else {
-                const int cols = r1.end_b >= 0 ? r1.end_b + 1 : pd.lb;
-                atomicAdd(&acc[2], 1ull);
-                atomicAdd(&acc[3], (unsigned long long)(r1.end_a + 1) * (unsigned long long)cols);
+            const int cols = r1.end_b >= 0 ? r1.end_b + 1 : pd.lb;
+            const bool direct = stats_mode == 1 || 100LL * r1.score >= (long long)direct_pct * pd.la;
+            bin_of[q] = direct && can_trace(T, pd) ? kToTrace : (int8_t)rows_bin(r1.end_a + 1);
+            if (direct) p1[q].pad = -1;  // no start bound
+            // in full-records mode every such pair takes the statistics pass;
+            // otherwise the last binning counts its pairs
+            const int at = stats_mode == 1 ? 0 : 2;
+            if (stats_mode == 1 || !direct) {
+                atomicAdd(&acc[at], 1ull);
+                atomicAdd(&acc[at + 1], (unsigned long long)(r1.end_a + 1) * (unsigned long long)cols);
             }
         } else {
             sw_final_record(pd, r1, q, out, bin_of);
@@ -758,24 +771,25 @@ __device__ __forceinline__ void bound_body(const SwArgs &A, int bin, char *lds, 
 }
 
 // Pairs binned for the statistics pass whose coverage bound already fails
-// get their final record here; the rest keep their bin.  counters[1] and [2]
-// count the pairs and cells left for pass 2.
+// get their final record here; the rest are listed for the traceback or keep
+// their bin.  counters[1] and [2] count the pairs and cells left.
 __global__ __launch_bounds__(256) void sw_bin3_kernel(const PairDesc *__restrict__ pairs,
                                                       const SwPass1Out *__restrict__ p1, int64_t npairs,
-                                                      int cov_pct, pastis_pair_record *__restrict__ out,
+                                                      int cov_pct, TraceRule T, pastis_pair_record *__restrict__ out,
                                                       int8_t *__restrict__ bin_of,
                                                       unsigned long long *__restrict__ counters) {
     __shared__ unsigned long long acc[4];  // counters[1..4]; [1] and [2] here
     if (threadIdx.x < 4) acc[threadIdx.x] = 0;
     __syncthreads();
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < npairs && bin_of[q] >= 0) {
+    if (q < npairs && bin_of[q] != -1) {
         const PairDesc pd = pairs[q];
         const SwPass1Out r1 = p1[q];
         // pad < 0: sent straight here (bound 0 in effect: the coverage test of
         // the first binning already holds)
         if (r1.pad < 0 || 100LL * (r1.end_a - r1.pad + 1) >= (long long)cov_pct * pd.la) {
             const int cols = r1.end_b >= 0 ? r1.end_b + 1 : pd.lb;
+            if (can_trace(T, pd)) bin_of[q] = kToTrace;
             atomicAdd(&acc[0], 1ull);
             atomicAdd(&acc[1], (unsigned long long)(r1.end_a + 1) * (unsigned long long)cols);
         } else {
@@ -783,6 +797,23 @@ __global__ __launch_bounds__(256) void sw_bin3_kernel(const PairDesc *__restrict
         }
     }
     flush_counts(acc, counters);
+}
+
+// The traceback's list, in the order of pass 1's sorted items (so that pairs
+// of one sequence a stay together): flags by sorted position, then (after an
+// exclusive scan of them) the kept items and their class bounds.
+__global__ void trace_flags_kernel(const int *__restrict__ idx, const int8_t *__restrict__ bin_of, int npairs,
+                                   uint8_t *__restrict__ flag) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x < npairs) flag[x] = bin_of[idx[x]] == kToTrace ? 1 : 0;
+}
+
+__global__ void trace_list_kernel(const int *__restrict__ idx, const uint8_t *__restrict__ flag,
+                                  const uint32_t *__restrict__ pos, int npairs, const int *__restrict__ bounds,
+                                  int *__restrict__ list, int *__restrict__ list_bounds) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x < npairs && flag[x]) list[pos[x]] = idx[x];
+    if (x <= 2 * kNumBins) list_bounds[x] = (int)pos[min(bounds[x], npairs)];  // pos[npairs]: the total
 }
 
 // ---------------------------------------------------------------- pass 2
@@ -1131,14 +1162,23 @@ constexpr int kGroupWpb[kGroups] = {4, 4, 2, 2, 2};
 // blocks that fit on the device at once: the LDS footprint of the profiles
 // (26, 52, 39 and 52 KB per block) on 256 CUs
 constexpr int kGroupBlocks[kGroups] = {256 * 6, 256 * 3, 256 * 4, 256 * 3, 256 * 3};
-// pairs per block of the 16-bit kernels: strips of 16 or 32 lanes take 8 or 4
-// pairs per wave, the wider bins two pairs per wave
-constexpr int kGroupBlocks16[kGroups] = {256 * 6, 256 * 3, 256 * 8, 256 * 6, 256 * 3};
-
 // intra-pair pass 1: one block of four waves per pair, one block per CU (the
 // four strip profiles take up to 100 KB of LDS); the row buffers of the
 // block's slots are four of the per-wave boundary buffers
 constexpr int kIntraBlocks = 256;
+
+// 16-bit kernels: the blocks resident at once, those that also take the
+// multi-strip bins in the traceback, and the call size up to which the bins of
+// up to 8 rows per lane run across all 64 lanes.  With that many pairs two to
+// a wave, every SIMD has about four waves (3,164 pairs of up to 600 rows: pass
+// 1 in 0.37 ms across 64 lanes, 0.57 in strips of 16 and 32).
+constexpr int kBlocks16 = 256 * 6, kTraceMultiBlocks = 256;
+constexpr int64_t kWidePairs = 8192;
+
+// Traceback: a pair's direction bits take up to 1 KB per column and strip and
+// live only while its wave works on it; pairs of a longer b go to the
+// statistics kernels.
+constexpr int kTraceCols = 2048, kTraceColsMulti = 4096;
 
 // Resident blocks per CU of the one-strip statistics kernels: they keep no
 // profile in LDS, so registers set their occupancy, which the runtime reports
@@ -1167,14 +1207,14 @@ void sw_bin_shape(int bin, int32_t *rows_per_lane, int32_t *multi) {
 }
 
 // Only the multi-strip bins use the boundary buffers (one per wave of the
-// grid, 32-bit or 16-bit kernel).
+// grid).
 int sw_one_strip_max_rows() { return kWave * kSingleBins; }
 
 int64_t sw_scratch_waves() {
-    int64_t w = (int64_t)kGroupBlocks[kMultiGroup] * kGroupWpb[kMultiGroup];
-    w = std::max<int64_t>(w, (int64_t)kGroupBlocks16[kMultiGroup] * sw16_waves(kMultiGroup));
-    return std::max<int64_t>(w, (int64_t)kIntraBlocks * kIntraWaves);
+    return std::max<int64_t>((int64_t)kGroupBlocks[kMultiGroup] * kGroupWpb[kMultiGroup],
+                             (int64_t)kIntraBlocks * kIntraWaves);
 }
+int64_t sw16_scratch_waves() { return (int64_t)kBlocks16 * sw16_waves(); }
 
 // The 16-bit profile holds each biased score s + o + e in one byte, with
 // s <= 11 in BLOSUM62; other gap costs run in 32-bit lanes.
@@ -1194,47 +1234,68 @@ hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &w
 }
 
 // The launches of a call, from its pairs per bin.
-SwPlan sw_plan(const unsigned long long *bin_pairs, const Scoring &sc, int max16, const pastis_tuning &tune) {
+SwPlan sw_plan(const unsigned long long *bin_pairs, int max16, int max_len, const pastis_tuning &tune) {
     SwPlan p;
     p.max16 = max16;
     p.intra = tune.sw_intra_pair;
-    p.narrow = tune.sw16_narrow_rows;
     // multi-strip launches: at most long_blocks blocks per CU (they run beside
     // the one-strip bins on another stream; fewer resident waves leave the
     // one-strip kernels more room).  Fewer blocks than the default never
     // exceed the boundary buffers, which are sized for the default grids.
-    auto fit = [&](int g, int blocks, int64_t pairs, int per_block) {
+    auto fit = [&](int g, int blocks, int64_t pairs) {
         const int scale = g == kMultiGroup ? 1 : g < 2 ? tune.sw_grid_scale : tune.sw_grid_scale_wide;
-        int64_t b = g == kMultiGroup ? std::min(blocks, 256 * tune.sw_long_blocks) : (int64_t)blocks * scale;
+        const int64_t b = g == kMultiGroup ? std::min(blocks, 256 * tune.sw_long_blocks) : (int64_t)blocks * scale;
         // no launch needs more blocks than its pairs could fill
-        b = std::min<int64_t>(b, (pairs + per_block - 1) / per_block);
-        return (int)b;
+        return (int)std::min<int64_t>(b, (pairs + kGroupWpb[g] - 1) / kGroupWpb[g]);
     };
-    // every bin from the group's tallest non-empty one down may hold pairs of
-    // the later passes, whose end rectangles are no taller than the pairs; a
+    // every group from the tallest non-empty one down may hold pairs of the
+    // later passes, whose end rectangles are no taller than the pairs; a
     // multi-strip pair may end in any bin
-    int64_t later = 0;
+    int64_t later = 0, n16 = 0, wide16 = 0, strips16 = 0, multi16 = 0;
+    bool any32 = false;
     for (int g = kMultiGroup; g >= 0; --g) {
-        int64_t n16 = 0, n32 = 0;
-        p.bins16[g] = p.bins32[g] = 0;
+        int64_t n32 = 0;
         for (int b = 0; b < kNumBins; ++b) {
             if (!((kGroupBins[g] >> b) & 1u) || bin_pairs[b] == 0) continue;
+            const int64_t n = (int64_t)bin_pairs[b];
+            later += n;
             if (sw_bin_is16(b, max16)) {
-                n16 += (int64_t)bin_pairs[b];
-                p.bins16[g] |= 1u << b;
+                n16 += n;
+                (b < kSplitBins ? strips16 : wide16) += n;
+                if (b >= kMulti16Bin) multi16 += n;
+                p.p16.bins |= 1u << b;
             } else {
-                n32 += (int64_t)bin_pairs[b];
+                n32 += n;
                 p.bins32[g] |= 1u << b;
             }
         }
-        later += n16 + n32;
-        const int per16 = g == 0 ? (p.narrow > 0 ? 32 : 16) : g == 1 ? 16 : g == kMultiGroup ? 8 : 4;
-        p.blocks16[g] = n16 ? fit(g, kGroupBlocks16[g], n16, per16) : 0;
-        p.blocks32[g] = n32 ? fit(g, kGroupBlocks[g], n32, kGroupWpb[g]) : 0;
-        p.blocks_bound[g] = later ? fit(g, kGroupBlocks[g], later, kGroupWpb[g]) : 0;
+        any32 = any32 || n32 > 0;
+        p.blocks32[g] = n32 ? fit(g, kGroupBlocks[g], n32) : 0;
+        p.blocks_bound[g] = later ? fit(g, kGroupBlocks[g], later) : 0;
         const int per_cu = g == kMultiGroup ? 3 : std::max(1, stats_blocks_per_cu[g].load(std::memory_order_acquire));
-        p.blocks_stats[g] = later ? fit(g, 256 * per_cu, later, kGroupWpb[g]) : 0;
+        p.blocks_stats[g] = later ? fit(g, 256 * per_cu, later) : 0;
     }
+    if (n16 == 0) return p;
+    Sw16Launch &k = p.p16;
+    k.narrow = tune.sw16_narrow_rows;
+    k.wide = n16 <= kWidePairs ? 1 : 0;
+    // a block takes four pairs of the full-wave bins, eight or sixteen in strips
+    const int64_t windows = (wide16 + 3) / 4 + (strips16 + (k.wide ? 3 : 7)) / (k.wide ? 4 : 8);
+    const int scale = std::max(tune.sw_grid_scale, tune.sw_grid_scale_wide);
+    k.blocks = (int)std::min<int64_t>((int64_t)kBlocks16 * (multi16 ? 1 : scale), std::max<int64_t>(windows, 1));
+    k.multi_blocks = std::min(k.blocks, kBlocks16 * tune.sw_long_blocks / 4);
+    p.t16 = k;
+    // the traceback's list is thinner than pass 1's (large: 9 pairs of a family
+    // share a sequence a where 43 candidates do), so windows of eight pairs
+    // fill worse: strips of 32 lanes took 128 ms where those of 16 took 139
+    p.t16.narrow = 0;
+    p.t16.blocks = std::min(k.blocks, kBlocks16);
+    p.t16.multi_blocks = multi16 ? std::min(p.t16.blocks, kTraceMultiBlocks) : 0;
+    p.dirs_per_wave = (int64_t)(std::min(max_len, kTraceCols) + kWave) * sw16_step_words();
+    p.dirs_per_multi = (int64_t)kTraceStrips * (std::min(max_len, kTraceColsMulti) + kWave) * sw16_step_words();
+    p.dirs_words =
+        sw16_waves() * (p.t16.blocks * p.dirs_per_wave + p.t16.multi_blocks * p.dirs_per_multi);
+    p.stats_after_trace = any32 || max_len > kTraceCols;
     return p;
 }
 
@@ -1247,28 +1308,32 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     auto end = [&](int st) { return timed ? stage_end(ctx, st, s) : hipSuccess; };
     if (npairs <= 0) return hipSuccess;
     // The groups of a pass run beside one another on streams of the context:
-    // the multi-strip group on the long stream, the others on the call's
-    // stream and the side streams.  run(phase, f) calls f(group, stream) for
-    // every group and orders its work after the call's stream's and before
-    // what follows on it.
-    auto run = [&](int phase, auto &&busy, auto &&f) -> hipError_t {
+    // the multi-strip group on the long stream, the others on the side streams
+    // and the call's, where the 16-bit kernel (own, called as group -1) goes
+    // too.  run(phase, own, busy, f) calls f(group, stream) for every busy
+    // group and orders its work after the call's stream's and before what
+    // follows on it.
+    auto run = [&](int phase, bool own, auto &&busy, auto &&f) -> hipError_t {
         hipStream_t st[kGroups] = {ctx->side_stream[0], s, ctx->side_stream[1], ctx->side_stream[2], ctx->long_stream};
-        int first = -1, n = 0;
+        int only = -1, n = own ? 1 : 0;
         for (int g = 0; g < kGroups; ++g)
             if (busy(g)) {
                 ++n;
-                first = g;
+                only = g;
             }
         if (n == 0) return hipSuccess;
-        if (n == 1) return f(first, s);  // alone: no fork
+        if (n == 1) return f(own ? -1 : only, s);  // alone: no fork
         hipError_t e = hipEventRecord(ctx->fork_ev[phase], s);
         if (e != hipSuccess) return e;
         for (int g = kGroups - 1; g >= 0; --g) {  // long pairs first
-            if (!busy(g)) continue;
-            if (st[g] != s && (e = hipStreamWaitEvent(st[g], ctx->fork_ev[phase], 0)) != hipSuccess) return e;
+            if (!busy(g) || st[g] == s) continue;
+            if ((e = hipStreamWaitEvent(st[g], ctx->fork_ev[phase], 0)) != hipSuccess) return e;
             if ((e = f(g, st[g])) != hipSuccess) return e;
-            if (st[g] != s && (e = hipEventRecord(ctx->join_ev[phase][g], st[g])) != hipSuccess) return e;
+            if ((e = hipEventRecord(ctx->join_ev[phase][g], st[g])) != hipSuccess) return e;
         }
+        if (own && (e = f(-1, s)) != hipSuccess) return e;
+        for (int g = 0; g < kGroups; ++g)
+            if (busy(g) && st[g] == s && (e = f(g, s)) != hipSuccess) return e;
         for (int g = 0; g < kGroups; ++g)
             if (busy(g) && st[g] != s && (e = hipStreamWaitEvent(s, ctx->join_ev[phase][g], 0)) != hipSuccess) return e;
         return hipSuccess;
@@ -1310,49 +1375,79 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         return e;
     }
     if ((e = end(kStSched)) != hipSuccess || (e = begin(kStAlign1)) != hipSuccess) return e;
-    e = run(0, [&](int g) { return plan.blocks16[g] + plan.blocks32[g] > 0; },
+    // the 16-bit kernel runs beside the 32-bit groups, on the call's stream
+    e = run(0, plan.p16.blocks > 0, [&](int g) { return plan.blocks32[g] > 0; },
             [&](int g, hipStream_t st) -> hipError_t {
-                if (plan.blocks16[g]) {
-                    A.queue = wk.queue;
-                    const hipError_t r = launch_sw16(g, plan.blocks16[g], plan.narrow, A, plan.bins16[g], st);
-                    if (r != hipSuccess) return r;
+                if (g < 0) {
+                    SwArgs B = A;
+                    B.queue = wk.queue;
+                    B.scratch = wk.scratch16;
+                    B.scratch_per_wave = wk.scratch16_per_wave;
+                    return launch_sw16(false, plan.p16, B, st);
                 }
-                if (plan.blocks32[g]) {
-                    A.queue = wk.queue + 2 * kNumBins;
-                    if (g == kMultiGroup && plan.intra)
-                        sw_intra_pass1_kernel<9, 16><<<kIntraBlocks, 64 * kIntraWaves, 0, st>>>(A, plan.bins32[g]);
-                    else
-                        kPass1[g]<<<plan.blocks32[g], 64 * kGroupWpb[g], 0, st>>>(A, plan.bins32[g]);
-                    return hipGetLastError();
-                }
-                return hipSuccess;
+                A.queue = wk.queue + 2 * kNumBins;
+                if (g == kMultiGroup && plan.intra)
+                    sw_intra_pass1_kernel<9, 16><<<kIntraBlocks, 64 * kIntraWaves, 0, st>>>(A, plan.bins32[g]);
+                else
+                    kPass1[g]<<<plan.blocks32[g], 64 * kGroupWpb[g], 0, st>>>(A, plan.bins32[g]);
+                return hipGetLastError();
             });
     if (e != hipSuccess || (e = end(kStAlign1)) != hipSuccess || (e = begin(kStAlign2)) != hipSuccess) return e;
-    sw_bin2_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, stats_mode, sc.direct_pct, out, wk.bin_of,
+    const bool trace = wk.dirs != nullptr;
+    const TraceRule T{trace ? plan.p16.bins : 0u, kTraceCols, kTraceColsMulti};
+    const int *const idx1 = A.idx;  // pass 1's sorted items
+    sw_bin2_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, stats_mode, sc.direct_pct, T, out, wk.bin_of,
                                       wk.counters);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (stats_mode == 2) return end(kStAlign2);  // every record is final
-    if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) != hipSuccess)
-        return e;
+    // without a pair that the traceback refuses, only the start bound uses bins
+    const bool stats = !trace || plan.stats_after_trace;
     A.idx = wk.idx2;
     A.starts = wk.starts2;
     if (stats_mode == 0) {
         // start bound, then only the pairs whose coverage can still hold
+        if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
+            hipSuccess)
+            return e;
         A.queue = wk.queue + 3 * kNumBins;
-        e = run(1, [&](int g) { return plan.blocks_bound[g] > 0; },
+        e = run(1, false, [&](int g) { return plan.blocks_bound[g] > 0; },
                 [&](int g, hipStream_t st) {
                     kBound[g]<<<plan.blocks_bound[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
                     return hipGetLastError();
                 });
         if (e != hipSuccess) return e;
-        sw_bin3_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, out, wk.bin_of, wk.counters);
-        if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
-            hipSuccess)
+        sw_bin3_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, T, out, wk.bin_of, wk.counters);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (stats && (e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
+                     hipSuccess)
+        return e;
+    SwArgs B = A;  // the traceback's launches
+    if (trace) {
+        // the sort's keys are spent: their buffers hold the flags and the list,
+        // and the scan
+        uint8_t *flag = (uint8_t *)wk.sort_keys;
+        int *list = (int *)(wk.sort_keys + (npairs + 1) / 2);
+        uint32_t *pos = (uint32_t *)wk.sort_keys_alt;
+        trace_flags_kernel<<<nb, 256, 0, s>>>(idx1, wk.bin_of, (int)npairs, flag);
+        if ((e = exclusive_scan<uint8_t, uint32_t>(flag, npairs, pos, pos + npairs, wk.sort_temp, s)) != hipSuccess)
             return e;
+        trace_list_kernel<<<nb, 256, 0, s>>>(idx1, flag, pos, (int)npairs, wk.bounds, list, wk.trace_bounds);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        B.idx = list;
+        B.scratch = wk.scratch16;
+        B.scratch_per_wave = wk.scratch16_per_wave;
+        B.bounds = wk.trace_bounds;
+        B.queue = wk.queue + 5 * kNumBins;
+        B.dirs_per_wave = plan.dirs_per_wave;
+        B.dirs_per_multi = plan.dirs_per_multi;
+        B.dirs = wk.dirs;
+        B.dirs_multi = wk.dirs + sw16_waves() * plan.t16.blocks * plan.dirs_per_wave;
     }
     A.queue = wk.queue + 4 * kNumBins;
-    e = run(2, [&](int g) { return plan.blocks_stats[g] > 0; },
-            [&](int g, hipStream_t st) {
+    e = run(2, trace, [&](int g) { return stats && plan.blocks_stats[g] > 0; },
+            [&](int g, hipStream_t st) -> hipError_t {
+                if (g < 0) return launch_sw16(true, plan.t16, B, st);
                 kStats[g]<<<plan.blocks_stats[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
                 return hipGetLastError();
             });

@@ -1,5 +1,6 @@
 // Smith-Waterman in 16-bit lanes: two pairs in the halves of every DP word.
 #include <algorithm>
+#include <climits>
 
 #include "sw16.hpp"
 
@@ -71,6 +72,243 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
 }
 
 
+__device__ __forceinline__ int wave_min_i32(int v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, kWave));
+    return v;
+}
+
+__device__ __forceinline__ int wave_max_i32(int v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
+    return v;
+}
+
+// ---------------------------------------------------------------- traceback
+//
+// The statistics of a pair that can still pass the cut (begin, matches,
+// columns of the canonical alignment) come from a traceback.  The forward
+// sweep is pass 1's, with four direction bits per cell in place of the row
+// maxima:
+//   A  h != d          (else the diagonal, which wins ties)
+//   B  f > e           (else the horizontal gap, which wins over the vertical)
+//   C  e was opened    (else extended, which wins ties)
+//   D  f was opened
+// On the path every state's value is positive, where the floored recurrences
+// compare exactly as the unfloored ones.  The differences d - (e or f), e - f,
+// ... carry the bits in their signs; a byte permute spreads two differences'
+// signs (both pairs) to bytes of ones or zeros and a bit-select by a constant
+// files them under the row, eight ops for the four bits of two cells.  A cell
+// costs 8.5 ops where carrying the statistics along costs 27, and the bits of
+// a step leave as 4, 8, 12 or 16 contiguous bytes per lane (half a byte per
+// cell).  The walk then goes back from the end cell: a group of S / 2 lanes per
+// pair fetches the bits of at least 16 rows (9 in the wider bins) over at
+// least 16 columns at a time, so a pair waits for memory once per fetch instead of once per
+// cell, and knows its value h at every cell, which is how it finds the begin
+// (the diagonal predecessor's h is 0).
+//
+// Word k of a lane's step holds its rows 4 k .. 4 k + 3 in bits 0..3 of each
+// byte and their C / D bits in bits 4..7: bytes 0 and 1 are pair P's (A | C,
+// B | D), bytes 2 and 3 pair Q's.
+template <int RP>
+constexpr int dir_words() {
+    return (RP + 3) / 4;
+}
+
+template <int NW>
+__device__ __forceinline__ void store_dirs(uint32_t *p, const uint32_t (&w)[NW]) {
+    if constexpr (NW == 1) {
+        *p = w[0];
+    } else if constexpr (NW == 2) {
+        *(uint2 *)p = make_uint2(w[0], w[1]);
+    } else if constexpr (NW == 3) {
+        *(uint3 *)p = make_uint3(w[0], w[1], w[2]);
+    } else {
+        *(uint4 *)p = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+// files the direction bits of row r (d, e, f: the row's candidates; x, y: the
+// extended gaps; g, gu: the opened ones)
+template <int NW>
+__device__ __forceinline__ void file_dirs(uint32_t (&w)[NW], int r, short2_t d, short2_t m, short2_t e, short2_t f,
+                                          short2_t x, short2_t g, short2_t y, short2_t gu) {
+    // selectors 8 / 9 and 10 / 11 spread the sign bits of the second and the
+    // first operand's halves
+    const uint32_t ab = __builtin_amdgcn_perm(u2(d - m), u2(e - f), 0x090B080Au);
+    const uint32_t cd = __builtin_amdgcn_perm(u2(x - g), u2(y - gu), 0x090B080Au);
+    const uint32_t k1 = 0x01010101u << (r & 3), k2 = 0x10101010u << (r & 3);
+    uint32_t v = w[r >> 2];
+    v = (ab & k1) | (v & ~k1);
+    v = (cd & k2) | (v & ~k2);
+    w[r >> 2] = v;
+}
+
+// A walk's fetch: the bits of kSlots lanes' rows (at least 16 rows where a
+// strip has one piece) over kCols columns.
+template <int S, int RP, bool MULTI>
+struct WalkShape {
+    static constexpr int W = S / 2;  // lanes of the group
+    static constexpr int kSlots = MULTI || RP > 8 ? 1 : (15 + RP) / RP;
+    static constexpr int kCols = W < 16 ? 16 : W;
+    static constexpr int kRows = kSlots * RP;
+    static constexpr int NW = dir_words<RP>();
+    struct Lds {
+        uint32_t dir[kCols][kSlots * NW];
+        uint8_t b[kCols];
+        uint8_t a[(kRows + 3) / 4 * 4];
+    };
+};
+
+struct Walk {
+    int i, j;        // the end cell, then the begin cell
+    int h;           // the end cell's score
+    int matches = 0, diag = 0;
+};
+
+// Walks one pair back from its end cell.  The calling lanes are a group of W =
+// S / 2 (lane `sub` of it) that share the pair and the LDS area; slot0 is the
+// wave lane of the pair's row block 0, half its half of the words, dirs the
+// wave's direction words and strip_words the distance between strips.  A run of
+// diagonal steps is taken at once: lane k looks at the k-th cell up the
+// diagonal, a ballot ends the run at the first cell that is not diagonal, and a
+// prefix sum of the scores finds the begin (h falls to 0); gap cells go one by
+// one.
+template <int S, int RP, bool MULTI>
+__device__ __forceinline__ void walk_back(Walk &P, bool act, const uint32_t *dirs, int64_t strip_words,
+                                          const uint8_t *__restrict__ a, int la, const uint8_t *__restrict__ b,
+                                          int slot0, int half, int sub,
+                                          typename WalkShape<S, RP, MULTI>::Lds &L, const int8_t *sblosum, int go_ge,
+                                          int ge) {
+    using T = WalkShape<S, RP, MULTI>;
+    constexpr int W = T::W, NW = T::NW;
+    const int g0 = (int)(threadIdx.x & (kWave - 1)) - sub;  // the group's first lane
+    const unsigned long long gmask = W == 64 ? ~0ull : (1ull << W) - 1ull;
+    int i = P.i, j = P.j, h = P.h, state = 0;  // 0: H, 1: horizontal gap, 2: vertical gap
+    bool done = !act || i < 0 || j < 0;
+    while (!done) {
+        const int blk = i / RP, j0 = j;
+        const int p = MULTI ? blk % kWave : blk;
+        const int pb = p - (T::kSlots - 1);           // first slot fetched (may be negative)
+        const int r0 = (blk - (T::kSlots - 1)) * RP;  // its first row
+        const uint32_t *src = dirs + (MULTI ? (blk / kWave) * strip_words : 0);
+#pragma unroll
+        for (int m = 0; m < T::kCols / W; ++m) {
+            const int c = m * W + sub, col = j0 - c;
+            if (col < 0) continue;
+#pragma unroll
+            for (int k = 0; k < T::kSlots; ++k) {
+                if (pb + k < 0) continue;
+                const uint32_t *w = src + (int64_t)(col + pb + k) * (kWave * NW) + (slot0 + pb + k) * NW;
+#pragma unroll
+                for (int x = 0; x < NW; ++x) L.dir[c][k * NW + x] = vload(w + x);
+            }
+            L.b[c] = b[col];
+        }
+        for (int r = sub; r < T::kRows; r += W)
+            if (r0 + r >= 0 && r0 + r < la) L.a[r] = a[r0 + r];
+        __builtin_amdgcn_wave_barrier();
+        int r = i - r0, c = 0;
+        const int cend = min(T::kCols, j0 + 1);
+        auto bits_at = [&](int rr, int cc) {
+            const int s = rr / RP, x = rr % RP;
+            return L.dir[cc][s * NW + (x >> 2)] >> ((x & 3) + 16 * half);
+        };
+        while (r >= 0 && c < cend && !done) {
+            if (state == 0) {
+                const int rr = r - sub, cc = c + sub;
+                bool stop = true, match = false;
+                int sum = 0;
+                if (rr >= 0 && cc < cend) {
+                    stop = (bits_at(rr, cc) & 1u) != 0;
+                    const int ca = L.a[rr], cb = L.b[cc];
+                    match = ca == cb;
+                    sum = sblosum[ca * kProfCodes + cb];
+                }
+                const unsigned long long stops = (__ballot(stop) >> g0) & gmask;
+                const int run = stops ? __ffsll((long long)stops) - 1 : W;
+#pragma unroll
+                for (int d = 1; d < W; d <<= 1) {
+                    const int o = __shfl_up(sum, d, W);
+                    sum += sub >= d ? o : 0;
+                }
+                const unsigned long long zero = (__ballot(sub < run && h == sum) >> g0) & gmask;
+                const int n = zero ? __ffsll((long long)zero) : run;  // diagonal cells taken
+                const unsigned long long taken = n >= 64 ? ~0ull : (1ull << n) - 1ull;
+                P.diag += n;
+                P.matches += __popcll((__ballot(match) >> g0) & taken);
+                if (zero) {  // the path starts at the last of them
+                    r -= n - 1;
+                    c += n - 1;
+                    done = true;
+                    break;
+                }
+                const int back = __shfl(sum, max(n - 1, 0), W);
+                h -= n > 0 ? back : 0;
+                r -= n;
+                c += n;
+                // the run ended inside the fetch: at a cell that is not diagonal
+                if (n == W || r < 0 || c >= cend) continue;
+                state = (bits_at(r, c) & 0x100u) ? 2 : 1;
+            }
+            const bool opened = (bits_at(r, c) & (state == 1 ? 0x10u : 0x1000u)) != 0;
+            h += opened ? go_ge : ge;
+            if (state == 1)
+                ++c;
+            else
+                --r;
+            if (opened) state = 0;
+        }
+        i = r0 + r;
+        j = j0 - c;
+        done = done || i < 0 || j < 0;
+        __builtin_amdgcn_wave_barrier();
+    }
+    P.i = i;
+    P.j = j;
+}
+
+// the record of a walked pair (its descriptor is read again rather than kept
+// in registers through the sweep)
+__device__ __forceinline__ void walk_record(const SwArgs &A, const Walk &P, int score, int end_a, int end_b, int q) {
+    const PairDesc pd = A.pairs[q];
+    pastis_pair_record rec;
+    rec.score = score;
+    rec.end_a = end_a;
+    rec.end_b = end_b;
+    rec.beg_a = P.i;
+    rec.beg_b = P.j;
+    rec.matches = P.matches;
+    rec.columns = (end_a - P.i + 1) + (end_b - P.j + 1) - P.diag;
+    rec.seed_used = -1;
+    const long long span = (long long)end_a - P.i + 1;
+    rec.passed = (100LL * rec.matches >= (long long)A.id_pct * rec.columns) &&
+                 (100LL * span >= (long long)A.cov_pct * pd.la);
+    rec.swapped = pd.swapped;
+    rec.cells = (int64_t)pd.la * pd.lb;
+    A.rec[q] = rec;
+}
+
+// Pass 1's hint at a pair's end column: the first column the end row can
+// reach its maximum in.  Every 16 steps a lane compares the maximum over its
+// rows with the one 16 steps before; the last change marks the 16 steps in
+// which the lane first reached its final maximum, which no later column can
+// precede.  Kept per half (pair), in units of 16 steps.
+template <int RP>
+__device__ __forceinline__ void note_rise(const uint32_t (&M)[RP], uint32_t &seen, uint32_t &when, int chunk) {
+    uint32_t m = M[0];
+#pragma unroll
+    for (int r = 1; r < RP; ++r) m = u2(pmax(s2(m), s2(M[r])));
+    const uint32_t diff = m ^ seen;
+    seen = m;
+    const uint32_t mask = ((diff & 0xFFFFu) ? 0xFFFFu : 0u) | ((diff >> 16) ? 0xFFFF0000u : 0u);
+    when = (when & ~mask) | (((uint32_t)chunk * 0x10001u) & mask);
+}
+
+// SwPass1Out::end_b while the end column is unknown: -2 - (first possible column)
+__device__ __forceinline__ int hint_code(int chunk, int pos) { return -2 - max(16 * chunk - pos, 0); }
+__device__ __forceinline__ int first_col(int end_b) { return end_b >= 0 ? end_b : max(-2 - end_b, 0); }
+
 // Full-wave layout for the wider bins.  A block takes 2 * WPB consecutive
 // pairs (two per wave) and its waves share one profile, built once per
 // distinct sequence a among them (pairs are sorted by a), so the LDS of a
@@ -87,10 +325,12 @@ struct WaveLds {
     int take;  // the block's window, claimed from the bin's queue
 };
 
-template <int R, int WPB, bool MULTI>
+// TRACE: the statistics pass of the pairs listed (see the traceback above), in
+// the same layout.
+template <int R, int WPB, bool MULTI, bool TRACE>
 __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds, const int8_t *sblosum,
                                             WaveLds<WPB> &L) {
-    static_assert(R > 8 && R <= kMax16R, "more than 512 rows per strip");
+    static_assert(R <= kMax16R, "at most 1024 rows per strip");
     constexpr int NI = 2 * WPB;  // pairs per block
     constexpr int RS = kWave * R;  // rows per strip
     const uint8_t *__restrict__ codes = A.codes;
@@ -102,15 +342,22 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
     auto &s_next = L.next;
     int &s_take = L.take;
     const int item_begin = A.bounds[2 * bin];
+    constexpr int NW = dir_words<R>();
+    const int64_t gwave = (int64_t)blockIdx.x * WPB + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    uint32_t *const dirs =
+        !TRACE ? nullptr : MULTI ? A.dirs_multi + gwave * A.dirs_per_multi : A.dirs + gwave * A.dirs_per_wave;
+    const int64_t strip_words = A.dirs_per_multi / kTraceStrips;
     bool any = false;
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
+    // wave-uniform values are made so for the compiler, which keeps them (and
+    // the loops they bound) out of the vector registers
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int item_end = A.bounds[2 * bin + 2];
     const uint32_t OE2 = (uint32_t)go_ge * 0x10001u, GE2 = (uint32_t)ge * 0x10001u;
     const uint32_t G0 = ((uint32_t)(-go_ge) & 0xFFFFu) * 0x10001u;  // G of an H = 0 cell
     uint32_t *bnd_g = nullptr, *bnd_f = nullptr;
     if constexpr (MULTI) {
-        bnd_g = (uint32_t *)A.scratch + ((int64_t)blockIdx.x * WPB + wave) * A.scratch_per_wave;
+        bnd_g = (uint32_t *)A.scratch + gwave * A.scratch_per_wave;
         bnd_f = bnd_g + A.scratch_per_wave / 2;
     }
     int par = 0;
@@ -120,10 +367,10 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
         // first barrier, so thread 0 may claim the next one
         if (threadIdx.x == 0) s_take = atomicAdd(A.queue + 2 * bin, NI);
         __syncthreads();
-        const int64_t w = item_begin + (int64_t)s_take;
+        const int w = item_begin + __builtin_amdgcn_readfirstlane(s_take);
         if (w >= item_end) break;
         any = true;
-        const int nit = (int)min((int64_t)NI, item_end - w);
+        const int nit = min(NI, item_end - w);
         const int iP = 2 * wave, iQ = iP + 1;
         const int qP = iP < nit ? idx[w + iP] : -1;
         const int qQ = iQ < nit ? idx[w + iQ] : -1;
@@ -137,6 +384,7 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
             int first = NI;
 #pragma unroll
             for (int k = 0; k < WPB; ++k) first = min(first, s_next[par][k]);
+            first = __builtin_amdgcn_readfirstlane(first);
             par ^= 1;
             if (first >= NI) break;
             const PairDesc dA = pairs[idx[w + first]];
@@ -147,8 +395,25 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
             const int lb = max(lbP, lbQ);
             const int steps = lb > 0 ? lb + kWave - 1 : 0;
             const int nstrips = MULTI ? (laA + RS - 1) / RS : 1;
-            // best row of each pair: (score << 16) | (0xFFFF - row), maximised
+            // best row of each pair: (score << 16) | (0xFFFF - row), maximised,
+            // and the lane's hint at its end column
             unsigned kp = 0u, kq = 0u;
+            int hintP = 0, hintQ = 0;
+            // TRACE: each pair's end row, first possible end column and score, and
+            // the last strip that holds an end cell
+            int rowP = -1, rowQ = -1, fcP = 0, fcQ = 0, scP = 0, scQ = 0;
+            int endP = -1, endQ = -1, last_strip = 0;
+            if constexpr (TRACE) {
+                if (actP) {
+                    const SwPass1Out r1 = A.p1[qP];
+                    rowP = r1.end_a, fcP = first_col(r1.end_b), scP = r1.score;
+                }
+                if (actQ) {
+                    const SwPass1Out r1 = A.p1[qQ];
+                    rowQ = r1.end_a, fcQ = first_col(r1.end_b), scQ = r1.score;
+                }
+                if constexpr (MULTI) last_strip = __builtin_amdgcn_readfirstlane(max(max(rowP, rowQ), 0) / RS);
+            }
             for (int sidx = 0; sidx < nstrips; ++sidx) {
                 const int base = sidx * RS;
                 if (sidx > 0) __syncthreads();  // every wave is done with the last strip's profile
@@ -157,13 +422,27 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
                 __syncthreads();
                 const bool from_above = MULTI && sidx > 0;
                 const bool to_below = MULTI && sidx + 1 < nstrips;
-                uint32_t G[R], E[R], M[R];
+                if (TRACE && sidx > last_strip) continue;  // nothing below this wave's end cells
+                uint32_t G[R], E[R], M[TRACE ? 1 : R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     G[r] = G0;
                     E[r] = 0u;
-                    M[r] = 0u;
+                    if constexpr (!TRACE) M[r] = 0u;
                 }
+                uint32_t seen = 0u, when = 0u;
+                int noted = 0;  // step of the last note_rise
+                // TRACE: does this lane hold an end cell of this strip still to be
+                // found, and the first step one can be found in (tn, wave-uniform)
+                const int eP = rowP - base, eQ = rowQ - base;
+                bool needP = TRACE && eP >= 0 && eP < RS && eP / R == lane;
+                bool needQ = TRACE && eQ >= 0 && eQ < RS && eQ / R == lane;
+                const int reP = eP % R, reQ = eQ % R;
+                auto first_step = [&]() {
+                    return __builtin_amdgcn_readfirstlane(
+                        wave_min_i32(min(needP ? fcP + lane : INT_MAX, needQ ? fcQ + lane : INT_MAX)));
+                };
+                int tn = TRACE ? first_step() : INT_MAX;
                 uint32_t glast = G0, flast = 0u, gprev = G0;
                 // column residues travel as byte offsets into the profile, P's
                 // in the low half and Q's in the high half (at most 24 * 1024)
@@ -217,6 +496,7 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
                     const ProfWord<R> cP = *(const ProfWord<R> *)(plane + ((uint32_t)cres & 0xFFFFu));
                     const ProfWord<R> cQ = *(const ProfWord<R> *)(plane + ((uint32_t)cres >> 16));
                     short2_t gd = s2(gprev), gu = s2(rg), fu = s2(rf);
+                    uint32_t dw[NW] = {};
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
                         // byte r of P's and Q's words into the two halves
@@ -224,21 +504,26 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
                             (uint32_t)(r & 3) | 0x0C00u | ((uint32_t)(4 + (r & 3)) << 16) | 0x0C000000u;
                         const short2_t sig =
                             s2(__builtin_amdgcn_perm(prof_word<R>(cQ, r), prof_word<R>(cP, r), sel));
-                        const short2_t e = pmax(psubs(s2(E[r]), GE2), s2(G[r]));
-                        const short2_t f = pmax(psubs(fu, GE2), gu);
+                        const short2_t ex = psubs(s2(E[r]), GE2), fx = psubs(fu, GE2);
+                        const short2_t e = pmax(ex, s2(G[r]));
+                        const short2_t f = pmax(fx, gu);
                         const short2_t d = gd + sig;
-                        const short2_t h = pmax(d, pmax(e, f));
+                        const short2_t m = pmax(e, f);
+                        const short2_t h = pmax(d, m);
+                        if constexpr (TRACE) file_dirs(dw, r, d, m, e, f, ex, s2(G[r]), fx, gu);
                         gd = s2(G[r]);
                         const short2_t g = h - s2(OE2);
                         G[r] = u2(g);
                         E[r] = u2(e);
-                        M[r] = u2(pmax(s2(M[r]), h));
+                        if constexpr (!TRACE) M[r] = u2(pmax(s2(M[r]), h));
                         gu = g;
                         fu = f;
                     }
                     glast = G[R - 1];
                     flast = u2(fu);
                     gprev = rg;
+                    if constexpr (TRACE)
+                        store_dirs(dirs + (MULTI ? sidx * strip_words : 0) + (int64_t)t * (kWave * NW) + lane * NW, dw);
                     if (to_below) {
                         const int j = t - (kWave - 1);
                         if (lane == kWave - 1 && j >= 0 && j < lb) {
@@ -247,46 +532,116 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
                         }
                     }
                 };
+                // one step, and in TRACE the test for the end cells it can hold:
+                // the end column is the first where row end_a reaches the score
+                auto advance = [&](const int t, auto top_tag) {
+                    step(t, top_tag);
+                    if constexpr (TRACE) {
+                        if (t < tn) return;
+                        // (the empty statement keeps the row tests here: hoisted out
+                        // of the loop they would hold two masks per row)
+                        int rp = reP, rq = reQ;
+                        asm volatile("" : "+v"(rp), "+v"(rq));
+                        uint32_t gP = G[0], gQ = G[0];
+#pragma unroll
+                        for (int r = 1; r < R; ++r) {
+                            gP = rp == r ? G[r] : gP;
+                            gQ = rq == r ? G[r] : gQ;
+                        }
+                        const int c = t - lane;
+                        const bool hitP = needP && c >= 0 && (int)(int16_t)(gP & 0xFFFFu) + go_ge == scP;
+                        const bool hitQ = needQ && c >= 0 && ((int)gQ >> 16) + go_ge == scQ;
+                        if (hitP) endP = c;
+                        if (hitQ) endQ = c;
+                        needP = needP && !hitP;
+                        needQ = needQ && !hitQ;
+                        if (__ballot(hitP || hitQ)) tn = first_step();
+                    }
+                };
+                // (TRACE) every end cell of the wave is found
+                auto found = [&]() { return TRACE && tn == INT_MAX && sidx == last_strip; };
                 // two steps per iteration, so the old and new G registers can
                 // swap roles instead of being copied back every step
                 int t = 0;
                 if (from_above) {
-                    for (; t + 1 < lb; t += 2) {
-                        step(t, std::true_type{});
-                        step(t + 1, std::true_type{});
+                    for (; t + 1 < lb && !found(); t += 2) {
+                        if constexpr (!TRACE)
+                            if ((t & 15) == 0) note_rise(M, seen, when, (noted = t, (t >> 4) - 1));
+                        advance(t, std::true_type{});
+                        advance(t + 1, std::true_type{});
                     }
-                    if (t < lb) step(t++, std::true_type{});
+                    if (t < lb && !found()) advance(t++, std::true_type{});
                 }
-                for (; t + 1 < steps; t += 2) {
-                    step(t, std::false_type{});
-                    step(t + 1, std::false_type{});
+                for (; t + 1 < steps && !found(); t += 2) {
+                    if constexpr (!TRACE)
+                        if ((t & 15) <= 1) note_rise(M, seen, when, (noted = t, (t >> 4) - 1));
+                    advance(t, std::false_type{});
+                    advance(t + 1, std::false_type{});
                 }
-                if (t < steps) step(t, std::false_type{});
+                if (t < steps && !found()) advance(t, std::false_type{});
+                if constexpr (!TRACE) {
+                    note_rise(M, seen, when, noted >> 4);  // the steps since the last note
+                    unsigned sp = 0u, sq = 0u;
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int row = base + lane * R + r;
-                    const unsigned rk = 0xFFFFu - (unsigned)row;
-                    if (row < laA) {
-                        kp = max(kp, ((M[r] & 0xFFFFu) << 16) | rk);
-                        kq = max(kq, (M[r] & 0xFFFF0000u) | rk);
+                    for (int r = 0; r < R; ++r) {
+                        const int row = base + lane * R + r;
+                        const unsigned rk = 0xFFFFu - (unsigned)row;
+                        if (row < laA) {
+                            sp = max(sp, ((M[r] & 0xFFFFu) << 16) | rk);
+                            sq = max(sq, (M[r] & 0xFFFF0000u) | rk);
+                        }
+                    }
+                    if (sp > kp) {
+                        kp = sp;
+                        hintP = hint_code((int)(when & 0xFFFFu), lane);
+                    }
+                    if (sq > kq) {
+                        kq = sq;
+                        hintQ = hint_code((int)(when >> 16), lane);
                     }
                 }
                 if (to_below) __threadfence_block();  // lane 0 of the next strip reads lane 63's row
             }
+            if constexpr (TRACE) {
+                __syncthreads();  // every wave is done with the profile: its LDS serves the walks
+                __threadfence_block();
+                const int half = lane / 32, sub = lane % 32;
+                const bool act = half ? actQ : actP;
+                const int q = half ? qQ : qP;
+                const int colP = __shfl(endP, max(rowP, 0) % RS / R, kWave);
+                const int colQ = __shfl(endQ, max(rowQ, 0) % RS / R, kWave);
+                const int end_a = half ? rowQ : rowP, end_b = half ? colQ : colP, score = half ? scQ : scP;
+                Walk P;
+                P.i = end_a;
+                P.j = end_b;
+                P.h = score;
+                auto *wl = (typename WalkShape<kWave, R, MULTI>::Lds *)lds + 2 * wave + half;
+                walk_back<kWave, R, MULTI>(P, act, dirs, strip_words, codes + dA.a_off, laA, half ? bQ : bP, 0, half,
+                                           sub, *wl, sblosum, go_ge, ge);
+                if (act && sub == 0) walk_record(A, P, score, end_a, end_b, q);
+                doneP = doneP || actP;
+                doneQ = doneQ || actQ;
+                continue;
+            }
+            const unsigned lp = kp, lq = kq;  // the lane's own
             kp = wave_max_u32(kp);
             kq = wave_max_u32(kq);
+            // the winning lane's hint (its key holds its row, so it is alone)
+            const int hp = __shfl(hintP, __ffsll((long long)__ballot(lp == kp)) - 1, kWave);
+            const int hq = __shfl(hintQ, __ffsll((long long)__ballot(lq == kq)) - 1, kWave);
             if (lane == 0) {
                 SwPass1Out o;
-                o.end_b = -1;
                 o.pad = 0;
                 if (actP) {
                     o.score = (int32_t)(kp >> 16);
                     o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kp & 0xFFFFu)) : -1;
+                    o.end_b = o.score > 0 ? hp : -1;
                     out[qP] = o;
                 }
                 if (actQ) {
                     o.score = (int32_t)(kq >> 16);
                     o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kq & 0xFFFFu)) : -1;
+                    o.end_b = o.score > 0 ? hq : -1;
                     out[qQ] = o;
                 }
             }
@@ -344,22 +699,9 @@ __device__ __forceinline__ unsigned strip_max_u32(unsigned v) {
     return v;
 }
 
-__device__ __forceinline__ int wave_min_i32(int v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
-__device__ __forceinline__ int wave_max_i32(int v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
-
 // One rows class of a bin's pairs (sorted by rows class first): class c holds
 // the items [bounds[2 bin + c], bounds[2 bin + c + 1]) and has its own queue.
-template <int S, int RP>
+template <int S, int RP, bool TRACE>
 __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds, size_t wave_bytes,
                                              const int8_t *sblosum) {
     static_assert((S == 16 || S == 32) && RP <= kMax16R, "strip shape");
@@ -377,6 +719,9 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
     ProfWord<RP>(*prof)[S] = (ProfWord<RP>(*)[S])(lds + (size_t)wave * wave_bytes);
     const int item_begin = A.bounds[cls], item_end = A.bounds[cls + 1];
     int *const counter = A.queue + cls;
+    constexpr int NW = dir_words<RP>();
+    uint32_t *const dirs =
+        TRACE ? A.dirs + ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * A.dirs_per_wave : nullptr;
     bool any = false;
     const uint32_t OE2 = (uint32_t)go_ge * 0x10001u, GE2 = (uint32_t)ge * 0x10001u;
     const uint32_t G0 = ((uint32_t)(-go_ge) & 0xFFFFu) * 0x10001u;  // G of an H = 0 cell
@@ -414,13 +759,36 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
             __builtin_amdgcn_wave_barrier();
             const int lbmax = wave_max_i32(max(lbP, lbQ));
             const int steps = __builtin_amdgcn_readfirstlane(lbmax > 0 ? lbmax + S - 1 : 0);
-            uint32_t G[RP], E[RP], M[RP];
+            uint32_t G[RP], E[RP], M[TRACE ? 1 : RP];
 #pragma unroll
             for (int r = 0; r < RP; ++r) {
                 G[r] = G0;
                 E[r] = 0u;
-                M[r] = 0u;
+                if constexpr (!TRACE) M[r] = 0u;
             }
+            uint32_t seen = 0u, when = 0u;
+                int noted = 0;  // step of the last note_rise
+            // TRACE: each pair's end cell, whether this lane holds one still to
+            // be found, and the first step one can be found in (tn, wave-uniform)
+            int rowP = -1, rowQ = -1, fcP = 0, fcQ = 0, scP = 0, scQ = 0;
+            if constexpr (TRACE) {
+                if (actP) {
+                    const SwPass1Out r1 = A.p1[qP];
+                    rowP = r1.end_a, fcP = first_col(r1.end_b), scP = r1.score;
+                }
+                if (actQ) {
+                    const SwPass1Out r1 = A.p1[qQ];
+                    rowQ = r1.end_a, fcQ = first_col(r1.end_b), scQ = r1.score;
+                }
+            }
+            int endP = -1, endQ = -1;
+            bool needP = TRACE && rowP >= 0 && rowP / RP == pos, needQ = TRACE && rowQ >= 0 && rowQ / RP == pos;
+            const int reP = rowP % RP, reQ = rowQ % RP;
+            auto first_step = [&]() {
+                return __builtin_amdgcn_readfirstlane(
+                    wave_min_i32(min(needP ? fcP + pos : INT_MAX, needQ ? fcQ + pos : INT_MAX)));
+            };
+            int tn = TRACE ? first_step() : INT_MAX;
             uint32_t glast = G0, flast = 0u, gprev = G0;
             // column residues travel as byte offsets into the profile, P's in
             // the low half and Q's in the high half (at most 24 * 512 bytes)
@@ -464,62 +832,122 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
                     cQ = at(cres >> 16);
                 }
                 short2_t gd = s2(gprev), gu = s2(rg), fu = s2(rf);
+                uint32_t dw[NW] = {};
 #pragma unroll
                 for (int r = 0; r < RP; ++r) {
                     const uint32_t sel =
                         (uint32_t)(r & 3) | 0x0C00u | ((uint32_t)(4 + (r & 3)) << 16) | 0x0C000000u;
                     const short2_t sig = s2(__builtin_amdgcn_perm(prof_word<RP>(cQ, r), prof_word<RP>(cP, r), sel));
-                    const short2_t e = pmax(psubs(s2(E[r]), GE2), s2(G[r]));
-                    const short2_t f = pmax(psubs(fu, GE2), gu);
+                    const short2_t ex = psubs(s2(E[r]), GE2), fx = psubs(fu, GE2);
+                    const short2_t e = pmax(ex, s2(G[r]));
+                    const short2_t f = pmax(fx, gu);
                     const short2_t d = gd + sig;
-                    const short2_t h = pmax(d, pmax(e, f));
+                    const short2_t m = pmax(e, f);
+                    const short2_t h = pmax(d, m);
+                    if constexpr (TRACE) file_dirs(dw, r, d, m, e, f, ex, s2(G[r]), fx, gu);
                     gd = s2(G[r]);
                     const short2_t g = h - s2(OE2);
                     G[r] = u2(g);
                     E[r] = u2(e);
-                    M[r] = u2(pmax(s2(M[r]), h));
+                    if constexpr (!TRACE) M[r] = u2(pmax(s2(M[r]), h));
                     gu = g;
                     fu = f;
                 }
                 glast = G[RP - 1];
                 flast = u2(fu);
                 gprev = rg;
+                if constexpr (TRACE) {
+                    store_dirs(dirs + (int64_t)t * (kWave * NW) + lane * NW, dw);
+                    if (t < tn) return;
+                    // the end column is the first where row end_a reaches the score
+                    // (the empty statement keeps the row tests here: hoisted out
+                    // of the loop they would hold two masks per row)
+                    int rp = reP, rq = reQ;
+                    asm volatile("" : "+v"(rp), "+v"(rq));
+                    uint32_t gP = G[0], gQ = G[0];
+#pragma unroll
+                    for (int r = 1; r < RP; ++r) {
+                        gP = rp == r ? G[r] : gP;
+                        gQ = rq == r ? G[r] : gQ;
+                    }
+                    const int c = t - pos;
+                    const bool hitP = needP && c >= 0 && (int)(int16_t)(gP & 0xFFFFu) + go_ge == scP;
+                    const bool hitQ = needQ && c >= 0 && ((int)gQ >> 16) + go_ge == scQ;
+                    if (hitP) endP = c;
+                    if (hitQ) endQ = c;
+                    needP = needP && !hitP;
+                    needQ = needQ && !hitQ;
+                    if (__ballot(hitP || hitQ)) tn = first_step();
+                }
             };
+            // (TRACE) every end cell of the wave is found
+            auto found = [&]() { return TRACE && tn == INT_MAX; };
             if constexpr (kAhead) {
                 feed(0);
                 wP = at(cres & 0xFFFFu);
                 wQ = at(cres >> 16);
             }
             int t = 0;
-            for (; t + 1 < steps; t += 2) {
+            for (; t + 1 < steps && !found(); t += 2) {
+                if constexpr (!TRACE)
+                    if ((t & 15) == 0) note_rise(M, seen, when, (noted = t, (t >> 4) - 1));
                 step(t);
                 step(t + 1);
             }
-            if (t < steps) step(t);
+            if (t < steps && !found()) step(t);
+            if constexpr (TRACE) {
+                // the wave's own profile is done with: its LDS serves the walks
+                __threadfence_block();
+                const int half = pos / (S / 2), sub = pos % (S / 2);
+                const bool act = half ? actQ : actP;
+                const int q = half ? qQ : qP;
+                const int colP = __shfl(endP, strip * S + max(rowP, 0) / RP, kWave);
+                const int colQ = __shfl(endQ, strip * S + max(rowQ, 0) / RP, kWave);
+                const int end_a = half ? rowQ : rowP, end_b = half ? colQ : colP, score = half ? scQ : scP;
+                Walk P;
+                P.i = end_a;
+                P.j = end_b;
+                P.h = score;
+                auto *wl = (typename WalkShape<S, RP, false>::Lds *)(lds + (size_t)wave * wave_bytes) + 2 * strip + half;
+                walk_back<S, RP, false>(P, act, dirs, 0, codes + a_off, la, half ? bQ : bP, strip * S, half, sub, *wl,
+                                        sblosum, go_ge, ge);
+                if (act && sub == 0) walk_record(A, P, score, end_a, end_b, q);
+                doneP = doneP || actP;
+                doneQ = doneQ || actQ;
+                continue;
+            }
             unsigned kp = 0u, kq = 0u;
+            if constexpr (!TRACE) {
+                note_rise(M, seen, when, noted >> 4);  // the steps since the last note
 #pragma unroll
-            for (int r = 0; r < RP; ++r) {
-                const int row = pos * RP + r;
-                const unsigned rk = 0xFFFFu - (unsigned)row;
-                if (row < la) {
-                    kp = max(kp, ((M[r] & 0xFFFFu) << 16) | rk);
-                    kq = max(kq, (M[r] & 0xFFFF0000u) | rk);
+                for (int r = 0; r < RP; ++r) {
+                    const int row = pos * RP + r;
+                    const unsigned rk = 0xFFFFu - (unsigned)row;
+                    if (row < la) {
+                        kp = max(kp, ((M[r] & 0xFFFFu) << 16) | rk);
+                        kq = max(kq, (M[r] & 0xFFFF0000u) | rk);
+                    }
                 }
             }
             kp = strip_max_u32<S>(kp);
             kq = strip_max_u32<S>(kq);
+            // the end rows' lanes and their hints at the end columns
+            const int posP = (int)(0xFFFFu - (kp & 0xFFFFu)) / RP % S, posQ = (int)(0xFFFFu - (kq & 0xFFFFu)) / RP % S;
+            const uint32_t whenP = (uint32_t)__shfl((int)when, strip * S + posP, kWave);
+            const uint32_t whenQ = (uint32_t)__shfl((int)when, strip * S + posQ, kWave);
             if (pos == 0) {
                 SwPass1Out o;
-                o.end_b = -1;
                 o.pad = 0;
                 if (actP) {
                     o.score = (int32_t)(kp >> 16);
                     o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kp & 0xFFFFu)) : -1;
+                    o.end_b = o.score > 0 ? hint_code((int)(whenP & 0xFFFFu), posP) : -1;
                     out[qP] = o;
                 }
                 if (actQ) {
                     o.score = (int32_t)(kq >> 16);
                     o.end_a = o.score > 0 ? (int32_t)(0xFFFFu - (kq & 0xFFFFu)) : -1;
+                    o.end_b = o.score > 0 ? hint_code((int)(whenQ >> 16), posQ) : -1;
                     out[qQ] = o;
                 }
             }
@@ -530,37 +958,73 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
     return any;
 }
 
-// ---------------------------------------------------------------- group kernels
+// ---------------------------------------------------------------- kernel
 
-// f(integral HI), f(integral HI - 1), ...
+// f(integral HI), f(integral HI - 1), ... down to 1 + HI - count
 template <int HI, typename F, int... I>
 __device__ __forceinline__ void descending(F &f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, HI - I>{}), ...);
 }
 
-// The bins of a group, tallest first, in one launch (see the group launches
-// of the 32-bit kernels); a bin of up to 8 rows per lane runs its taller rows
-// class first.
-template <int HI, int... I>
-__device__ __forceinline__ void strip_bins(const SwArgs &A, uint32_t bins, int narrow, char *lds, size_t wave_bytes,
-                                           const int8_t *sblosum, std::integer_sequence<int, I...>) {
+// One launch for every bin in 16-bit lanes, the tallest first: waves take a
+// bin's windows until its queue is empty, then go on to the next bin, so the
+// launch has one tail, made of the shortest windows (see the 32-bit groups for
+// what a tail per bin cost).  Blocks of two waves: a pair of more than 512 rows
+// shares its profile between the block's waves, and a window of four pairs
+// keeps the rounds per distinct sequence a few where sequences have few
+// partners; 26 KB of LDS and at most 168 registers keep six blocks (three
+// waves per SIMD) on a CU, which issue 0.94 of its slots.
+//
+// Bins of up to 8 rows per lane run in strips of 16 lanes (R <= narrow: 4 R
+// rows per lane, eight pairs per wave) or 32 lanes (2 R rows, four pairs), the
+// taller rows class first.  A call of few pairs (wide) runs them across all 64
+// lanes, two pairs per wave: a lone wave issues one instruction every 10 to 12
+// cycles whatever its mix, so the fewest rows per lane finish first while the
+// chip has waves to spare.
+constexpr int kBlockWaves = 2;
+constexpr size_t kBlockLds = kProfCodes * kWave * 16;  // a full-wave profile of 16 rows per lane
+
+template <bool TRACE>
+__global__ __launch_bounds__(64 * kBlockWaves, 3) void sw16_kernel(SwArgs A, Sw16Launch P) {
+    __shared__ __align__(16) char lds[kBlockLds];
+    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
+    __shared__ WaveLds<kBlockWaves> L;
+    load_blosum(sblosum, A.blosum);
+    auto full = [&](auto r_tag, auto multi_tag, int bin) {
+        if (!((P.bins >> bin) & 1u) || A.bounds[2 * bin] >= A.bounds[2 * bin + 2]) return;
+        const unsigned long long t0 = span_now();
+        if (wave16_body<decltype(r_tag)::value, kBlockWaves, decltype(multi_tag)::value, TRACE>(A, bin, lds, sblosum,
+                                                                                               L) &&
+            !TRACE)
+            span_add(A.span + 2 * bin, t0);
+        __syncthreads();  // every wave has read the last window before the next bin's first claim
+    };
+    auto multi = [&](auto r_tag) {
+        full(r_tag, std::true_type{}, kMulti16Bin + decltype(r_tag)::value - kMultiMinR);
+    };
+    auto one = [&](auto r_tag) { full(r_tag, std::false_type{}, decltype(r_tag)::value - 1); };
+    if (blockIdx.x < (unsigned)P.multi_blocks) descending<kMaxR>(multi, std::make_integer_sequence<int, kMaxR - kMultiMinR + 1>{});
+    descending<kMaxR>(one, std::make_integer_sequence<int, kMaxR - kSplitBins>{});
+    if (P.wide) {
+        descending<kSplitBins>(one, std::make_integer_sequence<int, kSplitBins>{});
+        return;
+    }
     auto cls = [&](auto s_tag, auto rp_tag, int c) {
         if (A.bounds[c] >= A.bounds[c + 1]) return;
         const unsigned long long t0 = span_now();
-        if (strip16_body<decltype(s_tag)::value, decltype(rp_tag)::value>(A, c, lds, wave_bytes, sblosum))
+        if (strip16_body<decltype(s_tag)::value, decltype(rp_tag)::value, TRACE>(A, c, lds, kBlockLds / kBlockWaves,
+                                                                                 sblosum) &&
+            !TRACE)
             span_add(A.span + (c & ~1), t0);
     };
-    auto one = [&](auto r_tag) {
+    auto strips = [&](auto r_tag) {
         constexpr int R = decltype(r_tag)::value;
         constexpr int bin = R - 1;
-        if (!((bins >> bin) & 1u)) return;
+        if (!((P.bins >> bin) & 1u)) return;
         std::integral_constant<int, 16> s16;
         std::integral_constant<int, 32> s32;
         if constexpr (R <= 4) {
-            // strips of 16 lanes with 4 R rows per lane (eight pairs per
-            // wave), or, when not narrow, of 32 lanes with 2 R rows (four
-            // pairs per wave: fewer pairs that must share their sequence a)
-            if (R <= narrow) {
+            if (R <= P.narrow) {
                 cls(s16, std::integral_constant<int, 4 * R>{}, 2 * bin + 1);
                 cls(s16, std::integral_constant<int, 4 * R - 2>{}, 2 * bin);
                 return;
@@ -569,58 +1033,19 @@ __device__ __forceinline__ void strip_bins(const SwArgs &A, uint32_t bins, int n
         cls(s32, std::integral_constant<int, 2 * R>{}, 2 * bin + 1);
         cls(s32, std::integral_constant<int, 2 * R - 1>{}, 2 * bin);
     };
-    descending<HI>(one, std::integer_sequence<int, I...>{});
+    descending<kSplitBins>(strips, std::make_integer_sequence<int, kSplitBins>{});
 }
-
-constexpr int kStripWaves = 4;
-
-template <int LO, int HI>
-__global__ __launch_bounds__(64 * kStripWaves) void sw16s_pass1_kernel(SwArgs A, uint32_t bins, int narrow) {
-    // strips of 16 lanes with 4 R rows each take no more than those of 32
-    // lanes with 2 R rows: sixteen bytes per code and lane at most
-    constexpr size_t kWaveBytes = kProfCodes * (HI <= 4 ? 16 * 16 : 32 * 16);
-    __shared__ __align__(16) char lds[kStripWaves * kWaveBytes];
-    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
-    load_blosum(sblosum, A.blosum);
-    strip_bins<HI>(A, bins, narrow, lds, kWaveBytes, sblosum, std::make_integer_sequence<int, HI - LO + 1>{});
-}
-
-template <int LO, int HI, int WPB, bool MULTI>
-__global__ __launch_bounds__(64 * WPB) void sw16_pass1_kernel(SwArgs A, uint32_t bins, int) {
-    __shared__ __align__(16) char lds[kProfCodes * kWave * sizeof(ProfWord<HI>)];
-    __shared__ int8_t sblosum[kProfCodes * kProfCodes];
-    __shared__ WaveLds<WPB> L;
-    load_blosum(sblosum, A.blosum);
-    auto one = [&](auto r_tag) {
-        constexpr int R = decltype(r_tag)::value;
-        constexpr int bin = MULTI ? kMulti16Bin + R - kMultiMinR : R - 1;
-        if (!((bins >> bin) & 1u) || A.bounds[2 * bin] >= A.bounds[2 * bin + 2]) return;
-        const unsigned long long t0 = span_now();
-        if (wave16_body<R, WPB, MULTI>(A, bin, lds, sblosum, L)) span_add(A.span + 2 * bin, t0);
-        __syncthreads();  // every wave has read the last window before the next bin's first claim
-    };
-    descending<HI>(one, std::make_integer_sequence<int, HI - LO + 1>{});
-}
-
-// one-strip bins of more than 512 rows share a profile between the waves of a
-// block, and a block runs one round per distinct sequence a of its window:
-// two waves (four pairs) per block keep those rounds few where sequences have
-// few partners, and eight (six) such blocks per CU keep four (three) waves
-// per SIMD within LDS
-constexpr int kWpbShared = 2;
-constexpr int kWpbMulti = 4;
 
 }  // namespace
 
-int sw16_waves(int group) { return group < 2 ? kStripWaves : group < 4 ? kWpbShared : kWpbMulti; }
+int sw16_waves() { return kBlockWaves; }
+int sw16_step_words() { return kWave * dir_words<kMaxR>(); }
 
-hipError_t launch_sw16(int group, int blocks, int narrow, const SwArgs &A, uint32_t bins, hipStream_t s) {
-    typedef void (*Kernel)(SwArgs, uint32_t, int);
-    static const Kernel kernels[5] = {sw16s_pass1_kernel<1, 4>, sw16s_pass1_kernel<5, 8>,
-                                      sw16_pass1_kernel<9, 12, kWpbShared, false>,
-                                      sw16_pass1_kernel<13, 16, kWpbShared, false>,
-                                      sw16_pass1_kernel<9, 16, kWpbMulti, true>};
-    kernels[group]<<<blocks, 64 * sw16_waves(group), 0, s>>>(A, bins, narrow);
+hipError_t launch_sw16(bool trace, const Sw16Launch &P, const SwArgs &A, hipStream_t s) {
+    if (trace)
+        sw16_kernel<true><<<P.blocks, 64 * kBlockWaves, 0, s>>>(A, P);
+    else
+        sw16_kernel<false><<<P.blocks, 64 * kBlockWaves, 0, s>>>(A, P);
     return hipGetLastError();
 }
 

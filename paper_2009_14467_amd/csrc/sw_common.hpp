@@ -27,6 +27,10 @@ struct SwArgs {
     unsigned long long *span;  // per bin: two words (span_add)
     unsigned long long *flag;  // intra-pair mode: a wait ran out
     int cov_pct, id_pct;
+    // traced statistics pass: direction words of each wave of the grid for
+    // one-strip pairs, and of the waves of the multi-strip blocks
+    uint32_t *dirs, *dirs_multi;
+    int64_t dirs_per_wave, dirs_per_multi;
 };
 
 namespace {
@@ -46,6 +50,9 @@ constexpr int kMultiMinR = kMaxR / 2 + 1;
 constexpr int kMulti16Bin = kMultiBin + kMaxR - kMultiMinR + 1;
 constexpr int kNumBins = kMulti16Bin + kMaxR - kMultiMinR + 1;
 constexpr int kMax16Rows = 32767 / 11;
+constexpr int kSplitBins = 8;   // one-strip bins 0..7 (up to 8 rows per lane) have two rows classes
+constexpr int kTraceStrips = 3;  // strips of a pair of kMax16Rows rows
+static_assert(kTraceStrips * kMaxR * kWave >= kMax16Rows, "strips of the tallest traced pair");
 static_assert(kNumBins <= 32, "bin tables hold 32 entries");
 
 __host__ __device__ constexpr int rows_of_bin(int bin) {

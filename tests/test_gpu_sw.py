@@ -372,3 +372,65 @@ def test_sw_other_gap_costs(gpu, orc, tiny, go, ge):
     for width in (0, 16):
         got_e = P.Context(P.Params(k=6, ck_min=1, score_width=width, **gaps)).search(res, off)
         assert got_e.size == want_e.size and got_e.tobytes() == want_e.tobytes()
+
+
+@pytest.mark.parametrize("copies", [1, 80])
+@pytest.mark.parametrize("params", [dict(full_records=True), dict(score_width=16), dict(full_records=True, gap_open=5,
+                                                                                        gap_extend=2)])
+def test_sw_traced_statistics(gpu, orc, params, copies):
+    """The traceback's edges: rows at both sides of its fetches and of a lane's,
+    a strip's and a rows class's end, long gaps either way (walks that leave a
+    fetch sideways), alignments that start or end inside the sequences, columns
+    at both sides of the direction buffers' limits (2048 for one strip, 4096 for
+    several: longer pairs take the statistics kernels), one strip and several;
+    as one call of few pairs (two to a wave over 64 lanes) and, with copies, of
+    more than 8,192 (strips of 16 and 32 lanes)."""
+    from synth.families import FamilySet
+
+    rng = np.random.default_rng(17)
+
+    def related(L, pre, post, gaps):
+        a = rng.integers(0, 20, L)
+        b = a.copy()
+        sub = rng.random(L) < 0.2
+        b[sub] = rng.integers(0, 20, int(sub.sum()))
+        for at, g in gaps:  # g > 0: residues inserted into b, g < 0: removed from it
+            at = int(at * b.size)
+            b = np.concatenate([b[:at], rng.integers(0, 20, g), b[at:]]) if g > 0 else np.delete(
+                b, slice(at, at - g))
+        return [a, np.concatenate([rng.integers(0, 20, pre), b, rng.integers(0, 20, post)])]
+
+    pairs = []
+    for L in (1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 161, 224, 225, 256, 257, 353,
+              480, 481, 512, 513, 640, 769, 1023, 1024, 1025, 1537, 2049):
+        pairs.append(related(L, int(rng.integers(0, 40)), int(rng.integers(0, 40)), []))
+    for L in (90, 200, 300, 500, 700, 1000, 1300):  # long gaps: both ways, single residues, several
+        pairs.append(related(L, 3, 0, [(0.5, 40)]))
+        pairs.append(related(L, 0, 9, [(0.5, -25)]))
+        pairs.append(related(L, 0, 0, [(0.3, 1), (0.5, -1), (0.7, 17), (0.8, -9)]))
+    for total in (2047, 2048, 2049):
+        pairs.append(related(300, total - 300 - 50, 50, []))
+    for total in (4095, 4096, 4097):
+        pairs.append(related(1100, total - 1100 - 50, 50, []))
+    for _ in range(40):  # unrelated: short local alignments anywhere
+        pairs.append([rng.integers(0, 20, int(rng.integers(20, 600))), rng.integers(0, 20, int(rng.integers(20, 900)))])
+    seqs = [x for p in pairs for x in p]
+    letters = np.frombuffer(b"ARNDCQEGHILKMFPSTWYV", np.uint8)
+    off = np.zeros(len(seqs) + 1, np.int64)
+    np.cumsum([len(x) for x in seqs], out=off[1:])
+    s = FamilySet(np.concatenate([letters[x] for x in seqs]).astype(np.uint8), off, np.zeros(len(seqs), np.int32), {})
+    lo = np.arange(0, len(seqs), 2, dtype=np.uint32)
+    hi = lo + 1
+    # pairs that share their shorter sequence: several to a window
+    lo = np.concatenate([lo, np.full(11, 60, np.uint32)])
+    hi = np.concatenate([hi, np.arange(63, 85, 2, dtype=np.uint32)])
+    gaps = {k: v for k, v in params.items() if k.startswith("gap")}
+    want = orc.align_pairs(orc.encode(s.residues), s.offsets, lo, hi, mode="sw", **gaps)
+    got = _gpu_records(gpu, s, np.tile(lo, copies), np.tile(hi, copies), **params)
+    assert copies == 1 or got.size > 8192
+    for c in range(copies):
+        part = got[c * lo.size : (c + 1) * lo.size]
+        if params.get("full_records"):
+            _compare(part, want)
+        else:
+            _check16(part, want)
