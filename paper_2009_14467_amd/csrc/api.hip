@@ -385,7 +385,8 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
         const int max16 = !use16 ? 0 : P.score_width == 16 ? 16 : ctx->tune.sw16_max_rows;
         if (max16 > 0) PASTIS_TRY(make_sort_work(ctx, npairs, wk));
         ctx->last_max16 = max16;
-        const SwPlan plan = sw_plan(c + kCounterBinPairs, max16, st.max_len, ctx->tune);
+        SwPlan plan = sw_plan(c + kCounterBinPairs, max16, st.max_len, ctx->tune);
+        plan.forward_bound = max16 > 0 && !ctx->records_internal ? 1 : 0;
         if (traced && stats_mode != 2 && plan.dirs_words > 0) {
             void *dirs = nullptr;
             // a device too full for the direction bits runs the statistics kernels

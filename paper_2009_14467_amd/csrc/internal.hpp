@@ -273,10 +273,12 @@ struct SwPlan {
     Sw16Launch p16, t16;
     uint32_t bins32[5] = {};
     int blocks32[5] = {}, blocks_bound[5] = {}, blocks_stats[5] = {};
-    // whether some pair may still need the statistics kernels, and the
+    // whether some pair may still need the statistics kernels, whether the
+    // start bound is the forward one (16-bit records that leave the library),
+    // and the
     // traceback's direction words: per wave of the grid, per wave of its
     // multi-strip blocks, and in all
-    int stats_after_trace = 0, pad = 0;
+    int stats_after_trace = 0, forward_bound = 0;
     int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
 };
 static_assert(sizeof(SwPlan) == (2 + 10 + 20 + 2) * 4 + 3 * 8, "no hidden padding: the plan is hashed as words");

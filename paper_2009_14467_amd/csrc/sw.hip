@@ -460,18 +460,6 @@ __global__ void sw_bounds_kernel(const uint64_t *__restrict__ keys, int npairs, 
 
 // ---------------------------------------------------------------- between the passes
 
-// Rows up to 64 * kMaxR take one strip of 64 * R rows with the smallest R;
-// longer ones take the fewest strips of at most 64 * kMaxR rows, with R as
-// small as that strip count allows (padding under one row per lane and strip).
-__device__ __forceinline__ int rows_bin(int rows) {
-    if (rows <= 0) return 0;
-    const int r = (rows + kWave - 1) / kWave;
-    if (r <= kSingleBins) return r - 1;
-    const int strips = (rows + kWave * kSingleBins - 1) / (kWave * kSingleBins);
-    const int rm = (rows + kWave * strips - 1) / (kWave * strips);  // in [kMultiMinR, kMaxR]
-    return (rows <= kMax16Rows ? kMulti16Bin : kMultiBin) + rm - kMultiMinR;
-}
-
 // Bins by rows per lane; counters[0] += DP cells of the pairs, and
 // counters[kCounterBinCells + bin] / [kCounterBinPairs + bin] += the cells and
 // pairs of each bin (the host plans the launches from the latter).
@@ -509,52 +497,28 @@ __device__ __forceinline__ void flush_counts(unsigned long long (&acc)[4], unsig
     if (threadIdx.x < 4 && acc[threadIdx.x]) atomicAdd(&counters[1 + threadIdx.x], acc[threadIdx.x]);
 }
 
-// the final record of a pair that takes no statistics pass
-__device__ __forceinline__ void sw_final_record(const PairDesc &pd, const SwPass1Out &r1, int64_t q,
-                                                pastis_pair_record *__restrict__ out, int8_t *__restrict__ bin_of) {
-    bin_of[q] = -1;
-    pastis_pair_record rec;
-    rec.score = r1.score;
-    rec.beg_a = rec.beg_b = -1;
-    rec.end_a = r1.end_a;
-    rec.end_b = max(r1.end_b, -1);  // (a 16-bit pair's end column is a hint until a later pass finds it)
-    rec.matches = rec.columns = 0;
-    rec.seed_used = -1;
-    rec.passed = 0;
-    rec.swapped = pd.swapped;
-    rec.cells = (int64_t)pd.la * pd.lb;
-    out[q] = rec;
-}
-
-// Pairs whose statistics come from the traceback: 16-bit pass-1 bins whose
-// longer sequence fits the direction buffers.
-struct TraceRule {
-    uint32_t bins;              // pass-1 bins in 16-bit lanes (0: no traceback)
-    int max_cols, max_cols_multi;  // longest b of one-strip and of multi-strip pairs
-};
-constexpr int8_t kToTrace = -2;  // bin_of of a pair listed for the traceback
-
-__device__ __forceinline__ bool can_trace(const TraceRule &T, const PairDesc &pd) {
-    const int bin = rows_bin(pd.la);
-    return ((T.bins >> bin) & 1u) && pd.lb <= (bin < kSingleBins ? T.max_cols : T.max_cols_multi);
-}
-
 // Records of pairs that need no statistics pass are final here; the others
-// are listed for the traceback, or binned by the height of their end
-// rectangle (counters[3], [4]: pairs and cells of the start-bound pass;
-// counters[1], [2] in full-records mode).  stats_mode: 0 = only pairs whose
-// coverage cut can hold, 1 = every aligned pair, 2 = none (the
-// normalised-score weight needs no traceback).
+// are listed for the start bound (its list and count) or go on to the
+// statistics.  stats_mode: 0 = only pairs whose coverage cut can hold, 1 =
+// every aligned pair, 2 = none (the normalised-score weight needs no
+// traceback).  forward: the start bound is the forward one (bins by the height
+// of the end rectangle; see sw_bound_kernel), and the last binning counts the
+// pairs left.  counters[3], [4]: pairs and cells of the start bound, [1], [2]
+// of the statistics.
 __global__ __launch_bounds__(256) void sw_bin2_kernel(const PairDesc *__restrict__ pairs,
                                                       SwPass1Out *__restrict__ p1, int64_t npairs, int cov_pct,
-                                                      int stats_mode, int direct_pct, TraceRule T,
+                                                      int stats_mode, int direct_pct, int forward, TraceRule T,
                                                       pastis_pair_record *__restrict__ out,
-                                                      int8_t *__restrict__ bin_of,
+                                                      int8_t *__restrict__ bin_of, int *__restrict__ list,
+                                                      int *__restrict__ list_count,
                                                       unsigned long long *__restrict__ counters) {
     __shared__ unsigned long long acc[4];  // counters[1..4]
+    __shared__ int s_n, s_base;
     if (threadIdx.x < 4) acc[threadIdx.x] = 0;
+    if (threadIdx.x == 0) s_n = 0;
     __syncthreads();
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int slot = -1;
     if (q < npairs) {
         const PairDesc pd = pairs[q];
         const SwPass1Out r1 = p1[q];
@@ -563,13 +527,19 @@ __global__ __launch_bounds__(256) void sw_bin2_kernel(const PairDesc *__restrict
                           (stats_mode == 1 || 100LL * (r1.end_a + 1) >= (long long)cov_pct * pd.la);
         if (need) {
             const int cols = r1.end_b >= 0 ? r1.end_b + 1 : pd.lb;
-            const bool direct = stats_mode == 1 || 100LL * r1.score >= (long long)direct_pct * pd.la;
-            bin_of[q] = direct && can_trace(T, pd) ? kToTrace : (int8_t)rows_bin(r1.end_a + 1);
-            if (direct) p1[q].pad = -1;  // no start bound
-            // in full-records mode every such pair takes the statistics pass;
-            // otherwise the last binning counts its pairs
-            const int at = stats_mode == 1 ? 0 : 2;
-            if (stats_mode == 1 || !direct) {
+            bool direct = stats_mode == 1 || 100LL * r1.score >= (long long)direct_pct * pd.la;
+            // the backward bound holds scores below 2^15
+            if (!forward) direct = direct || r1.score > kBoundMaxScore;
+            const int8_t bin = (int8_t)rows_bin(r1.end_a + 1);
+            if (direct || forward) {
+                bin_of[q] = direct && can_trace(T, pd) ? kToTrace : bin;
+                if (forward) p1[q].pad = direct ? -1 : 0;  // (-1: no start bound)
+            } else {
+                bin_of[q] = kToBound;
+                slot = atomicAdd(&s_n, 1);
+            }
+            const int at = direct ? 0 : 2;
+            if (!(direct && forward && stats_mode == 0)) {
                 atomicAdd(&acc[at], 1ull);
                 atomicAdd(&acc[at + 1], (unsigned long long)(r1.end_a + 1) * (unsigned long long)cols);
             }
@@ -578,6 +548,9 @@ __global__ __launch_bounds__(256) void sw_bin2_kernel(const PairDesc *__restrict
         }
     }
     flush_counts(acc, counters);
+    if (threadIdx.x == 0 && s_n > 0) s_base = atomicAdd(list_count, s_n);
+    __syncthreads();
+    if (slot >= 0) list[s_base + slot] = (int)q;
 }
 
 // ---------------------------------------------------------------- start bound
@@ -587,6 +560,9 @@ __global__ __launch_bounds__(256) void sw_bin2_kernel(const PairDesc *__restrict
 constexpr int kBoundMaxRows = 32000 / 11;
 constexpr int kBoundMaxRowsCoarse = (1 << 19) / 11;
 
+// The forward start bound, for records that leave the library from 16-bit
+// lanes (score_width 16 in an alignment call): it finds the end column of the
+// pairs it rejects, which their records then carry.
 // For a pair that still needs the statistics pass, recompute its end
 // rectangle [0, end_a] x [0, end_b] with every DP value packed as
 // score * 65536 + (65535 - start row).  Each max then keeps the higher score
@@ -1396,20 +1372,22 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     const bool trace = wk.dirs != nullptr;
     const TraceRule T{trace ? plan.p16.bins : 0u, kTraceCols, kTraceColsMulti};
     const int *const idx1 = A.idx;  // pass 1's sorted items
-    sw_bin2_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, stats_mode, sc.direct_pct, T, out, wk.bin_of,
-                                      wk.counters);
+    const bool forward = plan.forward_bound != 0;
+    int *const bound_queue = wk.queue + 3 * kNumBins;  // claims, then the list's length
+    sw_bin2_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, stats_mode, sc.direct_pct, forward ? 1 : 0, T, out,
+                                      wk.bin_of, wk.idx2, bound_queue + 1, wk.counters);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (stats_mode == 2) return end(kStAlign2);  // every record is final
-    // without a pair that the traceback refuses, only the start bound uses bins
+    // without a pair that the traceback refuses, only the forward bound uses bins
     const bool stats = !trace || plan.stats_after_trace;
     A.idx = wk.idx2;
     A.starts = wk.starts2;
-    if (stats_mode == 0) {
+    A.queue = bound_queue;
+    if (stats_mode == 0 && forward) {
         // start bound, then only the pairs whose coverage can still hold
         if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
             hipSuccess)
             return e;
-        A.queue = wk.queue + 3 * kNumBins;
         e = run(1, false, [&](int g) { return plan.blocks_bound[g] > 0; },
                 [&](int g, hipStream_t st) {
                     kBound[g]<<<plan.blocks_bound[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
@@ -1418,6 +1396,8 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         if (e != hipSuccess) return e;
         sw_bin3_kernel<<<nb, 256, 0, s>>>(pairs, p1, npairs, sc.cov_pct, T, out, wk.bin_of, wk.counters);
         if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else if (stats_mode == 0) {
+        if ((e = launch_sw16_bound(npairs, A, T, wk.bin_of, wk.counters, s)) != hipSuccess) return e;
     }
     if (stats && (e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
                      hipSuccess)

@@ -305,10 +305,6 @@ __device__ __forceinline__ void note_rise(const uint32_t (&M)[RP], uint32_t &see
     when = (when & ~mask) | (((uint32_t)chunk * 0x10001u) & mask);
 }
 
-// SwPass1Out::end_b while the end column is unknown: -2 - (first possible column)
-__device__ __forceinline__ int hint_code(int chunk, int pos) { return -2 - max(16 * chunk - pos, 0); }
-__device__ __forceinline__ int first_col(int end_b) { return end_b >= 0 ? end_b : max(-2 - end_b, 0); }
-
 // Full-wave layout for the wider bins.  A block takes 2 * WPB consecutive
 // pairs (two per wave) and its waves share one profile, built once per
 // distinct sequence a among them (pairs are sorted by a), so the LDS of a
@@ -958,6 +954,191 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
     return any;
 }
 
+// ---------------------------------------------------------------- start bound
+//
+// Before the statistics: pairs whose score does not already promise a long
+// alignment are checked against the coverage cut.  The DP is run backwards
+// from the end row, upwards and to the left, from every column of pass 1's
+// window at the end column: the value of a cell is then the best score of an
+// alignment from it to the end row, and the cells that reach the pair's score
+// are the starts of optimal alignments, so the highest of their rows bounds the
+// canonical alignment's coverage.  (The window begins at or before the first
+// column that holds the score in the end row, so it contains that column if any
+// cell reaches the score; where none does, another row of pass 1's lane held
+// the maximum first, and the pair goes on to the statistics.)  No value
+// exceeds the score (the largest of the matrix), and every proper suffix of an
+// optimal alignment scores above 0, so the sweep ends when no value is above 0:
+// after some 120 columns for unrelated pairs, against the whole width for a
+// forward sweep, and over the 256 rows above the end row whatever the
+// sequences' length.  An alignment that is still alive in the topmost of them
+// cannot be bounded here and goes on to the statistics (138,000 of 3.07 million
+// at 250,000 sequences, 14 ms of traceback).  There the forward kernel, which
+// sweeps the end rectangle in 32-bit lanes, took 132 ms, this one 36; where
+// sequences reach 25,000 residues 115 against 1.3.
+//
+// Two pairs per strip of 16 lanes and 16 rows per lane, eight pairs per wave,
+// in 16-bit lanes as in pass 1, but with saturating adds and dead cells at
+// -2^15 (a dead path gains at most 11 per row and never gets near 0).  The
+// pairs share nothing, so scores come from the 25 x 25 table in LDS, one read
+// per row and pair, which costs as much as the vector instructions beside it.
+constexpr int kBoundLanes = 16, kBoundRP = 16, kBoundRows = kBoundLanes * kBoundRP;
+constexpr int kBoundWaves = 4;
+constexpr int kBoundWindow = 18;  // columns a hint can stand for: 16 steps, and the last note's odd ones
+
+__device__ __forceinline__ short2_t adds(short2_t a, short2_t b) { return __builtin_elementwise_add_sat(a, b); }
+__device__ __forceinline__ short2_t subss(short2_t a, short2_t b) { return __builtin_elementwise_sub_sat(a, b); }
+
+__global__ __launch_bounds__(64 * kBoundWaves, 4) void sw16_bound_kernel(SwArgs A, TraceRule T,
+                                                                         int8_t *__restrict__ bin_of,
+                                                                         unsigned long long *__restrict__ counters) {
+    constexpr int S = kBoundLanes, RP = kBoundRP, NI = 2 * kWave / S;
+    __shared__ uint32_t stab[kProfCodes * kProfCodes];  // score + o + e, in the low half
+    for (int t = threadIdx.x; t < kProfCodes * kProfCodes; t += blockDim.x)
+        stab[t] = (uint32_t)(A.blosum[t] + A.go_ge) & 0xFFFFu;
+    __syncthreads();
+    const uint8_t *__restrict__ codes = A.codes;
+    const int lane = threadIdx.x & (kWave - 1), pos = lane % S, strip = lane / S;
+    const int go_ge = A.go_ge;
+    const uint32_t OE2 = (uint32_t)go_ge * 0x10001u, GE2 = (uint32_t)A.ge * 0x10001u;
+    const uint32_t kDead = 0x80008000u;
+    const uint32_t G0 = ((uint32_t)(-go_ge) & 0xFFFFu) * 0x10001u;  // G of an H = 0 cell
+    const int n = A.queue[1];  // listed pairs
+    for (int64_t w = take_from(A.queue, 0, NI); w < n; w = take_from(A.queue, 0, NI)) {
+        int q[2], la[2], score[2], end_a[2], hi[2], win[2];
+        const uint8_t *pa[2], *pb[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int64_t at = w + 2 * strip + x;
+            q[x] = at < n ? A.idx[at] : -1;
+            la[x] = score[x] = 0;
+            end_a[x] = hi[x] = -1;
+            win[x] = 0;
+            pa[x] = pb[x] = codes;
+            if (q[x] >= 0) {
+                const PairDesc pd = A.pairs[q[x]];
+                const SwPass1Out r1 = A.p1[q[x]];
+                const int lo = first_col(r1.end_b);
+                la[x] = pd.la;
+                score[x] = r1.score;
+                end_a[x] = r1.end_a;
+                hi[x] = r1.end_b >= 0 ? lo : min(lo + kBoundWindow, pd.lb) - 1;
+                win[x] = hi[x] - lo + 1;
+                pa[x] = codes + pd.a_off;
+                pb[x] = codes + pd.b_off;
+            }
+        }
+        // byte offsets into the table, P's in the low half and Q's in the high
+        // half: rows (code * 100, at most 2,400) and columns (code * 4)
+        uint32_t row[RP];
+#pragma unroll
+        for (int r = 0; r < RP; ++r) {
+            const int iP = end_a[0] - (pos * RP + r), iQ = end_a[1] - (pos * RP + r);
+            const uint32_t x = iP >= 0 ? (uint32_t)pa[0][iP] : (uint32_t)kPadCode;
+            const uint32_t y = iQ >= 0 ? (uint32_t)pa[1][iQ] : (uint32_t)kPadCode;
+            row[r] = (x | y << 16) * (4u * kProfCodes);
+        }
+        auto col = [&](int v) -> uint32_t {
+            const int jP = hi[0] - v, jQ = hi[1] - v;
+            const uint32_t x = jP >= 0 ? (uint32_t)pb[0][jP] : (uint32_t)kPadCode;
+            const uint32_t y = jQ >= 0 ? (uint32_t)pb[1][jQ] : (uint32_t)kPadCode;
+            return (x * 4u) | (y * 4u << 16);
+        };
+        const int steps = __builtin_amdgcn_readfirstlane(wave_max_i32(max(hi[0], hi[1]))) + S;
+        uint32_t G[RP], E[RP], M[RP];
+#pragma unroll
+        for (int r = 0; r < RP; ++r) {
+            G[r] = kDead;
+            E[r] = kDead;
+            M[r] = 0u;
+        }
+        // the row below the end row: H = 0 left of every window column (an
+        // alignment ends in a diagonal step), else dead
+        uint32_t gprev = pos == 0 ? G0 : kDead, glast = kDead, flast = kDead, out = kDead;
+        uint32_t cres = (kPadCode * 4u) * 0x10001u, chunk = col(pos), nx = col(16 + pos);
+        for (int t = 0; t < steps; ++t) {
+            if ((t & 15) == 0 && t > 0) {
+                chunk = nx;
+                nx = col(t + 16 + pos);
+                if (t >= kBoundWindow) {
+                    // values above 0 anywhere: the rows', or on their way down
+                    uint32_t g = u2(pmax(s2(gprev), s2(glast))), e = flast;
+#pragma unroll
+                    for (int r = 0; r < RP; ++r) {
+                        g = u2(pmax(s2(g), s2(G[r])));
+                        e = u2(pmax(s2(e), s2(E[r])));
+                    }
+                    const uint32_t m = u2(pmax(adds(s2(g), s2(OE2)), s2(e)));
+                    const uint32_t o = (uint32_t)__shfl((int)out, strip * S + S - 1, kWave);  // G in the top row
+                    const bool overP = end_a[0] >= kBoundRows && (int)(int16_t)(o & 0xFFFFu) + go_ge > 0;
+                    const bool overQ = end_a[1] >= kBoundRows && ((int)o >> 16) + go_ge > 0;
+                    const bool live = ((int)(int16_t)(m & 0xFFFFu) > 0 && !overP && q[0] >= 0) ||
+                                      (((int)m >> 16) > 0 && !overQ && q[1] >= 0);
+                    if (__ballot(live) == 0ull) break;
+                }
+            }
+            uint32_t first = kDead;
+            if (t < kBoundWindow)
+                first = ((t + 1 < win[0] ? G0 : kDead) & 0xFFFFu) | ((t + 1 < win[1] ? G0 : kDead) & 0xFFFF0000u);
+            const uint32_t rg = strip_shr<S>(first, glast, lane), rf = strip_shr<S>(kDead, flast, lane);
+            cres = strip_shr<S>(chunk, cres, lane);
+            chunk = (uint32_t)__builtin_amdgcn_mov_dpp((int)chunk, kDppRowRor15, 0xF, 0xF, false);
+            short2_t gd = s2(gprev), gu = s2(rg), fu = s2(rf);
+#pragma unroll
+            for (int r = 0; r < RP; ++r) {
+                const uint32_t at = row[r] + cres;
+                const uint32_t sp = *(const uint32_t *)((const char *)stab + (at & 0xFFFFu));
+                const uint32_t sq = *(const uint32_t *)((const char *)stab + (at >> 16));
+                const short2_t e = pmax(subss(s2(E[r]), s2(GE2)), s2(G[r]));
+                const short2_t f = pmax(subss(fu, s2(GE2)), gu);
+                const short2_t d = adds(gd, s2(sp | (sq << 16)));
+                const short2_t h = pmax(d, pmax(e, f));
+                gd = s2(G[r]);
+                const short2_t g = subss(h, s2(OE2));
+                G[r] = u2(g);
+                E[r] = u2(e);
+                M[r] = u2(pmax(s2(M[r]), h));
+                gu = g;
+                fu = f;
+            }
+            glast = G[RP - 1];
+            flast = u2(fu);
+            gprev = rg;
+            out = u2(pmax(s2(out), s2(glast)));
+        }
+        // the highest row with the pair's score, counted from the end row
+        int up = -1, uq = -1;
+#pragma unroll
+        for (int r = 0; r < RP; ++r) {
+            up = (int)(M[r] & 0xFFFFu) == score[0] ? pos * RP + r : up;
+            uq = (int)(M[r] >> 16) == score[1] ? pos * RP + r : uq;
+        }
+#pragma unroll
+        for (int off = S / 2; off > 0; off >>= 1) {
+            up = max(up, __shfl_xor(up, off, kWave));
+            uq = max(uq, __shfl_xor(uq, off, kWave));
+        }
+        const uint32_t o = (uint32_t)__shfl((int)out, strip * S + S - 1, kWave);
+        const bool over[2] = {end_a[0] >= kBoundRows && (int)(int16_t)(o & 0xFFFFu) + go_ge > 0,
+                              end_a[1] >= kBoundRows && ((int)o >> 16) + go_ge > 0};
+        const int top[2] = {up, uq};
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            if (pos != x || q[x] < 0) continue;
+            const PairDesc pd = A.pairs[q[x]];
+            const SwPass1Out r1 = A.p1[q[x]];
+            // (a pair whose score was met in no row is not bounded)
+            if (!over[x] && top[x] >= 0 && 100LL * (top[x] + 1) < (long long)A.cov_pct * la[x]) {
+                sw_final_record(pd, r1, q[x], A.rec, bin_of);
+                continue;
+            }
+            bin_of[q[x]] = can_trace(T, pd) ? kToTrace : (int8_t)rows_bin(end_a[x] + 1);
+            const int cols = r1.end_b >= 0 ? r1.end_b + 1 : pd.lb;
+            atomicAdd(&counters[1], 1ull);
+            atomicAdd(&counters[2], (unsigned long long)(end_a[x] + 1) * (unsigned long long)cols);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- kernel
 
 // f(integral HI), f(integral HI - 1), ... down to 1 + HI - count
@@ -1040,6 +1221,15 @@ __global__ __launch_bounds__(64 * kBlockWaves, 3) void sw16_kernel(SwArgs A, Sw1
 
 int sw16_waves() { return kBlockWaves; }
 int sw16_step_words() { return kWave * dir_words<kMaxR>(); }
+
+hipError_t launch_sw16_bound(int64_t npairs, const SwArgs &A, const TraceRule &T, int8_t *bin_of,
+                             unsigned long long *counters, hipStream_t s) {
+    // a resident grid (four blocks per CU: 128 registers) draining the list
+    const int64_t per_block = 2 * kWave / kBoundLanes * kBoundWaves;
+    const int blocks = (int)std::min<int64_t>(256 * 4, (npairs + per_block - 1) / per_block);
+    sw16_bound_kernel<<<blocks, 64 * kBoundWaves, 0, s>>>(A, T, bin_of, counters);
+    return hipGetLastError();
+}
 
 hipError_t launch_sw16(bool trace, const Sw16Launch &P, const SwArgs &A, hipStream_t s) {
     if (trace)

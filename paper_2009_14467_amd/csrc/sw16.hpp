@@ -12,4 +12,10 @@ int sw16_step_words();  // most words of direction bits a step stores per wave
 // A.queue holds one counter per (bin, rows class).
 hipError_t launch_sw16(bool trace, const Sw16Launch &P, const SwArgs &A, hipStream_t s);
 
+// The backward start bound of the A.queue[1] pairs listed in A.idx: rejected
+// pairs get their final record, the others are listed for the traceback or
+// binned for the statistics kernels (bin_of) and counted (counters[1], [2]).
+hipError_t launch_sw16_bound(int64_t npairs, const SwArgs &A, const TraceRule &T, int8_t *bin_of,
+                             unsigned long long *counters, hipStream_t s);
+
 }  // namespace pastis

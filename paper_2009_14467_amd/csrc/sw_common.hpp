@@ -33,6 +33,13 @@ struct SwArgs {
     int64_t dirs_per_wave, dirs_per_multi;
 };
 
+// Pairs whose statistics come from the traceback: 16-bit pass-1 bins whose
+// longer sequence fits the direction buffers.
+struct TraceRule {
+    uint32_t bins;              // pass-1 bins in 16-bit lanes (0: no traceback)
+    int max_cols, max_cols_multi;  // longest b of one-strip and of multi-strip pairs
+};
+
 namespace {
 
 constexpr int kWave = 64;
@@ -50,6 +57,7 @@ constexpr int kMultiMinR = kMaxR / 2 + 1;
 constexpr int kMulti16Bin = kMultiBin + kMaxR - kMultiMinR + 1;
 constexpr int kNumBins = kMulti16Bin + kMaxR - kMultiMinR + 1;
 constexpr int kMax16Rows = 32767 / 11;
+constexpr int kBoundMaxScore = 30000;  // scores the backward start bound holds in 16 bits
 constexpr int kSplitBins = 8;   // one-strip bins 0..7 (up to 8 rows per lane) have two rows classes
 constexpr int kTraceStrips = 3;  // strips of a pair of kMax16Rows rows
 static_assert(kTraceStrips * kMaxR * kWave >= kMax16Rows, "strips of the tallest traced pair");
@@ -166,6 +174,49 @@ __device__ __forceinline__ int64_t take_from(int *counter, int begin, int count)
 __device__ __forceinline__ int subs(int x, int y) {
     return (int)__builtin_elementwise_sub_sat((unsigned)x, (unsigned)y);
 }
+
+// Rows up to 64 * kMaxR take one strip of 64 * R rows with the smallest R;
+// longer ones take the fewest strips of at most 64 * kMaxR rows, with R as
+// small as that strip count allows (padding under one row per lane and strip).
+__device__ __forceinline__ int rows_bin(int rows) {
+    if (rows <= 0) return 0;
+    const int r = (rows + kWave - 1) / kWave;
+    if (r <= kSingleBins) return r - 1;
+    const int strips = (rows + kWave * kSingleBins - 1) / (kWave * kSingleBins);
+    const int rm = (rows + kWave * strips - 1) / (kWave * strips);  // in [kMultiMinR, kMaxR]
+    return (rows <= kMax16Rows ? kMulti16Bin : kMultiBin) + rm - kMultiMinR;
+}
+
+// bin_of between the passes: the bin of the statistics kernels, or
+constexpr int8_t kFinal = -1;    // the record is final
+constexpr int8_t kToTrace = -2;  // listed for the traceback
+constexpr int8_t kToBound = -3;  // listed for the start bound
+
+__device__ __forceinline__ bool can_trace(const TraceRule &T, const PairDesc &pd) {
+    const int bin = rows_bin(pd.la);
+    return ((T.bins >> bin) & 1u) && pd.lb <= (bin < kSingleBins ? T.max_cols : T.max_cols_multi);
+}
+
+// the final record of a pair that takes no statistics pass
+__device__ __forceinline__ void sw_final_record(const PairDesc &pd, const SwPass1Out &r1, int64_t q,
+                                                pastis_pair_record *__restrict__ out, int8_t *__restrict__ bin_of) {
+    bin_of[q] = kFinal;
+    pastis_pair_record rec;
+    rec.score = r1.score;
+    rec.beg_a = rec.beg_b = -1;
+    rec.end_a = r1.end_a;
+    rec.end_b = max(r1.end_b, -1);  // (a 16-bit pair's end column is a hint until a later pass finds it)
+    rec.matches = rec.columns = 0;
+    rec.seed_used = -1;
+    rec.passed = 0;
+    rec.swapped = pd.swapped;
+    rec.cells = (int64_t)pd.la * pd.lb;
+    out[q] = rec;
+}
+
+// SwPass1Out::end_b while the end column is unknown: -2 - (first possible column)
+__device__ __forceinline__ int hint_code(int chunk, int pos) { return -2 - max(16 * chunk - pos, 0); }
+__device__ __forceinline__ int first_col(int end_b) { return end_b >= 0 ? end_b : max(-2 - end_b, 0); }
 
 // First claim and last finish of a bin's pass-1 windows, in ticks of the
 // device's wall clock: span[0] holds the complement of the earliest begin,

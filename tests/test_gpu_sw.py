@@ -434,3 +434,42 @@ def test_sw_traced_statistics(gpu, orc, params, copies):
             _compare(part, want)
         else:
             _check16(part, want)
+
+
+@pytest.mark.parametrize("width", [0, 32])
+@pytest.mark.parametrize("gaps", [dict(), dict(gap_open=1, gap_extend=1)])
+def test_start_bound_keeps_every_edge(gpu, orc, width, gaps):
+    """The backward start bound at the coverage cut's two sides, with the
+    alignment's rows at both sides of the 256 that it sweeps, a known end column
+    (32-bit pass 1) and a window of columns (16-bit), and end rows that tie with
+    the next one (a residue pair of score 0 follows); every pair takes it."""
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(5)
+    seqs = []
+    for L in (40, 90, 181, 255, 256, 257, 300, 364, 365, 366, 367, 500, 900, 1100, 3100):
+        for share in (0.6, 0.695, 0.7, 0.705, 0.8, 1.0):
+            n = max(int(round(share * L)), 1)
+            core = rng.integers(0, 20, n)
+            other = core.copy()
+            sub = rng.random(n) < 0.15
+            other[sub] = rng.integers(0, 20, int(sub.sum()))
+            before = int(rng.integers(0, L - n + 1))
+            tie = L - n - before > 0 and rng.random() < 0.5  # A against T scores 0
+            a = np.concatenate([rng.integers(0, 20, before), core, rng.integers(0, 20, L - n - before)])
+            b = np.concatenate([rng.integers(0, 20, int(rng.integers(0, 60))), other, rng.integers(0, 20, L // 2 + 9)])
+            if tie:
+                a[before + n] = 0
+                b[b.size - (L // 2 + 9)] = 16
+            seqs += [a, b]
+    letters = np.frombuffer(b"ARNDCQEGHILKMFPSTWYV", np.uint8)
+    off = np.zeros(len(seqs) + 1, np.int64)
+    np.cumsum([len(x) for x in seqs], out=off[1:])
+    res = letters[np.concatenate(seqs)]
+    want = orc.search(res, off, k=6, ck_min=1, mode="sw", **gaps)
+    ctx = P.Context(P.Params(k=6, ck_min=1, score_width=width, **gaps))
+    ctx.set_tuning(sw_direct_pct=100000)
+    got = ctx.search(_to_dev(res, gpu), _to_dev(off, gpu))
+    st = ctx.stats()
+    assert st["bound_pass_pairs"] > 0 and want.size > 0
+    assert got.size == want.size and got.tobytes() == want.tobytes()
