@@ -17,6 +17,7 @@
 // stores of one array share one address with immediate offsets, and both
 // operands of the weight-gradient GEMMs (reductions over the batch) load 4
 // consecutive pairs of a feature per lane, 512 contiguous bytes per wave.
+#include <algorithm>
 #include <cmath>
 
 #include "internal.hpp"
@@ -52,38 +53,75 @@ __device__ __forceinline__ bf16x4 load4(const uint16_t *p) {
     return r;
 }
 
-// group of residue code c (0..23), or -1
-__device__ __forceinline__ int group_of(int c) {
-    // A R N D C Q E G H I L K M F P S T W Y V B Z X *
-    const int8_t g[24] = {0, 4, 3, 2, 8, 3, 2, 0, 4, 5, 6, 4, 6, 7, 9, 1, 1, 7, 7, 5, -1, -1, -1, -1};
-    return g[c];
+// two non-negative floats to bf16, rounded to nearest even (one instruction)
+__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
+    typedef float float2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    const float2_t v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-__global__ void comp_kernel(const uint8_t *__restrict__ codes, const int64_t *__restrict__ offsets, int64_t n,
-                            float *__restrict__ comp) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        int cnt[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+// group of residue code c (0..23), or 15: four bits per code
+__device__ __forceinline__ int group_of(int c) {
+    // A R N D C Q E G H I L K M F P S, then T W Y V B Z X *
+    constexpr uint64_t lo = 0x1976465402382340ull;
+    constexpr uint32_t hi = 0xFFFF5771u;
+    return c < 16 ? (int)(lo >> (4 * c) & 15u) : (int)(hi >> (4 * (c - 16)) & 15u);
+}
+
+// Compositions, one wave per sequence: 64 residues at a time, counted by ten
+// ballots.  (One thread per sequence read single bytes at the stride of a
+// sequence: 479 us for 10,000 sequences of 350 residues, one wave 15 us.)
+// Rows of comp hold kMlpComp floats, ten of them in use.
+constexpr int kGroups = 10;
+__global__ __launch_bounds__(256) void comp_kernel(const uint8_t *__restrict__ codes,
+                                                   const int64_t *__restrict__ offsets, int64_t n,
+                                                   float *__restrict__ comp) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {
+        int cnt[kGroups] = {};
         const int64_t b = offsets[i], e = offsets[i + 1];
-        for (int64_t x = b; x < e; ++x) {
-            const int g = group_of(codes[x]);
-            if (g >= 0) cnt[g]++;
+        for (int64_t x = b + lane; x - lane < e; x += 64) {
+            const int g = x < e ? group_of(codes[x]) : 15;
+#pragma unroll
+            for (int k = 0; k < kGroups; ++k) cnt[k] += __popcll(__ballot(g == k));
         }
         const float L = (float)((e - b) > 0 ? (e - b) : 1);
-        for (int g = 0; g < 10; ++g) comp[i * 10 + g] = (float)cnt[g] / L;
+        int mine = 0;
+#pragma unroll
+        for (int k = 0; k < kGroups; ++k) mine = lane == k ? cnt[k] : mine;
+        if (lane < kMlpComp) comp[i * kMlpComp + lane] = (float)mine / L;
     }
 }
 
-__global__ void features_kernel(const uint32_t *__restrict__ lo, const uint32_t *__restrict__ hi,
-                                const uint32_t *__restrict__ count, const uint32_t *__restrict__ s1,
-                                const uint32_t *__restrict__ s2, int64_t n, const int64_t *__restrict__ offsets,
-                                const float *__restrict__ comp, float *__restrict__ F) {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x) {
+// One thread per pair; the 64-byte rows of F leave through LDS, 1 KB of
+// consecutive bytes per store (bound by the 64 bytes written per pair; stored
+// from their threads, a float at a time, 149 us for the 3.67 million candidates
+// of 10,000 sequences, so 125).
+__global__ __launch_bounds__(256) void features_kernel(
+    const uint32_t *__restrict__ lo, const uint32_t *__restrict__ hi, const uint32_t *__restrict__ count,
+    const uint32_t *__restrict__ s1, const uint32_t *__restrict__ s2, int64_t n, const int64_t *__restrict__ offsets,
+    const float *__restrict__ comp, float *__restrict__ F, int wide) {
+    __shared__ float4 rows[4][64][kIn / 4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int64_t q0 = ((int64_t)blockIdx.x * 4 + wave) * 64; q0 < n; q0 += (int64_t)gridDim.x * 256) {
+        const int64_t q = min(q0 + lane, n - 1);
         const uint32_t i = lo[q], j = hi[q];
         const int64_t Li = offsets[i + 1] - offsets[i], Lj = offsets[j + 1] - offsets[j];
         const bool swap = !(Li < Lj || (Li == Lj && i < j));
         const float La = (float)(swap ? Lj : Li), Lb = (float)(swap ? Li : Lj);
         const uint32_t ia = swap ? j : i, ib = swap ? i : j;
-        float *f = F + q * kIn;
+        float f[kIn], c[kMlpComp];
+        const float4 *ca = (const float4 *)(comp + (int64_t)ia * kMlpComp);
+        const float4 *cb = (const float4 *)(comp + (int64_t)ib * kMlpComp);
+#pragma unroll
+        for (int x = 0; x < kMlpComp / 4; ++x) {
+            const float4 u = ca[x], v = cb[x];
+            c[4 * x] = fabsf(u.x - v.x);
+            c[4 * x + 1] = fabsf(u.y - v.y);
+            c[4 * x + 2] = fabsf(u.z - v.z);
+            c[4 * x + 3] = fabsf(u.w - v.w);
+        }
         f[0] = (float)count[q];
         const uint32_t k1 = s1[q], k2 = s2[q];
         auto diag = [&](uint32_t key) {
@@ -98,7 +136,30 @@ __global__ void features_kernel(const uint32_t *__restrict__ lo, const uint32_t 
         f[3] = logf(La);
         f[4] = logf(Lb);
         f[5] = La / Lb;
-        for (int g = 0; g < 10; ++g) f[6 + g] = fabsf(comp[ia * 10 + g] - comp[ib * 10 + g]);
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) f[6 + g] = c[g];
+        // (slots swapped by row, so that neither side's accesses share banks)
+#pragma unroll
+        for (int x = 0; x < kIn / 4; ++x)
+            rows[wave][lane][x ^ (lane & 3)] = make_float4(f[4 * x], f[4 * x + 1], f[4 * x + 2], f[4 * x + 3]);
+        __builtin_amdgcn_wave_barrier();
+        const int live = (int)min((int64_t)64, n - q0);
+#pragma unroll
+        for (int x = 0; x < kIn / 4; ++x) {
+            const int row = 16 * x + (lane >> 2), part = lane & 3;
+            const float4 v = rows[wave][row][part ^ (row & 3)];
+            if (row >= live) continue;
+            float *o = F + (q0 + row) * kIn + 4 * part;
+            if (wide) {
+                *(float4 *)o = v;
+            } else {  // a caller's buffer off the 16-byte grid
+                o[0] = v.x;
+                o[1] = v.y;
+                o[2] = v.z;
+                o[3] = v.w;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -166,17 +227,131 @@ __device__ __forceinline__ void forward_tile(bf16x4 zop, const Net &N, int lane,
     o.y = part + N.b3[0];
 }
 
-__global__ __launch_bounds__(256) void forward_kernel(const float *__restrict__ X, int64_t n, Net N,
-                                                      float *__restrict__ logits) {
-    const int lane = threadIdx.x & 63;
-    const int64_t tiles = (n + 15) / 16;
-    for (int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); tile < tiles; tile += (int64_t)gridDim.x * 4) {
-        const int64_t p = tile * 16 + (lane & 15);
-        float zf[4];
-        const bf16x4 z = input_operand(X, p, p < n, lane >> 4, N, zf);
-        Fwd o;
-        forward_tile(z, N, lane, o);
-        if (lane < 16 && p < n) logits[p] = o.y;
+// The network on n pairs.  A block keeps the weights in LDS (38 KB, so four
+// blocks and 16 waves on a CU) and each wave takes 32 pairs at a time, two B
+// operands for every A operand read, with the next pairs' inputs under way: an
+// iteration reads 36 KB of LDS for 32 pairs where 16 pairs used to take as much
+// through the vector cache.  3.67 million pairs took 616 us that way, 361 with
+// W2 in registers (two waves fit on a SIMD and leave half of its issue slots
+// empty), 232 so.  The four layer-2 accumulators of a half and pair tile
+// advance side by side, each over its K tiles in forward_tile's order, so the
+// logits are the same bits (the K = 32 instruction sums in another order).
+// Bound by instruction issue: some 290 vector instructions per 16 pairs for
+// inputs, bias and activation beside the 72 matrix ones.
+constexpr int kFwdTiles = 2;  // tiles of 16 pairs per wave and iteration
+__global__ __launch_bounds__(256, 4) void forward_kernel(const float *__restrict__ X, int64_t n, Net N,
+                                                         float *__restrict__ logits, int wide) {
+    __shared__ __align__(16) float sb1[kH], sb2[kH], sw3[kH];
+    __shared__ __align__(16) uint2 sw1[kH * kIn / 4];
+    __shared__ __align__(16) uint2 sw2[8][4][64][2];  // [t2][t / 2][lane][t % 2]
+    const int lane = threadIdx.x & 63, col = lane & 15, kg = lane >> 4;
+    if (threadIdx.x < kH) {
+        sb1[threadIdx.x] = N.b1[threadIdx.x];
+        sb2[threadIdx.x] = N.b2[threadIdx.x];
+        sw3[threadIdx.x] = from_bf16(N.w3b[threadIdx.x]);
+    }
+    for (int x = threadIdx.x; x < kH * kIn / 4; x += 256) sw1[x] = ((const uint2 *)N.W1b)[x];
+    for (int x = threadIdx.x >> 6; x < 64; x += 4)  // tile (t2, t) of W2
+        sw2[x >> 3][(x & 7) >> 1][lane][x & 1] =
+            *(const uint2 *)(N.W2b + (16 * (x >> 3) + col) * kH + 16 * (x & 7) + 4 * kg);
+    __syncthreads();
+    const float b3 = N.b3[0];
+    float mean[4], stdv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        mean[i] = N.mean[4 * kg + i];
+        stdv[i] = N.stdv[4 * kg + i];
+    }
+    const int64_t groups = (n + 16 * kFwdTiles - 1) / (16 * kFwdTiles);
+    // inputs of a group, fetched one group ahead (lanes past the last pair take
+    // the last pair's)
+    float4 next[kFwdTiles];
+    auto fetch = [&](int64_t grp) {
+#pragma unroll
+        for (int x = 0; x < kFwdTiles; ++x) {
+            const float *src = X + min(grp * (16 * kFwdTiles) + 16 * x + col, n - 1) * kIn + 4 * kg;
+            if (wide)
+                next[x] = *(const float4 *)src;
+            else  // a caller's buffer off the 16-byte grid
+                next[x] = make_float4(src[0], src[1], src[2], src[3]);
+        }
+    };
+    int64_t grp = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (grp < groups) fetch(grp);
+    for (; grp < groups; grp += (int64_t)gridDim.x * 4) {
+        const int64_t p0 = grp * (16 * kFwdTiles) + col;
+        float in[kFwdTiles][4];
+#pragma unroll
+        for (int x = 0; x < kFwdTiles; ++x)
+            in[x][0] = next[x].x, in[x][1] = next[x].y, in[x][2] = next[x].z, in[x][3] = next[x].w;
+        if (grp + (int64_t)gridDim.x * 4 < groups) fetch(grp + (int64_t)gridDim.x * 4);
+        bf16x4 h1[kFwdTiles][8];
+#pragma unroll
+        for (int x = 0; x < kFwdTiles; ++x) {
+            bf16x4 z;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] = (short)to_bf16((in[x][i] - mean[i]) / stdv[i]);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const f32x4 a = mfma(__builtin_bit_cast(bf16x4, sw1[(16 * t + col) * (kIn / 4) + kg]), z,
+                                     f32x4{0.f, 0.f, 0.f, 0.f});
+                const float4 b = *(const float4 *)(sb1 + 16 * t + 4 * kg);
+                const float q0 = a[0] + b.x, q1 = a[1] + b.y, q2 = a[2] + b.z, q3 = a[3] + b.w;
+                const uint2 v = make_uint2(to_bf16x2(q0 > 0.f ? q0 : 0.f, q1 > 0.f ? q1 : 0.f),
+                                           to_bf16x2(q2 > 0.f ? q2 : 0.f, q3 > 0.f ? q3 : 0.f));
+                h1[x][t] = __builtin_bit_cast(bf16x4, v);
+                if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        float part[kFwdTiles] = {};
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            f32x4 acc[kFwdTiles][4];
+#pragma unroll
+            for (int x = 0; x < kFwdTiles; ++x)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[x][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int tp = 0; tp < 4; ++tp) {
+                // (the scheduler would lift every read of the weights to the top
+                // and spill them)
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint4 w = *(const uint4 *)&sw2[4 * half + u][tp][lane][0];
+                    const bf16x4 lo = __builtin_bit_cast(bf16x4, make_uint2(w.x, w.y));
+                    const bf16x4 hi = __builtin_bit_cast(bf16x4, make_uint2(w.z, w.w));
+#pragma unroll
+                    for (int x = 0; x < kFwdTiles; ++x) acc[x][u] = mfma(lo, h1[x][2 * tp], acc[x][u]);
+#pragma unroll
+                    for (int x = 0; x < kFwdTiles; ++x) acc[x][u] = mfma(hi, h1[x][2 * tp + 1], acc[x][u]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int f = 16 * (4 * half + u) + 4 * kg;
+                const float4 b = *(const float4 *)(sb2 + f), w = *(const float4 *)(sw3 + f);
+#pragma unroll
+                for (int x = 0; x < kFwdTiles; ++x) {
+                    const f32x4 a = acc[x][u];
+                    const float q0 = a[0] + b.x, q1 = a[1] + b.y, q2 = a[2] + b.z, q3 = a[3] + b.w;
+                    const uint32_t v0 = to_bf16x2(q0 > 0.f ? q0 : 0.f, q1 > 0.f ? q1 : 0.f);
+                    const uint32_t v1 = to_bf16x2(q2 > 0.f ? q2 : 0.f, q3 > 0.f ? q3 : 0.f);
+                    part[x] += w.x * __uint_as_float(v0 << 16);
+                    part[x] += w.y * __uint_as_float(v0 & 0xFFFF0000u);
+                    part[x] += w.z * __uint_as_float(v1 << 16);
+                    part[x] += w.w * __uint_as_float(v1 & 0xFFFF0000u);
+                }
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < kFwdTiles; ++x) {
+            float y = part[x];
+            y += __shfl_xor(y, 16, 64);
+            y += __shfl_xor(y, 32, 64);
+            if (lane < 16 && p0 + 16 * x < n) logits[p0 + 16 * x] = y + b3;
+        }
     }
 }
 
@@ -537,21 +712,22 @@ hipError_t mlp_features(const uint8_t *codes, const int64_t *offsets, int64_t n,
                         const uint32_t *hi, const uint32_t *count, const uint32_t *s1, const uint32_t *s2,
                         int64_t npairs, float *comp, float *F, hipStream_t s) {
     if (n > 0) {
-        comp_kernel<<<grid_for(n), 256, 0, s>>>(codes, offsets, n, comp);
+        comp_kernel<<<(unsigned)std::min<int64_t>((n + 3) / 4, 16384), 256, 0, s>>>(codes, offsets, n, comp);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (npairs <= 0) return hipSuccess;
-    features_kernel<<<grid_for(npairs), 256, 0, s>>>(lo, hi, count, s1, s2, npairs, offsets, comp, F);
+    features_kernel<<<grid_for(npairs), 256, 0, s>>>(lo, hi, count, s1, s2, npairs, offsets, comp, F,
+                                                      ((uintptr_t)F & 15u) == 0 ? 1 : 0);
     return hipGetLastError();
 }
 
 hipError_t mlp_forward(const MlpState &S, const float *X, int64_t n, float *logits, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const int64_t tiles = (n + 15) / 16;
-    int64_t blocks = (tiles + 3) / 4;
-    if (blocks > 4096) blocks = 4096;
-    forward_kernel<<<(unsigned)blocks, 256, 0, s>>>(X, n, net_of(S), logits);
+    const int64_t groups = (n + 16 * kFwdTiles - 1) / (16 * kFwdTiles);
+    int64_t blocks = (groups + 3) / 4;
+    if (blocks > 1024) blocks = 1024;  // what fits on the device: the weights are fetched once a block
+    forward_kernel<<<(unsigned)blocks, 256, 0, s>>>(X, n, net_of(S), logits, ((uintptr_t)X & 15u) == 0 ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@
 namespace pastis {
 
 constexpr int kMlpIn = 16, kMlpHidden = 128;
+constexpr int kMlpComp = 12;  // floats per row of the composition table (10 used; rows of 48 bytes)
 // flat fp32 parameter vector: W1 [128][16], b1 [128], W2 [128][128], b2 [128], w3 [128], b3 [1]
 constexpr int kMlpOffW1 = 0;
 constexpr int kMlpOffB1 = kMlpOffW1 + kMlpHidden * kMlpIn;

@@ -75,7 +75,7 @@ pastis_status mlp_filter_candidates(pastis_ctx *ctx, const Staged &st, const uin
     if (nc == 0) return PASTIS_OK;
     HIP_TRY(ctx, stage_begin(ctx, kStLearned, s), "event");
     void *comp, *feat, *logit, *keep, *pos, *tmp, *temp;
-    PASTIS_TRY(ensure(ctx, kBufMlpComp, sizeof(float) * 10 * (size_t)std::max<int64_t>(n, 1), &comp));
+    PASTIS_TRY(ensure(ctx, kBufMlpComp, sizeof(float) * kMlpComp * (size_t)std::max<int64_t>(n, 1), &comp));
     PASTIS_TRY(ensure(ctx, kBufMlpFeat, sizeof(float) * kMlpIn * (size_t)nc, &feat));
     PASTIS_TRY(ensure(ctx, kBufMlpLogit, sizeof(float) * (size_t)nc, &logit));
     PASTIS_TRY(ensure(ctx, kBufMlpKeep, (size_t)nc + 8, &keep));
@@ -236,7 +236,7 @@ pastis_status pastis_mlp_features(pastis_ctx *ctx, const uint8_t *residues, cons
     PASTIS_TRY(read_flags(ctx, d_flags, h_flags, 1, s));
     if (h_flags[0] != ~0ull) return set_error(ctx, PASTIS_E_BAD_RESIDUE, "bad residue");
     void *comp = nullptr;
-    PASTIS_TRY(ensure(ctx, kBufMlpComp, sizeof(float) * 10 * (size_t)std::max<int64_t>(n, 1), &comp));
+    PASTIS_TRY(ensure(ctx, kBufMlpComp, sizeof(float) * kMlpComp * (size_t)std::max<int64_t>(n, 1), &comp));
     HIP_TRY(ctx,
             mlp_features(codes, st.d_off, n, (const uint32_t *)ctx->buf[kBufCandLo].ptr,
                          (const uint32_t *)ctx->buf[kBufCandHi].ptr, (const uint32_t *)ctx->buf[kBufCandCnt].ptr,
@@ -470,7 +470,7 @@ pastis_status mlp_pool_append(pastis_ctx *ctx, const Staged &st, const uint8_t *
     MlpState &S = ctx->mlp;
     PASTIS_TRY(mlp_pool_reserve(ctx, S.pool_n + nc, s));
     void *comp = nullptr;
-    PASTIS_TRY(ensure(ctx, kBufMlpComp, sizeof(float) * 10 * (size_t)std::max<int64_t>(n, 1), &comp));
+    PASTIS_TRY(ensure(ctx, kBufMlpComp, sizeof(float) * kMlpComp * (size_t)std::max<int64_t>(n, 1), &comp));
     HIP_TRY(ctx,
             mlp_features(codes, st.d_off, n, (const uint32_t *)ctx->buf[kBufCandLo].ptr,
                          (const uint32_t *)ctx->buf[kBufCandHi].ptr, (const uint32_t *)ctx->buf[kBufCandCnt].ptr,

@@ -92,6 +92,31 @@ def test_forward_matches_oracle(gpu, n):
     assert rel.max() <= 1e-2, rel.max()
 
 
+@pytest.mark.parametrize("n", [15, 16, 31, 32, 33, 131073])
+def test_forward_tiles_and_unaligned_input(gpu, n):
+    """Pair counts around a wave's 32 pairs, and more than one iteration of the
+    resident grid (131,072 pairs); a pair's logit depends on neither its place
+    nor the input's alignment, so moved rows and an input 4 bytes off the
+    16-byte grid give the same bits."""
+    import torch
+
+    import paper_2009_14467_amd as P
+
+    theta, X = _net(4), _features(n, seed=n)
+    mean, std = X.mean(0), X.std(0) + 1e-3
+    ctx = P.Context()
+    ctx.mlp_set(theta, mean, std)
+    x = _dev(X, gpu)
+    y = ctx.mlp_forward(x)
+    want, _ = M.forward(theta, M.normalise(X, mean, std))
+    rel = np.abs(y.cpu().numpy().astype(np.float64) - want) / (1 + np.abs(want))
+    assert np.median(rel) <= 1e-6 and rel.max() <= 1e-2  # as test_forward_matches_oracle
+    assert torch.equal(ctx.mlp_forward(torch.roll(x, 7, 0).contiguous()), torch.roll(y, 7, 0))
+    off = torch.empty(n * 16 + 1, dtype=torch.float32, device=x.device)[1:].view(n, 16)
+    off.copy_(x)
+    assert off.data_ptr() % 16 == 4 and torch.equal(ctx.mlp_forward(off), y)
+
+
 @pytest.mark.parametrize("n,pw", [(16, 1.0), (999, 3.0), (4096, 10.0), (65536, 2.0)])
 def test_gradient_matches_oracle(gpu, n, pw):
     """One minibatch gradient, from 16 pairs to the largest batch (65,536
