@@ -75,11 +75,11 @@ __global__ void cc_label_kernel(uint32_t *parent, int64_t n, uint32_t *__restric
         label[v] = find_root(parent, (uint32_t)v);
 }
 
-// key = cluster << 32 | family, a sequence outside every family being the
+// key = cluster << fbits | family, a sequence outside every family being the
 // family n + v of its own; bad[0] gets the smallest v whose cluster or
 // family is >= n
 __global__ void score_keys_kernel(const uint32_t *__restrict__ cluster, const int32_t *__restrict__ family,
-                                  int64_t n, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
+                                  int64_t n, int fbits, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
                                   unsigned long long *__restrict__ bad) {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         uint32_t c = cluster[v];
@@ -89,7 +89,7 @@ __global__ void score_keys_kernel(const uint32_t *__restrict__ cluster, const in
             c = 0;  // keeps the key inside the tables; the call fails anyway
         }
         const uint32_t fk = f >= 0 && (int64_t)f < n ? (uint32_t)f : (uint32_t)(n + v);
-        keys[v] = ((uint64_t)c << 32) | fk;
+        keys[v] = ((uint64_t)c << fbits) | fk;
         vals[v] = (uint32_t)v;
     }
 }
@@ -99,31 +99,46 @@ __global__ void run_start_kernel(const uint64_t *__restrict__ keys, int64_t n, u
         start[x] = (x == 0 || keys[x] != keys[x - 1]) ? 1u : 0u;
 }
 
-// run_of[x] = exclusive scan of run starts: the run of sorted position x is
-// run_of[x] + start[x] - 1; every run adds its length into len[run]
-__global__ void run_len_kernel(const uint32_t *__restrict__ start, const uint32_t *__restrict__ run_of, int64_t n,
-                               uint32_t *__restrict__ len) {
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(len + (run_of[x] + start[x] - 1u), 1u);
+// run_of[x] = exclusive scan of run starts, run_of[n] their number: pos[r] =
+// the first sorted position of run r, pos[number] = n
+__global__ void run_pos_kernel(const uint32_t *__restrict__ start, const uint32_t *__restrict__ run_of, int64_t n,
+                               uint32_t *__restrict__ pos) {
+    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x <= n; x += (int64_t)gridDim.x * blockDim.x)
+        if (x == n || start[x]) pos[run_of[x]] = (uint32_t)x;
 }
 
 __global__ void run_max_kernel(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ start,
-                               const uint32_t *__restrict__ run_of, const uint32_t *__restrict__ len, int64_t n,
-                               uint32_t *__restrict__ cmax, uint32_t *__restrict__ fmax) {
+                               const uint32_t *__restrict__ run_of, const uint32_t *__restrict__ pos, int64_t n,
+                               int fbits, uint32_t *__restrict__ cmax, uint32_t *__restrict__ fmax) {
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) {
         if (!start[x]) continue;
-        const uint32_t m = len[run_of[x]];
-        atomicMax(cmax + (keys[x] >> 32), m);
-        atomicMax(fmax + (uint32_t)keys[x], m);
+        const uint32_t m = pos[run_of[x] + 1] - (uint32_t)x;
+        atomicMax(cmax + (keys[x] >> fbits), m);
+        atomicMax(fmax + (keys[x] & ((1ull << fbits) - 1ull)), m);
     }
 }
 
-__global__ void sum_kernel(const uint32_t *__restrict__ a, int64_t n, unsigned long long *__restrict__ out) {
-    unsigned long long acc = 0;
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
-        acc += a[x];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if ((threadIdx.x & 63) == 0 && acc) atomicAdd(out, acc);
+// out[0] += sum of a[0..n), out[1] += sum of a[n..3n): block sums, one atomic
+// per block and sum (an atomic per wave to the one address took 50 us for
+// 250,000 entries)
+__global__ __launch_bounds__(256) void sums_kernel(const uint32_t *__restrict__ a, int64_t n,
+                                                   unsigned long long *__restrict__ out) {
+    __shared__ unsigned long long acc[2];
+    if (threadIdx.x < 2) acc[threadIdx.x] = 0;
+    __syncthreads();
+    unsigned long long c = 0, f = 0;
+    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < 3 * n; x += (int64_t)gridDim.x * blockDim.x)
+        (x < n ? c : f) += a[x];
+    for (int off = 32; off > 0; off >>= 1) {
+        c += __shfl_xor(c, off, 64);
+        f += __shfl_xor(f, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&acc[0], c);
+        atomicAdd(&acc[1], f);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) atomicAdd(out + threadIdx.x, acc[threadIdx.x]);
 }
 
 inline unsigned blocks_for(int64_t n) {
@@ -199,7 +214,7 @@ pastis_status pastis_cluster_scores(pastis_ctx *ctx, const uint32_t *cluster, co
         return PASTIS_OK;
     }
     uint64_t *keys, *keys_alt;
-    uint32_t *vals, *vals_alt, *start, *run_of, *len, *mx;
+    uint32_t *vals, *vals_alt, *start, *run_of, *pos, *mx;
     unsigned long long *flag;
     char *temp;
     PASTIS_TRY(get(ctx, kCcKeys, (size_t)n, &keys));
@@ -209,30 +224,29 @@ pastis_status pastis_cluster_scores(pastis_ctx *ctx, const uint32_t *cluster, co
     PASTIS_TRY(get(ctx, kCcTemp, std::max(radix_temp_bytes(n), scan_temp_bytes(n)) + 256, &temp));
     PASTIS_TRY(get(ctx, kCcStart, (size_t)n, &start));
     PASTIS_TRY(get(ctx, kCcRunOf, (size_t)n + 1, &run_of));
-    PASTIS_TRY(get(ctx, kCcLen, (size_t)n, &len));
+    PASTIS_TRY(get(ctx, kCcLen, (size_t)n + 1, &pos));
     // cluster maxima [n], family maxima [2n] (families < n, own families n + v)
     PASTIS_TRY(get(ctx, kCcMax, 3 * (size_t)n, &mx));
     PASTIS_TRY(get(ctx, kCcFlag, 3, &flag));
+    const int fbits = bits_for((uint64_t)(2 * n - 1));  // families, own ones n + v included
     HIP_TRY(ctx, fill<unsigned long long>(flag, 1, ~0ull, s), "reset");
     HIP_TRY(ctx, fill<unsigned long long>(flag + 1, 2, 0ull, s), "reset");
-    HIP_TRY(ctx, fill<uint32_t>(len, n, 0u, s), "reset");
     HIP_TRY(ctx, fill<uint32_t>(mx, 3 * n, 0u, s), "reset");
-    score_keys_kernel<<<blocks_for(n), 256, 0, s>>>(cluster, family, n, keys, vals, flag);
+    score_keys_kernel<<<blocks_for(n), 256, 0, s>>>(cluster, family, n, fbits, keys, vals, flag);
     HIP_TRY(ctx, hipGetLastError(), "score kernels");
     unsigned long long h0 = 0;
     PASTIS_TRY(read_device(ctx, flag, &h0, sizeof(h0), s));
     if (h0 != ~0ull)
         return set_error(ctx, PASTIS_E_INVAL, "cluster label or family >= n at sequence " + std::to_string(h0));
     bool alt = false;
-    HIP_TRY(ctx, radix_sort(keys, vals, keys_alt, vals_alt, n, 32 + bits_for((uint64_t)n), temp, s, &alt), "sort");
+    HIP_TRY(ctx, radix_sort(keys, vals, keys_alt, vals_alt, n, fbits + bits_for((uint64_t)n), temp, s, &alt), "sort");
     const uint64_t *sk = alt ? keys_alt : keys;
     run_start_kernel<<<blocks_for(n), 256, 0, s>>>(sk, n, start);
     HIP_TRY(ctx, hipGetLastError(), "score kernels");
     HIP_TRY(ctx, (exclusive_scan<uint32_t, uint32_t>(start, n, run_of, run_of + n, temp, s)), "scan");
-    run_len_kernel<<<blocks_for(n), 256, 0, s>>>(start, run_of, n, len);
-    run_max_kernel<<<blocks_for(n), 256, 0, s>>>(sk, start, run_of, len, n, mx, mx + n);
-    sum_kernel<<<blocks_for(n), 256, 0, s>>>(mx, n, flag + 1);
-    sum_kernel<<<blocks_for(2 * n), 256, 0, s>>>(mx + n, 2 * n, flag + 2);
+    run_pos_kernel<<<blocks_for(n + 1), 256, 0, s>>>(start, run_of, n, pos);
+    run_max_kernel<<<blocks_for(n), 256, 0, s>>>(sk, start, run_of, pos, n, fbits, mx, mx + n);
+    sums_kernel<<<std::min(blocks_for(3 * n), 256u), 256, 0, s>>>(mx, n, flag + 1);
     HIP_TRY(ctx, hipGetLastError(), "score kernels");
     unsigned long long h[2];
     PASTIS_TRY(read_device(ctx, flag + 1, h, sizeof(h), s));

@@ -77,6 +77,21 @@ def test_scores_match_oracle(gpu, orc, n, n_clusters, n_fams):
     assert got == orc.weighted_scores(clus, fam)
 
 
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 4095, 4096, 4097, 6144, 6145, 262_144, 262_145])
+def test_scores_at_the_sort_sizes(gpu, orc, n):
+    """Key counts at both sides of the sort's variants: one block (4,096), tiles
+    of 2,048 keys that sum the histogram rows themselves (262,144), scanned
+    histograms beyond; every other sequence is in no family."""
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(n)
+    cluster = rng.integers(0, max(n // 3, 1), n).astype(np.uint32)
+    family = rng.integers(0, max(n // 7, 1), n).astype(np.int32)
+    family[::2] = -1
+    ctx = P.Context(P.Params())
+    assert ctx.cluster_scores(_dev(cluster, gpu), _dev(family, gpu)) == orc.weighted_scores(cluster, family)
+
+
 def test_scores_reject_labels_out_of_range(gpu):
     import paper_2009_14467_amd as P
 
