@@ -235,12 +235,12 @@ pastis_status make_sw_work(pastis_ctx *ctx, int64_t npairs, int max_len, SwWork 
     void *p = nullptr;
     PASTIS_TRY(ensure(ctx, kBufBinOf, (size_t)std::max<int64_t>(npairs, 1), &p));
     wk.bin_of = (int8_t *)p;
-    constexpr int kMetaInts = 512;
+    constexpr int kMetaInts = 640;
     PASTIS_TRY(ensure(ctx, kBufBinMeta, sizeof(int) * kMetaInts + sizeof(unsigned long long) * kNumCounters, &p));
     wk.counts = (int *)p;
     wk.counters = (unsigned long long *)((int *)p + kMetaInts);
     // counts: 32 bins; starts, starts2: 33 bounds each; cursor: 32; bounds,
-    // trace_bounds: 65 each; seven work queues of 32 bins
+    // trace_bounds: 65 each; seven work queues of 32 bins, two window counts of 64
     wk.starts = wk.counts + 32;
     wk.starts2 = wk.counts + 72;
     wk.cursor = wk.counts + 112;

@@ -321,6 +321,74 @@ struct WaveLds {
     int take;  // the block's window, claimed from the bin's queue
 };
 
+// Windows.  What a block or wave takes at once shares sequence a: a sequence's
+// pairs (neighbours in the sorted list) are cut into windows of `width` pairs,
+// so that none straddles two sequences.  (Windows at multiples of the width
+// did, and ran their sequences one after the other: with ten partners per
+// sequence pass 1 of 10,000 sequences took 5.8 ms, its last tall window 5.2 of
+// them, and takes 4.6 so; with 43, 534 ms of 250,000 sequences are 511.)  The order of a class's windows is that of the list up to blocks of 1,024
+// items.  Sequences count as one if they agree in the 24 bits that the list is
+// sorted by; the kernels check a_seq itself.
+constexpr int kClasses = 2 * kNumBins, kWindowBlock = 1024;
+__device__ __forceinline__ bool same_seq24(int x, int y) { return ((x ^ y) & 0xFFFFFF) == 0; }
+
+__global__ __launch_bounds__(kWindowBlock) void sw16_windows_kernel(const PairDesc *__restrict__ pairs,
+                                                                    const int *__restrict__ idx,
+                                                                    const int *__restrict__ bounds, Sw16Launch P,
+                                                                    int *__restrict__ win, int *__restrict__ nwin) {
+    __shared__ int sb[kClasses + 1], count[kClasses], base[kClasses], seq[kWindowBlock];
+    const int tid = threadIdx.x, i0 = blockIdx.x * kWindowBlock, i = i0 + tid;
+    const int n = bounds[kClasses];
+    if (i0 >= n) return;
+    if (tid <= kClasses) sb[tid] = bounds[tid];
+    if (tid < kClasses) count[tid] = 0;
+    const int a = i < n ? pairs[idx[i]].a_seq : 0;
+    seq[tid] = a;
+    __syncthreads();
+    int cls = 0, rank = -1;
+    if (i < n) {
+        int hi = kClasses;  // the last class that begins at or before i
+        while (cls < hi) {
+            const int mid = (cls + hi + 1) / 2;
+            if (sb[mid] <= i)
+                cls = mid;
+            else
+                hi = mid - 1;
+        }
+        auto same = [&](int x) { return same_seq24(x >= i0 ? seq[x - i0] : pairs[idx[x]].a_seq, a); };
+        // head: the first item of the sequence in the class; out: one before it
+        int head = i, step = 1;
+        while (head - step >= sb[cls] && same(head - step)) {
+            head -= step;
+            step *= 2;
+        }
+        int out = max(head - step, sb[cls] - 1);
+        while (head - out > 1) {
+            const int mid = out + (head - out) / 2;
+            if (same(mid))
+                head = mid;
+            else
+                out = mid;
+        }
+        const int bin = cls / 2;
+        const int width = !P.wide && bin < 4 && bin < P.narrow ? 8 : 4;
+        if ((i - head) % width == 0) rank = atomicAdd(&count[cls], 1);
+    }
+    __syncthreads();
+    if (tid < kClasses && count[tid] > 0) base[tid] = atomicAdd(nwin + tid, count[tid]);
+    __syncthreads();
+    if (rank >= 0) win[sb[cls] + base[cls] + rank] = i;
+}
+
+// pairs of the window at item w that share its sequence (at most `width`)
+template <int WIDTH>
+__device__ __forceinline__ int window_size(const SwArgs &A, int w, int end) {
+    const int a = A.pairs[A.idx[w]].a_seq;
+    int n = 1;
+    while (n < WIDTH && w + n < end && same_seq24(A.pairs[A.idx[w + n]].a_seq, a)) ++n;
+    return n;
+}
+
 // TRACE: the statistics pass of the pairs listed (see the traceback above), in
 // the same layout.
 template <int R, int WPB, bool MULTI, bool TRACE>
@@ -337,7 +405,8 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
     ProfWord<R>(*prof)[kWave] = (ProfWord<R>(*)[kWave])lds;
     auto &s_next = L.next;
     int &s_take = L.take;
-    const int item_begin = A.bounds[2 * bin];
+    // a bin's two rows classes (bins of up to 8 rows per lane) count as one here
+    const int tall = A.nwin[2 * bin + 1], windows = tall + A.nwin[2 * bin];
     constexpr int NW = dir_words<R>();
     const int64_t gwave = (int64_t)blockIdx.x * WPB + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     uint32_t *const dirs =
@@ -348,7 +417,6 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
     // wave-uniform values are made so for the compiler, which keeps them (and
     // the loops they bound) out of the vector registers
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    const int item_end = A.bounds[2 * bin + 2];
     const uint32_t OE2 = (uint32_t)go_ge * 0x10001u, GE2 = (uint32_t)ge * 0x10001u;
     const uint32_t G0 = ((uint32_t)(-go_ge) & 0xFFFFu) * 0x10001u;  // G of an H = 0 cell
     uint32_t *bnd_g = nullptr, *bnd_f = nullptr;
@@ -361,12 +429,14 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
     for (;;) {
         // every thread has read the last window before the round loop's
         // first barrier, so thread 0 may claim the next one
-        if (threadIdx.x == 0) s_take = atomicAdd(A.queue + 2 * bin, NI);
+        if (threadIdx.x == 0) s_take = atomicAdd(A.queue + 2 * bin, 1);
         __syncthreads();
-        const int w = item_begin + __builtin_amdgcn_readfirstlane(s_take);
-        if (w >= item_end) break;
+        const int k = __builtin_amdgcn_readfirstlane(s_take);
+        if (k >= windows) break;
         any = true;
-        const int nit = min(NI, item_end - w);
+        const int cls = 2 * bin + (k < tall ? 1 : 0);
+        const int w = __builtin_amdgcn_readfirstlane(A.win[A.bounds[cls] + (k < tall ? k : k - tall)]);
+        const int nit = __builtin_amdgcn_readfirstlane(window_size<NI>(A, w, A.bounds[cls + 1]));
         const int iP = 2 * wave, iQ = iP + 1;
         const int qP = iP < nit ? idx[w + iP] : -1;
         const int qQ = iQ < nit ? idx[w + iQ] : -1;
@@ -713,7 +783,7 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
     // waves of a block may be in bins of different profile sizes: each has a
     // fixed share of the block's LDS
     ProfWord<RP>(*prof)[S] = (ProfWord<RP>(*)[S])(lds + (size_t)wave * wave_bytes);
-    const int item_begin = A.bounds[cls], item_end = A.bounds[cls + 1];
+    const int item_begin = A.bounds[cls], item_end = A.bounds[cls + 1], windows = A.nwin[cls];
     int *const counter = A.queue + cls;
     constexpr int NW = dir_words<RP>();
     uint32_t *const dirs =
@@ -722,9 +792,10 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
     const uint32_t OE2 = (uint32_t)go_ge * 0x10001u, GE2 = (uint32_t)ge * 0x10001u;
     const uint32_t G0 = ((uint32_t)(-go_ge) & 0xFFFFu) * 0x10001u;  // G of an H = 0 cell
 
-    for (int64_t w = take_from(counter, item_begin, NI); w < item_end; w = take_from(counter, item_begin, NI)) {
+    for (int64_t k = take_from(counter, 0, 1); k < windows; k = take_from(counter, 0, 1)) {
         any = true;
-        const int nit = (int)min((int64_t)NI, item_end - w);
+        const int w = __builtin_amdgcn_readfirstlane(A.win[item_begin + k]);
+        const int nit = __builtin_amdgcn_readfirstlane(window_size<NI>(A, w, item_end));
         const int iP = 2 * strip, iQ = iP + 1;
         const int qP = iP < nit ? idx[w + iP] : -1;
         const int qQ = iQ < nit ? idx[w + iQ] : -1;
@@ -1228,6 +1299,13 @@ hipError_t launch_sw16_bound(int64_t npairs, const SwArgs &A, const TraceRule &T
     const int64_t per_block = 2 * kWave / kBoundLanes * kBoundWaves;
     const int blocks = (int)std::min<int64_t>(256 * 4, (npairs + per_block - 1) / per_block);
     sw16_bound_kernel<<<blocks, 64 * kBoundWaves, 0, s>>>(A, T, bin_of, counters);
+    return hipGetLastError();
+}
+
+hipError_t launch_sw16_windows(int64_t npairs, const Sw16Launch &P, const SwArgs &A, int *win, int *nwin,
+                               hipStream_t s) {
+    sw16_windows_kernel<<<(unsigned)((npairs + kWindowBlock - 1) / kWindowBlock), kWindowBlock, 0, s>>>(
+        A.pairs, A.idx, A.bounds, P, win, nwin);
     return hipGetLastError();
 }
 

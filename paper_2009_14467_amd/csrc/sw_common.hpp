@@ -17,6 +17,8 @@ struct SwArgs {
     const int *idx;      // pair indices by bin
     const int *starts;   // bin b: items [starts[b], starts[b + 1])
     const int *bounds;   // 16-bit kernels: rows class c of bin b: [bounds[2 b + c], bounds[2 b + c + 1])
+    const int *win;      // 16-bit kernels: windows of class c: win[bounds[c] .. + nwin[c]), their first items
+    const int *nwin;
     const int8_t *blosum;
     int go_ge, ge;
     SwPass1Out *p1;
@@ -68,7 +70,8 @@ __host__ __device__ constexpr int rows_of_bin(int bin) {
                                                                                    : bin + 1;
 }
 constexpr int kDppWaveShr1 = 0x138;
-constexpr int kSwQueues = 7 * kNumBins;  // work-queue counters of a call
+// work-queue counters of a call, and the window counts of pass 1 and traceback
+constexpr int kSwQueues = 11 * kNumBins, kWindows1 = 7 * kNumBins, kWindowsTrace = 9 * kNumBins;
 
 // lane l receives lane l-1's value; lane 0 receives `lane0`
 __device__ __forceinline__ int shr1(int lane0, int v) {

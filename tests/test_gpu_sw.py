@@ -473,3 +473,50 @@ def test_start_bound_keeps_every_edge(gpu, orc, width, gaps):
     st = ctx.stats()
     assert st["bound_pass_pairs"] > 0 and want.size > 0
     assert got.size == want.size and got.tobytes() == want.tobytes()
+
+
+@pytest.mark.parametrize("copies", [1, 130])
+def test_sw16_windows(gpu, orc, copies):
+    """Windows of pairs that share sequence a: groups of one to nine pairs, in
+    one-strip bins (both rows classes) and multi-strip bins, and, with copies,
+    groups that span the blocks in which the windows are cut (1,024 items); rows
+    at both sides of strip heights, b far longer than a (one past the
+    traceback's 4,096 columns)."""
+    from synth.families import FamilySet
+
+    rng = np.random.default_rng(23)
+    seqs = []
+    shapes = [(L, L + d) for L in (1025, 1280, 1281, 1536, 1537, 1793, 2305, 2560, 2561, 2816, 2817, 2978)
+              for d in (0, int(rng.integers(1, 90)))]
+    shapes += [(1025, n) for n in (1087, 1088, 1089, 1151, 1152, 1153, 4096, 4097)]
+    for la, lb in shapes:
+        n = int(rng.integers(la // 3, la + 1))  # the shared segment
+        at, bt = int(rng.integers(0, la - n + 1)), int(rng.integers(0, lb - n + 1))
+        a, b = rng.integers(0, 20, la), rng.integers(0, 20, lb)
+        seg = a[at : at + n].copy()
+        sub = rng.random(n) < 0.25
+        seg[sub] = rng.integers(0, 20, int(sub.sum()))
+        b[bt : bt + n] = seg
+        seqs += [a, b]
+    short = len(seqs)
+    for L in (20, 33, 64, 65, 97, 129, 200, 300, 449, 512, 700, 1000):
+        seqs += [rng.integers(0, 20, L), rng.integers(0, 20, L)]
+    letters = np.frombuffer(b"ARNDCQEGHILKMFPSTWYV", np.uint8)
+    off = np.zeros(len(seqs) + 1, np.int64)
+    np.cumsum([len(x) for x in seqs], out=off[1:])
+    s = FamilySet(letters[np.concatenate(seqs)].astype(np.uint8), off, np.zeros(len(seqs), np.int32), {})
+    lo = np.arange(0, len(seqs), 2, dtype=np.uint32)
+    hi = lo + 1
+    group = rng.permutation(np.repeat(np.arange(12), [1, 1, 2, 3, 3, 4, 4, 5, 5, 7, 8, 9]))
+    shares = short + 2 * group.astype(np.uint32)  # as a, against every longer sequence
+    lo, hi = np.concatenate([lo, shares]), np.concatenate([hi, np.arange(shares.size, dtype=np.uint32)])
+    want = orc.align_pairs(orc.encode(s.residues), s.offsets, lo, hi, mode="sw")
+    for params in (dict(full_records=True), dict(score_width=16)):
+        got = _gpu_records(gpu, s, np.tile(lo, copies), np.tile(hi, copies), **params)
+        assert copies == 1 or got.size > 8192
+        for c in range(copies):
+            part = got[c * lo.size : (c + 1) * lo.size]
+            if params.get("full_records"):
+                _compare(part, want)
+            else:
+                _check16(part, want)
