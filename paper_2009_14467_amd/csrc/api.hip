@@ -386,7 +386,7 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
         if (max16 > 0) PASTIS_TRY(make_sort_work(ctx, npairs, wk));
         ctx->last_max16 = max16;
         SwPlan plan = sw_plan(c + kCounterBinPairs, max16, st.max_len, ctx->tune);
-        plan.forward_bound = max16 > 0 && !ctx->records_internal ? 1 : 0;
+        plan.forward_bound = ctx->records_internal ? 0 : 1;
         if (traced && stats_mode != 2 && plan.dirs_words > 0) {
             void *dirs = nullptr;
             // a device too full for the direction bits runs the statistics kernels

@@ -274,7 +274,7 @@ struct SwPlan {
     uint32_t bins32[5] = {};
     int blocks32[5] = {}, blocks_bound[5] = {}, blocks_stats[5] = {};
     // whether some pair may still need the statistics kernels, whether the
-    // start bound is the forward one (16-bit records that leave the library),
+    // start bound is the forward one (records that leave the library),
     // and the
     // traceback's direction words: per wave of the grid, per wave of its
     // multi-strip blocks, and in all

@@ -561,9 +561,9 @@ __global__ __launch_bounds__(256) void sw_bin2_kernel(const PairDesc *__restrict
 constexpr int kBoundMaxRows = 32000 / 11;
 constexpr int kBoundMaxRowsCoarse = (1 << 19) / 11;
 
-// The forward start bound, for records that leave the library from 16-bit
-// lanes (score_width 16 in an alignment call): it finds the end column of the
-// pairs it rejects, which their records then carry.
+// The forward start bound, for records that leave the library: which pairs
+// carry statistics then depends on the exact bound alone, and it finds the end
+// column of the pairs it rejects, which 16-bit records then carry.
 // For a pair that still needs the statistics pass, recompute its end
 // rectangle [0, end_a] x [0, end_b] with every DP value packed as
 // score * 65536 + (65535 - start row).  Each max then keeps the higher score

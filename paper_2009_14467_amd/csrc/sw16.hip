@@ -1042,7 +1042,8 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
 // after some 120 columns for unrelated pairs, against the whole width for a
 // forward sweep, and over the 256 rows above the end row whatever the
 // sequences' length.  An alignment that is still alive in the topmost of them
-// cannot be bounded here and goes on to the statistics (138,000 of 3.07 million
+// cannot be bounded here and goes on to the statistics, where it fails the cut
+// like any other; only the edges of a search use this bound (138,000 of 3.07 million
 // at 250,000 sequences, 14 ms of traceback).  There the forward kernel, which
 // sweeps the end rectangle in 32-bit lanes, took 132 ms, this one 36; where
 // sequences reach 25,000 residues 115 against 1.3.

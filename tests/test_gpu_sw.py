@@ -520,3 +520,42 @@ def test_sw16_windows(gpu, orc, copies):
                 _compare(part, want)
             else:
                 _check16(part, want)
+
+
+def test_records_do_not_depend_on_the_bound(gpu):
+    """Which pairs of an alignment call carry statistics is a matter of their
+    scores and of the coverage that the start bound leaves, in either score
+    width: weakly similar segments of 100 to 700 rows at and under the coverage
+    cut (far beyond the rows a shortened sweep would see)."""
+    from synth.families import FamilySet
+
+    rng = np.random.default_rng(31)
+    seqs = []
+    for L in (300, 420, 600, 800, 1000):
+        for share in (0.3, 0.5, 0.6, 0.66, 0.69, 0.72):
+            for rate in (0.55, 0.62, 0.68, 0.72):
+                n = int(share * L)
+                a, b = rng.integers(0, 20, L), rng.integers(0, 20, L + 10)
+                at = L - n  # the segment ends with a, so that pass 1 alone cannot tell
+                seg = a[at:].copy()
+                sub = rng.random(n) < rate
+                seg[sub] = rng.integers(0, 20, int(sub.sum()))
+                b[5 : 5 + n] = seg
+                seqs += [a, b]
+    letters = np.frombuffer(b"ARNDCQEGHILKMFPSTWYV", np.uint8)
+    off = np.zeros(len(seqs) + 1, np.int64)
+    np.cumsum([len(x) for x in seqs], out=off[1:])
+    s = FamilySet(letters[np.concatenate(seqs)].astype(np.uint8), off, np.zeros(len(seqs), np.int32), {})
+    lo = np.arange(0, len(seqs), 2, dtype=np.uint32)
+    full = _gpu_records(gpu, s, lo, lo + 1, full_records=True)
+    for width in (0, 16, 32):
+        got = _gpu_records(gpu, s, lo, lo + 1, score_width=width)
+        span = full["end_a"] - full["beg_a"] + 1
+        la = np.diff(off)[::2]
+        assert 0 < (got["beg_a"] < 0).sum() < got.size
+        none = got["beg_a"] < 0
+        assert np.all(100 * span[none] < 70 * la[none])
+        _compare(got, full, FIELDS, ~none)
+        if width == 0:
+            first = none
+        np.testing.assert_array_equal(none, first)
