@@ -297,7 +297,7 @@ static pastis_status sw_graph(pastis_ctx *ctx, const uint8_t *codes, const PairD
     uint64_t key = 0;
     const uint64_t parts[] = {(uint64_t)npairs, (uint64_t)codes, (uint64_t)pairs, (uint64_t)p1, (uint64_t)out,
                               (uint64_t)wk.counters, (uint64_t)wk.bin_of, (uint64_t)wk.counts, (uint64_t)wk.idx,
-                              (uint64_t)wk.idx2, (uint64_t)wk.bounds, (uint64_t)wk.dirs, (uint64_t)wk.scratch, (uint64_t)wk.scratch_per_wave, (uint64_t)wk.scratch16,
+                              (uint64_t)wk.idx2, (uint64_t)wk.bounds, (uint64_t)wk.dirs, (uint64_t)wk.long_scratch, (uint64_t)wk.scratch, (uint64_t)wk.scratch_per_wave, (uint64_t)wk.scratch16,
                               (uint64_t)wk.sort_keys, (uint64_t)wk.sort_keys_alt, (uint64_t)wk.sort_vals_alt,
                               (uint64_t)wk.sort_temp, (uint64_t)sc.gap_open, (uint64_t)sc.gap_extend,
                               (uint64_t)sc.id_pct, (uint64_t)sc.cov_pct, (uint64_t)sc.direct_pct,
@@ -385,7 +385,7 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
         const int max16 = !use16 ? 0 : P.score_width == 16 ? 16 : ctx->tune.sw16_max_rows;
         if (max16 > 0) PASTIS_TRY(make_sort_work(ctx, npairs, wk));
         ctx->last_max16 = max16;
-        SwPlan plan = sw_plan(c + kCounterBinPairs, max16, st.max_len, ctx->tune);
+        SwPlan plan = sw_plan(c + kCounterBinPairs, (int64_t)c[kCounterLongB], max16, st.max_len, traced, ctx->tune);
         plan.forward_bound = ctx->records_internal ? 0 : 1;
         if (traced && stats_mode != 2 && plan.dirs_words > 0) {
             void *dirs = nullptr;
@@ -393,6 +393,16 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
             const pastis_status ds = ensure(ctx, kBufDirs, sizeof(uint32_t) * (size_t)plan.dirs_words, &dirs);
             if (ds != PASTIS_OK && ds != PASTIS_E_NOMEM) return ds;
             wk.dirs = ds == PASTIS_OK ? (uint32_t *)dirs : nullptr;
+        }
+        if (plan.long_slot > 0) {
+            void *slots = nullptr;
+            const int blocks = std::max(plan.long_blocks1, plan.long_blocks2);
+            // a device too full for the slots runs the multi-strip kernels
+            const pastis_status ls =
+                ensure(ctx, kBufLong, sizeof(int) * (size_t)plan.long_slot * (size_t)blocks, &slots);
+            if (ls != PASTIS_OK && ls != PASTIS_E_NOMEM) return ls;
+            if (ls != PASTIS_OK) plan.long_blocks1 = plan.long_blocks2 = 0;
+            wk.long_scratch = (int *)slots;
         }
         if (P.graph_mode) {
             PASTIS_TRY(sw_graph(ctx, codes, (const PairDesc *)pairs, npairs, sc, (SwPass1Out *)p1, out, wk, stats_mode,
@@ -415,7 +425,7 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
                 "xd kernels");
     }
     PASTIS_TRY(read_device(ctx, wk.counters, c, sizeof(c), s));
-    if (c[kCounterIntraFlag]) return set_error(ctx, PASTIS_E_DEVICE, "intra-pair pass 1: a strip hand-off wait ran out");
+    if (c[kCounterIntraFlag]) return set_error(ctx, PASTIS_E_DEVICE, "a strip hand-off wait ran out");
     ctx->stats.cells = (int64_t)c[0];
     ctx->stats.stats_pass_pairs = (int64_t)c[1];
     ctx->stats.stats_pass_cells = (int64_t)c[2];

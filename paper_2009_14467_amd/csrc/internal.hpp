@@ -172,6 +172,7 @@ enum BufId {
     kBufSortValsAlt,
     kBufSortTemp,
     kBufDirs,
+    kBufLong,
     kBufCount  // first id used by the discovery stage
 };
 constexpr int kNumBufs = 128;
@@ -215,7 +216,8 @@ constexpr int kCounterBad = 7;        // a pair index out of range (bit 0)
 constexpr int kCounterBinCells = 8;
 constexpr int kCounterBinPairs = kCounterBinCells + 32;
 constexpr int kCounterSpan = kCounterBinPairs + 32;  // two words per bin
-constexpr int kNumCounters = kCounterSpan + 64;
+constexpr int kCounterLongB = kCounterSpan + 64;  // multi-strip pairs in 16-bit bins past the traceback's columns
+constexpr int kNumCounters = kCounterLongB + 1;
 
 struct SwWork {
     unsigned long long *counters;
@@ -236,6 +238,7 @@ struct SwWork {
     // traced statistics pass: direction words (null: statistics kernels only)
     // and the list's class bounds
     uint32_t *dirs = nullptr;
+    int *long_scratch = nullptr;  // long pairs: SwPlan::long_slot words per block
     int *trace_bounds;
 };
 int sw_num_bins();
@@ -279,15 +282,22 @@ struct SwPlan {
     // traceback's direction words: per wave of the grid, per wave of its
     // multi-strip blocks, and in all
     int stats_after_trace = 0, forward_bound = 0;
+    // long pairs, one block each: the blocks of pass 1 and of the statistics (0:
+    // the multi-strip kernels), and the scratch words of a block
+    int long_blocks1 = 0, long_blocks2 = 0;
+    int64_t long_slot = 0;
     int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
 };
-static_assert(sizeof(SwPlan) == (2 + 10 + 20 + 2) * 4 + 3 * 8, "no hidden padding: the plan is hashed as words");
+static_assert(sizeof(SwPlan) == (2 + 10 + 20 + 4) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
 // max16 > 0: pass 1 of one-strip pairs with at most max16 rows per lane in
 // 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
 // that skip the statistics pass.  tune: the grid scales of the one-strip
 // groups, intra-pair pass 1 of the 32-bit multi-strip bins, the 16-bit bins
 // in strips of 16 lanes, and the multi-strip grids.
-SwPlan sw_plan(const unsigned long long *bin_pairs, int max16, int max_len, const pastis_tuning &tune);
+// long_b: 16-bit multi-strip pairs that the traceback refuses; traced: whether
+// the call may allocate the traceback's and the long pairs' memory.
+SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool traced,
+               const pastis_tuning &tune);
 // Bins of the pairs (bin_of, the per-bin counters) and cleared work queues;
 // the counters must be zero before.
 hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &wk, hipStream_t s);

@@ -35,6 +35,7 @@
 #include "sw_common.hpp"
 #include "prim.hpp"
 #include "sw16.hpp"
+#include "sw_long.hpp"
 
 namespace pastis {
 
@@ -226,28 +227,12 @@ __device__ __forceinline__ bool pass1_body(const SwArgs &A, int bin, char *lds, 
 // released and acquired at workgroup scope, which orders the row buffer's
 // global stores and loads between the waves of the block.
 constexpr int kIntraWaves = 4;
-constexpr int kIntraSpinLimit = 1 << 24;
 
 struct IntraLds {
     int prod[kIntraWaves], cons[kIntraWaves];
     unsigned long long best[kIntraWaves];
     int take;
 };
-
-__device__ __forceinline__ int lds_acquire(int *p) {
-    return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void lds_release(int *p, int v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-// wait until *p >= need; false when the bound runs out
-__device__ __forceinline__ bool lds_wait(int *p, int need) {
-    for (int spin = 0; spin < kIntraSpinLimit; ++spin) {
-        if (__builtin_amdgcn_readfirstlane(lds_acquire(p)) >= need) return true;
-        __builtin_amdgcn_s_sleep(1);
-    }
-    return false;
-}
 
 template <int R>
 __device__ __forceinline__ bool intra_body(const SwArgs &A, int bin, char *lds, size_t wave_bytes,
@@ -469,7 +454,8 @@ __global__ void sw_bin1_kernel(const PairDesc *__restrict__ pairs, int64_t npair
     if (blockIdx.x == 0)
         for (int x = threadIdx.x; x < kSwQueues; x += blockDim.x) queue[x] = 0;
     __shared__ unsigned long long cells[kNumBins];
-    __shared__ unsigned count[kNumBins];
+    __shared__ unsigned count[kNumBins], long_b;
+    if (threadIdx.x == 0) long_b = 0;
     if (threadIdx.x < kNumBins) {
         cells[threadIdx.x] = 0;
         count[threadIdx.x] = 0;
@@ -482,8 +468,10 @@ __global__ void sw_bin1_kernel(const PairDesc *__restrict__ pairs, int64_t npair
         bin_of[q] = (int8_t)bin;
         atomicAdd(&cells[bin], (unsigned long long)pd.la * (unsigned long long)pd.lb);
         atomicAdd(&count[bin], 1u);
+        if (bin >= kMulti16Bin && pd.lb > kTraceColsMulti) atomicAdd(&long_b, 1u);
     }
     __syncthreads();
+    if (threadIdx.x == 0 && long_b) atomicAdd(&counters[kCounterLongB], (unsigned long long)long_b);
     if (threadIdx.x < kNumBins && count[threadIdx.x]) {
         atomicAdd(&counters[0], cells[threadIdx.x]);
         atomicAdd(&counters[kCounterBinCells + threadIdx.x], cells[threadIdx.x]);
@@ -1152,10 +1140,14 @@ constexpr int kIntraBlocks = 256;
 constexpr int kBlocks16 = 256 * 6, kTraceMultiBlocks = 256;
 constexpr int64_t kWidePairs = 8192;
 
-// Traceback: a pair's direction bits take up to 1 KB per column and strip and
-// live only while its wave works on it; pairs of a longer b go to the
-// statistics kernels.
-constexpr int kTraceCols = 2048, kTraceColsMulti = 4096;
+// Pairs of the 32-bit multi-strip bins, and pairs that may need the multi-strip
+// statistics, up to this many take one block of eight waves each (sw_long.hip);
+// beyond, the waves that work strip after strip keep the chip as busy.  1,225
+// pairs of 3,000 to 25,000 rows took 245 ms in pass 1 and 443 with statistics by
+// single waves, 149 and 118 so.  A block's scratch grows with the longest
+// sequence (20 MB for 25,000 residues); blocks are dropped beyond 16 GB.
+constexpr int64_t kLongPairs = 2048, kLongBytes = (int64_t)16 << 30;
+constexpr int kLongBlocks = 256;
 
 // Resident blocks per CU of the one-strip statistics kernels: they keep no
 // profile in LDS, so registers set their occupancy, which the runtime reports
@@ -1211,7 +1203,8 @@ hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &w
 }
 
 // The launches of a call, from its pairs per bin.
-SwPlan sw_plan(const unsigned long long *bin_pairs, int max16, int max_len, const pastis_tuning &tune) {
+SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool traced,
+               const pastis_tuning &tune) {
     SwPlan p;
     p.max16 = max16;
     p.intra = tune.sw_intra_pair;
@@ -1251,6 +1244,25 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, int max16, int max_len, cons
         p.blocks_bound[g] = later ? fit(g, kGroupBlocks[g], later) : 0;
         const int per_cu = g == kMultiGroup ? 3 : std::max(1, stats_blocks_per_cu[g].load(std::memory_order_acquire));
         p.blocks_stats[g] = later ? fit(g, 256 * per_cu, later) : 0;
+    }
+    // pairs of the multi-strip bins: those of pass 1 in 32-bit lanes, and those
+    // that may come to the multi-strip statistics
+    int64_t long32 = 0, long_stats = 0;
+    for (int b = kMultiBin; b < kNumBins; ++b) {
+        const bool is16 = sw_bin_is16(b, max16);
+        long32 += is16 ? 0 : (int64_t)bin_pairs[b];
+        long_stats += is16 && traced ? 0 : (int64_t)bin_pairs[b];
+    }
+    if (n16 > 0 && traced) long_stats += long_b;
+    if (traced) {
+        p.long_slot = sw_long_slot_words(max_len);
+        const int64_t fit = std::max<int64_t>(8, kLongBytes / (int64_t)(p.long_slot * sizeof(int)));
+        auto blocks = [&](int64_t pairs) {
+            return pairs > kLongPairs ? 0 : (int)std::min<int64_t>({kLongBlocks, fit, pairs});
+        };
+        p.long_blocks1 = blocks(long32);
+        p.long_blocks2 = blocks(long_stats);
+        if (p.long_blocks1 == 0 && p.long_blocks2 == 0) p.long_slot = 0;
     }
     if (n16 == 0) return p;
     Sw16Launch &k = p.p16;
@@ -1369,6 +1381,12 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
                     return launch_sw16(false, plan.p16, B, st);
                 }
                 A.queue = wk.queue + 2 * kNumBins;
+                if (g == kMultiGroup && plan.long_blocks1 > 0) {
+                    SwArgs B = A;
+                    B.scratch = wk.long_scratch;
+                    B.scratch_per_wave = plan.long_slot;
+                    return launch_sw_long(false, plan.long_blocks1, plan.bins32[g], B, st);
+                }
                 if (g == kMultiGroup && plan.intra)
                     sw_intra_pass1_kernel<9, 16><<<kIntraBlocks, 64 * kIntraWaves, 0, st>>>(A, plan.bins32[g]);
                 else
@@ -1441,6 +1459,12 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     e = run(2, trace, [&](int g) { return stats && plan.blocks_stats[g] > 0; },
             [&](int g, hipStream_t st) -> hipError_t {
                 if (g < 0) return launch_sw16(true, plan.t16, B, st);
+                if (g == kMultiGroup && plan.long_blocks2 > 0) {
+                    SwArgs C = A;
+                    C.scratch = wk.long_scratch;
+                    C.scratch_per_wave = plan.long_slot;
+                    return launch_sw_long(true, plan.long_blocks2, kGroupBins[g], C, st);
+                }
                 kStats[g]<<<plan.blocks_stats[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
                 return hipGetLastError();
             });

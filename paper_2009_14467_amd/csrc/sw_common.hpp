@@ -61,6 +61,10 @@ constexpr int kNumBins = kMulti16Bin + kMaxR - kMultiMinR + 1;
 constexpr int kMax16Rows = 32767 / 11;
 constexpr int kBoundMaxScore = 30000;  // scores the backward start bound holds in 16 bits
 constexpr int kSplitBins = 8;   // one-strip bins 0..7 (up to 8 rows per lane) have two rows classes
+// longest b of a pair whose direction bits the traceback keeps, one strip and
+// several (up to 1 KB per column and strip, only while its wave works on it);
+// pairs of a longer b go to the statistics kernels
+constexpr int kTraceCols = 2048, kTraceColsMulti = 4096;
 constexpr int kTraceStrips = 3;  // strips of a pair of kMax16Rows rows
 static_assert(kTraceStrips * kMaxR * kWave >= kMax16Rows, "strips of the tallest traced pair");
 static_assert(kNumBins <= 32, "bin tables hold 32 entries");
@@ -220,6 +224,24 @@ __device__ __forceinline__ void sw_final_record(const PairDesc &pd, const SwPass
 // SwPass1Out::end_b while the end column is unknown: -2 - (first possible column)
 __device__ __forceinline__ int hint_code(int chunk, int pos) { return -2 - max(16 * chunk - pos, 0); }
 __device__ __forceinline__ int first_col(int end_b) { return end_b >= 0 ? end_b : max(-2 - end_b, 0); }
+
+// Hand-offs between the waves of a block: monotone counters in LDS, released
+// and acquired at workgroup scope.  Every wait is bounded.
+constexpr int kSpinLimit = 1 << 24;
+__device__ __forceinline__ int lds_acquire(int *p) {
+    return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_release(int *p, int v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// wait until *p >= need; false when the bound runs out
+__device__ __forceinline__ bool lds_wait(int *p, int need) {
+    for (int spin = 0; spin < kSpinLimit; ++spin) {
+        if (__builtin_amdgcn_readfirstlane(lds_acquire(p)) >= need) return true;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return false;
+}
 
 // First claim and last finish of a bin's pass-1 windows, in ticks of the
 // device's wall clock: span[0] holds the complement of the earliest begin,

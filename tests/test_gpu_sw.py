@@ -522,6 +522,50 @@ def test_sw16_windows(gpu, orc, copies):
                 _check16(part, want)
 
 
+@pytest.mark.parametrize("copies", [1, 130])
+def test_long_pairs_in_a_block(gpu, orc, copies):
+    """Pairs of several strips in 32-bit lanes, one block of eight waves each
+    (few pairs) and one wave each (with copies, more than 2,048): rows at both
+    sides of a strip (512) and of eight of them (a wave's second strip), columns
+    at both sides of a tile (512 steps), gaps that leave a tile or a strip,
+    alignments that begin and end inside, unrelated pairs."""
+    from synth.families import FamilySet
+
+    rng = np.random.default_rng(29)
+    seqs = []
+
+    def add(a, b):
+        sub = rng.random(b.size) < 0.2
+        b = b.copy()
+        b[sub] = rng.integers(0, 20, int(sub.sum()))
+        seqs.extend([a, b])
+
+    for L in (1025, 1536, 1537, 2047, 2560, 4095, 4096, 4097, 4609):
+        a = rng.integers(0, 20, L)
+        add(a, np.concatenate([rng.integers(0, 20, int(rng.integers(0, 70))), a, rng.integers(0, 20, 5)]))
+    for L, g in ((2600, 700), (2600, -600), (1500, 1), (1500, -1)):
+        a = rng.integers(0, 20, L)
+        m = L // 2
+        add(a, np.concatenate([a[:m], rng.integers(0, 20, g), a[m:]]) if g > 0 else np.delete(a, slice(m, m - g)))
+    a = rng.integers(0, 20, 3000)
+    add(np.concatenate([rng.integers(0, 20, 700), a[500:2000], rng.integers(0, 20, 900)]), a)
+    add(rng.integers(0, 20, 1300), rng.integers(0, 20, 1800))
+    letters = np.frombuffer(b"ARNDCQEGHILKMFPSTWYV", np.uint8)
+    off = np.zeros(len(seqs) + 1, np.int64)
+    np.cumsum([len(x) for x in seqs], out=off[1:])
+    s = FamilySet(letters[np.concatenate(seqs)].astype(np.uint8), off, np.zeros(len(seqs), np.int32), {})
+    lo = np.arange(0, len(seqs), 2, dtype=np.uint32)
+    hi = lo + 1
+    lo, hi = np.concatenate([lo, [0, 12]]).astype(np.uint32), np.concatenate([hi, [14, 16]]).astype(np.uint32)
+    want = orc.align_pairs(orc.encode(s.residues), s.offsets, lo, hi, mode="sw")
+    assert copies == 1 or copies * lo.size > 2048
+    for full in (True, False):
+        got = _gpu_records(gpu, s, np.tile(lo, copies), np.tile(hi, copies), full_records=full, score_width=32)
+        fields = FIELDS if full else ("score", "end_a", "end_b", "passed", "swapped", "cells")
+        for c in range(copies):
+            _compare(got[c * lo.size : (c + 1) * lo.size], want, fields)
+
+
 def test_records_do_not_depend_on_the_bound(gpu):
     """Which pairs of an alignment call carry statistics is a matter of their
     scores and of the coverage that the start bound leaves, in either score
