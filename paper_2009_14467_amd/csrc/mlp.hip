@@ -170,61 +170,16 @@ struct Net {
 };
 
 // B operand of layer 1 for this lane: features 4*kg..+3 of pair p, normalised
-__device__ __forceinline__ bf16x4 input_operand(const float *X, int64_t p, bool valid, int kg, const Net &N,
-                                                float zf[4]) {
+// (of a pair of the table where it is not valid: every load is issued at once)
+__device__ __forceinline__ bf16x4 input_operand(const float *X, int64_t p, bool valid, int kg, const Net &N) {
     bf16x4 z;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int f = 4 * kg + i;
-        const float v = valid ? (X[p * kIn + f] - N.mean[f]) / N.stdv[f] : 0.f;
-        const uint16_t h = valid ? to_bf16(v) : (uint16_t)0;
-        z[i] = (short)h;
-        zf[i] = from_bf16(h);
+        const uint16_t h = to_bf16((X[p * kIn + f] - N.mean[f]) / N.stdv[f]);
+        z[i] = valid ? (short)h : (short)0;
     }
     return z;
-}
-
-struct Fwd {
-    bf16x4 h1[8];        // B operands of layer 2
-    float a1p[8][4];     // pre-activations of layer 1 (sign only is used)
-    float h2[8][4];      // bf16-valued layer-2 activations
-    float a2p[8][4];
-    float y;             // logit of pair l % 16 (all four lane groups hold it)
-};
-
-__device__ __forceinline__ void forward_tile(bf16x4 zop, const Net &N, int lane, Fwd &o) {
-    const int col = lane & 15, kg = lane >> 4;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const bf16x4 a = load4(N.W1b + (16 * t + col) * kIn + 4 * kg);
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mfma(a, zop, acc);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float pre = acc[i] + N.b1[16 * t + 4 * kg + i];
-            o.a1p[t][i] = pre;
-            o.h1[t][i] = (short)to_bf16(pre > 0.f ? pre : 0.f);
-        }
-    }
-    float part = 0.f;
-#pragma unroll
-    for (int t2 = 0; t2 < 8; ++t2) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc = mfma(load4(N.W2b + (16 * t2 + col) * kH + 16 * t + 4 * kg), o.h1[t], acc);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int f = 16 * t2 + 4 * kg + i;
-            const float pre = acc[i] + N.b2[f];
-            o.a2p[t2][i] = pre;
-            const float h = from_bf16(to_bf16(pre > 0.f ? pre : 0.f));
-            o.h2[t2][i] = h;
-            part += from_bf16(N.w3b[f]) * h;
-        }
-    }
-    part += __shfl_xor(part, 16, 64);
-    part += __shfl_xor(part, 32, 64);
-    o.y = part + N.b3[0];
 }
 
 // The network on n pairs.  A block keeps the weights in LDS (38 KB, so four
@@ -234,8 +189,8 @@ __device__ __forceinline__ void forward_tile(bf16x4 zop, const Net &N, int lane,
 // through the vector cache.  3.67 million pairs took 616 us that way, 361 with
 // W2 in registers (two waves fit on a SIMD and leave half of its issue slots
 // empty), 232 so.  The four layer-2 accumulators of a half and pair tile
-// advance side by side, each over its K tiles in forward_tile's order, so the
-// logits are the same bits (the K = 32 instruction sums in another order).
+// advance side by side, each over its K tiles in order, as in
+// training, so the logits are the same bits (the K = 32 instruction sums in another order).
 // Bound by instruction issue: some 290 vector instructions per 16 pairs for
 // inputs, bias and activation beside the 72 matrix ones.
 constexpr int kFwdTiles = 2;  // tiles of 16 pairs per wave and iteration
@@ -389,8 +344,8 @@ __device__ __forceinline__ void adam_one(const AdamArgs &A, int x, float g) {
 // Forward + backward of 16 pairs per wave for one minibatch.  Pairs of the
 // batch are examples order[off + p]; p >= count are padding (zero input and
 // gradient).  Writes ZT, H1, DH2 and DH1 (bf16, [B / 16][feature][16]) and,
-// per block, the sums of the loss and of the bias /
-// w3 gradients over its pairs into part[block][kMlpPartN] (slot 0 the loss,
+// per tile, the sums of the loss and of the bias /
+// w3 gradients over its pairs into part[tile][kMlpPartN] (slot 0 the loss,
 // then b1, b2, w3, b3), in a fixed order: no atomics, so a minibatch's
 // gradient is the same on every run.
 struct Train {
@@ -427,100 +382,159 @@ __device__ __forceinline__ void group_reduce_scatter(float (&v)[N], int col) {
     }
 }
 
+// One block per tile of 16 pairs, its four waves splitting the feature tiles of
+// layer 2 and of both backward products (two of eight each); layer 1, the loss
+// and the output gradient are cheap and every wave has them for itself.  The
+// batch of a step is small (8,192 pairs are 512 tiles for 1,024 SIMDs), so a
+// step takes as long as one wave's instructions: 38.6 us with a wave per tile,
+// 21.7 so.  The waves exchange layer 2's pre-activations through LDS, and every
+// sum runs in the order of one wave, so the gradients are the same bits.
 __global__ __launch_bounds__(64 * kMlpTrainWaves) void train_tile_kernel(Net N, Train T) {
-    constexpr int W = kMlpTrainWaves;
-    __shared__ float acc_lds[W][kMlpPartN];  // one row per wave
-    const int lane = threadIdx.x & 63, col = lane & 15, kg = lane >> 4, w = threadIdx.x >> 6;
-    for (int x = threadIdx.x; x < W * kMlpPartN; x += blockDim.x) (&acc_lds[0][0])[x] = 0.f;
-    __syncthreads();
-    float *my = acc_lds[w];
-    const int tile = blockIdx.x * W + w;  // the grid holds one wave per tile
-    if (tile < T.B / 16) {
-        const int pb = tile * 16 + col;  // pair index within the batch
-        const bool valid = pb < T.count;
-        const int64_t ex = valid ? (int64_t)T.order[T.off + pb] : 0;
-        float zf[4];
-        const bf16x4 z = input_operand(T.X, ex, valid, kg, N, zf);
-        uint16_t *const zt = T.ZT + (size_t)tile * kIn * 16 + col;
-        uint16_t *const h1 = T.H1 + (size_t)tile * kH * 16 + col;
-        uint16_t *const dh2 = T.DH2 + (size_t)tile * kH * 16 + col;
-        uint16_t *const dh1 = T.DH1 + (size_t)tile * kH * 16 + col;
+    constexpr int W = kMlpTrainWaves, kOwn = 8 / W;  // feature tiles per wave
+    __shared__ float4 pre2[8][64];                    // [t2][lane]: features 16 t2 + 4 kg .. + 3 of pair col
+    const int lane = threadIdx.x & 63, col = lane & 15, kg = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int tile = blockIdx.x, own = kOwn * w;
+    const int pb = tile * 16 + col;  // pair index within the batch
+    const bool valid = pb < T.count;
+    const int64_t ex = valid ? (int64_t)T.order[T.off + pb] : 0;
+    // every weight the wave needs is under way before the first is used
+    bf16x4 w1[8], w3[8], w2[kOwn][8], w2t[kOwn][8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) zt[(4 * kg + i) * 16] = (uint16_t)z[i];
-        Fwd o;
-        forward_tile(z, N, lane, o);
-        const float t = valid ? (float)T.labels[ex] : 0.f;
-        const float s = 1.f / (1.f + expf(-o.y));
-        const float dy = valid ? (T.pos_weight * t * (s - 1.f) + (1.f - t) * s) * T.inv_n : 0.f;
-        // loss: softplus(-y) for positives, softplus(y) for negatives, computed stably
-        const float sp = log1pf(expf(-fabsf(o.y)));
-        float lo = valid ? (T.pos_weight * t * (fmaxf(-o.y, 0.f) + sp) + (1.f - t) * (fmaxf(o.y, 0.f) + sp)) * T.inv_n
-                         : 0.f;
-        float sdy = dy;
+    for (int t = 0; t < 8; ++t) {
+        w1[t] = load4(N.W1b + (16 * t + col) * kIn + 4 * kg);
+        w3[t] = load4(N.w3b + 16 * t + 4 * kg);
+    }
 #pragma unroll
-        for (int m = 1; m < 16; m <<= 1) {
-            lo += __shfl_xor(lo, m, 64);
-            sdy += __shfl_xor(sdy, m, 64);
-        }
-        if (lane == 0) {
-            my[0] += lo;
-            my[kPartB3] += sdy;
-        }
-        // layer 3 / layer 2 backward, in the accumulator layout
-        bf16x4 dh2op[8];
-        float gw3[32], gb2[32];  // [4 * t2 + i]: feature 16 * t2 + 4 * kg + i
-#pragma unroll
-        for (int t2 = 0; t2 < 8; ++t2) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int f = 16 * t2 + 4 * kg + i;
-                gw3[4 * t2 + i] = dy * o.h2[t2][i];
-                const float d = o.a2p[t2][i] > 0.f ? dy * from_bf16(N.w3b[f]) : 0.f;
-                gb2[4 * t2 + i] = d;
-                const uint16_t db = to_bf16(d);
-                dh2op[t2][i] = (short)db;
-                dh2[f * 16] = db;
-                h1[f * 16] = (uint16_t)o.h1[t2][i];
-            }
-        }
-        group_reduce_scatter(gw3, col);
-        group_reduce_scatter(gb2, col);
-        // lane col now holds j = 2 col, 2 col + 1: feature 16 (j / 4) + 4 kg + j % 4
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int j = 2 * col + r, f = 16 * (j >> 2) + 4 * kg + (j & 3);
-            my[kPartW3 + f] += gw3[r];
-            my[kPartB2 + f] += gb2[r];
-        }
-        // dH1 = W2^T dH2 (transposed weights as the A operand)
-        float gb1[32];
+    for (int x = 0; x < kOwn; ++x)
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int t2 = 0; t2 < 8; ++t2)
-                acc = mfma(load4(N.W2Tb + (16 * t + col) * kH + 16 * t2 + 4 * kg), dh2op[t2], acc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int f = 16 * t + 4 * kg + i;
-                const float d = o.a1p[t][i] > 0.f ? acc[i] : 0.f;
-                gb1[4 * t + i] = d;
-                dh1[f * 16] = to_bf16(d);
-            }
+            w2[x][t] = load4(N.W2b + (16 * (own + x) + col) * kH + 16 * t + 4 * kg);
+            w2t[x][t] = load4(N.W2Tb + (16 * (own + x) + col) * kH + 16 * t + 4 * kg);
         }
-        group_reduce_scatter(gb1, col);
+    const uint8_t label = T.labels[ex];
+    __builtin_amdgcn_sched_barrier(0);
+    const bf16x4 z = input_operand(T.X, ex, valid, kg, N);
+    const size_t at = (size_t)tile * kH * 16 + col;
+    if (w == 0) {
+        uint16_t *const zt = T.ZT + (size_t)tile * kIn * 16 + col;
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int j = 2 * col + r;
-            my[kPartB1 + 16 * (j >> 2) + 4 * kg + (j & 3)] += gb1[r];
+        for (int i = 0; i < 4; ++i) zt[(4 * kg + i) * 16] = (uint16_t)z[i];
+    }
+    // forward (K tiles in order)
+    bf16x4 h1[8];
+    float own1[kOwn][4];  // layer-1 pre-activations of the wave's own tiles
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const f32x4 a = mfma(w1[t], z, f32x4{0.f, 0.f, 0.f, 0.f});
+        const float4 b = *(const float4 *)(N.b1 + 16 * t + 4 * kg);
+        const float p[4] = {a[0] + b.x, a[1] + b.y, a[2] + b.z, a[3] + b.w};
+#pragma unroll
+        for (int x = 0; x < kOwn; ++x)
+            if (own + x == t) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) own1[x][i] = p[i];
+            }
+        const uint2 v = make_uint2(to_bf16x2(p[0] > 0.f ? p[0] : 0.f, p[1] > 0.f ? p[1] : 0.f),
+                                   to_bf16x2(p[2] > 0.f ? p[2] : 0.f, p[3] > 0.f ? p[3] : 0.f));
+        h1[t] = __builtin_bit_cast(bf16x4, v);
+        if (t >= own && t < own + kOwn) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) T.H1[at + (16 * t + 4 * kg + i) * 16] = (uint16_t)h1[t][i];
         }
     }
-    __syncthreads();
-    for (int x = threadIdx.x; x < kMlpPartN; x += blockDim.x) {
-        float a = acc_lds[0][x];
+    float own2[kOwn][4];
 #pragma unroll
-        for (int i = 1; i < W; ++i) a += acc_lds[i][x];
-        T.part[(size_t)blockIdx.x * kMlpPartN + x] = a;
+    for (int x = 0; x < kOwn; ++x) {
+        const int t2 = own + x;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc = mfma(w2[x][t], h1[t], acc);
+        const float4 b = *(const float4 *)(N.b2 + 16 * t2 + 4 * kg);
+        own2[x][0] = acc[0] + b.x;
+        own2[x][1] = acc[1] + b.y;
+        own2[x][2] = acc[2] + b.z;
+        own2[x][3] = acc[3] + b.w;
+        pre2[t2][lane] = make_float4(own2[x][0], own2[x][1], own2[x][2], own2[x][3]);
+    }
+    __syncthreads();
+    float part = 0.f;
+#pragma unroll
+    for (int t2 = 0; t2 < 8; ++t2) {
+        const float4 q = pre2[t2][lane];
+        const float p[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float h = from_bf16(to_bf16(p[i] > 0.f ? p[i] : 0.f));
+            part += from_bf16((uint16_t)w3[t2][i]) * h;
+        }
+    }
+    part += __shfl_xor(part, 16, 64);
+    part += __shfl_xor(part, 32, 64);
+    const float y = part + N.b3[0];
+    const float t = valid ? (float)label : 0.f;
+    const float s = 1.f / (1.f + expf(-y));
+    const float dy = valid ? (T.pos_weight * t * (s - 1.f) + (1.f - t) * s) * T.inv_n : 0.f;
+    // layer 3 / layer 2 backward, in the accumulator layout
+    bf16x4 dh2op[8];
+#pragma unroll
+    for (int t2 = 0; t2 < 8; ++t2) {
+        const float4 q = pre2[t2][lane];
+        const float p[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            dh2op[t2][i] = (short)to_bf16(p[i] > 0.f ? dy * from_bf16((uint16_t)w3[t2][i]) : 0.f);
+    }
+    // the wave's own gradients of w3, b2 and b1, [4 x + i]: feature 16 (own + x) + 4 kg + i
+    float g[32] = {};
+#pragma unroll
+    for (int x = 0; x < kOwn; ++x) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = 16 * (own + x) + 4 * kg + i;
+            const float p = own2[x][i];
+            g[4 * x + i] = dy * from_bf16(to_bf16(p > 0.f ? p : 0.f));
+            const float d = p > 0.f ? dy * from_bf16(N.w3b[f]) : 0.f;
+            g[8 + 4 * x + i] = d;
+            T.DH2[at + f * 16] = to_bf16(d);
+        }
+    }
+    // dH1 = W2^T dH2 (transposed weights as the A operand)
+#pragma unroll
+    for (int x = 0; x < kOwn; ++x) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t2 = 0; t2 < 8; ++t2)
+            acc = mfma(w2t[x][t2], dh2op[t2], acc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = 16 * (own + x) + 4 * kg + i;
+            const float d = own1[x][i] > 0.f ? acc[i] : 0.f;
+            g[16 + 4 * x + i] = d;
+            T.DH1[at + f * 16] = to_bf16(d);
+        }
+    }
+    group_reduce_scatter(g, col);
+    // lane col now holds entries 2 col and 2 col + 1
+    float *const out = T.part + (size_t)tile * kMlpPartN;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int e = 2 * col + q, f = 16 * (own + (e >> 2 & 1)) + 4 * kg + (e & 3);
+        if (e < 24) out[(e < 8 ? kPartW3 : e < 16 ? kPartB2 : kPartB1) + f] = 0.f + g[q];
+    }
+    if (w != 0) return;
+    // loss: softplus(-y) for positives, softplus(y) for negatives, computed stably
+    const float sp = log1pf(expf(-fabsf(y)));
+    float lo = valid ? (T.pos_weight * t * (fmaxf(-y, 0.f) + sp) + (1.f - t) * (fmaxf(y, 0.f) + sp)) * T.inv_n : 0.f;
+    float sdy = dy;
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) {
+        lo += __shfl_xor(lo, m, 64);
+        sdy += __shfl_xor(sdy, m, 64);
+    }
+    if (lane == 0) {
+        out[0] = 0.f + lo;
+        out[kPartB3] = 0.f + sdy;
     }
 }
 
@@ -560,10 +574,10 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const uint16_t *__restrict__
 // The minibatch gradient from the partials, summed in a fixed order, then
 // (A.update) the Adam step of every parameter.  Threads [0, nW) take one
 // weight of W1 or W2 each (sum over the chunks); then one wave per part slot
-// sums the blocks' values (lane-strided, then a fixed shuffle tree) into the
+// sums the tiles' values (by four, lane-strided, then a fixed shuffle tree) into the
 // bias / w3 gradient, and slot 0 adds the batch loss to *loss.  The gradient
 // is written to grad either way.
-__global__ __launch_bounds__(256) void grad_reduce_kernel(const float *__restrict__ part, int nblk,
+__global__ __launch_bounds__(256) void grad_reduce_kernel(const float *__restrict__ part, int tiles,
                                                           const float *__restrict__ wp2,
                                                           const float *__restrict__ wp1, int chunks,
                                                           float *__restrict__ grad, float *__restrict__ loss,
@@ -586,7 +600,13 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const float *__restric
     const int slot = blockIdx.x * 4 + (threadIdx.x >> 6) - wbase, lane = threadIdx.x & 63;
     if (slot < 0 || slot >= kMlpPartN) return;
     float a = 0.f;
-    for (int b = lane; b < nblk; b += 64) a += part[(size_t)b * kMlpPartN + slot];
+    for (int b = 4 * lane; b < tiles; b += 256) {
+        const float *p = part + (size_t)b * kMlpPartN + slot;
+        float four = p[0];
+#pragma unroll
+        for (int q = 1; q < 4; ++q) four += b + q < tiles ? p[q * kMlpPartN] : 0.f;
+        a += four;
+    }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) a += __shfl_xor(a, m, 64);
     if (lane != 0) return;
@@ -759,8 +779,8 @@ hipError_t mlp_batch_grad(const MlpState &S, const float *X, const uint8_t *labe
     T.DH2 = S.DH2;
     T.DH1 = S.DH1;
     T.part = S.part;
-    const int tiles = B / 16, nblk = (tiles + kMlpTrainWaves - 1) / kMlpTrainWaves;  // rows of part
-    train_tile_kernel<<<nblk, 64 * kMlpTrainWaves, 0, s>>>(net_of(S), T);
+    const int tiles = B / 16;  // rows of part
+    train_tile_kernel<<<tiles, 64 * kMlpTrainWaves, 0, s>>>(net_of(S), T);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int chunks = (B + kMlpSplitK - 1) / kMlpSplitK;  // <= batch_cap / kMlpSplitK
@@ -770,7 +790,7 @@ hipError_t mlp_batch_grad(const MlpState &S, const float *X, const uint8_t *labe
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int nW = kH * kIn + kH * kH;
     const int rblocks = (nW + 255) / 256 + (kMlpPartN + 3) / 4;
-    grad_reduce_kernel<<<rblocks, 256, 0, s>>>(S.part, nblk, wp2, wp1, chunks, S.grad, loss,
+    grad_reduce_kernel<<<rblocks, 256, 0, s>>>(S.part, tiles, wp2, wp1, chunks, S.grad, loss,
                                                 adam_args(S, lr, step));
     return hipGetLastError();
 }

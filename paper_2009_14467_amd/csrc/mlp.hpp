@@ -17,8 +17,8 @@ constexpr int kMlpOffB2 = kMlpOffW2 + kMlpHidden * kMlpHidden;
 constexpr int kMlpOffW3 = kMlpOffB2 + kMlpHidden;
 constexpr int kMlpOffB3 = kMlpOffW3 + kMlpHidden;
 constexpr int kMlpParams = kMlpOffB3 + 1;
-// per-block partial sums of one training minibatch: loss, b1, b2, w3, b3;
-// a training block holds kMlpTrainWaves waves of 16 pairs each
+// partial sums of one training minibatch per tile of 16 pairs: loss, b1, b2,
+// w3, b3; a tile takes one block of kMlpTrainWaves waves
 constexpr int kMlpPartN = 1 + 3 * kMlpHidden + 1;
 constexpr int kMlpTrainWaves = 4;
 // the weight-gradient reductions over a minibatch are split into chunks of
@@ -33,7 +33,7 @@ struct MlpState {
     double *moments;                       // 2 * kMlpIn
     uint16_t *ZT, *H1, *DH2, *DH1;         // per-batch activations, feature-major
     int batch_cap;                         // pairs the activation buffers hold
-    float *part;                           // [batch_cap / (16 * kMlpTrainWaves)][kMlpPartN] block partials
+    float *part;                           // [batch_cap / 16][kMlpPartN] tile partials
     float *wpart;                          // [batch_cap / kMlpSplitK][W2 then W1] chunk partials
     // labelled examples collected for training: features [pool_cap][16], labels
     float *pool_X = nullptr;

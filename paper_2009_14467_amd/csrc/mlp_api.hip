@@ -43,7 +43,7 @@ pastis_status mlp_alloc(pastis_ctx *ctx) {
     PASTIS_TRY(grab((void **)&S.H1, 2 * (size_t)kMlpHidden * kMaxBatch));
     PASTIS_TRY(grab((void **)&S.DH2, 2 * (size_t)kMlpHidden * kMaxBatch));
     PASTIS_TRY(grab((void **)&S.DH1, 2 * (size_t)kMlpHidden * kMaxBatch));
-    PASTIS_TRY(grab((void **)&S.part, sizeof(float) * (size_t)(kMaxBatch / (16 * kMlpTrainWaves)) * kMlpPartN));
+    PASTIS_TRY(grab((void **)&S.part, sizeof(float) * (size_t)(kMaxBatch / 16) * kMlpPartN));
     PASTIS_TRY(grab((void **)&S.wpart, sizeof(float) * (size_t)(kMaxBatch / kMlpSplitK) *
                                            (kMlpHidden * kMlpHidden + kMlpHidden * kMlpIn)));
     ctx->mlp_alloc = true;
