@@ -214,14 +214,13 @@ STAGE_NAMES = ["encode", "kmers", "subs_AS", "spgemm", "schedule", "sw_pass1", "
 
 
 def kernel_name(b):
-    """The pass-1 kernel a length bin runs in: one launch per group of bins."""
-    R = b["rows_per_lane"]
-    if b["multi_strip"]:
-        return "sw16_pass1_kernel<9, 16, 4, true>" if b["bits"] == 16 else "sw_pass1_kernel<9, 16, true>"
-    lo = (R - 1) // 4 * 4 + 1
+    """The pass-1 kernel a length bin runs in: one launch for all 16-bit bins,
+    one per group of bins in 32-bit lanes."""
     if b["bits"] == 16:
-        return "sw16s_pass1_kernel<%d, %d>" % (lo, lo + 3) if R <= 8 else "sw16_pass1_kernel<%d, %d, 2, false>" % (
-            lo, lo + 3)
+        return "sw16_kernel<false>"
+    if b["multi_strip"]:
+        return "sw_pass1_kernel<9, 16, true>"
+    lo = (b["rows_per_lane"] - 1) // 4 * 4 + 1
     return "sw_pass1_kernel<%d, %d, false>" % (lo, lo + 3)
 
 
@@ -229,10 +228,10 @@ def roofline(st, pass1_ms):
     """The dominant length bin of pass 1 (the one with the most DP work) against
     the integer VALU peak of its lane width: its cells x the method's 11 ops
     per cell over its span on the device's clock, from the first claim of its
-    queue to the last finish.  The groups of bins run beside one another, so
-    a span includes time shared with other bins; all_pass1_bins divides the
-    work of all of them by the stage's time.  The kernel's own formulation
-    count (10 or 9 ops per cell) is reported beside it."""
+    queue to the last finish.  The bins of a launch and the launches run beside
+    one another, so a span includes time shared with other bins; all_pass1_bins
+    divides the work of all of them by the stage's time.  The kernel's own
+    formulation count (10 or 9 ops per cell) is reported beside it."""
 
     def ops(b):
         return OPS_PER_SW_CELL[(b["bits"], bool(b["multi_strip"]))]
