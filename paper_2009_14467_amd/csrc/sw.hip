@@ -1300,11 +1300,15 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     // The groups of a pass run beside one another on streams of the context:
     // the multi-strip group on the long stream, the others on the side streams
     // and the call's, where the 16-bit kernel (own, called as group -1) goes
-    // too.  run(phase, own, busy, f) calls f(group, stream) for every busy
-    // group and orders its work after the call's stream's and before what
-    // follows on it.
-    auto run = [&](int phase, bool own, auto &&busy, auto &&f) -> hipError_t {
-        hipStream_t st[kGroups] = {ctx->side_stream[0], s, ctx->side_stream[1], ctx->side_stream[2], ctx->long_stream};
+    // too.  swap: those two change places, for the long pairs' blocks, which
+    // need most of a CU's LDS each and wait for the whole 16-bit launch if its
+    // blocks come first; the call's stream begins a few microseconds before the
+    // streams that wait for its event.  run(phase, own, swap, busy, f) calls
+    // f(group, stream) for every busy group and orders its work after the call's
+    // stream's and before what follows on it.
+    auto run = [&](int phase, bool own, bool swap, auto &&busy, auto &&f) -> hipError_t {
+        hipStream_t st[kGroups] = {ctx->side_stream[0], s, ctx->side_stream[1], ctx->side_stream[2],
+                                   swap ? s : ctx->long_stream};
         int only = -1, n = own ? 1 : 0;
         for (int g = 0; g < kGroups; ++g)
             if (busy(g)) {
@@ -1315,17 +1319,20 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         if (n == 1) return f(own ? -1 : only, s);  // alone: no fork
         hipError_t e = hipEventRecord(ctx->fork_ev[phase], s);
         if (e != hipSuccess) return e;
-        for (int g = kGroups - 1; g >= 0; --g) {  // long pairs first
-            if (!busy(g) || st[g] == s) continue;
-            if ((e = hipStreamWaitEvent(st[g], ctx->fork_ev[phase], 0)) != hipSuccess) return e;
-            if ((e = f(g, st[g])) != hipSuccess) return e;
-            if ((e = hipEventRecord(ctx->join_ev[phase][g], st[g])) != hipSuccess) return e;
-        }
-        if (own && (e = f(-1, s)) != hipSuccess) return e;
-        for (int g = 0; g < kGroups; ++g)
+        auto fork = [&](int g, hipStream_t stream, int join) -> hipError_t {
+            hipError_t x = hipStreamWaitEvent(stream, ctx->fork_ev[phase], 0);
+            if (x == hipSuccess) x = f(g, stream);
+            return x == hipSuccess ? hipEventRecord(ctx->join_ev[phase][join], stream) : x;
+        };
+        if (swap && busy(kMultiGroup) && (e = f(kMultiGroup, s)) != hipSuccess) return e;
+        for (int g = kGroups - 1; g >= 0; --g)  // long pairs first
+            if (busy(g) && st[g] != s && (e = fork(g, st[g], g)) != hipSuccess) return e;
+        if (own && (e = swap ? fork(-1, ctx->long_stream, kMultiGroup) : f(-1, s)) != hipSuccess) return e;
+        for (int g = 0; g < kMultiGroup; ++g)
             if (busy(g) && st[g] == s && (e = f(g, s)) != hipSuccess) return e;
         for (int g = 0; g < kGroups; ++g)
-            if (busy(g) && st[g] != s && (e = hipStreamWaitEvent(s, ctx->join_ev[phase][g], 0)) != hipSuccess) return e;
+            if ((busy(g) && st[g] != s) || (g == kMultiGroup && swap && own))
+                if ((e = hipStreamWaitEvent(s, ctx->join_ev[phase][g], 0)) != hipSuccess) return e;
         return hipSuccess;
     };
     const int nb = (int)((npairs + 255) / 256);
@@ -1371,7 +1378,7 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     }
     if ((e = end(kStSched)) != hipSuccess || (e = begin(kStAlign1)) != hipSuccess) return e;
     // the 16-bit kernel runs beside the 32-bit groups, on the call's stream
-    e = run(0, plan.p16.blocks > 0, [&](int g) { return plan.blocks32[g] > 0; },
+    e = run(0, plan.p16.blocks > 0, plan.long_blocks1 > 0, [&](int g) { return plan.blocks32[g] > 0; },
             [&](int g, hipStream_t st) -> hipError_t {
                 if (g < 0) {
                     SwArgs B = A;
@@ -1417,7 +1424,7 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
             hipSuccess)
             return e;
-        e = run(1, false, [&](int g) { return plan.blocks_bound[g] > 0; },
+        e = run(1, false, false, [&](int g) { return plan.blocks_bound[g] > 0; },
                 [&](int g, hipStream_t st) {
                     kBound[g]<<<plan.blocks_bound[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
                     return hipGetLastError();
@@ -1456,7 +1463,7 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         B.dirs_multi = wk.dirs + sw16_waves() * plan.t16.blocks * plan.dirs_per_wave;
     }
     A.queue = wk.queue + 4 * kNumBins;
-    e = run(2, trace, [&](int g) { return stats && plan.blocks_stats[g] > 0; },
+    e = run(2, trace, stats && plan.long_blocks2 > 0, [&](int g) { return stats && plan.blocks_stats[g] > 0; },
             [&](int g, hipStream_t st) -> hipError_t {
                 if (g < 0) return launch_sw16(true, plan.t16, B, st);
                 if (g == kMultiGroup && plan.long_blocks2 > 0) {
