@@ -217,7 +217,7 @@ def kernel_name(b):
     """The pass-1 kernel a length bin runs in: one launch for all 16-bit bins,
     one per group of bins in 32-bit lanes."""
     if b["bits"] == 16:
-        return "sw16_kernel<false>"
+        return "sw16_kernel<false, 3>"
     if b["multi_strip"]:
         return "sw_pass1_kernel<9, 16, true>"
     lo = (b["rows_per_lane"] - 1) // 4 * 4 + 1

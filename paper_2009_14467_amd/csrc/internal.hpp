@@ -261,10 +261,11 @@ int sw_one_strip_max_rows();
 
 // One launch of a 16-bit kernel: its bins, grid, the blocks that take the
 // multi-strip bins, the bins of up to 4 rows per lane in strips of 16 lanes,
-// and whether those of up to 8 run across all 64 lanes instead.
+// whether those of up to 8 run across all 64 lanes instead, and whether the
+// traceback makes room for two waves per SIMD only.
 struct Sw16Launch {
     uint32_t bins = 0;
-    int blocks = 0, multi_blocks = 0, narrow = 0, wide = 0;
+    int blocks = 0, multi_blocks = 0, narrow = 0, wide = 0, lean = 0;
 };
 
 // The launches of a Smith-Waterman call, planned on the host from the pairs
@@ -288,7 +289,7 @@ struct SwPlan {
     int64_t long_slot = 0;
     int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
 };
-static_assert(sizeof(SwPlan) == (2 + 10 + 20 + 4) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
+static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 4) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
 // max16 > 0: pass 1 of one-strip pairs with at most max16 rows per lane in
 // 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
 // that skip the statistics pass.  tune: the grid scales of the one-strip

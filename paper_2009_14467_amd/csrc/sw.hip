@@ -1268,6 +1268,7 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, i
     Sw16Launch &k = p.p16;
     k.narrow = tune.sw16_narrow_rows;
     k.wide = n16 <= kWidePairs ? 1 : 0;
+    k.lean = n16 <= kWidePairs / 2 ? 1 : 0;  // two pairs per wave: two waves per SIMD take them all
     // a block takes up to four pairs of the full-wave bins, eight or sixteen in
     // strips, of one sequence a; half as many where sequences have few partners
     const int64_t windows = (wide16 + 1) / 2 + (strips16 + (k.wide ? 1 : 3)) / (k.wide ? 2 : 4);

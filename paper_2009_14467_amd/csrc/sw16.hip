@@ -1237,8 +1237,14 @@ __device__ __forceinline__ void descending(F &f, std::integer_sequence<int, I...
 constexpr int kBlockWaves = 2;
 constexpr size_t kBlockLds = kProfCodes * kWave * 16;  // a full-wave profile of 16 rows per lane
 
-template <bool TRACE>
-__global__ __launch_bounds__(64 * kBlockWaves, 3) void sw16_kernel(SwArgs A, Sw16Launch P) {
+//
+// WAVES: waves per SIMD to make room for.  The traceback's bodies spill 115
+// registers at three (outside the step, but every window pays them) and none at
+// two; two are all that a call of up to 4,096 pairs has (3,164 pairs: a search
+// of 1.79 ms against 1.65), more pairs want the third (250,001: 9.6 ms against
+// 10.9 in the pass).
+template <bool TRACE, int WAVES>
+__global__ __launch_bounds__(64 * kBlockWaves, WAVES) void sw16_kernel(SwArgs A, Sw16Launch P) {
     __shared__ __align__(16) char lds[kBlockLds];
     __shared__ int8_t sblosum[kProfCodes * kProfCodes];
     __shared__ WaveLds<kBlockWaves> L;
@@ -1311,10 +1317,12 @@ hipError_t launch_sw16_windows(int64_t npairs, const Sw16Launch &P, const SwArgs
 }
 
 hipError_t launch_sw16(bool trace, const Sw16Launch &P, const SwArgs &A, hipStream_t s) {
-    if (trace)
-        sw16_kernel<true><<<P.blocks, 64 * kBlockWaves, 0, s>>>(A, P);
+    if (trace && P.lean)
+        sw16_kernel<true, 2><<<P.blocks, 64 * kBlockWaves, 0, s>>>(A, P);
+    else if (trace)
+        sw16_kernel<true, 3><<<P.blocks, 64 * kBlockWaves, 0, s>>>(A, P);
     else
-        sw16_kernel<false><<<P.blocks, 64 * kBlockWaves, 0, s>>>(A, P);
+        sw16_kernel<false, 3><<<P.blocks, 64 * kBlockWaves, 0, s>>>(A, P);
     return hipGetLastError();
 }
 
