@@ -440,19 +440,22 @@ typedef struct pastis_tuning {
                               than the call's pairs can fill).  Every launch drains a
                               work queue, so 1 (a resident grid) suffices */
     int32_t sw_grid_scale_wide; /* the same for 9..16 rows per lane (1..64) */
-    int32_t sw_intra_pair; /* 1: pass 1 of sequences a longer than 2978 rows (32-bit lanes)
-                              runs one workgroup of four waves per pair, strips
-                              pipelined across the waves (intra-pair mode); 0: one
-                              wave per pair (inter-pair mode) */
+    int32_t sw_intra_pair; /* more than 2048 pairs of sequences a longer than 2978 rows
+                              (32-bit lanes), 1: pass 1 runs one workgroup of four waves
+                              per pair, strips pipelined across the waves (intra-pair
+                              mode); 0: one wave per pair (inter-pair mode).  Fewer such
+                              pairs run one workgroup of eight waves each either way
+                              (the call without allocations follows the knob) */
     int32_t sw16_narrow_rows; /* pairs per wavefront of the 16-bit bins of at most 4 rows per
                                  lane: bins of at most this many rows per lane (0..4) run
                                  strips of 16 lanes, eight pairs per wave; the others
                                  strips of 32 lanes, four pairs per wave (a wave's pairs
                                  share their shorter sequence, so sets with few candidates
                                  per sequence fill fewer slots of the wider grouping) */
-    int32_t sw_long_blocks; /* blocks per CU (1..4) of the multi-strip launches (sequences a
-                               over 1024 rows), which run on the context's second stream
-                               beside the one-strip bins: fewer leave those more waves */
+    int32_t sw_long_blocks; /* blocks per CU (1..4, in 32-bit lanes; in 16-bit lanes quarters
+                               of the launch's blocks) that take multi-strip pairs
+                               (sequences a over 1024 rows) beside the one-strip bins:
+                               fewer leave those more waves */
     int32_t reserved[1];
 } pastis_tuning;
 

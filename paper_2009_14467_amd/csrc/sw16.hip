@@ -10,16 +10,17 @@ namespace {
 // Two pairs per wave in the 16-bit halves of every DP word (pair P low, Q
 // high), same lane layout as the 32-bit pass, one strip (R <= 16).  The two
 // pairs share their shorter sequence a (pairs are sorted by bin, then a, then
-// the longer b first), so one int8 profile serves both; a wave whose two
-// items differ in a runs them one after the other.  Only G = H - (o + e) is
+// the longer b first), so one int8 profile serves both (see the windows below;
+// items that share the sort key's 24 bits of a but differ in a run one after
+// the other).  Only G = H - (o + e) is
 // kept per row: the diagonal term H(i-1, j-1) + s becomes G(i-1, j-1) +
 // (s + o + e), with the biased scores s + o + e >= 0 in the profile (each
 // row's two bytes are spread into the halves by one byte permute).  Padding
 // residues score -(o + e).  Each row keeps only its maximum: cells outside a
 // pair (padding rows and columns, columns before the first) score strictly
 // below its best real cell, so the score and the first row holding it are
-// exact; the end column is found later, for the pairs that need it (end_b =
-// -1 here).  Scores stay below 11 * 1024, far from the 16-bit limit.
+// exact; the end column is found later, for the pairs that need it (end_b
+// holds a hint here, see hint_code).  Scores stay below 11 * 1024, far from the 16-bit limit.
 // The gap states are kept floored at zero, E' = max(E, 0) and F' = max(F, 0):
 // their recurrences stay closed (max(E' - e, 0) = max(E - e, 0) for e >= 0,
 // one saturating subtract), and max(d, E', F') then already holds the local
