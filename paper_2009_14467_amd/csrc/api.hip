@@ -59,21 +59,6 @@ pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out) {
     return PASTIS_OK;
 }
 
-pastis_status ensure_pinned(pastis_ctx *ctx, size_t bytes, void **out) {
-    if (ctx->arena && ctx->h_pinned_bytes < bytes)
-        return set_error(ctx, PASTIS_E_INVAL, "a no-allocation call takes device inputs and outputs only");
-    if (ctx->h_pinned_bytes < bytes) {
-        if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
-        ctx->h_pinned = nullptr;
-        ctx->h_pinned_bytes = 0;
-        hipError_t e = hipHostMalloc(&ctx->h_pinned, bytes, hipHostMallocDefault);
-        if (e != hipSuccess) return set_error(ctx, PASTIS_E_NOMEM, "pinned host allocation failed");
-        ctx->h_pinned_bytes = bytes;
-    }
-    *out = ctx->h_pinned;
-    return PASTIS_OK;
-}
-
 hipError_t stage_begin(pastis_ctx *ctx, int stage, hipStream_t s) {
     ctx->ev_used[stage] = true;
     return hipEventRecord(ctx->ev[2 * stage], s);
@@ -207,6 +192,15 @@ pastis_status encode_into(pastis_ctx *ctx, const uint8_t *d_res, int64_t n_res, 
 }
 
 pastis_status read_device(pastis_ctx *ctx, const void *d, void *h, size_t bytes, hipStream_t s) {
+    // counters and flags go through the context's pinned page: a copy to
+    // pageable memory is staged by the runtime (components and scores of 250,000 sequences, three
+    // read-backs: 304 us that way, 265 through the page)
+    if (ctx->h_pinned && bytes <= kPinnedBytes) {
+        HIP_TRY(ctx, hipMemcpyAsync(ctx->h_pinned, d, bytes, hipMemcpyDeviceToHost, s), "read device");
+        HIP_TRY(ctx, hipStreamSynchronize(s), "sync");
+        memcpy(h, ctx->h_pinned, bytes);
+        return PASTIS_OK;
+    }
     HIP_TRY(ctx, hipMemcpyAsync(h, d, bytes, hipMemcpyDeviceToHost, s), "read device");
     HIP_TRY(ctx, hipStreamSynchronize(s), "sync");
     return PASTIS_OK;
@@ -214,19 +208,16 @@ pastis_status read_device(pastis_ctx *ctx, const void *d, void *h, size_t bytes,
 
 pastis_status read_flags(pastis_ctx *ctx, unsigned long long *d_flags, unsigned long long *h_flags, int count,
                          hipStream_t s) {
-    HIP_TRY(ctx, hipMemcpyAsync(h_flags, d_flags, sizeof(unsigned long long) * count, hipMemcpyDeviceToHost, s),
-            "read flags");
-    HIP_TRY(ctx, hipStreamSynchronize(s), "sync");
-    return PASTIS_OK;
+    return read_device(ctx, d_flags, h_flags, sizeof(unsigned long long) * count, s);
 }
 
 // flags[0]: smallest bad residue index (init ~0), flags[1]: pair errors
 pastis_status reset_flags(pastis_ctx *ctx, unsigned long long **d_flags, hipStream_t s) {
     void *f = nullptr;
     PASTIS_TRY(ensure(ctx, kBufFlag, 4 * sizeof(unsigned long long), &f));
-    const unsigned long long init[4] = {~0ull, 0ull, 0ull, 0ull};
-    HIP_TRY(ctx, hipMemcpyAsync(f, init, sizeof(init), hipMemcpyHostToDevice, s), "reset flags");
     *d_flags = (unsigned long long *)f;
+    HIP_TRY(ctx, fill<unsigned long long>(*d_flags, 1, ~0ull, s), "reset flags");
+    HIP_TRY(ctx, fill<unsigned long long>(*d_flags + 1, 3, 0ull, s), "reset flags");
     return PASTIS_OK;
 }
 
@@ -534,6 +525,10 @@ pastis_status pastis_create(const pastis_params *p, int device, pastis_ctx **out
             pastis_destroy(ctx);
             return PASTIS_E_DEVICE;
         }
+    }
+    if (hipHostMalloc(&ctx->h_pinned, kPinnedBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();  // read-backs then go to pageable memory
+        ctx->h_pinned = nullptr;
     }
     int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0) {

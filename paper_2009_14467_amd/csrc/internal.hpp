@@ -93,6 +93,8 @@ pastis_status read_device(pastis_ctx *ctx, const void *d, void *h, size_t bytes,
 
 }  // namespace pastis
 
+constexpr size_t kPinnedBytes = 4096;
+
 struct pastis_ctx {
     pastis_params params;
     int device = 0;
@@ -115,8 +117,7 @@ struct pastis_ctx {
     bool mlp_alloc = false, mlp_set = false;
     float mlp_tau = 0.f;
     int mlp_step = 0;
-    void *h_pinned = nullptr;
-    size_t h_pinned_bytes = 0;
+    void *h_pinned = nullptr;  // kPinnedBytes for small read-backs (null: pageable memory)
     hipEvent_t ev[2 * 9] = {};
     double ms_per_tick = 0.0;  // device wall clock
     // the SW groups of a pass run beside one another: the multi-strip (long)
@@ -181,7 +182,6 @@ pastis_status set_error(pastis_ctx *ctx, pastis_status s, const std::string &msg
 pastis_status hip_error(pastis_ctx *ctx, hipError_t e, const char *what);
 // Make buffer `id` at least `bytes` long (contents not preserved on growth).
 pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out);
-pastis_status ensure_pinned(pastis_ctx *ctx, size_t bytes, void **out);
 // Record the start / end of a stage on stream s; collect() adds elapsed times
 // of every recorded stage into ctx->stats.ms_stage (after synchronising s).
 hipError_t stage_begin(pastis_ctx *ctx, int stage, hipStream_t s);
