@@ -3,6 +3,7 @@
 #include <climits>
 
 #include "sw16.hpp"
+#include "walk_reach.hpp"
 
 namespace pastis {
 namespace {
@@ -150,8 +151,8 @@ __device__ __forceinline__ void file_dirs(uint32_t (&w)[NW], int r, short2_t d, 
 template <int S, int RP, bool MULTI>
 struct WalkShape {
     static constexpr int W = S / 2;  // lanes of the group
-    static constexpr int kSlots = MULTI || RP > 8 ? 1 : (15 + RP) / RP;
-    static constexpr int kCols = W < 16 ? 16 : W;
+    static constexpr int kSlots = walk_slots(RP, MULTI);
+    static constexpr int kCols = walk_cols(W);
     static constexpr int kRows = kSlots * RP;
     static constexpr int NW = dir_words<RP>();
     struct Lds {
@@ -190,8 +191,8 @@ __device__ __forceinline__ void walk_back(Walk &P, bool act, const uint32_t *dir
     while (!done) {
         const int blk = i / RP, j0 = j;
         const int p = MULTI ? blk % kWave : blk;
-        const int pb = p - (T::kSlots - 1);           // first slot fetched (may be negative)
-        const int r0 = (blk - (T::kSlots - 1)) * RP;  // its first row
+        const int pb = p - (T::kSlots - 1);               // first slot fetched (may be negative)
+        const int r0 = walk_first_row(blk, RP, T::kSlots);  // its first row (so may this)
         const uint32_t *src = dirs + (MULTI ? (blk / kWave) * strip_words : 0);
 #pragma unroll
         for (int m = 0; m < T::kCols / W; ++m) {
@@ -207,7 +208,7 @@ __device__ __forceinline__ void walk_back(Walk &P, bool act, const uint32_t *dir
             L.b[c] = b[col];
         }
         for (int r = sub; r < T::kRows; r += W)
-            if (r0 + r >= 0 && r0 + r < la) L.a[r] = a[r0 + r];
+            if (walk_holds_row(r0, r, la)) L.a[r] = a[r0 + r];
         __builtin_amdgcn_wave_barrier();
         int r = i - r0, c = 0;
         const int cend = min(T::kCols, j0 + 1);
@@ -220,7 +221,7 @@ __device__ __forceinline__ void walk_back(Walk &P, bool act, const uint32_t *dir
                 const int rr = r - sub, cc = c + sub;
                 bool stop = true, match = false;
                 int sum = 0;
-                if (rr >= 0 && cc < cend) {
+                if (walk_reads(r0, rr, cc, cend)) {
                     stop = (bits_at(rr, cc) & 1u) != 0;
                     const int ca = L.a[rr], cb = L.b[cc];
                     match = ca == cb;
