@@ -1045,7 +1045,11 @@ __device__ __forceinline__ bool strip16_body(const SwArgs &A, int cls, char *lds
 // forward sweep, and over the 256 rows above the end row whatever the
 // sequences' length.  An alignment that is still alive in the topmost of them
 // cannot be bounded here and goes on to the statistics, where it fails the cut
-// like any other; only the edges of a search use this bound (138,000 of 3.07 million
+// like any other; a pair that has ended (by either test, or at its first column)
+// is dead in every cell from then on, since a value of 0 or less could rise again
+// and its pair's answer would depend on how long the wave's other pairs keep the
+// sweep going.  Only the
+// edges of a search use this bound (138,000 of 3.07 million
 // at 250,000 sequences, 14 ms of traceback).  There the forward kernel, which
 // sweeps the end rectangle in 32-bit lanes, took 132 ms, this one 36; where
 // sequences reach 25,000 residues 115 against 1.3.
@@ -1117,7 +1121,8 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void sw16_bound_kernel(SwArgs 
             const uint32_t y = jQ >= 0 ? (uint32_t)pb[1][jQ] : (uint32_t)kPadCode;
             return (x * 4u) | (y * 4u << 16);
         };
-        const int steps = __builtin_amdgcn_readfirstlane(wave_max_i32(max(hi[0], hi[1]))) + S;
+        // (whole chunks of 16 steps: a pair's sweep ends at the same step in any wave)
+        const int steps = (__builtin_amdgcn_readfirstlane(wave_max_i32(max(hi[0], hi[1]))) + S + 15) & ~15;
         uint32_t G[RP], E[RP], M[RP];
 #pragma unroll
         for (int r = 0; r < RP; ++r) {
@@ -1128,6 +1133,7 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void sw16_bound_kernel(SwArgs 
         // the row below the end row: H = 0 left of every window column (an
         // alignment ends in a diagonal step), else dead
         uint32_t gprev = pos == 0 ? G0 : kDead, glast = kDead, flast = kDead, out = kDead;
+        uint32_t ended = 0u;  // the halves whose pair has ended
         uint32_t cres = (kPadCode * 4u) * 0x10001u, chunk = col(pos), nx = col(16 + pos);
         for (int t = 0; t < steps; ++t) {
             if ((t & 15) == 0 && t > 0) {
@@ -1145,9 +1151,18 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void sw16_bound_kernel(SwArgs 
                     const uint32_t o = (uint32_t)__shfl((int)out, strip * S + S - 1, kWave);  // G in the top row
                     const bool overP = end_a[0] >= kBoundRows && (int)(int16_t)(o & 0xFFFFu) + go_ge > 0;
                     const bool overQ = end_a[1] >= kBoundRows && ((int)o >> 16) + go_ge > 0;
-                    const bool live = ((int)(int16_t)(m & 0xFFFFu) > 0 && !overP && q[0] >= 0) ||
-                                      (((int)m >> 16) > 0 && !overQ && q[1] >= 0);
-                    if (__ballot(live) == 0ull) break;
+                    const unsigned long long strip_lanes = 0xFFFFull << (S * strip);
+                    const bool onP = (__ballot((int)(int16_t)(m & 0xFFFFu) > 0) & strip_lanes) && !overP && t < hi[0] + S;
+                    const bool onQ = (__ballot(((int)m >> 16) > 0) & strip_lanes) && !overQ && t < hi[1] + S;
+                    const uint32_t settled = (onP ? 0u : 0xFFFFu) | (onQ ? 0u : 0xFFFF0000u);
+                    if (__ballot(settled != ~0u) == 0ull) break;
+                    if (__ballot((settled & ~ended) != 0u)) {
+                        ended |= settled;
+                        auto kill = [&](uint32_t x) { return (kDead & ended) | (x & ~ended); };
+                        gprev = kill(gprev), glast = kill(glast), flast = kill(flast);
+#pragma unroll
+                        for (int r = 0; r < RP; ++r) G[r] = kill(G[r]), E[r] = kill(E[r]);
+                    }
                 }
             }
             uint32_t first = kDead;

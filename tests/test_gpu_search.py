@@ -192,3 +192,25 @@ def test_row_block_of_one_sequence_over_the_limit_fails(gpu):
     assert e.value.status == 5  # PASTIS_E_CAPACITY
     with pytest.raises(P.PastisError):
         P.Context(P.Params(block_entries=-1))
+
+
+def test_counters_do_not_depend_on_the_run(gpu):
+    """The counters of a search (pairs and cells of every pass) are those of its
+    input: pairs that share a wave of the start bound, in whatever order its list
+    was written, do not decide about one another."""
+    import paper_2009_14467_amd as P
+    from synth import make_family_set
+
+    s = make_family_set(n_families=20, family_size=20, mean_len=500, min_len=30, max_len=3000, divergence=0.4,
+                        stream=56)
+    res, off = _dev(s.residues, gpu), _dev(s.offsets, gpu)
+    ctx = P.Context(P.Params(k=5, n_subs=25, ck_min=2))
+    ctx.set_tuning(sw_direct_pct=100000)  # every pair takes the bound
+    seen = set()
+    for _ in range(8):
+        ctx.search(res, off)
+        st = ctx.stats()
+        seen.add(tuple(st[k] for k in ("n_aligned", "cells", "bound_pass_pairs", "bound_pass_cells",
+                                       "stats_pass_pairs", "stats_pass_cells", "n_edges")))
+    assert st["bound_pass_pairs"] > 10000
+    assert len(seen) == 1, seen
