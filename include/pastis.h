@@ -425,7 +425,7 @@ pastis_status pastis_mlp_load(pastis_ctx *ctx, const char *path);
 
 /* ---- schedule of the Smith-Waterman stage ----
  * Knobs of the length-binned launches (every setting gives the same results;
- * only the time changes).  A new context starts at {16, 50, 1, 1, 0, 4, 4}.  pastis_autotune times candidate settings on a
+ * only the time changes).  A new context starts at {16, 50, 1, 1, 0, 4, 4, 0}.  pastis_autotune times candidate settings on a
  * sample of the given sequences' own candidate pairs and keeps the fastest. */
 typedef struct pastis_tuning {
     int32_t sw16_max_rows; /* bins with at most this many rows per lane run two pairs per
@@ -456,7 +456,12 @@ typedef struct pastis_tuning {
                                of the launch's blocks) that take multi-strip pairs
                                (sequences a over 1024 rows) beside the one-strip bins:
                                fewer leave those more waves */
-    int32_t reserved[1];
+    int32_t sw_extra_mib; /* most MiB that the context holds for each of two buffers that
+                             only save time, the traceback's direction bits (up to 12,576)
+                             and the long pairs' slots (up to 16,384); 0: as many as they
+                             take.  A call that needs more of one, or finds the device
+                             too full for it, runs the kernels that do without it: the
+                             same records, more slowly.  >= 0; not tuned */
 } pastis_tuning;
 
 pastis_status pastis_get_tuning(const pastis_ctx *ctx, pastis_tuning *out);

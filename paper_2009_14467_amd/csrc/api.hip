@@ -59,6 +59,34 @@ pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out) {
     return PASTIS_OK;
 }
 
+pastis_status ensure_extra(pastis_ctx *ctx, int id, size_t bytes, size_t most, void **out) {
+    *out = nullptr;
+    DeviceBuffer &b = ctx->buf[id];
+    const size_t limit = (size_t)ctx->tune.sw_extra_mib << 20;
+    const bool fits = limit == 0 || bytes <= limit;
+    if (limit) most = std::min(most, limit);
+    if (b.ptr && (b.bytes < bytes || (limit && b.bytes > limit))) {
+        const hipError_t e = hipFree(b.ptr);
+        if (e != hipSuccess) return hip_error(ctx, e, "hipFree");
+        b.ptr = nullptr;
+        b.bytes = 0;
+    }
+    if (!fits) return PASTIS_OK;
+    if (!b.ptr) {
+        const size_t sizes[] = {std::max(bytes, std::min(bytes + bytes / 4, most)), bytes};
+        for (size_t want : sizes) {
+            if (hipMalloc(&b.ptr, want) == hipSuccess) {
+                b.bytes = want;
+                break;
+            }
+            (void)hipGetLastError();
+            b.ptr = nullptr;
+        }
+    }
+    *out = b.ptr;
+    return PASTIS_OK;
+}
+
 hipError_t stage_begin(pastis_ctx *ctx, int stage, hipStream_t s) {
     ctx->ev_used[stage] = true;
     return hipEventRecord(ctx->ev[2 * stage], s);
@@ -376,24 +404,29 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
         const int max16 = !use16 ? 0 : P.score_width == 16 ? 16 : ctx->tune.sw16_max_rows;
         if (max16 > 0) PASTIS_TRY(make_sort_work(ctx, npairs, wk));
         ctx->last_max16 = max16;
-        SwPlan plan = sw_plan(c + kCounterBinPairs, (int64_t)c[kCounterLongB], max16, st.max_len, traced, ctx->tune);
-        plan.forward_bound = ctx->records_internal ? 0 : 1;
+        auto plan_with = [&](bool trace, bool slots) {
+            SwPlan p = sw_plan(c + kCounterBinPairs, (int64_t)c[kCounterLongB], max16, st.max_len, trace, slots,
+                               ctx->tune);
+            p.forward_bound = ctx->records_internal ? 0 : 1;
+            return p;
+        };
+        SwPlan plan = plan_with(traced, traced);
         if (traced && stats_mode != 2 && plan.dirs_words > 0) {
             void *dirs = nullptr;
-            // a device too full for the direction bits runs the statistics kernels
-            const pastis_status ds = ensure(ctx, kBufDirs, sizeof(uint32_t) * (size_t)plan.dirs_words, &dirs);
-            if (ds != PASTIS_OK && ds != PASTIS_E_NOMEM) return ds;
-            wk.dirs = ds == PASTIS_OK ? (uint32_t *)dirs : nullptr;
+            PASTIS_TRY(ensure_extra(ctx, kBufDirs, sizeof(uint32_t) * (size_t)plan.dirs_words,
+                                    sw_dirs_most(st.max_len), &dirs));
+            wk.dirs = (uint32_t *)dirs;
+            // without room for the direction bits every pair may come to the
+            // statistics kernels
+            if (!dirs) plan = plan_with(false, traced);
         }
         if (plan.long_slot > 0) {
             void *slots = nullptr;
             const int blocks = std::max(plan.long_blocks1, plan.long_blocks2);
-            // a device too full for the slots runs the multi-strip kernels
-            const pastis_status ls =
-                ensure(ctx, kBufLong, sizeof(int) * (size_t)plan.long_slot * (size_t)blocks, &slots);
-            if (ls != PASTIS_OK && ls != PASTIS_E_NOMEM) return ls;
-            if (ls != PASTIS_OK) plan.long_blocks1 = plan.long_blocks2 = 0;
+            PASTIS_TRY(ensure_extra(ctx, kBufLong, sizeof(int) * (size_t)plan.long_slot * (size_t)blocks, kLongBytes,
+                                    &slots));
             wk.long_scratch = (int *)slots;
+            if (!slots) plan = plan_with(wk.dirs != nullptr, false);  // the multi-strip kernels
         }
         if (P.graph_mode) {
             PASTIS_TRY(sw_graph(ctx, codes, (const PairDesc *)pairs, npairs, sc, (SwPass1Out *)p1, out, wk, stats_mode,

@@ -111,7 +111,7 @@ struct pastis_ctx {
     bool records_internal = false;  // the current alignment's records feed edges only
     int last_max16 = 0;             // the last SW call ran 16-bit pass-1 bins up to this R
     uint64_t last_n_dir = 0;        // directional entries of the last candidate discovery
-    pastis_tuning tune{16, 50, 1, 1, 0, 4, 4, {0}};
+    pastis_tuning tune{16, 50, 1, 1, 0, 4, 4, 0};
     // learned filter
     pastis::MlpState mlp{};
     bool mlp_alloc = false, mlp_set = false;
@@ -182,6 +182,10 @@ pastis_status set_error(pastis_ctx *ctx, pastis_status s, const std::string &msg
 pastis_status hip_error(pastis_ctx *ctx, hipError_t e, const char *what);
 // Make buffer `id` at least `bytes` long (contents not preserved on growth).
 pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out);
+// The same for a buffer that only saves time: *out is null (and the call goes on)
+// where it would pass tune.sw_extra_mib or does not fit on the device.  No
+// headroom beyond `most` bytes.
+pastis_status ensure_extra(pastis_ctx *ctx, int id, size_t bytes, size_t most, void **out);
 // Record the start / end of a stage on stream s; collect() adds elapsed times
 // of every recorded stage into ctx->stats.ms_stage (after synchronising s).
 hipError_t stage_begin(pastis_ctx *ctx, int stage, hipStream_t s);
@@ -295,10 +299,13 @@ static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 4) * 4 + 4 * 8, "no hidden paddin
 // that skip the statistics pass.  tune: the grid scales of the one-strip
 // groups, intra-pair pass 1 of the 32-bit multi-strip bins, the 16-bit bins
 // in strips of 16 lanes, and the multi-strip grids.
-// long_b: 16-bit multi-strip pairs that the traceback refuses; traced: whether
-// the call may allocate the traceback's and the long pairs' memory.
-SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool traced,
+// long_b: 16-bit multi-strip pairs that the traceback refuses; trace: whether the
+// call has, or may have, its direction bits; slots: the long pairs' slots.
+SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool trace, bool slots,
                const pastis_tuning &tune);
+// Most bytes that the direction bits of a call take.
+size_t sw_dirs_most(int max_len);
+constexpr size_t kLongBytes = (size_t)16 << 30;  // and the long pairs' slots
 // Bins of the pairs (bin_of, the per-bin counters) and cleared work queues;
 // the counters must be zero before.
 hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &wk, hipStream_t s);

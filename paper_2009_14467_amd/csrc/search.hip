@@ -883,10 +883,8 @@ pastis_status pastis_set_tuning(pastis_ctx *ctx, const pastis_tuning *t) {
     if (t->sw16_max_rows < 0 || t->sw16_max_rows > 16 || t->sw_direct_pct < 0 || t->sw_grid_scale < 1 ||
         t->sw_grid_scale > 64 || t->sw_grid_scale_wide < 1 || t->sw_grid_scale_wide > 64 || t->sw_intra_pair < 0 ||
         t->sw_intra_pair > 1 || t->sw16_narrow_rows < 0 || t->sw16_narrow_rows > 4 || t->sw_long_blocks < 1 ||
-        t->sw_long_blocks > 4)
+        t->sw_long_blocks > 4 || t->sw_extra_mib < 0)
         return set_error(ctx, PASTIS_E_INVAL, "tuning value out of range");
-    for (int i = 0; i < 1; ++i)
-        if (t->reserved[i] != 0) return set_error(ctx, PASTIS_E_INVAL, "reserved fields must be zero");
     ctx->tune = *t;
     return PASTIS_OK;
 }

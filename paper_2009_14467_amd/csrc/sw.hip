@@ -1145,8 +1145,8 @@ constexpr int64_t kWidePairs = 8192;
 // beyond, the waves that work strip after strip keep the chip as busy.  1,225
 // pairs of 3,000 to 25,000 rows took 245 ms in pass 1 and 443 with statistics by
 // single waves, 149 and 118 so.  A block's scratch grows with the longest
-// sequence (20 MB for 25,000 residues); blocks are dropped beyond 16 GB.
-constexpr int64_t kLongPairs = 2048, kLongBytes = (int64_t)16 << 30;
+// sequence (20 MB for 25,000 residues); blocks are dropped beyond kLongBytes.
+constexpr int64_t kLongPairs = 2048;
 constexpr int kLongBlocks = 256;
 
 // Resident blocks per CU of the one-strip statistics kernels: they keep no
@@ -1202,8 +1202,19 @@ hipError_t launch_sw_bins(const PairDesc *pairs, int64_t npairs, const SwWork &w
     return hipGetLastError();
 }
 
+// direction words of a wave's one-strip and multi-strip pairs
+static int64_t dirs_of_wave(int max_len) { return (int64_t)(std::min(max_len, kTraceCols) + kWave) * sw16_step_words(); }
+static int64_t dirs_of_multi(int max_len) {
+    return (int64_t)kTraceStrips * (std::min(max_len, kTraceColsMulti) + kWave) * sw16_step_words();
+}
+
+size_t sw_dirs_most(int max_len) {
+    return sizeof(uint32_t) * (size_t)sw16_waves() *
+           (size_t)(kBlocks16 * dirs_of_wave(max_len) + kTraceMultiBlocks * dirs_of_multi(max_len));
+}
+
 // The launches of a call, from its pairs per bin.
-SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool traced,
+SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool trace, bool slots,
                const pastis_tuning &tune) {
     SwPlan p;
     p.max16 = max16;
@@ -1251,12 +1262,12 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, i
     for (int b = kMultiBin; b < kNumBins; ++b) {
         const bool is16 = sw_bin_is16(b, max16);
         long32 += is16 ? 0 : (int64_t)bin_pairs[b];
-        long_stats += is16 && traced ? 0 : (int64_t)bin_pairs[b];
+        long_stats += is16 && trace ? 0 : (int64_t)bin_pairs[b];
     }
-    if (n16 > 0 && traced) long_stats += long_b;
-    if (traced) {
+    if (n16 > 0 && trace) long_stats += long_b;
+    if (slots) {
         p.long_slot = sw_long_slot_words(max_len);
-        const int64_t fit = std::max<int64_t>(8, kLongBytes / (int64_t)(p.long_slot * sizeof(int)));
+        const int64_t fit = std::max<int64_t>(8, (int64_t)kLongBytes / (int64_t)(p.long_slot * sizeof(int)));
         auto blocks = [&](int64_t pairs) {
             return pairs > kLongPairs ? 0 : (int)std::min<int64_t>({kLongBlocks, fit, pairs});
         };
@@ -1282,8 +1293,8 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, i
     p.t16.narrow = 0;
     p.t16.blocks = std::min(k.blocks, kBlocks16);
     p.t16.multi_blocks = multi16 ? std::min(p.t16.blocks, kTraceMultiBlocks) : 0;
-    p.dirs_per_wave = (int64_t)(std::min(max_len, kTraceCols) + kWave) * sw16_step_words();
-    p.dirs_per_multi = (int64_t)kTraceStrips * (std::min(max_len, kTraceColsMulti) + kWave) * sw16_step_words();
+    p.dirs_per_wave = dirs_of_wave(max_len);
+    p.dirs_per_multi = dirs_of_multi(max_len);
     p.dirs_words =
         sw16_waves() * (p.t16.blocks * p.dirs_per_wave + p.t16.multi_blocks * p.dirs_per_multi);
     p.stats_after_trace = any32 || max_len > kTraceCols;

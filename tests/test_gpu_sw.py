@@ -603,3 +603,61 @@ def test_records_do_not_depend_on_the_bound(gpu):
         if width == 0:
             first = none
         np.testing.assert_array_equal(none, first)
+
+
+def _family_of(seqs):
+    from synth.families import FamilySet
+
+    letters = np.frombuffer(b"ARNDCQEGHILKMFPSTWYV", np.uint8)
+    off = np.zeros(len(seqs) + 1, np.int64)
+    np.cumsum([len(x) for x in seqs], out=off[1:])
+    return FamilySet(letters[np.concatenate(seqs)].astype(np.uint8), off, np.zeros(len(seqs), np.int32), {})
+
+
+def _related(rng, L, rate=0.2, pre=20, post=9):
+    a = rng.integers(0, 20, L)
+    b = a.copy()
+    sub = rng.random(L) < rate
+    b[sub] = rng.integers(0, 20, int(sub.sum()))
+    return [a, np.concatenate([rng.integers(0, 20, pre), b, rng.integers(0, 20, post)])]
+
+
+def test_calls_without_room_for_the_extra_buffers(gpu, orc):
+    """A device too full (here: a limit of the context) for the traceback's
+    direction bits, or for the long pairs' slots as well, gives the same records
+    without an error left behind, and the few blocks planned for the few long
+    pairs do not get the statistics of every other pair of several strips."""
+    import time
+
+    import torch
+
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(37)
+    seqs = []
+    for L in (1030, 1100, 1152, 1153, 1200, 1281, 90, 300, 700, 1000):
+        seqs += _related(rng, L)
+    several = len(seqs)
+    for L in (3000, 3100, 3200):  # 32-bit lanes
+        seqs += _related(rng, L)
+    s = _family_of(seqs)
+    lo = np.arange(0, len(seqs), 2, dtype=np.uint32)
+    want = orc.align_pairs(orc.encode(s.residues), s.offsets, lo, lo + 1, mode="sw")
+    copies = 400  # 2,400 pairs of several strips in 16-bit lanes, and three long ones
+    at = np.concatenate([np.tile(np.arange(several // 2), copies), np.arange(several // 2, lo.size)])
+    args = [_to_dev(x, gpu) for x in (s.residues, s.offsets, lo[at], lo[at] + 1)]
+    times = {}
+    for mib in (0, 64, 1):  # all fits; no direction bits; no slots either
+        ctx = P.Context(P.Params(full_records=True))
+        ctx.set_tuning(sw_extra_mib=mib)
+        for rep in range(3):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            out = ctx.align_pairs(*args)
+            torch.cuda.synchronize()
+            dt = time.perf_counter() - t0
+            times[mib] = min(times.get(mib, dt), dt)
+        _compare(P.records_to_numpy(out), want[at])
+        assert P.lib().pastis_last_error(ctx._ctx) == b""
+    print({k: round(1e3 * v, 2) for k, v in times.items()}, "ms")
+    assert times[64] < 12 * times[0] and times[1] < 12 * times[0], times
