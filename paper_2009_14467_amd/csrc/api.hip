@@ -19,6 +19,28 @@ pastis_status hip_error(pastis_ctx *ctx, hipError_t e, const char *what) {
     return set_error(ctx, PASTIS_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+hipError_t device_alloc(pastis_ctx *ctx, void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    *p = nullptr;
+    bool freed = false;
+    for (int id : {(int)kBufDirs, (int)kBufLong}) {
+        DeviceBuffer &b = ctx->buf[id];
+        if (!b.ptr) continue;
+        if (hipFree(b.ptr) != hipSuccess) (void)hipGetLastError();
+        b.ptr = nullptr;
+        b.bytes = 0;
+        freed = true;
+    }
+    if (!freed) return e;
+    if ((e = hipMalloc(p, bytes)) != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+
 pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out) {
     if (bytes == 0) bytes = 256;
     if (ctx->arena) {
@@ -48,9 +70,7 @@ pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out) {
             b.bytes = 0;
         }
         size_t want = bytes + bytes / 4;  // some headroom against regrowth
-        hipError_t e = hipMalloc(&b.ptr, want);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
+        if (device_alloc(ctx, &b.ptr, want) != hipSuccess) {
             return set_error(ctx, PASTIS_E_NOMEM, "device allocation of " + std::to_string(want) + " bytes failed");
         }
         b.bytes = want;

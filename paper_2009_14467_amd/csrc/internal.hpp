@@ -182,7 +182,10 @@ pastis_status set_error(pastis_ctx *ctx, pastis_status s, const std::string &msg
 pastis_status hip_error(pastis_ctx *ctx, hipError_t e, const char *what);
 // Make buffer `id` at least `bytes` long (contents not preserved on growth).
 pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out);
-// The same for a buffer that only saves time: *out is null (and the call goes on)
+// hipMalloc for a context: where it fails, the buffers that only save time are given
+// back and it is tried again (no call holds them past its own synchronisation).
+hipError_t device_alloc(pastis_ctx *ctx, void **p, size_t bytes);
+// The same as ensure for a buffer that only saves time: *out is null (and the call goes on)
 // where it would pass tune.sw_extra_mib or does not fit on the device.  No
 // headroom beyond `most` bytes.
 pastis_status ensure_extra(pastis_ctx *ctx, int id, size_t bytes, size_t most, void **out);

@@ -20,11 +20,8 @@ pastis_status mlp_alloc(pastis_ctx *ctx) {
     MlpState &S = ctx->mlp;
     auto grab = [&](void **p, size_t bytes) -> pastis_status {
         if (*p) return PASTIS_OK;  // kept from an earlier, partly failed call
-        if (hipMalloc(p, bytes) != hipSuccess) {
-            *p = nullptr;
-            (void)hipGetLastError();
+        if (device_alloc(ctx, p, bytes) != hipSuccess)
             return set_error(ctx, PASTIS_E_NOMEM, "network allocation failed");
-        }
         return PASTIS_OK;
     };
     PASTIS_TRY(grab((void **)&S.theta, sizeof(float) * kMlpParams));
@@ -385,10 +382,8 @@ struct TrainBufs {
     template <typename T>
     pastis_status get(pastis_ctx *ctx, int64_t count, T **out) {
         void *p = nullptr;
-        if (hipMalloc(&p, sizeof(T) * (size_t)std::max<int64_t>(count, 1)) != hipSuccess) {
-            (void)hipGetLastError();
+        if (device_alloc(ctx, &p, sizeof(T) * (size_t)std::max<int64_t>(count, 1)) != hipSuccess)
             return set_error(ctx, PASTIS_E_NOMEM, "training buffer allocation failed");
-        }
         ptrs.push_back(p);
         *out = (T *)p;
         return PASTIS_OK;
@@ -441,9 +436,8 @@ pastis_status mlp_pool_reserve(pastis_ctx *ctx, int64_t want, hipStream_t s) {
     const int64_t cap = std::max<int64_t>(want + want / 4, 1 << 16);
     float *X = nullptr;
     uint8_t *y = nullptr;
-    if (hipMalloc(&X, sizeof(float) * kMlpIn * (size_t)cap) != hipSuccess ||
-        hipMalloc(&y, (size_t)cap) != hipSuccess) {
-        (void)hipGetLastError();
+    if (device_alloc(ctx, (void **)&X, sizeof(float) * kMlpIn * (size_t)cap) != hipSuccess ||
+        device_alloc(ctx, (void **)&y, (size_t)cap) != hipSuccess) {
         if (X) (void)hipFree(X);
         return set_error(ctx, PASTIS_E_NOMEM, "example pool allocation failed");
     }

@@ -733,10 +733,8 @@ pastis_status pastis_search(pastis_ctx *ctx, const uint8_t *residues, const int6
         PASTIS_TRY(read_device(ctx, M.n_edges, &ne, sizeof(ne), s));
         pastis_edge *d = nullptr;
         if (ne > 0) {
-            if (hipMalloc(&d, sizeof(pastis_edge) * ne) != hipSuccess) {
-                (void)hipGetLastError();
+            if (device_alloc(ctx, (void **)&d, sizeof(pastis_edge) * ne) != hipSuccess)
                 return set_error(ctx, PASTIS_E_NOMEM, "edge allocation failed");
-            }
             parts.v.push_back({d, (int64_t)ne});
             edge_write_kernel<<<grid_for(nc), 256, 0, s>>>(
                 rec, flag, pos, nc, (const uint32_t *)ctx->buf[kBufCandLo].ptr,
@@ -761,8 +759,7 @@ pastis_status pastis_search(pastis_ctx *ctx, const uint8_t *residues, const int6
         res->d_edges = parts.v[0].first;
         parts.v[0].first = nullptr;
     } else if (n_edges > 0) {
-        if (hipMalloc(&res->d_edges, sizeof(pastis_edge) * n_edges) != hipSuccess) {
-            (void)hipGetLastError();
+        if (device_alloc(ctx, (void **)&res->d_edges, sizeof(pastis_edge) * n_edges) != hipSuccess) {
             delete res;
             return set_error(ctx, PASTIS_E_NOMEM, "edge allocation failed");
         }

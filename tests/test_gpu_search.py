@@ -214,3 +214,42 @@ def test_counters_do_not_depend_on_the_run(gpu):
                                        "stats_pass_pairs", "stats_pass_cells", "n_edges")))
     assert st["bound_pass_pairs"] > 10000
     assert len(seen) == 1, seen
+
+
+def test_buffers_that_only_save_time_make_room(gpu):
+    """The direction bits that an alignment call left with the context are given
+    back when a later call of it finds the device full."""
+    import torch
+
+    import paper_2009_14467_amd as P
+    from synth import make_family_set
+
+    long = make_family_set(n_families=3, family_size=40, mean_len=1300, min_len=1100, max_len=1600, divergence=0.3,
+                           stream=57)
+    short = make_family_set(n_families=4, family_size=10, mean_len=40, min_len=20, max_len=60, divergence=0.3,
+                            stream=58)
+    lo, hi = (_dev(x.astype(np.uint32), gpu) for x in np.triu_indices(long.n, 1))
+    lo2, hi2 = (_dev(x.astype(np.uint32), gpu) for x in np.triu_indices(short.n, 1))
+    copies = 40000  # 31 million pairs, about 115 bytes each
+    many = [_dev(short.residues, gpu), _dev(short.offsets, gpu), lo2.repeat(copies), hi2.repeat(copies)]
+    want = P.Context(P.Params(full_records=True)).align_pairs(*many[:2], lo2, hi2)
+    ctx = P.Context(P.Params(full_records=True))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    ctx.align_pairs(_dev(long.residues, gpu), _dev(long.offsets, gpu), lo, hi)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    assert before - free > 5 << 30
+    full = None
+    try:
+        try:  # room for the records and 2 GiB
+            full = torch.empty(free - copies * lo2.numel() * 48 - (2 << 30), dtype=torch.uint8, device=gpu)
+        except torch.cuda.OutOfMemoryError:
+            pytest.skip("the device is shared")
+        got = ctx.align_pairs(*many).view(copies, -1)
+        assert all(bool((part == want).all()) for part in got.split(4000))
+    finally:
+        del full
+        torch.cuda.empty_cache()
