@@ -5,6 +5,7 @@
 
 #include "internal.hpp"
 #include "prim.hpp"
+#include "sw16.hpp"
 
 using namespace pastis;
 
@@ -293,13 +294,23 @@ pastis_status make_sw_work(pastis_ctx *ctx, int64_t npairs, int max_len, SwWork 
     wk.scratch_per_wave = 6 * (int64_t)std::max(max_len, 1);
     wk.scratch16_per_wave = 2 * (int64_t)std::max(max_len, 1);
     // only multi-strip pairs (a sequence a longer than one strip) touch the
-    // boundary rows; without such a sequence the buffer is never read.  The
-    // 16-bit kernels, which run beside the 32-bit ones, have rows of their own.
-    const int64_t words32 = wk.scratch_per_wave * sw_scratch_waves(), words16 = wk.scratch16_per_wave * sw16_scratch_waves();
-    const bool multi = max_len > sw_one_strip_max_rows();
-    PASTIS_TRY(ensure(ctx, kBufScratch, multi ? sizeof(int) * (size_t)(words32 + words16) : 256, &p));
-    wk.scratch = (int *)p;
-    wk.scratch16 = multi ? wk.scratch + words32 : wk.scratch;
+    // boundary rows; without such a sequence the buffer is never read
+    const size_t scratch_bytes = max_len > sw_one_strip_max_rows()
+                                     ? sizeof(int) * (size_t)wk.scratch_per_wave * (size_t)sw_scratch_waves()
+                                     : 256;
+    PASTIS_TRY(ensure(ctx, kBufScratch, scratch_bytes, &p));
+    wk.scratch = wk.scratch16 = (int *)p;
+    return PASTIS_OK;
+}
+
+// The 16-bit kernels, which run beside the 32-bit ones, have boundary rows of
+// their own, for the blocks of the plan that take multi-strip pairs.
+static pastis_status make_sw16_rows(pastis_ctx *ctx, const SwPlan &plan, SwWork &wk) {
+    const int64_t waves = (int64_t)sw16_waves() * std::max(plan.p16.multi_blocks, plan.t16.multi_blocks);
+    if (!sw_bins_multi(plan.p16.bins)) return PASTIS_OK;
+    void *p = nullptr;
+    PASTIS_TRY(ensure(ctx, kBufScratch16, sizeof(int) * (size_t)(wk.scratch16_per_wave * waves), &p));
+    wk.scratch16 = (int *)p;
     return PASTIS_OK;
 }
 
@@ -431,6 +442,7 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
             return p;
         };
         SwPlan plan = plan_with(traced, traced);
+        PASTIS_TRY(make_sw16_rows(ctx, plan, wk));
         if (traced && stats_mode != 2 && plan.dirs_words > 0) {
             void *dirs = nullptr;
             PASTIS_TRY(ensure_extra(ctx, kBufDirs, sizeof(uint32_t) * (size_t)plan.dirs_words,

@@ -172,6 +172,7 @@ enum BufId {
     kBufSortKeysAlt,
     kBufSortValsAlt,
     kBufSortTemp,
+    kBufScratch16,
     kBufDirs,
     kBufLong,
     kBufCount  // first id used by the discovery stage
@@ -210,8 +211,8 @@ struct SwPass1Out {
 // Work buffers of an alignment stage (device): per-pair bin ids, bin counts,
 // bin starts for the two passes, a cursor, the two binned index lists, and
 // boundary-row scratch for pairs taller than one strip (6 planes of max_len
-// ints per wave, for sw_scratch_waves() waves; 2 planes for the
-// sw16_scratch_waves() waves of the 16-bit kernels).
+// ints per wave, for sw_scratch_waves() waves; 2 planes for the waves of the
+// 16-bit kernels' blocks that take such pairs).
 // counters: [0] cells, [1] statistics-pass pairs, [2] their cells, [3]
 // start-bound pairs, [4] their cells, [kCounterXdQueue] the x-drop kernel's
 // work queue, [kCounterBinCells + b] and [kCounterBinPairs + b] pass-1 cells
@@ -259,7 +260,7 @@ hipError_t launch_xd(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
                      const int8_t *blosum, const Scoring &sc, int k, pastis_pair_record *out, uint32_t *redo,
                      uint32_t *n_redo, int *gring, unsigned long long *counters, hipStream_t s);
 int64_t sw_scratch_waves();
-int64_t sw16_scratch_waves();
+bool sw_bins_multi(uint32_t bins);  // any multi-strip bin among them
 // Queries the resident blocks of the SW kernels whose grids follow their
 // occupancy (once per process, before any launch is captured).
 void sw_init_occupancy();

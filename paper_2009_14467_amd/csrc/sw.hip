@@ -1183,7 +1183,7 @@ int64_t sw_scratch_waves() {
     return std::max<int64_t>((int64_t)kGroupBlocks[kMultiGroup] * kGroupWpb[kMultiGroup],
                              (int64_t)kIntraBlocks * kIntraWaves);
 }
-int64_t sw16_scratch_waves() { return (int64_t)kBlocks16 * sw16_waves(); }
+bool sw_bins_multi(uint32_t bins) { return (bins & kGroupBins[kMultiGroup]) != 0; }
 
 // The 16-bit profile holds each biased score s + o + e in one byte, with
 // s <= 11 in BLOSUM62; other gap costs run in 32-bit lanes.

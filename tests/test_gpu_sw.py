@@ -661,3 +661,28 @@ def test_calls_without_room_for_the_extra_buffers(gpu, orc):
         assert P.lib().pastis_last_error(ctx._ctx) == b""
     print({k: round(1e3 * v, 2) for k, v in times.items()}, "ms")
     assert times[64] < 12 * times[0] and times[1] < 12 * times[0], times
+
+
+def test_calls_in_32_bit_lanes_hold_no_rows_for_16_bits(gpu):
+    """Boundary rows of the 16-bit kernels belong to calls that have pairs of
+    several strips in 16-bit lanes: a long pair in 32-bit lanes holds those of the
+    32-bit kernels alone (24 bytes per residue of the longest sequence and each of
+    1,536 waves, and a quarter's headroom)."""
+    import torch
+
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(41)
+    s = _family_of(_related(rng, 20000))
+    args = [_to_dev(x, gpu) for x in (s.residues, s.offsets, np.array([0], np.uint32), np.array([1], np.uint32))]
+    ctx = P.Context(P.Params(score_width=32))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    ctx.align_pairs(*args)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = before - torch.cuda.mem_get_info()[0]
+    rows = 24 * 20029 * 1536 * 5 // 4
+    print(held, rows)
+    assert held < rows + (100 << 20)
