@@ -158,6 +158,35 @@ hipError_t bind_scratch(int device, char **out) {
     return hipSuccess;
 }
 
+// The lanes of a device and the contexts that hold them.
+struct Lanes {
+    std::mutex mu;
+    int users = 0;
+    hipStream_t s[kLanes] = {};
+};
+Lanes g_lanes[kMaxDevices];
+
+// default priority; non-blocking so that they never wait on the null stream
+hipError_t make_lanes(hipStream_t (&s)[kLanes]) {
+    for (hipStream_t &x : s) {
+        const hipError_t e = hipStreamCreateWithFlags(&x, hipStreamNonBlocking);
+        if (e != hipSuccess) {
+            x = nullptr;
+            return e;
+        }
+    }
+    return hipSuccess;
+}
+
+void end_lanes(hipStream_t (&s)[kLanes]) {
+    for (hipStream_t &x : s) {
+        if (!x) continue;
+        (void)hipStreamSynchronize(x);
+        (void)hipStreamDestroy(x);
+        x = nullptr;
+    }
+}
+
 pastis_status validate(const pastis_params *p, std::string &why) {
     if (p->k < 1 || p->k > 8) return why = "k must be in 1..8", PASTIS_E_INVAL;
     if (p->n_subs < 0 || p->n_subs > 64) return why = "n_subs must be in 0..64", PASTIS_E_INVAL;
@@ -188,6 +217,41 @@ pastis_status validate(const pastis_params *p, std::string &why) {
 }  // namespace
 
 namespace pastis {
+
+hipError_t fork_acquire(pastis_ctx *ctx) {
+    if (ctx->lanes_held) return hipSuccess;
+    if (ctx->graph_stream) {
+        const hipError_t e = make_lanes(ctx->lane);
+        if (e != hipSuccess)
+            end_lanes(ctx->lane);
+        else
+            ctx->lanes_held = 2;
+        return e;
+    }
+    Lanes &L = g_lanes[ctx->device];  // (a context's device is below kMaxDevices: bind_scratch)
+    std::lock_guard<std::mutex> lock(L.mu);
+    if (L.users == 0) {
+        const hipError_t e = make_lanes(L.s);
+        if (e != hipSuccess) {
+            end_lanes(L.s);
+            return e;
+        }
+    }
+    ++L.users;
+    for (int i = 0; i < kLanes; ++i) ctx->lane[i] = L.s[i];
+    ctx->lanes_held = 1;
+    return hipSuccess;
+}
+
+void fork_release(pastis_ctx *ctx) {
+    if (ctx->lanes_held == 2) end_lanes(ctx->lane);
+    if (ctx->lanes_held == 1) {
+        Lanes &L = g_lanes[ctx->device];
+        std::lock_guard<std::mutex> lock(L.mu);
+        if (--L.users == 0) end_lanes(L.s);
+    }
+    ctx->lanes_held = 0;
+}
 
 pastis_status stage_sequences(pastis_ctx *ctx, const uint8_t *residues, const int64_t *offsets, int64_t n,
                               int on_device, hipStream_t s, Staged &st) {
@@ -363,6 +427,7 @@ static pastis_status sw_graph(pastis_ctx *ctx, const uint8_t *codes, const PairD
             (void)hipGraphExecDestroy(ctx->sw_exec);
             ctx->sw_exec = nullptr;
         }
+        HIP_TRY(ctx, fork_acquire(ctx), "graph streams");
         HIP_TRY(ctx, hipStreamBeginCapture(gs, hipStreamCaptureModeThreadLocal), "graph capture");
         const hipError_t le =
             launch_sw(ctx, codes, pairs, npairs, ctx->d_blosum, sc, p1, out, wk, stats_mode, plan, false, gs);
@@ -601,17 +666,9 @@ pastis_status pastis_create(const pastis_params *p, int device, pastis_ctx **out
         khz = 100000;  // 100 MHz
     }
     ctx->ms_per_tick = 1.0 / (double)khz;
-    // default priority; non-blocking so that they never wait on the null stream
-    hipStream_t *const streams[] = {&ctx->long_stream, &ctx->side_stream[0], &ctx->side_stream[1],
-                                    &ctx->side_stream[2]};
-    for (hipStream_t *st : streams) {
-        if (hipStreamCreateWithFlags(st, hipStreamNonBlocking) != hipSuccess) {
-            pastis_destroy(ctx);
-            return PASTIS_E_DEVICE;
-        }
-    }
     for (int i = 0; i < 3; ++i) {
-        bool ok = hipEventCreateWithFlags(&ctx->fork_ev[i], hipEventDisableTiming) == hipSuccess;
+        bool ok = hipEventCreateWithFlags(&ctx->fork_ev[i], hipEventDisableTiming) == hipSuccess &&
+                  hipEventCreateWithFlags(&ctx->lead_ev[i], hipEventDisableTiming) == hipSuccess;
         for (auto &ev : ctx->join_ev[i]) ok = ok && hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess;
         if (!ok) {
             pastis_destroy(ctx);
@@ -642,13 +699,10 @@ void pastis_destroy(pastis_ctx *ctx) {
     for (auto &ev : ctx->ev)
         if (ev) (void)hipEventDestroy(ev);
     if (ctx->sw_exec) (void)hipGraphExecDestroy(ctx->sw_exec);
-    for (hipStream_t st : {ctx->long_stream, ctx->side_stream[0], ctx->side_stream[1], ctx->side_stream[2]}) {
-        if (!st) continue;
-        (void)hipStreamSynchronize(st);
-        (void)hipStreamDestroy(st);
-    }
+    fork_release(ctx);
     for (int i = 0; i < 3; ++i) {
         if (ctx->fork_ev[i]) (void)hipEventDestroy(ctx->fork_ev[i]);
+        if (ctx->lead_ev[i]) (void)hipEventDestroy(ctx->lead_ev[i]);
         for (auto &ev : ctx->join_ev[i])
             if (ev) (void)hipEventDestroy(ev);
     }

@@ -94,6 +94,10 @@ pastis_status read_device(pastis_ctx *ctx, const void *d, void *h, size_t bytes,
 }  // namespace pastis
 
 constexpr size_t kPinnedBytes = 4096;
+// Streams that the launches of a Smith-Waterman pass spread over: as many as the
+// runtime has hardware queues, so that streams made one after the other get one
+// each.
+constexpr int kLanes = 4;
 
 struct pastis_ctx {
     pastis_params params;
@@ -120,11 +124,11 @@ struct pastis_ctx {
     void *h_pinned = nullptr;  // kPinnedBytes for small read-backs (null: pageable memory)
     hipEvent_t ev[2 * 9] = {};
     double ms_per_tick = 0.0;  // device wall clock
-    // the SW groups of a pass run beside one another: the multi-strip (long)
-    // bins on the long stream, the others on the call's and the side streams;
-    // fork / join events of pass 1, start bound, statistics
-    hipStream_t long_stream = nullptr, side_stream[3] = {};
-    hipEvent_t fork_ev[3] = {}, join_ev[3][5] = {};
+    // the SW launches of a pass run beside one another on lanes (fork_acquire);
+    // fork / lead / join events of pass 1, start bound, statistics
+    hipStream_t lane[kLanes] = {};
+    int lanes_held = 0;  // 0: none yet, 1: the device's, 2: the context's own
+    hipEvent_t fork_ev[3] = {}, lead_ev[3] = {}, join_ev[3][kLanes] = {};
     // graph mode: the SW stage captured on a stream of the context
     hipStream_t graph_stream = nullptr;
     hipEvent_t graph_join[2] = {};
@@ -183,6 +187,14 @@ pastis_status set_error(pastis_ctx *ctx, pastis_status s, const std::string &msg
 pastis_status hip_error(pastis_ctx *ctx, hipError_t e, const char *what);
 // Make buffer `id` at least `bytes` long (contents not preserved on growth).
 pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out);
+// The context's lanes, at its first pass of several launches.  The contexts of a
+// device share one set, made for the first of them and destroyed with the last: a
+// set per context, beside the caller's streams, put long launches on one hardware
+// queue, one behind the other (the streams of a context made after others had
+// gone: a call of 41 ms took 50, a search of 340 ms 650).  A capture marks the
+// streams that it forks to, so contexts in graph mode have a set of their own.
+hipError_t fork_acquire(pastis_ctx *ctx);
+void fork_release(pastis_ctx *ctx);
 // hipMalloc for a context: where it fails, the buffers that only save time are given
 // back and it is tried again (no call holds them past its own synchronisation).
 hipError_t device_alloc(pastis_ctx *ctx, void **p, size_t bytes);

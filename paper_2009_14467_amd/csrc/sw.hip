@@ -1309,42 +1309,50 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     auto begin = [&](int st) { return timed ? stage_begin(ctx, st, s) : hipSuccess; };
     auto end = [&](int st) { return timed ? stage_end(ctx, st, s) : hipSuccess; };
     if (npairs <= 0) return hipSuccess;
-    // The groups of a pass run beside one another on streams of the context:
-    // the multi-strip group on the long stream, the others on the side streams
-    // and the call's, where the 16-bit kernel (own, called as group -1) goes
-    // too.  swap: those two change places, for the long pairs' blocks, which
-    // need most of a CU's LDS each and wait for the whole 16-bit launch if its
-    // blocks come first; the call's stream begins a few microseconds before the
-    // streams that wait for its event.  run(phase, own, swap, busy, f) calls
-    // f(group, stream) for every busy group and orders its work after the call's
-    // stream's and before what follows on it.
-    auto run = [&](int phase, bool own, bool swap, auto &&busy, auto &&f) -> hipError_t {
-        hipStream_t st[kGroups] = {ctx->side_stream[0], s, ctx->side_stream[1], ctx->side_stream[2],
-                                   swap ? s : ctx->long_stream};
-        int only = -1, n = own ? 1 : 0;
-        for (int g = 0; g < kGroups; ++g)
-            if (busy(g)) {
-                ++n;
-                only = g;
-            }
-        if (n == 0) return hipSuccess;
-        if (n == 1) return f(own ? -1 : only, s);  // alone: no fork
-        hipError_t e = hipEventRecord(ctx->fork_ev[phase], s);
-        if (e != hipSuccess) return e;
-        auto fork = [&](int g, hipStream_t stream, int join) -> hipError_t {
-            hipError_t x = hipStreamWaitEvent(stream, ctx->fork_ev[phase], 0);
-            if (x == hipSuccess) x = f(g, stream);
-            return x == hipSuccess ? hipEventRecord(ctx->join_ev[phase][join], stream) : x;
-        };
-        if (swap && busy(kMultiGroup) && (e = f(kMultiGroup, s)) != hipSuccess) return e;
+    // The launches of a pass run beside one another, each group of bins and the
+    // 16-bit kernel (own, called as group -1) on a lane; the call's stream, whose
+    // hardware queue may be that of any lane, only begins and ends them.  The
+    // multi-strip group and the 16-bit kernel have a lane to themselves.  lead: the
+    // multi-strip group begins first (the long pairs' blocks need most of a CU's
+    // LDS each, and wait for the whole 16-bit launch if its blocks come first): the
+    // other lanes wait for an event of its lane, a few microseconds after its launch.
+    // run(phase, own, lead, busy, f) calls f(group, stream) for every busy group
+    // and orders its work after the call's stream's and before what follows on it.
+    auto run = [&](int phase, bool own, bool lead, auto &&busy, auto &&f) -> hipError_t {
+        int job[kGroups + 1], n = 0;
         for (int g = kGroups - 1; g >= 0; --g)  // long pairs first
-            if (busy(g) && st[g] != s && (e = fork(g, st[g], g)) != hipSuccess) return e;
-        if (own && (e = swap ? fork(-1, ctx->long_stream, kMultiGroup) : f(-1, s)) != hipSuccess) return e;
-        for (int g = 0; g < kMultiGroup; ++g)
-            if (busy(g) && st[g] == s && (e = f(g, s)) != hipSuccess) return e;
-        for (int g = 0; g < kGroups; ++g)
-            if ((busy(g) && st[g] != s) || (g == kMultiGroup && swap && own))
-                if ((e = hipStreamWaitEvent(s, ctx->join_ev[phase][g], 0)) != hipSuccess) return e;
+            if (busy(g)) job[n++] = g;
+        if (own) job[n++] = -1;
+        if (n == 0) return hipSuccess;
+        if (n == 1) return f(job[0], s);  // alone: no fork
+        hipError_t e = fork_acquire(ctx);
+        if (e != hipSuccess || (e = hipEventRecord(ctx->fork_ev[phase], s)) != hipSuccess) return e;
+        const bool multi = busy(kMultiGroup);
+        lead = lead && multi;
+        const int first = (own ? 1 : 0) + (multi ? 1 : 0);  // the lanes of the one-strip groups
+        int next = first;
+        bool used[kLanes] = {};
+        // (a failed pass does not leave the lanes at work on the caller's inputs)
+        auto fail = [&](hipError_t x) {
+            for (int l = 0; l < kLanes; ++l)
+                if (used[l]) (void)hipStreamSynchronize(ctx->lane[l]);
+            return x;
+        };
+        for (int k = 0; k < n; ++k) {
+            const int l = job[k] == kMultiGroup ? 0 : job[k] < 0 ? first - 1 : next;
+            if (l == next) next = next + 1 < kLanes ? next + 1 : first;
+            hipStream_t st = ctx->lane[l];
+            if (!used[l] &&
+                (e = hipStreamWaitEvent(st, lead && l > 0 ? ctx->lead_ev[phase] : ctx->fork_ev[phase], 0)) != hipSuccess)
+                return fail(e);
+            used[l] = true;
+            if (lead && l == 0 && (e = hipEventRecord(ctx->lead_ev[phase], st)) != hipSuccess) return fail(e);
+            if ((e = f(job[k], st)) != hipSuccess) return fail(e);
+        }
+        for (int l = 0; l < kLanes; ++l)
+            if (used[l] && ((e = hipEventRecord(ctx->join_ev[phase][l], ctx->lane[l])) != hipSuccess ||
+                            (e = hipStreamWaitEvent(s, ctx->join_ev[phase][l], 0)) != hipSuccess))
+                return fail(e);
         return hipSuccess;
     };
     const int nb = (int)((npairs + 255) / 256);
@@ -1389,7 +1397,7 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         return e;
     }
     if ((e = end(kStSched)) != hipSuccess || (e = begin(kStAlign1)) != hipSuccess) return e;
-    // the 16-bit kernel runs beside the 32-bit groups, on the call's stream
+    // the 16-bit kernel runs beside the 32-bit groups
     e = run(0, plan.p16.blocks > 0, plan.long_blocks1 > 0, [&](int g) { return plan.blocks32[g] > 0; },
             [&](int g, hipStream_t st) -> hipError_t {
                 if (g < 0) {

@@ -686,3 +686,154 @@ def test_calls_in_32_bit_lanes_hold_no_rows_for_16_bits(gpu):
     rows = 24 * 20029 * 1536 * 5 // 4
     print(held, rows)
     assert held < rows + (100 << 20)
+
+
+def _best_ms(f, reps=4):
+    import time
+
+    import torch
+
+    best = 1e9
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * (time.perf_counter() - t0))
+    return best
+
+
+def test_long_pairs_run_beside_the_others_in_any_program(gpu):
+    """The launches of a pass overlap whatever streams the program has made and
+    destroyed: contexts that came after others had gone, beside others, and on
+    streams of the caller's own take the time of the first (a quarter more where
+    the long pairs and the 16-bit bins shared a hardware queue)."""
+    import torch
+
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(43)
+    seqs = []
+    for _ in range(8):
+        seqs += _related(rng, 12000 + int(rng.integers(0, 50)))
+    long = len(seqs)
+    for _ in range(40):
+        seqs += _related(rng, int(rng.integers(300, 500)))
+    s = _family_of(seqs)
+    lo = np.concatenate([np.tile(np.arange(0, long, 2), 4), np.tile(np.arange(long, len(seqs), 2), 3000)])
+    args = [_to_dev(x, gpu) for x in (s.residues, s.offsets, lo.astype(np.uint32), (lo + 1).astype(np.uint32))]
+
+    def context():
+        return P.Context(P.Params(full_records=True))
+
+    first = context()
+    alone = _best_ms(lambda: first.align_pairs(*args))
+    times = {}
+    others = [context() for _ in range(5)]
+    for k, c in enumerate(others):
+        times[f"beside {k + 1}"] = _best_ms(lambda: c.align_pairs(*args))
+    del others[1], others[2]
+    for k in range(3):
+        c = context()
+        times[f"after others {k}"] = _best_ms(lambda: c.align_pairs(*args))
+        others.append(c)
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    for k, q in enumerate(streams):
+        with torch.cuda.stream(q):
+            times[f"stream {k}"] = _best_ms(lambda: first.align_pairs(*args))
+    print(round(alone, 2), {k: round(v, 2) for k, v in times.items()})
+    assert max(times.values()) < 1.12 * alone, (alone, times)
+
+
+def test_contexts_are_made_without_streams(gpu):
+    """A context that never spreads a pass over several launches makes none of the
+    streams for it: it costs less than making and destroying four streams."""
+    import ctypes
+    import time
+
+    import torch
+
+    import paper_2009_14467_amd as P
+
+    hip = ctypes.CDLL("libamdhip64.so")
+    keep = P.Context(P.Params())  # the library's one-time work
+
+    def streams():
+        made = []
+        for _ in range(4):
+            q = ctypes.c_void_p()
+            assert hip.hipStreamCreateWithFlags(ctypes.byref(q), 1) == 0  # hipStreamNonBlocking
+            made.append(q)
+        for q in made:
+            assert hip.hipStreamDestroy(q) == 0
+
+    def context():
+        c = P.Context(P.Params())
+        del c
+
+    def median(f):
+        ts = []
+        for _ in range(40):
+            t0 = time.perf_counter()
+            f()
+            ts.append(1e6 * (time.perf_counter() - t0))
+        return sorted(ts)[20]
+
+    torch.cuda.synchronize()
+    a, b = median(context), median(streams)
+    print(f"context {a:.0f} us, four streams {b:.0f} us")
+    assert a < b
+    del keep
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_contexts_of_two_threads_share_the_lanes(gpu, graph):
+    """Two threads, a context and a stream each, with calls of several launches a
+    pass at the same time: every result is that of a call alone, also while one of
+    the contexts captures its passes as a graph."""
+    import threading
+
+    import torch
+
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(47)
+
+    def setting(k):
+        seqs = []
+        for _ in range(6):
+            seqs += _related(rng, 3000 + 700 * k + int(rng.integers(0, 50)))
+        for _ in range(60):
+            seqs += _related(rng, int(rng.integers(40, 1500)))
+        s = _family_of(seqs)
+        return _to_dev(s.residues, gpu), _to_dev(s.offsets, gpu)
+
+    sets = [setting(0), setting(1)]
+    args = [dict(k=6, ck_min=1, score_width=32), dict(k=6, ck_min=1, graph_mode=graph)]
+    want = [P.Context(P.Params(k=6, ck_min=1)).search(*x) for x in sets]
+    ctxs = [P.Context(P.Params(**a)) for a in args]
+    streams = [torch.cuda.Stream() for _ in sets]
+    torch.cuda.synchronize()
+    got = [[], []]
+    errors = []
+
+    def work(t):
+        try:
+            with torch.cuda.stream(streams[t]):
+                for rep in range(12):
+                    # (a set of the other thread's now and then: new pair counts, new captures)
+                    k = t if rep % 3 else 1 - t
+                    got[t].append((k, ctxs[t].search(*sets[k])))
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for t in range(2):
+        assert len(got[t]) == 12
+        for k, e in got[t]:
+            assert e.size > 0 and e.tobytes() == want[k].tobytes()
