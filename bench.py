@@ -213,18 +213,25 @@ def timed_steps(ctx, args, res, off):
 STAGE_NAMES = ["encode", "kmers", "subs_AS", "spgemm", "schedule", "sw_pass1", "sw_pass2", "edges", "mlp_filter"]
 
 
-def kernel_name(b):
+# pairs of several strips in 32-bit lanes up to which each has a block
+LONG_PAIRS = 2048
+
+
+def kernel_name(b, bins, intra):
     """The pass-1 kernel a length bin runs in: one launch for all 16-bit bins,
-    one per group of bins in 32-bit lanes."""
+    one per group of bins in 32-bit lanes (for pairs of several strips by their
+    number and the sw_intra_pair knob)."""
     if b["bits"] == 16:
         return "sw16_kernel<false, 3>"
     if b["multi_strip"]:
-        return "sw_pass1_kernel<9, 16, true>"
+        if sum(x["pairs"] for x in bins if x["multi_strip"] and x["bits"] == 32) <= LONG_PAIRS:
+            return "sw_long_kernel<false>"
+        return "sw_intra_pass1_kernel<9, 16>" if intra else "sw_pass1_kernel<9, 16, true>"
     lo = (b["rows_per_lane"] - 1) // 4 * 4 + 1
     return "sw_pass1_kernel<%d, %d, false>" % (lo, lo + 3)
 
 
-def roofline(st, pass1_ms):
+def roofline(st, pass1_ms, intra=0):
     """The dominant length bin of pass 1 (the one with the most DP work) against
     the integer VALU peak of its lane width: its cells x the method's 11 ops
     per cell over its span on the device's clock, from the first claim of its
@@ -241,7 +248,7 @@ def roofline(st, pass1_ms):
 
     # chosen by work, not by time: a bin's span includes time shared with others
     dom = max(st["sw_bins"], key=lambda b: b["cells"] / peak_of(b))
-    name = kernel_name(dom)
+    name = kernel_name(dom, st["sw_bins"], intra)
     peak = peak_of(dom)
     achieved = dom["cells"] * ALGO_OPS_PER_SW_CELL / (dom["ms"] * 1e-3) / 1e12
     kernel_ops = dom["cells"] * ops(dom) / (dom["ms"] * 1e-3) / 1e12
@@ -429,7 +436,7 @@ def mid_leg(P, args, dev):
         "cells": cells,
         "edges": int(edges.size),
         "stage_ms": dict(zip(STAGE_NAMES, stage)),
-        "roofline": roofline(st, stage[5]),
+        "roofline": roofline(st, stage[5], ctx.get_tuning()["sw_intra_pair"]),
         "spgemm": spgemm_line(st, stage[3], "mid" if args.families is None else None),
     }
     if not args.no_xd:
@@ -533,7 +540,7 @@ def main():
         "stage_ms": dict(zip(STAGE_NAMES, stage)),
         "align_gcups": cells / ((stage[5] + stage[6]) * 1e-3) / 1e9,
         "spgemm": spgemm_line(st, stage[3], args.workload if args.families is None else None),
-        "roofline": roofline(st, stage[5]),
+        "roofline": roofline(st, stage[5], ctx.get_tuning()["sw_intra_pair"]),
         "sw_bins": [dict(b, gcups=b["cells"] / max(b["ms"], 1e-9) / 1e6) for b in st["sw_bins"] if b["pairs"]],
         "schedule": tuning if tuning is not None else dict(ctx.get_tuning(), source="library default"),
     }
