@@ -444,8 +444,9 @@ typedef struct pastis_tuning {
                               (32-bit lanes), 1: pass 1 runs one workgroup of four waves
                               per pair, strips pipelined across the waves (intra-pair
                               mode); 0: one wave per pair (inter-pair mode).  Fewer such
-                              pairs run one workgroup of eight waves each either way
-                              (the call without allocations follows the knob) */
+                              pairs run one workgroup of eight waves each whatever its
+                              value (sw_extra_mib can forbid that), and the tuner leaves
+                              it alone */
     int32_t sw16_narrow_rows; /* pairs per wavefront of the 16-bit bins of at most 4 rows per
                                  lane: bins of at most this many rows per lane (0..4) run
                                  strips of 16 lanes, eight pairs per wave; the others

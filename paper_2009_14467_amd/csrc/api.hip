@@ -525,6 +525,7 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
             wk.long_scratch = (int *)slots;
             if (!slots) plan = plan_with(wk.dirs != nullptr, false);  // the multi-strip kernels
         }
+        ctx->intra_used = plan.intra_matters();
         if (P.graph_mode) {
             PASTIS_TRY(sw_graph(ctx, codes, (const PairDesc *)pairs, npairs, sc, (SwPass1Out *)p1, out, wk, stats_mode,
                                 plan, s));

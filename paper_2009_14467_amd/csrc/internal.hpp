@@ -127,6 +127,7 @@ struct pastis_ctx {
     // the SW launches of a pass run beside one another on lanes (fork_acquire);
     // fork / lead / join events of pass 1, start bound, statistics
     hipStream_t lane[kLanes] = {};
+    bool intra_used = false;  // the last pass 1 ran the kernels that sw_intra_pair chooses from
     int lanes_held = 0;  // 0: none yet, 1: the device's, 2: the context's own
     hipEvent_t fork_ev[3] = {}, lead_ev[3] = {}, join_ev[3][kLanes] = {};
     // graph mode: the SW stage captured on a stream of the context
@@ -307,6 +308,8 @@ struct SwPlan {
     // the multi-strip kernels), and the scratch words of a block
     int long_blocks1 = 0, long_blocks2 = 0;
     int64_t long_slot = 0;
+    // pass 1 has multi-strip pairs in 32-bit lanes, and not a block for each
+    bool intra_matters() const { return blocks32[4] > 0 && long_blocks1 == 0; }
     int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
 };
 static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 4) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");

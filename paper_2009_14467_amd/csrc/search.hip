@@ -956,10 +956,12 @@ pastis_status pastis_autotune(pastis_ctx *ctx, const uint8_t *residues, const in
         // force is timed again first, so each knob's values are compared
         // under the same conditions (clocks, caches) rather than against a
         // figure taken several sweeps earlier.
-        auto sweep = [&](int32_t *knob, const int *vals, int nv) -> pastis_status {
+        // (a knob that the last alignment made no use of keeps its value)
+        auto sweep = [&](int32_t *knob, const int *vals, int nv, const bool *used = nullptr) -> pastis_status {
             const int32_t keep = *knob;
             int32_t best_v = keep;
             PASTIS_TRY(measure(&cur));
+            if (used && !*used) return PASTIS_OK;
             double best_ms = cur;
             for (int i = 0; i < nv; ++i) {
                 if (vals[i] == keep) continue;
@@ -980,7 +982,7 @@ pastis_status pastis_autotune(pastis_ctx *ctx, const uint8_t *residues, const in
         PASTIS_TRY(sweep(&ctx->tune.sw_grid_scale, grid, 3));
         PASTIS_TRY(sweep(&ctx->tune.sw_grid_scale_wide, grid, 3));
         const int intra[] = {0, 1};
-        PASTIS_TRY(sweep(&ctx->tune.sw_intra_pair, intra, 2));
+        PASTIS_TRY(sweep(&ctx->tune.sw_intra_pair, intra, 2, &ctx->intra_used));
         const int narrow[] = {4, 2, 0};
         PASTIS_TRY(sweep(&ctx->tune.sw16_narrow_rows, narrow, 3));
         const int longb[] = {4, 2, 1};
@@ -1038,7 +1040,7 @@ pastis_status pastis_autotune(pastis_ctx *ctx, const uint8_t *residues, const in
             };
             const int route[] = {25, 50, 75, 100};
             PASTIS_TRY(refine(&ctx->tune.sw_direct_pct, route, 4));
-            PASTIS_TRY(refine(&ctx->tune.sw_intra_pair, intra, 2));
+            if (ctx->intra_used) PASTIS_TRY(refine(&ctx->tune.sw_intra_pair, intra, 2));
             PASTIS_TRY(refine(&ctx->tune.sw_long_blocks, longb, 3));
             // the grids of the one-strip bins, whose ends also shorten with
             // the sample (about 1% of large's step between their values)

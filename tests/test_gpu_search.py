@@ -253,3 +253,18 @@ def test_buffers_that_only_save_time_make_room(gpu):
     finally:
         del full
         torch.cuda.empty_cache()
+
+
+def test_autotune_leaves_a_knob_without_effect(gpu):
+    """A set with few or no long pairs runs the same kernels for both values of
+    sw_intra_pair: the tuner keeps the value it finds, whichever runs faster that
+    time."""
+    import paper_2009_14467_amd as P
+    from synth import workload
+
+    s = workload("tiny")
+    res, off = _dev(s.residues, gpu), _dev(s.offsets, gpu)
+    ctx = P.Context(P.Params(k=6, ck_min=1))
+    for rep in range(12):
+        ctx.set_tuning(sw_intra_pair=rep % 2)
+        assert ctx.autotune(res, off, max_pairs=500)["sw_intra_pair"] == rep % 2, rep
