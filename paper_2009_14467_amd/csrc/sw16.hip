@@ -734,6 +734,7 @@ __device__ __forceinline__ bool wave16_body(const SwArgs &A, int bin, char *lds,
 // rotated by one lane per step.
 constexpr int kDppRowShr1 = 0x111;
 constexpr int kDppRowRor15 = 0x12F;
+constexpr int kDppRowRor8 = 0x128, kDppRowRor4 = 0x124, kDppRowRor2 = 0x122, kDppRowRor1 = 0x121;
 
 // lane p of a strip receives lane p - 1's value; the strip's first lane
 // receives `first`
@@ -1133,7 +1134,6 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void sw16_bound_kernel(SwArgs 
         // the row below the end row: H = 0 left of every window column (an
         // alignment ends in a diagonal step), else dead
         uint32_t gprev = pos == 0 ? G0 : kDead, glast = kDead, flast = kDead, out = kDead;
-        uint32_t ended = 0u;  // the halves whose pair has ended
         uint32_t cres = (kPadCode * 4u) * 0x10001u, chunk = col(pos), nx = col(16 + pos);
         for (int t = 0; t < steps; ++t) {
             if ((t & 15) == 0 && t > 0) {
@@ -1147,18 +1147,21 @@ __global__ __launch_bounds__(64 * kBoundWaves, 4) void sw16_bound_kernel(SwArgs 
                         g = u2(pmax(s2(g), s2(G[r])));
                         e = u2(pmax(s2(e), s2(E[r])));
                     }
-                    const uint32_t m = u2(pmax(adds(s2(g), s2(OE2)), s2(e)));
+                    // (over the strip, whose lanes are a row of the wave's)
+                    uint32_t m = u2(pmax(adds(s2(g), s2(OE2)), s2(e)));
+                    m = u2(pmax(s2(m), s2((uint32_t)__builtin_amdgcn_mov_dpp((int)m, kDppRowRor8, 0xF, 0xF, false))));
+                    m = u2(pmax(s2(m), s2((uint32_t)__builtin_amdgcn_mov_dpp((int)m, kDppRowRor4, 0xF, 0xF, false))));
+                    m = u2(pmax(s2(m), s2((uint32_t)__builtin_amdgcn_mov_dpp((int)m, kDppRowRor2, 0xF, 0xF, false))));
+                    m = u2(pmax(s2(m), s2((uint32_t)__builtin_amdgcn_mov_dpp((int)m, kDppRowRor1, 0xF, 0xF, false))));
                     const uint32_t o = (uint32_t)__shfl((int)out, strip * S + S - 1, kWave);  // G in the top row
                     const bool overP = end_a[0] >= kBoundRows && (int)(int16_t)(o & 0xFFFFu) + go_ge > 0;
                     const bool overQ = end_a[1] >= kBoundRows && ((int)o >> 16) + go_ge > 0;
-                    const unsigned long long strip_lanes = 0xFFFFull << (S * strip);
-                    const bool onP = (__ballot((int)(int16_t)(m & 0xFFFFu) > 0) & strip_lanes) && !overP && t < hi[0] + S;
-                    const bool onQ = (__ballot(((int)m >> 16) > 0) & strip_lanes) && !overQ && t < hi[1] + S;
+                    const bool onP = (int)(int16_t)(m & 0xFFFFu) > 0 && !overP && t - S < hi[0];
+                    const bool onQ = ((int)m >> 16) > 0 && !overQ && t - S < hi[1];
                     const uint32_t settled = (onP ? 0u : 0xFFFFu) | (onQ ? 0u : 0xFFFF0000u);
                     if (__ballot(settled != ~0u) == 0ull) break;
-                    if (__ballot((settled & ~ended) != 0u)) {
-                        ended |= settled;
-                        auto kill = [&](uint32_t x) { return (kDead & ended) | (x & ~ended); };
+                    if (__ballot(settled != 0u)) {
+                        auto kill = [&](uint32_t x) { return (kDead & settled) | (x & ~settled); };
                         gprev = kill(gprev), glast = kill(glast), flast = kill(flast);
 #pragma unroll
                         for (int r = 0; r < RP; ++r) G[r] = kill(G[r]), E[r] = kill(E[r]);
