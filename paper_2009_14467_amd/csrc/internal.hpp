@@ -94,10 +94,10 @@ pastis_status read_device(pastis_ctx *ctx, const void *d, void *h, size_t bytes,
 }  // namespace pastis
 
 constexpr size_t kPinnedBytes = 4096;
-// Streams that the launches of a Smith-Waterman pass spread over: as many as the
-// runtime has hardware queues, so that streams made one after the other get one
-// each.
-constexpr int kLanes = 4;
+// Streams that the launches of a Smith-Waterman pass spread over, beside the call's:
+// with it, as many as the runtime has hardware queues, so that streams made one
+// after the other get one each.
+constexpr int kLanes = 3;
 
 struct pastis_ctx {
     pastis_params params;

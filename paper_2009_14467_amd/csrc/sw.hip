@@ -1309,13 +1309,16 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     auto begin = [&](int st) { return timed ? stage_begin(ctx, st, s) : hipSuccess; };
     auto end = [&](int st) { return timed ? stage_end(ctx, st, s) : hipSuccess; };
     if (npairs <= 0) return hipSuccess;
-    // The launches of a pass run beside one another, each group of bins and the
-    // 16-bit kernel (own, called as group -1) on a lane; the call's stream, whose
-    // hardware queue may be that of any lane, only begins and ends them.  The
-    // multi-strip group and the 16-bit kernel have a lane to themselves.  lead: the
-    // multi-strip group begins first (the long pairs' blocks need most of a CU's
-    // LDS each, and wait for the whole 16-bit launch if its blocks come first): the
-    // other lanes wait for an event of its lane, a few microseconds after its launch.
+    // The launches of a pass run beside one another: the multi-strip group on lane
+    // 0, the 16-bit kernel (own, called as group -1) on lane 1, both off the call's
+    // stream, whose hardware queue may be that of any lane; the one-strip groups on
+    // lane 2, the call's stream and (1-8 rows per lane) where room is.  Those come
+    // before the 16-bit kernel on its lane: its resident grid leaves later launches
+    // no room (statistics of 250,000 sequences: the groups of 1-8 rows, 3 ms of
+    // work, lasted as long as the traceback beside them, and both 150 ms; 137 with
+    // the groups first).  lead: the multi-strip group begins first (the long pairs'
+    // blocks need most of a CU's LDS each): the others wait for an event of its
+    // lane, a few microseconds after its launch.
     // run(phase, own, lead, busy, f) calls f(group, stream) for every busy group
     // and orders its work after the call's stream's and before what follows on it.
     auto run = [&](int phase, bool own, bool lead, auto &&busy, auto &&f) -> hipError_t {
@@ -1329,9 +1332,9 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         if (e != hipSuccess || (e = hipEventRecord(ctx->fork_ev[phase], s)) != hipSuccess) return e;
         const bool multi = busy(kMultiGroup);
         lead = lead && multi;
-        const int first = (own ? 1 : 0) + (multi ? 1 : 0);  // the lanes of the one-strip groups
-        int next = first;
-        bool used[kLanes] = {};
+        constexpr int kCall = kLanes;  // the call's stream
+        const int lane_of[kGroups + 1] = {1, 1, multi ? 1 : 0, kCall, 2, 0};  // [group + 1]
+        bool used[kLanes + 1] = {};
         // (a failed pass does not leave the lanes at work on the caller's inputs)
         auto fail = [&](hipError_t x) {
             for (int l = 0; l < kLanes; ++l)
@@ -1339,11 +1342,11 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
             return x;
         };
         for (int k = 0; k < n; ++k) {
-            const int l = job[k] == kMultiGroup ? 0 : job[k] < 0 ? first - 1 : next;
-            if (l == next) next = next + 1 < kLanes ? next + 1 : first;
-            hipStream_t st = ctx->lane[l];
-            if (!used[l] &&
-                (e = hipStreamWaitEvent(st, lead && l > 0 ? ctx->lead_ev[phase] : ctx->fork_ev[phase], 0)) != hipSuccess)
+            const int l = lane_of[job[k] + 1];
+            hipStream_t st = l == kCall ? s : ctx->lane[l];
+            const bool behind = lead && l > 0;
+            if (!used[l] && (behind || l != kCall) &&
+                (e = hipStreamWaitEvent(st, behind ? ctx->lead_ev[phase] : ctx->fork_ev[phase], 0)) != hipSuccess)
                 return fail(e);
             used[l] = true;
             if (lead && l == 0 && (e = hipEventRecord(ctx->lead_ev[phase], st)) != hipSuccess) return fail(e);
