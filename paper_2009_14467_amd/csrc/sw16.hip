@@ -1284,35 +1284,37 @@ __global__ __launch_bounds__(64 * kBlockWaves, WAVES) void sw16_kernel(SwArgs A,
     auto one = [&](auto r_tag) { full(r_tag, std::false_type{}, decltype(r_tag)::value - 1); };
     if (blockIdx.x < (unsigned)P.multi_blocks) descending<kMaxR>(multi, std::make_integer_sequence<int, kMaxR - kMultiMinR + 1>{});
     descending<kMaxR>(one, std::make_integer_sequence<int, kMaxR - kSplitBins>{});
-    if (P.wide) {
+    if (WAVES == 2 || P.wide) {  // (the kernel for two waves per SIMD runs calls of few pairs only)
         descending<kSplitBins>(one, std::make_integer_sequence<int, kSplitBins>{});
         return;
     }
-    auto cls = [&](auto s_tag, auto rp_tag, int c) {
-        if (A.bounds[c] >= A.bounds[c + 1]) return;
-        const unsigned long long t0 = span_now();
-        if (strip16_body<decltype(s_tag)::value, decltype(rp_tag)::value, TRACE>(A, c, lds, kBlockLds / kBlockWaves,
-                                                                                 sblosum) &&
-            !TRACE)
-            span_add(A.span + (c & ~1), t0);
-    };
-    auto strips = [&](auto r_tag) {
-        constexpr int R = decltype(r_tag)::value;
-        constexpr int bin = R - 1;
-        if (!((P.bins >> bin) & 1u)) return;
-        std::integral_constant<int, 16> s16;
-        std::integral_constant<int, 32> s32;
-        if constexpr (R <= 4) {
-            if (R <= P.narrow) {
-                cls(s16, std::integral_constant<int, 4 * R>{}, 2 * bin + 1);
-                cls(s16, std::integral_constant<int, 4 * R - 2>{}, 2 * bin);
-                return;
+    if constexpr (WAVES > 2) {
+        auto cls = [&](auto s_tag, auto rp_tag, int c) {
+            if (A.bounds[c] >= A.bounds[c + 1]) return;
+            const unsigned long long t0 = span_now();
+            if (strip16_body<decltype(s_tag)::value, decltype(rp_tag)::value, TRACE>(A, c, lds, kBlockLds / kBlockWaves,
+                                                                                     sblosum) &&
+                !TRACE)
+                span_add(A.span + (c & ~1), t0);
+        };
+        auto strips = [&](auto r_tag) {
+            constexpr int R = decltype(r_tag)::value;
+            constexpr int bin = R - 1;
+            if (!((P.bins >> bin) & 1u)) return;
+            std::integral_constant<int, 16> s16;
+            std::integral_constant<int, 32> s32;
+            if constexpr (R <= 4 && !TRACE) {  // (the traceback's launches have narrow = 0)
+                if (R <= P.narrow) {
+                    cls(s16, std::integral_constant<int, 4 * R>{}, 2 * bin + 1);
+                    cls(s16, std::integral_constant<int, 4 * R - 2>{}, 2 * bin);
+                    return;
+                }
             }
-        }
-        cls(s32, std::integral_constant<int, 2 * R>{}, 2 * bin + 1);
-        cls(s32, std::integral_constant<int, 2 * R - 1>{}, 2 * bin);
-    };
-    descending<kSplitBins>(strips, std::make_integer_sequence<int, kSplitBins>{});
+            cls(s32, std::integral_constant<int, 2 * R>{}, 2 * bin + 1);
+            cls(s32, std::integral_constant<int, 2 * R - 1>{}, 2 * bin);
+        };
+        descending<kSplitBins>(strips, std::make_integer_sequence<int, kSplitBins>{});
+    }
 }
 
 }  // namespace
