@@ -54,7 +54,7 @@ pastis_status ensure(pastis_ctx *ctx, int id, size_t bytes, void **out) {
         const size_t off = (ctx->arena_used + 255) & ~(size_t)255;
         if (off + bytes > ctx->arena_cap)
             return set_error(ctx, PASTIS_E_CAPACITY,
-                             "the call needs more than the " + std::to_string(ctx->arena_cap) +
+                             "the call needs more than the " + std::to_string(PASTIS_NOALLOC_BYTES) +
                                  " bytes of the no-allocation workspace");
         ctx->arena_off[id] = off;
         ctx->arena_len[id] = bytes;
@@ -137,8 +137,10 @@ namespace {
 // carved from it.  Each GPU holds its own copy until the process ends; all
 // calls on one GPU share it.  Host code reaches it only through the address
 // hipGetSymbolAddress gives for the current device (the array's name is a
-// host-side stand-in there).
-static __device__ __align__(256) unsigned char scratch[PASTIS_NOALLOC_BYTES];
+// host-side stand-in there).  A page more than the calls' data may take holds their
+// counters and tables, so that these can grow and calls that fit still do.
+constexpr size_t kScratchBytes = (size_t)PASTIS_NOALLOC_BYTES + 4096;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 char *g_scratch_ptr[kMaxDevices] = {};
@@ -819,7 +821,7 @@ pastis_status pastis_align_pairs_noalloc(pastis_ctx *ctx, const uint8_t *residue
     } guard{ctx, ctx->params.graph_mode};
     ctx->params.graph_mode = 0;
     ctx->arena = ctx->noalloc_ws;
-    ctx->arena_cap = PASTIS_NOALLOC_BYTES;
+    ctx->arena_cap = kScratchBytes;
     ctx->arena_used = 0;
     memset(ctx->arena_len, 0, sizeof(ctx->arena_len));
     return align_pairs_impl(ctx, residues, offsets, n, 1, pi, pj, seed1, seed2, npairs, out, stream);
