@@ -837,3 +837,56 @@ def test_contexts_of_two_threads_share_the_lanes(gpu, graph):
         assert len(got[t]) == 12
         for k, e in got[t]:
             assert e.size > 0 and e.tobytes() == want[k].tobytes()
+
+
+@pytest.mark.parametrize("total", [2048, 2049])
+@pytest.mark.parametrize("intra", [0, 1])
+def test_long_pairs_at_the_block_limit(gpu, orc, total, intra):
+    """Pairs of several strips in 32-bit lanes at the number up to which each has a
+    block: beyond it, pass 1 runs one wave a pair or (sw_intra_pair) a workgroup of
+    four waves, whose strips are pipelined; 2 to 9 strips, pairs that share
+    sequences, unrelated pairs, rows at both sides of a strip and of a round of the
+    workgroup's waves."""
+    rng = np.random.default_rng(53)
+    seqs = []
+    for L in (1025, 1100, 2047, 2500, 2979, 3100, 4096, 4097, 5000, 9000):
+        seqs += _related(rng, L, post=int(rng.integers(0, 60)))
+    s = _family_of(seqs)
+    lo = np.arange(0, len(seqs), 2, dtype=np.uint32)
+    lo, hi = np.concatenate([lo, [4, 6, 8, 10]]).astype(np.uint32), np.concatenate([lo + 1, [9, 11, 15, 13]])
+    hi = hi.astype(np.uint32)
+    want = orc.align_pairs(orc.encode(s.residues), s.offsets, lo, hi, mode="sw")
+    at = np.arange(total) % lo.size
+    for full in (True, False):
+        got = _gpu_records(gpu, s, lo[at], hi[at], tuning=dict(sw_intra_pair=intra), full_records=full, score_width=32)
+        _compare(got, want[at], FIELDS if full else ("score", "end_a", "end_b", "passed", "swapped", "cells"))
+
+
+@pytest.mark.parametrize("total", [4096, 4097, 8192, 8193])
+@pytest.mark.parametrize("narrow", [0, 4])
+def test_sw16_calls_at_the_sizes_of_its_layouts(gpu, orc, total, narrow):
+    """16-bit calls at both sides of the numbers of pairs that choose the layout:
+    traceback kernels for two waves per SIMD up to 4,096, bins of up to 8 rows per
+    lane across all 64 lanes up to 8,192, in strips of 16 (narrow 4) and 32 lanes
+    beyond; both rows classes of every bin, windows of one to five pairs of a
+    sequence, several strips, and columns past the direction buffers' limit."""
+    rng = np.random.default_rng(59)
+    lens = [1, 2, 31, 33, 63, 64, 65, 1023, 1024, 1025, 1100, 1537, 2049, 2978]
+    lens += [64 * R - 32 + d for R in range(1, 17) for d in (0, 1, 32)]
+    seqs = []
+    for L in lens:
+        seqs += _related(rng, L, rate=0.25, pre=int(rng.integers(0, 40)), post=5)
+    single = len(seqs)
+    seqs += [rng.integers(0, 20, 300), rng.integers(0, 20, 2049), rng.integers(0, 20, 1100), rng.integers(0, 20, 4097)]
+    s = _family_of(seqs)
+    lo = np.arange(0, single, 2, dtype=np.uint32)
+    hi = lo + 1
+    # more pairs of some sequences: windows of several
+    few = np.repeat(np.arange(14, 44, 2), np.arange(15) % 5)
+    lo = np.concatenate([lo, few, [single, single + 2]]).astype(np.uint32)
+    hi = np.concatenate([hi, few + 3 + 2 * (np.arange(few.size) % 7), [single + 1, single + 3]]).astype(np.uint32)
+    want = orc.align_pairs(orc.encode(s.residues), s.offsets, lo, hi, mode="sw")
+    at = np.arange(total) % lo.size
+    tuning = dict(sw16_narrow_rows=narrow)
+    _compare(_gpu_records(gpu, s, lo[at], hi[at], tuning=tuning, full_records=True), want[at])
+    _check16(_gpu_records(gpu, s, lo[at], hi[at], tuning=tuning, score_width=16), want[at])
