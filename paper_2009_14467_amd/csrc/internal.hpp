@@ -304,15 +304,17 @@ struct SwPlan {
     // traceback's direction words: per wave of the grid, per wave of its
     // multi-strip blocks, and in all
     int stats_after_trace = 0, forward_bound = 0;
-    // long pairs, one block each: the blocks of pass 1 and of the statistics (0:
-    // the multi-strip kernels), and the scratch words of a block
+    // long pairs, one block each: the blocks and the bins of pass 1 and of the
+    // statistics (the multi-strip kernels take the other bins), and the scratch
+    // words of a block
     int long_blocks1 = 0, long_blocks2 = 0;
+    uint32_t long_bins1 = 0, long_bins2 = 0;
     int64_t long_slot = 0;
-    // pass 1 has multi-strip pairs in 32-bit lanes, and not a block for each
-    bool intra_matters() const { return blocks32[4] > 0 && long_blocks1 == 0; }
+    // pass 1 has multi-strip pairs in 32-bit lanes beside those with a block each
+    bool intra_matters() const { return blocks32[4] > 0; }
     int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
 };
-static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 4) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
+static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 6) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
 // max16 > 0: pass 1 of one-strip pairs with at most max16 rows per lane in
 // 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
 // that skip the statistics pass.  tune: the grid scales of the one-strip

@@ -1111,6 +1111,9 @@ __global__ __launch_bounds__(64 * wpb32(HI), stats_waves(HI)) void sw_pass2_kern
 // The groups: one-strip bins of 1-4, 5-8, 9-12 and 13-16 rows per lane, and
 // the multi-strip bins (all of a group's kernels take the same mask of bins).
 constexpr int kGroups = 5, kMultiGroup = 4;
+constexpr int kLongGroup = 5;                 // the pairs of the multi-strip bins that take a block each
+constexpr uint32_t kOverBins = 0x00FF0000u;  // multi-strip bins of over kMax16Rows rows
+static_assert(kOverBins == (1u << kMulti16Bin) - (1u << kMultiBin), "bins of the tallest sequences");
 constexpr uint32_t kGroupBins[kGroups] = {0x000Fu, 0x00F0u, 0x0F00u, 0xF000u, 0xFFFF0000u};
 
 typedef void (*SwKernel)(SwArgs, uint32_t);
@@ -1142,7 +1145,8 @@ constexpr int64_t kWidePairs = 8192;
 
 // Pairs of the 32-bit multi-strip bins, and pairs that may need the multi-strip
 // statistics, up to this many take one block of eight waves each (sw_long.hip);
-// beyond, the waves that work strip after strip keep the chip as busy.  1,225
+// beyond, the waves that work strip after strip keep the chip as busy.  Where only
+// those of at most kMax16Rows rows are too many, the others still take blocks.  1,225
 // pairs of 3,000 to 25,000 rows took 245 ms in pass 1 and 443 with statistics by
 // single waves, 149 and 118 so.  A block's scratch grows with the longest
 // sequence (20 MB for 25,000 residues); blocks are dropped beyond kLongBytes.
@@ -1256,24 +1260,34 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, i
         const int per_cu = g == kMultiGroup ? 3 : std::max(1, stats_blocks_per_cu[g].load(std::memory_order_acquire));
         p.blocks_stats[g] = later ? fit(g, 256 * per_cu, later) : 0;
     }
-    // pairs of the multi-strip bins: those of pass 1 in 32-bit lanes, and those
-    // that may come to the multi-strip statistics
-    int64_t long32 = 0, long_stats = 0;
+    // pairs of the multi-strip bins of over kMax16Rows rows, and of fewer: those of
+    // pass 1 in 32-bit lanes, and those that may come to the multi-strip statistics
+    int64_t over = 0, low1 = 0, low2 = n16 > 0 && trace ? long_b : 0;
     for (int b = kMultiBin; b < kNumBins; ++b) {
         const bool is16 = sw_bin_is16(b, max16);
-        long32 += is16 ? 0 : (int64_t)bin_pairs[b];
-        long_stats += is16 && trace ? 0 : (int64_t)bin_pairs[b];
+        if (b < kMulti16Bin) over += (int64_t)bin_pairs[b];
+        if (b >= kMulti16Bin && !is16) low1 += (int64_t)bin_pairs[b];
+        if (b >= kMulti16Bin && !(is16 && trace)) low2 += (int64_t)bin_pairs[b];
     }
-    if (n16 > 0 && trace) long_stats += long_b;
     if (slots) {
-        p.long_slot = sw_long_slot_words(max_len);
-        const int64_t fit = std::max<int64_t>(8, (int64_t)kLongBytes / (int64_t)(p.long_slot * sizeof(int)));
-        auto blocks = [&](int64_t pairs) {
-            return pairs > kLongPairs ? 0 : (int)std::min<int64_t>({kLongBlocks, fit, pairs});
+        const int64_t slot = sw_long_slot_words(max_len);
+        const int64_t room = std::max<int64_t>(8, (int64_t)kLongBytes / (int64_t)(slot * sizeof(int)));
+        auto take = [&](int64_t low, uint32_t &bins, int &blocks) {
+            bins = over + low <= kLongPairs ? kGroupBins[kMultiGroup] : over <= kLongPairs ? kOverBins : 0u;
+            const int64_t pairs = bins == 0 ? 0 : bins == kOverBins ? over : over + low;
+            blocks = (int)std::min<int64_t>({kLongBlocks, room, pairs});
+            if (blocks == 0) bins = 0;
         };
-        p.long_blocks1 = blocks(long32);
-        p.long_blocks2 = blocks(long_stats);
-        if (p.long_blocks1 == 0 && p.long_blocks2 == 0) p.long_slot = 0;
+        take(low1, p.long_bins1, p.long_blocks1);
+        take(low2, p.long_bins2, p.long_blocks2);
+        if (p.long_blocks1 > 0 || p.long_blocks2 > 0) p.long_slot = slot;
+        p.long_bins1 &= p.bins32[kMultiGroup];
+        p.bins32[kMultiGroup] &= ~p.long_bins1;
+        if (p.bins32[kMultiGroup] == 0)
+            p.blocks32[kMultiGroup] = 0;
+        else if (p.long_bins1 != 0)
+            p.blocks32[kMultiGroup] = fit(kMultiGroup, kGroupBlocks[kMultiGroup], low1);
+        if (p.long_bins2 == kGroupBins[kMultiGroup]) p.blocks_stats[kMultiGroup] = 0;
     }
     if (n16 == 0) return p;
     Sw16Launch &k = p.p16;
@@ -1309,31 +1323,31 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     auto begin = [&](int st) { return timed ? stage_begin(ctx, st, s) : hipSuccess; };
     auto end = [&](int st) { return timed ? stage_end(ctx, st, s) : hipSuccess; };
     if (npairs <= 0) return hipSuccess;
-    // The launches of a pass run beside one another: the multi-strip group on lane
-    // 0, the 16-bit kernel (own, called as group -1) on lane 1, both off the call's
-    // stream, whose hardware queue may be that of any lane; the one-strip groups on
-    // lane 2, the call's stream and (1-8 rows per lane) where room is.  Those come
-    // before the 16-bit kernel on its lane: its resident grid leaves later launches
-    // no room (statistics of 250,000 sequences: the groups of 1-8 rows, 3 ms of
-    // work, lasted as long as the traceback beside them, and both 150 ms; 137 with
-    // the groups first).  lead: the multi-strip group begins first (the long pairs'
-    // blocks need most of a CU's LDS each): the others wait for an event of its
-    // lane, a few microseconds after its launch.
-    // run(phase, own, lead, busy, f) calls f(group, stream) for every busy group
-    // and orders its work after the call's stream's and before what follows on it.
-    auto run = [&](int phase, bool own, bool lead, auto &&busy, auto &&f) -> hipError_t {
-        int job[kGroups + 1], n = 0;
-        for (int g = kGroups - 1; g >= 0; --g)  // long pairs first
+    // The launches of a pass run beside one another: the multi-strip pairs on lane
+    // 0 (those of single waves on lane 2 where others take blocks), the 16-bit kernel
+    // (own, called as group -1) on lane 1, both off the call's stream, whose hardware
+    // queue may be that of any lane; the one-strip groups on lane 2, the call's stream
+    // and (1-8 rows per lane) where room is.  Those come before the 16-bit kernel on
+    // its lane: its resident grid leaves later launches no room (statistics of
+    // 250,000 sequences: the groups of 1-8 rows, 3 ms of work, lasted as long as the
+    // traceback beside them, and both 150 ms; 137 with the groups first).  The long
+    // pairs' blocks (kLongGroup) begin before all, as they need most of a CU's LDS
+    // each: the others wait for an event of their lane, a few microseconds after
+    // their launch.
+    // run(phase, own, busy, f) calls f(group, stream) for every busy group and
+    // orders its work after the call's stream's and before what follows on it.
+    auto run = [&](int phase, bool own, auto &&busy, auto &&f) -> hipError_t {
+        int job[kLongGroup + 2], n = 0;
+        for (int g = kLongGroup; g >= 0; --g)  // long pairs first
             if (busy(g)) job[n++] = g;
         if (own) job[n++] = -1;
         if (n == 0) return hipSuccess;
         if (n == 1) return f(job[0], s);  // alone: no fork
         hipError_t e = fork_acquire(ctx);
         if (e != hipSuccess || (e = hipEventRecord(ctx->fork_ev[phase], s)) != hipSuccess) return e;
-        const bool multi = busy(kMultiGroup);
-        lead = lead && multi;
+        const bool lead = busy(kLongGroup), multi = lead || busy(kMultiGroup);
         constexpr int kCall = kLanes;  // the call's stream
-        const int lane_of[kGroups + 1] = {1, 1, multi ? 1 : 0, kCall, 2, 0};  // [group + 1]
+        const int lane_of[kLongGroup + 2] = {1, 1, multi ? 1 : 0, kCall, 2, lead ? 2 : 0, 0};  // [group + 1]
         bool used[kLanes + 1] = {};
         // (a failed pass does not leave the lanes at work on the caller's inputs)
         auto fail = [&](hipError_t x) {
@@ -1401,7 +1415,8 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     }
     if ((e = end(kStSched)) != hipSuccess || (e = begin(kStAlign1)) != hipSuccess) return e;
     // the 16-bit kernel runs beside the 32-bit groups
-    e = run(0, plan.p16.blocks > 0, plan.long_blocks1 > 0, [&](int g) { return plan.blocks32[g] > 0; },
+    e = run(0, plan.p16.blocks > 0,
+            [&](int g) { return g == kLongGroup ? plan.long_blocks1 > 0 : plan.blocks32[g] > 0; },
             [&](int g, hipStream_t st) -> hipError_t {
                 if (g < 0) {
                     SwArgs B = A;
@@ -1411,11 +1426,11 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
                     return launch_sw16(false, plan.p16, B, st);
                 }
                 A.queue = wk.queue + 2 * kNumBins;
-                if (g == kMultiGroup && plan.long_blocks1 > 0) {
+                if (g == kLongGroup) {
                     SwArgs B = A;
                     B.scratch = wk.long_scratch;
                     B.scratch_per_wave = plan.long_slot;
-                    return launch_sw_long(false, plan.long_blocks1, plan.bins32[g], B, st);
+                    return launch_sw_long(false, plan.long_blocks1, plan.long_bins1, B, st);
                 }
                 if (g == kMultiGroup && plan.intra)
                     sw_intra_pass1_kernel<9, 16><<<kIntraBlocks, 64 * kIntraWaves, 0, st>>>(A, plan.bins32[g]);
@@ -1447,7 +1462,7 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         if ((e = launch_bins(wk.bin_of, npairs, kNumBins, wk.counts, wk.starts2, wk.cursor, wk.idx2, s)) !=
             hipSuccess)
             return e;
-        e = run(1, false, false, [&](int g) { return plan.blocks_bound[g] > 0; },
+        e = run(1, false, [&](int g) { return g < kGroups && plan.blocks_bound[g] > 0; },
                 [&](int g, hipStream_t st) {
                     kBound[g]<<<plan.blocks_bound[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
                     return hipGetLastError();
@@ -1486,16 +1501,19 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         B.dirs_multi = wk.dirs + sw16_waves() * plan.t16.blocks * plan.dirs_per_wave;
     }
     A.queue = wk.queue + 4 * kNumBins;
-    e = run(2, trace, stats && plan.long_blocks2 > 0, [&](int g) { return stats && plan.blocks_stats[g] > 0; },
+    e = run(2, trace,
+            [&](int g) {
+                return stats && (g == kLongGroup ? plan.long_blocks2 > 0 : plan.blocks_stats[g] > 0);
+            },
             [&](int g, hipStream_t st) -> hipError_t {
                 if (g < 0) return launch_sw16(true, plan.t16, B, st);
-                if (g == kMultiGroup && plan.long_blocks2 > 0) {
+                if (g == kLongGroup) {
                     SwArgs C = A;
                     C.scratch = wk.long_scratch;
                     C.scratch_per_wave = plan.long_slot;
-                    return launch_sw_long(true, plan.long_blocks2, kGroupBins[g], C, st);
+                    return launch_sw_long(true, plan.long_blocks2, plan.long_bins2, C, st);
                 }
-                kStats[g]<<<plan.blocks_stats[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g]);
+                kStats[g]<<<plan.blocks_stats[g], 64 * kGroupWpb[g], 0, st>>>(A, kGroupBins[g] & ~plan.long_bins2);
                 return hipGetLastError();
             });
     if (e != hipSuccess) return e;

@@ -890,3 +890,35 @@ def test_sw16_calls_at_the_sizes_of_its_layouts(gpu, orc, total, narrow):
     tuning = dict(sw16_narrow_rows=narrow)
     _compare(_gpu_records(gpu, s, lo[at], hi[at], tuning=tuning, full_records=True), want[at])
     _check16(_gpu_records(gpu, s, lo[at], hi[at], tuning=tuning, score_width=16), want[at])
+
+
+@pytest.mark.parametrize("width", [0, 32])
+def test_few_long_pairs_among_many_shorter(gpu, orc, width):
+    """Pairs of over 2,978 rows keep a block each when the multi-strip pairs of
+    fewer rows (here of more columns than the traceback takes) are too many for
+    blocks: the call takes about as long as the two kinds alone, not as long as
+    single waves take for the longest pairs."""
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(61)
+    seqs = []
+    for L in (3000, 4100, 5000, 12000, 11000, 10000):
+        seqs += _related(rng, L)
+    long = len(seqs)
+    for L in (1030, 1100, 1200, 1300):
+        a = rng.integers(0, 20, L)
+        seqs += [a, np.concatenate([rng.integers(0, 20, 1700), a, rng.integers(0, 20, 1400)])]
+    s = _family_of(seqs)
+    lo = np.arange(0, len(seqs), 2, dtype=np.uint32)
+    want = orc.align_pairs(orc.encode(s.residues), s.offsets, lo, lo + 1, mode="sw")
+    few = np.arange(60) % (long // 2)
+    many = long // 2 + np.arange(2100) % 4
+    ctx = P.Context(P.Params(full_records=True, score_width=width))
+    res, off = _to_dev(s.residues, gpu), _to_dev(s.offsets, gpu)
+    ms = []
+    for at in (few, many, np.concatenate([many[:1000], few, many[1000:]])):
+        i, j = _to_dev(lo[at], gpu), _to_dev(lo[at] + 1, gpu)
+        _compare(P.records_to_numpy(ctx.align_pairs(res, off, i, j)), want[at])
+        ms.append(_best_ms(lambda: ctx.align_pairs(res, off, i, j), 3))
+    print([round(x, 2) for x in ms], "ms")
+    assert ms[2] < 1.5 * (ms[0] + ms[1]), ms
