@@ -440,13 +440,14 @@ typedef struct pastis_tuning {
                               than the call's pairs can fill).  Every launch drains a
                               work queue, so 1 (a resident grid) suffices */
     int32_t sw_grid_scale_wide; /* the same for 9..16 rows per lane (1..64) */
-    int32_t sw_intra_pair; /* more than 2048 pairs of sequences a longer than 2978 rows
-                              (32-bit lanes), 1: pass 1 runs one workgroup of four waves
-                              per pair, strips pipelined across the waves (intra-pair
-                              mode); 0: one wave per pair (inter-pair mode).  Fewer such
-                              pairs run one workgroup of eight waves each whatever its
-                              value (sw_extra_mib can forbid that), and the tuner leaves
-                              it alone */
+    int32_t sw_intra_pair; /* pass 1 of pairs of several strips in 32-bit lanes (sequences
+                              a longer than 2978 rows, or longer than 1024 where 16-bit
+                              lanes are not in use) that are too many (2048) to take a
+                              workgroup of eight waves each, 1: one workgroup of four
+                              waves per pair, strips pipelined across the waves
+                              (intra-pair mode); 0: one wave per pair (inter-pair mode).
+                              Where no pair is left for it the knob has no effect, and
+                              the tuner leaves it alone */
     int32_t sw16_narrow_rows; /* pairs per wavefront of the 16-bit bins of at most 4 rows per
                                  lane: bins of at most this many rows per lane (0..4) run
                                  strips of 16 lanes, eight pairs per wave; the others

@@ -315,8 +315,8 @@ struct SwPlan {
     int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
 };
 static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 6) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
-// max16 > 0: pass 1 of one-strip pairs with at most max16 rows per lane in
-// 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
+// max16 > 0: pass 1 of pairs with at most max16 rows per lane (one strip, or
+// several of up to kMax16Rows rows) in 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
 // that skip the statistics pass.  tune: the grid scales of the one-strip
 // groups, intra-pair pass 1 of the 32-bit multi-strip bins, the 16-bit bins
 // in strips of 16 lanes, and the multi-strip grids.

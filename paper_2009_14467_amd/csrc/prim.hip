@@ -83,8 +83,10 @@ constexpr int kWavesPerSortBlock = kSortThreads / kWave;
 // has more of them, and a histogram of one row per tile, which every scatter
 // block sums for itself (a row is 1 KB, at most kMidMax / kMidTile of them,
 // from L2).  A pass is then two launches instead of five: 33 us with the scan
-// for 250,000 keys, 17 without.  Beyond that the rows to sum per block cost
-// more than the scan.
+// for 250,000 keys, 17 without.  A call of five passes (cluster scores) takes 136
+// us instead of 202 for 2^16 keys and 168 instead of 271 for 2^18.  The line bounds
+// the rows to sum, which grow as the square of the keys; it is on the safe side
+// (332 us instead of 402 for 2^20).
 constexpr int kMidItems = 8;
 constexpr int kMidTile = kSortThreads * kMidItems;
 constexpr int64_t kMidMax = 1 << 18;
@@ -257,7 +259,8 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
 // Small sizes: one block of 16 waves keeps the keys in LDS through every pass
 // (a wave's contiguous 256 in its registers), in place.  A call's pairing sort
 // of 3,000 keys took 18 launches and 200 us, mostly launches of a few us each;
-// one launch takes 19.
+// one launch takes 19.  Cluster scores of 1,024 keys take 65 us and 85 with the
+// middle path, of 4,096 77 and 106; the size is what the keys' LDS allows.
 constexpr int kOneWaves = 16, kOneChunks = 4;
 constexpr int kOneMax = kOneWaves * kOneChunks * kWave;
 __global__ __launch_bounds__(kOneWaves *kWave) void radix_one_kernel(uint64_t *__restrict__ keys,

@@ -1139,17 +1139,26 @@ constexpr int kIntraBlocks = 256;
 // multi-strip bins in the traceback, and the call size up to which the bins of
 // up to 8 rows per lane run across all 64 lanes.  With that many pairs two to
 // a wave, every SIMD has about four waves (3,164 pairs of up to 600 rows: pass
-// 1 in 0.37 ms across 64 lanes, 0.57 in strips of 16 and 32).
+// 1 in 0.37 ms across 64 lanes, 0.57 in strips of 16 and 32).  Full records of n
+// pairs of families of 350 residues: 2.3 ms across 64 lanes and 2.45 in strips at
+// 4,096, 2.4 and 3.1 at 8,192, 2.5 and 3.05 at 12,288, 3.3 and 3.65 at 16,384: the
+// line is where the chip is full, and pairs that share their sequence less than
+// these do not lose at it.
 constexpr int kBlocks16 = 256 * 6, kTraceMultiBlocks = 256;
 constexpr int64_t kWidePairs = 8192;
 
 // Pairs of the 32-bit multi-strip bins, and pairs that may need the multi-strip
 // statistics, up to this many take one block of eight waves each (sw_long.hip);
 // beyond, the waves that work strip after strip keep the chip as busy.  Where only
-// those of at most kMax16Rows rows are too many, the others still take blocks.  1,225
-// pairs of 3,000 to 25,000 rows took 245 ms in pass 1 and 443 with statistics by
-// single waves, 149 and 118 so.  A block's scratch grows with the longest
-// sequence (20 MB for 25,000 residues); blocks are dropped beyond kLongBytes.
+// those of at most kMax16Rows rows are too many, the others still take blocks.
+// Pass 1 + statistics, blocks against waves: n pairs of 3,000 to 4,000 rows 8.4 +
+// 15.2 ms against 11.4 + 20.8 (n = 1,024), 16.6 + 30.0 against 14.2 + 34.6 (2,048),
+// 32.8 + 59.6 against 24.6 + 67.1 (4,096); of 8,000 to 9,000 rows 80 + 110 against
+// 78 + 197 (2,048); of 3,000 to 25,000 rows, where single waves are as long as the
+// longest pair, 281 + 288 against 439 + 1,094 (2,048); of 1,030 to 1,500 rows 2.6 +
+// 5.4 against 1.8 + 3.0 (1,024), 5.2 + 10.5 against 2.1 + 4.8 (2,048).  A block's
+// scratch grows with the longest sequence (20 MB for 25,000 residues); blocks are
+// dropped beyond kLongBytes.
 constexpr int64_t kLongPairs = 2048;
 constexpr int kLongBlocks = 256;
 

@@ -9,7 +9,8 @@ namespace pastis {
 namespace {
 
 // Two pairs per wave in the 16-bit halves of every DP word (pair P low, Q
-// high), same lane layout as the 32-bit pass, one strip (R <= 16).  The two
+// high), same lane layout as the 32-bit pass, in strips of up to 16 rows per lane
+// (one strip, or up to three for sequences a of 1,025 to 2,978 rows).  The two
 // pairs share their shorter sequence a (pairs are sorted by bin, then a, then
 // the longer b first), so one int8 profile serves both (see the windows below;
 // items that share the sort key's 24 bits of a but differ in a run one after
@@ -21,12 +22,16 @@ namespace {
 // pair (padding rows and columns, columns before the first) score strictly
 // below its best real cell, so the score and the first row holding it are
 // exact; the end column is found later, for the pairs that need it (end_b
-// holds a hint here, see hint_code).  Scores stay below 11 * 1024, far from the 16-bit limit.
+// holds a hint here, see hint_code).  A row gains at most 11, so scores stay within
+// 11 * 2,978 = 32,758, nine below the 16-bit limit.
 // The gap states are kept floored at zero, E' = max(E, 0) and F' = max(F, 0):
 // their recurrences stay closed (max(E' - e, 0) = max(E - e, 0) for e >= 0,
 // one saturating subtract), and max(d, E', F') then already holds the local
 // alignment's zero, so a cell takes 10 packed ops instead of 11.
 constexpr int kMax16R = kMaxR;
+// (also the limit of the differences whose signs are the traceback's bits: their
+// terms are at least -(o + e), and a gap's value is o + e below some cell's)
+static_assert(11 * kMax16Rows <= 32767, "scores of 16-bit pairs stay below 2^15");
 
 typedef short short2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
@@ -1246,7 +1251,8 @@ __device__ __forceinline__ void descending(F &f, std::integer_sequence<int, I...
 // shares its profile between the block's waves, and a window of four pairs
 // keeps the rounds per distinct sequence a few where sequences have few
 // partners; 26 KB of LDS and at most 168 registers keep six blocks (three
-// waves per SIMD) on a CU, which issue 0.94 of its slots.
+// waves per SIMD) on a CU.  Pass 1 of 250,000 sequences issues vector instructions
+// in 0.96 of the slots (2.98e11 in 503 ms), their traceback in 0.87 (7.0e10 in 131).
 //
 // Bins of up to 8 rows per lane run in strips of 16 lanes (R <= narrow: 4 R
 // rows per lane, eight pairs per wave) or 32 lanes (2 R rows, four pairs), the
@@ -1258,11 +1264,14 @@ constexpr int kBlockWaves = 2;
 constexpr size_t kBlockLds = kProfCodes * kWave * 16;  // a full-wave profile of 16 rows per lane
 
 //
-// WAVES: waves per SIMD to make room for.  The traceback's bodies spill 115
-// registers at three (outside the step, but every window pays them) and none at
-// two; two are all that a call of up to 4,096 pairs has (3,164 pairs: a search
-// of 1.79 ms against 1.65), more pairs want the third (250,001: 9.6 ms against
-// 10.9 in the pass).
+// WAVES: waves per SIMD to make room for.  The traceback's bodies spill at three
+// (118 spills by the compiler's count, 120 bytes per lane; nearly all of them
+// outside the loops over steps, but every window pays them) and not at two.  Two
+// are what a call of up to 4,096 pairs fills (3,164 pairs: a search of 1.79 ms
+// against 1.65; full records of 4,096 family pairs 2.24 against 2.32).  Across 64
+// lanes two stay ahead of three beyond that (8,192 pairs 2.32 against 2.44, 16,384
+// 3.2 against 3.3), in strips they do not (250,001: 9.6 ms against 10.9 in the
+// pass).
 template <bool TRACE, int WAVES>
 __global__ __launch_bounds__(64 * kBlockWaves, WAVES) void sw16_kernel(SwArgs A, Sw16Launch P) {
     __shared__ __align__(16) char lds[kBlockLds];
