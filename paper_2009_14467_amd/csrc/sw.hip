@@ -1342,21 +1342,27 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
     // traceback beside them, and both 150 ms; 137 with the groups first).  The long
     // pairs' blocks (kLongGroup) begin before all, as they need most of a CU's LDS
     // each: the others wait for an event of their lane, a few microseconds after
-    // their launch.
+    // their launch.  Beside many multi-strip pairs in single waves it is the 16-bit
+    // kernel that begins: either grid fills the chip, and pass 1 of 52,650 such pairs
+    // and 5.5 million others takes 9.7 s with the 16-bit kernel first, up to 10.6
+    // with the other.
     // run(phase, own, busy, f) calls f(group, stream) for every busy group and
     // orders its work after the call's stream's and before what follows on it.
     auto run = [&](int phase, bool own, auto &&busy, auto &&f) -> hipError_t {
+        const bool blocks = busy(kLongGroup), waves = !blocks && own && busy(kMultiGroup);
         int job[kLongGroup + 2], n = 0;
-        for (int g = kLongGroup; g >= 0; --g)  // long pairs first
+        if (waves) job[n++] = -1;
+        for (int g = kLongGroup; g >= 0; --g)
             if (busy(g)) job[n++] = g;
-        if (own) job[n++] = -1;
+        if (own && !waves) job[n++] = -1;
         if (n == 0) return hipSuccess;
         if (n == 1) return f(job[0], s);  // alone: no fork
         hipError_t e = fork_acquire(ctx);
         if (e != hipSuccess || (e = hipEventRecord(ctx->fork_ev[phase], s)) != hipSuccess) return e;
-        const bool lead = busy(kLongGroup), multi = lead || busy(kMultiGroup);
         constexpr int kCall = kLanes;  // the call's stream
-        const int lane_of[kLongGroup + 2] = {1, 1, multi ? 1 : 0, kCall, 2, lead ? 2 : 0, 0};  // [group + 1]
+        const bool multi = blocks || busy(kMultiGroup), lead = blocks || waves;
+        const int first = waves ? 1 : 0;  // the leader's lane; [group + 1]:
+        const int lane_of[kLongGroup + 2] = {1, waves ? kCall : 1, waves ? 2 : multi ? 1 : 0, kCall, 2, blocks ? 2 : 0, 0};
         bool used[kLanes + 1] = {};
         // (a failed pass does not leave the lanes at work on the caller's inputs)
         auto fail = [&](hipError_t x) {
@@ -1367,12 +1373,12 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         for (int k = 0; k < n; ++k) {
             const int l = lane_of[job[k] + 1];
             hipStream_t st = l == kCall ? s : ctx->lane[l];
-            const bool behind = lead && l > 0;
+            const bool behind = lead && l != first;
             if (!used[l] && (behind || l != kCall) &&
                 (e = hipStreamWaitEvent(st, behind ? ctx->lead_ev[phase] : ctx->fork_ev[phase], 0)) != hipSuccess)
                 return fail(e);
             used[l] = true;
-            if (lead && l == 0 && (e = hipEventRecord(ctx->lead_ev[phase], st)) != hipSuccess) return fail(e);
+            if (lead && k == 0 && (e = hipEventRecord(ctx->lead_ev[phase], st)) != hipSuccess) return fail(e);
             if ((e = f(job[k], st)) != hipSuccess) return fail(e);
         }
         for (int l = 0; l < kLanes; ++l)
