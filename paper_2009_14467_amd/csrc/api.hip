@@ -503,8 +503,8 @@ pastis_status align_core(pastis_ctx *ctx, const Staged &st, const uint8_t *codes
         if (max16 > 0) PASTIS_TRY(make_sort_work(ctx, npairs, wk));
         ctx->last_max16 = max16;
         auto plan_with = [&](bool trace, bool slots) {
-            SwPlan p = sw_plan(c + kCounterBinPairs, (int64_t)c[kCounterLongB], max16, st.max_len, trace, slots,
-                               ctx->tune);
+            SwPlan p = sw_plan(c + kCounterBinPairs, c + kCounterBinCells, (int64_t)c[kCounterLongB], max16, st.max_len,
+                               trace, slots, ctx->tune);
             p.forward_bound = ctx->records_internal ? 0 : 1;
             return p;
         };

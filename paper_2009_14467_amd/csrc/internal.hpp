@@ -320,10 +320,10 @@ static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 6) * 4 + 4 * 8, "no hidden paddin
 // that skip the statistics pass.  tune: the grid scales of the one-strip
 // groups, intra-pair pass 1 of the 32-bit multi-strip bins, the 16-bit bins
 // in strips of 16 lanes, and the multi-strip grids.
-// long_b: 16-bit multi-strip pairs that the traceback refuses; trace: whether the
+// bin_pairs, bin_cells: pairs and cells per bin; long_b: 16-bit multi-strip pairs that the traceback refuses; trace: whether the
 // call has, or may have, its direction bits; slots: the long pairs' slots.
-SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool trace, bool slots,
-               const pastis_tuning &tune);
+SwPlan sw_plan(const unsigned long long *bin_pairs, const unsigned long long *bin_cells, int64_t long_b, int max16,
+               int max_len, bool trace, bool slots, const pastis_tuning &tune);
 // Most bytes that the direction bits of a call take.
 size_t sw_dirs_most(int max_len);
 constexpr size_t kLongBytes = (size_t)16 << 30;  // and the long pairs' slots

@@ -1150,7 +1150,10 @@ constexpr int64_t kWidePairs = 8192;
 // Pairs of the 32-bit multi-strip bins, and pairs that may need the multi-strip
 // statistics, up to this many take one block of eight waves each (sw_long.hip);
 // beyond, the waves that work strip after strip keep the chip as busy.  Where only
-// those of at most kMax16Rows rows are too many, the others still take blocks.
+// those of at most kMax16Rows rows are too many, the others still take blocks if a
+// single wave would take longer for the longest pair than the chip for all of them
+// (a wave takes 0.39 ns for a cell of 25,000 rows' pairs, the chip 0.42 ps: a factor
+// of about kWaveShare).
 // Pass 1 + statistics, blocks against waves: n pairs of 3,000 to 4,000 rows 8.4 +
 // 15.2 ms against 11.4 + 20.8 (n = 1,024), 16.6 + 30.0 against 14.2 + 34.6 (2,048),
 // 32.8 + 59.6 against 24.6 + 67.1 (4,096); of 8,000 to 9,000 rows 80 + 110 against
@@ -1159,7 +1162,7 @@ constexpr int64_t kWidePairs = 8192;
 // 5.4 against 1.8 + 3.0 (1,024), 5.2 + 10.5 against 2.1 + 4.8 (2,048).  A block's
 // scratch grows with the longest sequence (20 MB for 25,000 residues); blocks are
 // dropped beyond kLongBytes.
-constexpr int64_t kLongPairs = 2048;
+constexpr int64_t kLongPairs = 2048, kWaveShare = 1024;
 constexpr int kLongBlocks = 256;
 
 // Resident blocks per CU of the one-strip statistics kernels: they keep no
@@ -1227,8 +1230,8 @@ size_t sw_dirs_most(int max_len) {
 }
 
 // The launches of a call, from its pairs per bin.
-SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, int max_len, bool trace, bool slots,
-               const pastis_tuning &tune) {
+SwPlan sw_plan(const unsigned long long *bin_pairs, const unsigned long long *bin_cells, int64_t long_b, int max16,
+               int max_len, bool trace, bool slots, const pastis_tuning &tune) {
     SwPlan p;
     p.max16 = max16;
     p.intra = tune.sw_intra_pair;
@@ -1271,9 +1274,10 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, i
     }
     // pairs of the multi-strip bins of over kMax16Rows rows, and of fewer: those of
     // pass 1 in 32-bit lanes, and those that may come to the multi-strip statistics
-    int64_t over = 0, low1 = 0, low2 = n16 > 0 && trace ? long_b : 0;
+    int64_t over = 0, low1 = 0, low2 = n16 > 0 && trace ? long_b : 0, cells = 0;
     for (int b = kMultiBin; b < kNumBins; ++b) {
         const bool is16 = sw_bin_is16(b, max16);
+        cells += (int64_t)bin_cells[b];
         if (b < kMulti16Bin) over += (int64_t)bin_pairs[b];
         if (b >= kMulti16Bin && !is16) low1 += (int64_t)bin_pairs[b];
         if (b >= kMulti16Bin && !(is16 && trace)) low2 += (int64_t)bin_pairs[b];
@@ -1281,8 +1285,9 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, int64_t long_b, int max16, i
     if (slots) {
         const int64_t slot = sw_long_slot_words(max_len);
         const int64_t room = std::max<int64_t>(8, (int64_t)kLongBytes / (int64_t)(slot * sizeof(int)));
+        const bool apart = cells < kWaveShare * max_len * max_len;
         auto take = [&](int64_t low, uint32_t &bins, int &blocks) {
-            bins = over + low <= kLongPairs ? kGroupBins[kMultiGroup] : over <= kLongPairs ? kOverBins : 0u;
+            bins = over + low <= kLongPairs ? kGroupBins[kMultiGroup] : over <= kLongPairs && apart ? kOverBins : 0u;
             const int64_t pairs = bins == 0 ? 0 : bins == kOverBins ? over : over + low;
             blocks = (int)std::min<int64_t>({kLongBlocks, room, pairs});
             if (blocks == 0) bins = 0;
@@ -1361,8 +1366,12 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         if (e != hipSuccess || (e = hipEventRecord(ctx->fork_ev[phase], s)) != hipSuccess) return e;
         constexpr int kCall = kLanes;  // the call's stream
         const bool multi = blocks || busy(kMultiGroup), lead = blocks || waves;
-        const int first = waves ? 1 : 0;  // the leader's lane; [group + 1]:
-        const int lane_of[kLongGroup + 2] = {1, waves ? kCall : 1, waves ? 2 : multi ? 1 : 0, kCall, 2, blocks ? 2 : 0, 0};
+        const int first = waves ? 1 : 0;  // the leader's lane
+        // lanes by group + 1.  In pass 1, where every group may be large, the groups of
+        // 9-16 rows per lane share a lane (a search in 32-bit lanes 119 ms, 123 with a
+        // lane each); later the groups of few rows make room for the traceback.
+        const int lane_of[2][kLongGroup + 2] = {{1, own ? kCall : 1, kCall, 2, 2, blocks ? 2 : 0, 0},
+                                                {1, waves ? kCall : 1, waves ? 2 : multi ? 1 : 0, kCall, 2, blocks ? 2 : 0, 0}};
         bool used[kLanes + 1] = {};
         // (a failed pass does not leave the lanes at work on the caller's inputs)
         auto fail = [&](hipError_t x) {
@@ -1371,7 +1380,7 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
             return x;
         };
         for (int k = 0; k < n; ++k) {
-            const int l = lane_of[job[k] + 1];
+            const int l = lane_of[phase > 0][job[k] + 1];
             hipStream_t st = l == kCall ? s : ctx->lane[l];
             const bool behind = lead && l != first;
             if (!used[l] && (behind || l != kCall) &&
