@@ -304,6 +304,7 @@ struct SwPlan {
     // traceback's direction words: per wave of the grid, per wave of its
     // multi-strip blocks, and in all
     int stats_after_trace = 0, forward_bound = 0;
+    int trace_after_long = 0, pad = 0;  // the traceback waits for the long pairs' statistics
     // long pairs, one block each: the blocks and the bins of pass 1 and of the
     // statistics (the multi-strip kernels take the other bins), and the scratch
     // words of a block
@@ -314,7 +315,7 @@ struct SwPlan {
     bool intra_matters() const { return blocks32[4] > 0; }
     int64_t dirs_per_wave = 0, dirs_per_multi = 0, dirs_words = 0;
 };
-static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 6) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
+static_assert(sizeof(SwPlan) == (2 + 12 + 20 + 8) * 4 + 4 * 8, "no hidden padding: the plan is hashed as words");
 // max16 > 0: pass 1 of pairs with at most max16 rows per lane (one strip, or
 // several of up to kMax16Rows rows) in 16-bit lanes, two pairs per wave; its records leave end_b = -1 for pairs
 // that skip the statistics pass.  tune: the grid scales of the one-strip

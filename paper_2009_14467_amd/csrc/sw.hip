@@ -1275,10 +1275,16 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, const unsigned long long *bi
     // pairs of the multi-strip bins of over kMax16Rows rows, and of fewer: those of
     // pass 1 in 32-bit lanes, and those that may come to the multi-strip statistics
     int64_t over = 0, low1 = 0, low2 = n16 > 0 && trace ? long_b : 0, cells = 0;
+    int64_t over_cells = 0, cells16 = 0;
+    for (int b = 0; b < kNumBins; ++b)
+        if (sw_bin_is16(b, max16)) cells16 += (int64_t)bin_cells[b];
     for (int b = kMultiBin; b < kNumBins; ++b) {
         const bool is16 = sw_bin_is16(b, max16);
         cells += (int64_t)bin_cells[b];
-        if (b < kMulti16Bin) over += (int64_t)bin_pairs[b];
+        if (b < kMulti16Bin) {
+            over += (int64_t)bin_pairs[b];
+            over_cells += (int64_t)bin_cells[b];
+        }
         if (b >= kMulti16Bin && !is16) low1 += (int64_t)bin_pairs[b];
         if (b >= kMulti16Bin && !(is16 && trace)) low2 += (int64_t)bin_pairs[b];
     }
@@ -1302,6 +1308,12 @@ SwPlan sw_plan(const unsigned long long *bin_pairs, const unsigned long long *bi
         else if (p.long_bins1 != 0)
             p.blocks32[kMultiGroup] = fit(kMultiGroup, kGroupBlocks[kMultiGroup], low1);
         if (p.long_bins2 == kGroupBins[kMultiGroup]) p.blocks_stats[kMultiGroup] = 0;
+        // few long pairs, none of them long to do: the traceback comes after them.
+        // Beside them its first blocks, which take the multi-strip pairs, crowd on the
+        // CUs that the long pairs leave free (a search of 250,000 sequences with the
+        // learned filter: 5 ms of long pairs, then 107 of traceback; 118 side by side)
+        p.trace_after_long = p.long_blocks2 > 0 && 16 * over_cells < cells16 &&
+                             4 * kWaveShare * max_len * max_len < cells16;
     }
     if (n16 == 0) return p;
     Sw16Launch &k = p.p16;
@@ -1387,6 +1399,10 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
                 (e = hipStreamWaitEvent(st, behind ? ctx->lead_ev[phase] : ctx->fork_ev[phase], 0)) != hipSuccess)
                 return fail(e);
             used[l] = true;
+            if (job[k] < 0 && blocks && phase == 2 && plan.trace_after_long &&
+                ((e = hipEventRecord(ctx->join_ev[phase][0], ctx->lane[0])) != hipSuccess ||
+                 (e = hipStreamWaitEvent(st, ctx->join_ev[phase][0], 0)) != hipSuccess))
+                return fail(e);
             if (lead && k == 0 && (e = hipEventRecord(ctx->lead_ev[phase], st)) != hipSuccess) return fail(e);
             if ((e = f(job[k], st)) != hipSuccess) return fail(e);
         }
