@@ -1377,7 +1377,12 @@ hipError_t launch_sw(pastis_ctx *ctx, const uint8_t *codes, const PairDesc *pair
         hipError_t e = fork_acquire(ctx);
         if (e != hipSuccess || (e = hipEventRecord(ctx->fork_ev[phase], s)) != hipSuccess) return e;
         constexpr int kCall = kLanes;  // the call's stream
-        const bool multi = blocks || busy(kMultiGroup), lead = blocks || waves;
+        const bool multi = blocks || busy(kMultiGroup);
+        // (not in a capture, where the order of branches is the graph's: a wait for a
+        // lane's event makes the waiting stream that lane's branch, and two passes led
+        // by different lanes would make each lane a branch of the other, which ending
+        // the capture follows without end)
+        const bool lead = timed && (blocks || waves);
         const int first = waves ? 1 : 0;  // the leader's lane
         // lanes by group + 1.  In pass 1, where every group may be large, the groups of
         // 9-16 rows per lane share a lane (a search in 32-bit lanes 119 ms, 123 with a

@@ -268,3 +268,74 @@ def test_autotune_leaves_a_knob_without_effect(gpu):
     for rep in range(12):
         ctx.set_tuning(sw_intra_pair=rep % 2)
         assert ctx.autotune(res, off, max_pairs=500)["sw_intra_pair"] == rep % 2, rep
+
+
+def test_graph_mode_with_passes_of_several_launches(gpu):
+    """Replays of passes that spread over several streams (long pairs in blocks, then
+    the traceback; statistics of several groups of bins), with eager searches and
+    synchronizations in between, give the eager result every time, in both widths."""
+    import torch
+
+    import paper_2009_14467_amd as P
+    from synth import make_family_set
+
+    s = make_family_set(n_families=44, family_size=16, mean_len=900, min_len=30, max_len=2500, divergence=0.35,
+                        long_frac=0.06, long_range=(3050, 3200), stream=9)
+    res, off = _dev(s.residues, gpu), _dev(s.offsets, gpu)
+    L = np.diff(s.offsets)
+    assert (L > 2978).sum() > 1
+    eager = P.Context(P.Params(k=5, ck_min=1))
+    want = eager.search(res, off)
+    bins = eager.stats()["sw_bins"]
+    assert sum(b["pairs"] for b in bins if b["multi_strip"] and b["bits"] == 32) > 0
+    assert sum(b["cells"] for b in bins if b["bits"] == 16) > 4096 * int(L.max()) ** 2
+    for width in (0, 32):
+        graph = P.Context(P.Params(k=5, ck_min=1, graph_mode=True, score_width=width))
+        for rep in range(4):
+            got = graph.search(res, off)
+            assert got.tobytes() == want.tobytes(), (width, rep)
+            assert graph.stats()["sw_graph"] == (1 if rep == 0 else 2)
+            assert eager.search(res, off).tobytes() == want.tobytes()
+            torch.cuda.synchronize()
+
+
+def test_graph_mode_with_passes_led_by_different_lanes(gpu):
+    """One capture whose pass 1 gives the long pairs a block each and whose statistics
+    take them in single waves (too many pairs of fewer rows and a long b): the
+    capture ends, and its replays give the eager result."""
+    import torch
+
+    import paper_2009_14467_amd as P
+
+    rng = np.random.default_rng(67)
+    letters = np.frombuffer(b"ARNDCQEGHILKMFPSTWYV", np.uint8)
+    motif = rng.integers(0, 20, 60)
+    seqs = []
+    related = rng.integers(0, 20, 4300)
+    for L, n in ((4300, 20), (1300, 130)):
+        for _ in range(n):
+            x = rng.integers(0, 20, L + int(rng.integers(0, 150)))
+            if L == 4300:
+                x[:L] = np.where(rng.random(L) < 0.2, x[:L], related)
+            at = int(rng.integers(0, x.size - 60))
+            x[at : at + 60] = motif
+            seqs.append(x)
+    off = np.zeros(len(seqs) + 1, np.int64)
+    np.cumsum([len(x) for x in seqs], out=off[1:])
+    res, offd = _dev(letters[np.concatenate(seqs)], gpu), _dev(off, gpu)
+    eager = P.Context(P.Params(k=6, ck_min=2))
+    eager.set_tuning(sw_direct_pct=0)  # every pair whose coverage can hold takes statistics
+    want = eager.search(res, offd)
+    st = eager.stats()
+    L = np.diff(off)
+    assert want.size >= 190 and st["n_aligned"] == len(seqs) * (len(seqs) - 1) // 2
+    multi = [b for b in st["sw_bins"] if b["multi_strip"]]
+    assert 0 < sum(b["pairs"] for b in multi if b["bits"] == 32) <= 2048 < 20 * 130
+    assert sum(b["cells"] for b in multi) > 1024 * int(L.max()) ** 2
+    graph = P.Context(P.Params(k=6, ck_min=2, graph_mode=True))
+    graph.set_tuning(sw_direct_pct=0)
+    for rep in range(4):
+        assert graph.search(res, offd).tobytes() == want.tobytes(), rep
+        assert graph.stats()["sw_graph"] == (1 if rep == 0 else 2)
+        assert eager.search(res, offd).tobytes() == want.tobytes()
+        torch.cuda.synchronize()
